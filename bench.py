@@ -246,13 +246,39 @@ def select_bytes(n, precision):
     return 8 * k + (2 * k if precision == 1 else 0) + tiles * 8 * 8 + 12
 
 
+def factored_flops(n, precision):
+    """Matrix-core operations of one node-iteration with the correlation
+    factored through the atoms' outer products (T R T^T per family, two
+    products of 2 N^3): FP32 one product each; BF16 form three 16-bit
+    products each for the DCT (value and remainder) and two for the Haar."""
+    return (8 if precision == 0 else 20) * n ** 3
+
+
+def whole_level_roofline(n, stats, timing, precision):
+    """The largest level run as one launch: its matrix-core operations over
+    the level's time (gather, re-score, update and split test included)."""
+    lg = n.bit_length() - 1
+    peak = PEAK_BF16_TFLOPS if precision == 1 else PEAK_FP32_TFLOPS
+    ms = timing["level_ms"][lg]
+    flops = factored_flops(n, precision)
+    ach = flops * stats["iters_level"][lg] / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
+    return dict(bound="latency", achieved=round(ach, 2), peak=peak, unit="TFLOP/s", frac=round(ach / peak, 4),
+                traffic=None, kernel=f"k_pursuit_sep<{n}>", level_ms=round(ms, 4), flops_per_unit=flops,
+                units=int(stats["iters_level"][lg]),
+                unfactored_equivalent_tflops=round(4.0 * n ** 4 * stats["iters_level"][lg] / (ms * 1e-3) / 1e12, 1)
+                if ms > 0 else 0.0)
+
+
 def roofline(stats, timing, precision, kernel_name=None, workload=None):
     """Dominant kernel: the correlation of the largest block size.  Algorithmic
     work per node-iteration is 2*K*M = 4 N^4 flops (every atom correlated with
     the residual); one launch processes the nodes active in that MP step.
-    Each level also reports the select/update step against HBM bandwidth."""
+    Each level also reports the select/update step against HBM bandwidth.
+    Where the largest level runs as one launch, the factored form of the
+    correlation is what is counted (whole_level_roofline)."""
     lg = max(l for l in range(7) if stats["iters_level"][l] > 0)
     n = 1 << lg
+    whole = whole_level_roofline(n, stats, timing, precision) if n >= 32 and timing["corr_ms"][lg] == 0 else None
     flops = 4.0 * n ** 4 * stats["iters_level"][lg]
     ms = timing["corr_ms"][lg]
     steps = timing["steps"][lg]
@@ -282,12 +308,17 @@ def roofline(stats, timing, precision, kernel_name=None, workload=None):
     for l in range(7):
         if stats["iters_level"][l] and timing["corr_ms"][l] == 0 and timing["level_ms"][l] > 0:
             nn = 1 << l
+            if nn >= 32:
+                per_level[str(nn)] = dict(whole_level_roofline(nn, stats, timing, precision), kernel="whole-level pursuit")
+                continue
             bf16 = precision == 1 and nn in (8, 16)
             pk = peak if bf16 else PEAK_FP64_TFLOPS
             a = 4.0 * nn ** 4 * stats["iters_level"][l] / (timing["level_ms"][l] * 1e-3) / 1e12
             per_level[str(nn)] = dict(kernel="whole-level pursuit", level_ms=round(timing["level_ms"][l], 3),
                                       tflops=round(a, 3), frac=round(a / pk, 4),
                                       peak="bf16 mfma" if bf16 else "fp64")
+    if whole:
+        return dict(whole, per_level=per_level)
     kname = kernel_name(n) if kernel_name else f"correlation<N={n}>"
     return dict(bound="mfma", achieved=round(achieved, 2), peak=peak, unit="TFLOP/s",
                 frac=round(achieved / peak, 4), traffic=measured_traffic(kname, workload), traffic_unit="bytes per launch",
@@ -616,8 +647,24 @@ def main():
                       "timed inside a graph); in a kernel trace of this command these are the dispatches "
                       "between the two spin_kernel markers")
     code_t.free()
-    log(f"bf16 batched (stream, timed): {sec_t * 1e3:.3f} ms/step, corr {roof['achieved']} TFLOP/s")
+    log(f"bf16 batched (stream, timed): {sec_t * 1e3:.3f} ms/step, {roof['kernel']} {roof['achieved']} TFLOP/s")
     mark("headline_event_timed_encodes")
+
+    # Labelled variant: the same encode step by step, every level of N >= 16
+    # one unfactored correlation (all atoms as 4 N^4 flops) and one select
+    # launch per MP step.
+    code_s = A.Code(dic, imgs, w["params"], w["jobs"], precision=A.PREC_BF16, schedule=sched, timing=True,
+                    stepwise=True)
+    n_s = min(args.steps, 5)
+    for _ in range(2):
+        code_s.reencode(imgs)
+    tm_s, st_s, sec_s = timed_encodes(code_s, imgs, n_s)
+    stepwise_res = dict(ms_per_step=round(sec_s * 1e3, 4), steps=n_s,
+                        roofline=roofline(st_s, tm_s, A.PREC_BF16, lambda n: A.corr_kernel(n, A.PREC_BF16),
+                                          workload=args.workload),
+                        form="labelled variant: step by step, unfactored BF16 correlation")
+    code_s.free()
+    mark("stepwise_form")
 
     fp32 = None
     if not args.no_fp32:
@@ -738,7 +785,8 @@ def main():
         "dtype": "bf16",
         "data": "synthetic",
         "config": {"workload": w["name"], "jobs": len(w["jobs"]), "pixels_per_step": npx,
-                   "form": "batched: all jobs in one HIP graph, BF16 MFMA correlation, top-8 FP64 re-score"},
+                   "form": "batched: all jobs in one HIP graph, 16-bit MFMA correlation factored through the "
+                           "atoms' outer products, FP64 re-score"},
         "mp_iters_per_s": round(stats["iters_executed"] / sec, 1),
         "mp_iters_executed": int(stats["iters_executed"]),
         "mp_iters_emitted": int(stats["iters_emitted"]),
@@ -765,6 +813,7 @@ def main():
                           measured=tuned["measured"], seconds=tuned["seconds"], cached=tuned["cached"])
                      if tuned else None),
         "roofline": roof,
+        "bf16_stepwise": stepwise_res,
         "precision_report": prec_rep,
         "phase_seconds": dict(phases, timed_region=round(sec * args.steps, 4),
                               note="wall clock of each phase of this run; timed_region = steps x ms_per_step"),

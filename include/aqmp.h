@@ -121,7 +121,10 @@ enum { AQMP_SOLVER_DENSE = 0, AQMP_SOLVER_GRAM = 1, AQMP_SOLVER_OMP = 2 };   /* 
 
 typedef struct {
   int32_t precision;   /* AQMP_PREC_FP32: FP32 MFMA correlation;
-                          AQMP_PREC_BF16: BF16 MFMA, FP32 accumulate.
+                          AQMP_PREC_BF16: 16-bit MFMA, FP32 accumulate
+                          (BF16 operands, or in the whole-level pursuits of
+                          N = 32 and 64 every operand as the sum of two FP16
+                          values, which is nearer to FP32).
                           Both re-score the AQMP_CANDIDATES best atoms in
                           FP64 and take the coefficient and the stop/split
                           test in FP64. */
@@ -139,13 +142,16 @@ typedef struct {
                           aqmp_code_timing).  Events cannot be timed inside
                           a graph, so a timed batched encode issues the same
                           launches directly on the stream.
-                          AQMP_OPT_STEPWISE: run the N = 16 level of the
-                          BF16 form one MP step per launch (correlation
-                          and select) instead of the whole-level
-                          pursuit; same method, for comparison. */
-  int32_t corr_variant;  /* tuning: 0 = library default; 2, 3 or 6 force
-                            one family of BF16 correlation kernels (results
-                            are identical, only speed differs): 2 direct-
+                          AQMP_OPT_STEPWISE: run the levels of N >= 16 one
+                          MP step per launch (correlation and select)
+                          instead of the whole-level pursuits; same method,
+                          for comparison. */
+  int32_t corr_variant;  /* tuning: 0 = library default (N >= 32: the
+                            whole-level pursuit, whose correlation is
+                            factored through the atoms' outer products);
+                            2, 3 or 6 run the BF16 levels of N >= 32 step by
+                            step with one family of correlation kernels
+                            (results are identical, only speed differs): 2 direct-
                             to-LDS loads, two workgroups per CU (N >= 16);
                             3 register-staged loads (every N); 6 atoms
                             generated in registers (N = 32, 64; other N
@@ -176,7 +182,7 @@ typedef struct {
                                     corr_variant.  An autotuner fills it from
                                     timed encodes of the caller's workload. */
   uint32_t corr_tile_levels;     /* tuning of the generated-atom correlation
-                                    (variant 6, N = 32 and 64): the node tile of
+                                    (variant 6, N = 32 and 64 step by step): the node tile of
                                     a launch is 32 MB nodes, MB chosen from the
                                     active-node count inside [lo, hi].  Byte
                                     8 (lg - 5) holds lo in its low nibble and hi
@@ -213,9 +219,9 @@ typedef struct {
  * (start and end recorded by each dispatch); level times span the level's
  * launches on the stream. */
 typedef struct {
-  double corr_ms[7];        /* correlation + top-R key launches (Gram and
-                               OMP solvers, N >= 16: the initial-
-                               correlation launch)                         */
+  double corr_ms[7];        /* correlation + top-R key launches of the levels
+                               that run step by step (Gram and OMP solvers,
+                               N >= 16: the initial-correlation launch)     */
   double select_ms[7];      /* re-score / update / norm launches (Gram and
                                OMP solvers, N >= 16: the pursuit launch)    */
   double level_ms[7];       /* whole level: gather .. split/emit            */
@@ -415,9 +421,9 @@ int aqmp_worklist_split(const aqmp_params* prm, int n_prm, int n, const int32_t*
 const char* aqmp_last_error(void);
 
 /* Name of the correlation kernel (MP step (b) of Section 2.2, c = D^T r) that
- * an encode runs for block size n with the given precision (AQMP_PREC_*) and
- * aqmp_options.corr_variant (0 = library default), e.g. for labelling
- * profiles.  Static string owned by the library; "" for an invalid
+ * a step-by-step encode runs for block size n with the given precision
+ * (AQMP_PREC_*) and aqmp_options.corr_variant (0 = default), e.g. for
+ * labelling profiles.  Static string owned by the library; "" for an invalid
  * combination (n not a power of two in [AQMP_MIN_N, AQMP_MAX_N], unknown
  * precision or variant).  Levels with n <= 8 run the fused per-level pursuit
  * instead; their name is returned for those n. */

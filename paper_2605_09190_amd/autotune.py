@@ -1,26 +1,26 @@
-"""Autotuner for the batched encoder: correlation kernel per block size, the
-node-tile range of the generated-atom correlation, the form of the N = 16
-level, and the schedule.
+"""Autotuner for the batched encoder: form of every level from N = 16 up (one
+launch for the whole level, or a correlation and a select launch per MP step),
+correlation kernel and node-tile range of the step-by-step levels, and the
+schedule.
 
-The library offers several BF16 correlation kernel families that produce
-bit-identical keys (``aqmp_options.corr_variant``, per block size through
-``corr_variant_levels``), two forms of the N = 16 level of the BF16 form (one
-launch for the whole level, or a correlation and a select launch per MP
-step) and three schedules.  Which is fastest depends on how many nodes each
+The library runs a level as one launch unless it is asked for step by step;
+the step-by-step form has several BF16 correlation kernel families that
+produce bit-identical keys (``aqmp_options.corr_variant``, per block size
+through ``corr_variant_levels``), and there are three schedules.  Which is fastest depends on how many nodes each
 level holds at each step, so the tuner measures them on the caller's own
 workload:
 
 1. every kernel family is run once per candidate with the library's
-   per-launch HIP events (``aqmp_code_timing``): per block size N >= 32 the
-   correlation time of the level, per N = 16 the whole level's time (step by
-   step with that family, or as one launch), each the best of ``reps``
-   encodes;
+   per-launch HIP events (``aqmp_code_timing``): per block size N >= 16 the
+   level's time (step by step with that family, or as one launch), and per
+   N >= 32 the correlation time of the step-by-step level, each the best of
+   ``reps`` encodes;
 2. a candidate replaces the library default of a level only when it is
    faster by more than ``margin`` (so that timing noise does not flip it);
-3. where the generated-atom kernel runs (N = 32, 64), its node-tile range
-   [lo, hi] (the kernel picks the node-tile width 32 MB, lo <= MB <= hi, from
-   the active-node count of each step) is timed over a few candidate ranges
-   under the same rule against the library's range;
+3. where the generated-atom kernel runs (N = 32, 64 step by step), its
+   node-tile range [lo, hi] (the kernel picks the node-tile width 32 MB,
+   lo <= MB <= hi, from the active-node count of each step) is timed over a
+   few candidate ranges under the same rule against the library's range;
 4. the schedules are then timed as graph replays with the chosen kernels,
    under the same rule against the batched schedule.
 
@@ -177,45 +177,48 @@ def tune(A, dic, images, params, jobs, reps: int = 3, steps: int = 5, margin: fl
 def _tune(A, dic, images, params, jobs, reps, steps, margin, schedules) -> dict:
     levels = sorted({1 << l for p in params for l in range(p["n_min"].bit_length() - 1, p["n_max"].bit_length())},
                     reverse=True)
-    measured = {"corr_ms": {}, "level16_ms": {}, "schedule_ms": {}}
+    measured = {"corr_ms": {}, "level_ms": {}, "level16_ms": {}, "schedule_ms": {}}
     corr = {n: {} for n in (64, 32) if n in levels}
-    lvl16 = {}
+    form = {n: {} for n in (64, 32, 16) if n in levels}      # level times: ("step", family), ("whole", 0)
     for v in sorted({v for n in CANDIDATES for v in CANDIDATES[n]}):
         c_ms, l_ms = _timed(A, dic, images, params, jobs, reps, corr_variant=v, stepwise=True)
-        for n in corr:
-            if v in CANDIDATES[n] and c_ms[n.bit_length() - 1] > 0:
-                corr[n][v] = c_ms[n.bit_length() - 1]
-        if 16 in levels and v in CANDIDATES[16] and l_ms[4] > 0:
-            lvl16[("step", v)] = l_ms[4]
-    if 16 in levels:
+        for n in form:
+            lg = n.bit_length() - 1
+            if v in CANDIDATES[n] and l_ms[lg] > 0:
+                form[n][("step", v)] = l_ms[lg]
+            if n in corr and v in CANDIDATES[n] and c_ms[lg] > 0:
+                corr[n][v] = c_ms[lg]
+    if form:
         _, l_ms = _timed(A, dic, images, params, jobs, reps, stepwise=False)
-        if l_ms[4] > 0:
-            lvl16[("whole", 0)] = l_ms[4]
+        for n in form:
+            if l_ms[n.bit_length() - 1] > 0:
+                form[n][("whole", 0)] = l_ms[n.bit_length() - 1]
     per_n = {}
     for n, times in corr.items():
         measured["corr_ms"][str(n)] = {str(v): round(t, 4) for v, t in times.items()}
-        v = choose(times, DEFAULT[n], margin)
-        if v != DEFAULT[n]:
+    for n, times in form.items():
+        key = "level16_ms" if n == 16 else "level_ms"
+        got = {f"{k[0]}{k[1] or ''}": round(t, 4) for k, t in times.items()}
+        measured[key] = got if n == 16 else {**measured[key], str(n): got}
+    # A level runs as one launch unless a family step by step beats it: at
+    # N = 32, 64 by naming the family, at N = 16 by the step-by-step flag,
+    # which holds for every level, so only where they all prefer it.
+    picks = {n: choose(times, ("whole", 0), margin) for n, times in form.items()}
+    stepwise = bool(picks) and all(p[0] == "step" for p in picks.values())
+    for n, (kind, v) in picks.items():
+        if kind == "step" and (n >= 32 or (stepwise and v != DEFAULT[16])):
             per_n[n] = v
-    stepwise = False
-    if lvl16:
-        measured["level16_ms"] = {f"{k[0]}{k[1] or ''}": round(t, 4) for k, t in lvl16.items()}
-        form, v = choose(lvl16, ("whole", 0), margin)
-        if form == "step":
-            stepwise = True
-            if v != DEFAULT[16]:
-                per_n[16] = v
     # node-tile range of the generated-atom kernel, where it runs
     per_tile = {}
     measured["tile_ms"] = {}
     for n in (64, 32):
-        if n not in corr or per_n.get(n, DEFAULT[n]) != GEN_VARIANT:
+        if n not in corr or per_n.get(n) != GEN_VARIANT:
             continue
         lg = n.bit_length() - 1
         times = {}
         for rng in TILE_CANDIDATES[n]:
-            c_ms, _ = _timed(A, dic, images, params, jobs, reps, corr_variant_levels={**per_n, n: GEN_VARIANT},
-                             stepwise=stepwise, corr_tile_levels={n: rng})
+            c_ms, _ = _timed(A, dic, images, params, jobs, reps, corr_variant_levels=per_n, stepwise=stepwise,
+                             corr_tile_levels={n: rng})
             if c_ms[lg] > 0:
                 times[rng] = c_ms[lg]
         measured["tile_ms"][str(n)] = {f"{lo}-{hi}": round(t, 4) for (lo, hi), t in times.items()}

@@ -64,6 +64,7 @@ struct aqmp_code {
   aqmp::JobDev* djobs = nullptr;
   std::vector<aqmp::PassPlan> passes;
   aqmp::Counters* dcnt = nullptr;      // one per pass
+  aqmp::Queues* dqueue = nullptr;      // one per pass
   int32_t* dntop = nullptr;            // [pass][kLevels]
   int64_t cap_total[aqmp::kLevels] = {};
   int32_t kmax_total[aqmp::kLevels] = {};
@@ -309,11 +310,26 @@ void free_code(aqmp_code* c) {
   delete c;
 }
 
+// Correlation kernel family forced at one level (0: none).
+int forced_variant(const aqmp_code* c, int lg) {
+  const int v = (int)((c->opt.corr_variant_levels >> (4 * lg)) & 0xFu);
+  return v ? v : c->opt.corr_variant;
+}
+
+// Dense levels of N >= 32 that run as one launch with the factored
+// correlation: all but those asked for step by step, or (BF16) with a named
+// correlation kernel.
+bool sep_level(const aqmp_code* c, int n) {
+  if (n < 32 || c->opt.solver != AQMP_SOLVER_DENSE || (c->opt.flags & AQMP_OPT_STEPWISE)) return false;
+  return c->opt.precision != AQMP_PREC_BF16 || forced_variant(c, ilog2(n)) == 0;
+}
+
 // Levels that run without per-step launches: N <= kFusedMaxN in both forms
 // (dense FP64 pursuit), N = 16 in the BF16 form (whole-level MFMA pursuit),
-// and every level of the Gram solver.
-static bool whole_level(const aqmp_code* c, int n) {
-  if (n <= kFusedMaxN || c->opt.solver != AQMP_SOLVER_DENSE) return true;
+// N >= 32 with the factored correlation, and every level of the Gram and OMP
+// solvers.
+bool whole_level(const aqmp_code* c, int n) {
+  if (n <= kFusedMaxN || c->opt.solver != AQMP_SOLVER_DENSE || sep_level(c, n)) return true;
   return n == 16 && c->opt.precision == AQMP_PREC_BF16 && !(c->opt.flags & AQMP_OPT_STEPWISE);
 }
 
@@ -413,6 +429,7 @@ int build_plan(aqmp_code* c) {
   }
   ALLOC(c->djobs, sizeof(JobDev) * nj);
   ALLOC(c->dcnt, sizeof(Counters) * c->passes.size());
+  ALLOC(c->dqueue, sizeof(Queues) * c->passes.size());
   ALLOC(c->dntop, sizeof(int32_t) * kLevels * c->passes.size());
 #undef ALLOC
   hipStream_t s = c->stream;
@@ -484,7 +501,7 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
   aqmp_code::Work& wk = c->work[pi % c->work.size()];
   Counters* cnt = c->dcnt + pi;
   const aqmp_dict* d = c->dict;
-  AQMP_LAUNCH(launch_init_counts(cnt, c->dntop + pi * kLevels, s));
+  AQMP_LAUNCH(launch_init_counts(cnt, c->dqueue + pi, c->dntop + pi * kLevels, s));
   for (int l = pp.lg_hi; l >= pp.lg_lo; --l) {
     if (pp.cap[l] == 0) continue;
     const int n = 1 << l;
@@ -520,7 +537,10 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
           AQMP_LAUNCH(launch_gram_pursuit(n, c->djobs, a.lv, count, &cnt->next[l], l, d->nfam, D.d_tab, D.d_xg,
                                           wk.cbuf, s));
         if (se) AQMP_HIP(hipEventRecord(se->c, s));
-      } else if (n == 8 && c->opt.precision == AQMP_PREC_BF16)
+      } else if (sep_level(c, n))
+        AQMP_LAUNCH(launch_pursuit_sep(n, c->opt.precision, d->families, c->djobs, a.lv, count, c->dqueue[pi].at[l], pp.cap[l],
+                                       D.d_tab, D.d_sep[c->opt.precision], s));
+      else if (n == 8 && c->opt.precision == AQMP_PREC_BF16)
         AQMP_LAUNCH(launch_pursuit_bf16(8, c->djobs, a.lv, count, &cnt->next[l], pp.cap[l], D.m, d->nfam, D.d_tab,
                                         D.d_tabT32, s));
       else if (n <= kFusedMaxN)
@@ -550,8 +570,7 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
       a.clear_count = &cnt->act[(t + 2) % 3];
       const aqmp_code::StepEv* se = timing ? &c->sev[c->sev_pos++] : nullptr;
       a.corr_tile = l >= 5 ? (int32_t)((c->opt.corr_tile_levels >> (8 * (l - 5))) & 0xFFu) : 0;
-      const int lv_var = (int)((c->opt.corr_variant_levels >> (4 * l)) & 0xFu);
-      const int variant = c->wide_residual ? 3 : (lv_var ? lv_var : c->opt.corr_variant);
+      const int variant = c->wide_residual ? 3 : forced_variant(c, l);
       AQMP_LAUNCH(launch_corr(n, c->opt.precision, variant, atoms, a, D.m_pad, s, se ? se->a : nullptr,
                               se ? se->b : nullptr));
       AQMP_LAUNCH(launch_select(n, a, pp.cap[l], s, se ? se->c : nullptr, se ? se->d : nullptr));

@@ -30,6 +30,7 @@ constexpr int kScanTile = 1024;   // items per block of the stable scans
 constexpr int kFusedMaxN = 8;     // levels up to this size run the fused per-node pursuit
 constexpr int kBranches = 4;      // parallel graph branches of the concurrent schedule
 constexpr int kOmpMaxAtoms = AQMP_OMP_MAX_ATOMS;   // OMP: selected atoms per node (LDS factor size)
+constexpr int kQueues = 8, kQueuePad = 32;   // node queues of a level and the words between them
 constexpr int kSsimMomentBlocks = 1024;   // workgroups of the whole-plane SSIM moments
 
 // Kernel launch, with start/end events recorded by the dispatch when given.
@@ -61,6 +62,11 @@ struct JobDev {
   int32_t pad;
 };
 
+// Planes are device memory: global loads (a pointer taken from the job table
+// is generic to the compiler, and a flat load also waits on the LDS counter).
+typedef __attribute__((address_space(1))) double gmem_f64;
+typedef __attribute__((address_space(1))) float gmem_f32;
+
 // Pixel (y, x) of a job's plane in FP64.  Blocks tile the plane padded up
 // to a multiple of N_max; rows and columns past the image repeat its last
 // row and column (edge replication).
@@ -68,7 +74,7 @@ __device__ inline double job_pixel(const JobDev& jb, int y, int x) {
   y = y < jb.h ? y : jb.h - 1;
   x = x < jb.w ? x : jb.w - 1;
   const int64_t idx = (int64_t)y * jb.row_stride + x;
-  return jb.dtype == AQMP_F64 ? ((const double*)jb.img)[idx] : (double)((const float*)jb.img)[idx];
+  return jb.dtype == AQMP_F64 ? ((const gmem_f64*)jb.img)[idx] : (double)((const gmem_f32*)jb.img)[idx];
 }
 
 // Host checks of one parameter set (AQMP_E_INVALID with tag + reason), and
@@ -87,11 +93,11 @@ __device__ inline void job_pixels(const JobDev& jb, int y, int x0, double (&v)[W
 #pragma unroll
   for (int j = 0; j < W; ++j) xs[j] = x0 + j < jb.w ? x0 + j : jb.w - 1;
   if (jb.dtype == AQMP_F64) {
-    const double* p = (const double*)jb.img + row;
+    const gmem_f64* p = (const gmem_f64*)jb.img + row;
 #pragma unroll
     for (int j = 0; j < W; ++j) v[j] = p[xs[j]];
   } else {
-    const float* p = (const float*)jb.img + row;
+    const gmem_f32* p = (const gmem_f32*)jb.img + row;
 #pragma unroll
     for (int j = 0; j < W; ++j) v[j] = (double)p[xs[j]];
   }
@@ -117,6 +123,14 @@ struct Counters {
   int32_t act[3];           // active-list lengths (rotating: in, out, cleared)
   int32_t scan_error;       // set if a bounded scan wait ran out
   int32_t next[kLevels];    // work counter of the dynamically scheduled kernels per level
+};
+
+// Work counters of the pursuits whose nodes are taken by many small workers:
+// kQueues per level, a cache line each, queue q handing out every kQueues-th
+// node.  (Thousands of workers on one counter waited in line for it: about
+// 12 ns each, 25 us for 2 048 waves that start together.)
+struct Queues {
+  int32_t at[kLevels][kQueues * kQueuePad];
 };
 
 // Look-back scan bookkeeping: one 64-bit word per tile plus two counters.
@@ -156,7 +170,7 @@ struct StepArgs {
 // ---------------------------------------------------------------------------
 // Launch wrappers (defined in the kernel translation units).
 // ---------------------------------------------------------------------------
-hipError_t launch_init_counts(Counters* c, const int32_t* ntop_dev, hipStream_t s);
+hipError_t launch_init_counts(Counters* c, Queues* q, const int32_t* ntop_dev, hipStream_t s);
 // p[0] = v and p[1 .. n-1] = 0, by a fill kernel.
 hipError_t launch_head_zero_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_gather(int n, const StepArgs& a, const int32_t* count, hipStream_t s);
@@ -175,6 +189,15 @@ hipError_t launch_corr(int n, int precision, int variant, const void* dict_atoms
                        int32_t m_pad, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t launch_select(int n, const StepArgs& a, int64_t cap, hipStream_t s, hipEvent_t ev0 = nullptr,
                          hipEvent_t ev1 = nullptr);
+// Whole-level pursuit of the dense solver at N = 32 and 64 with the
+// correlation factored through the atoms' outer products (`queue`: the level's
+// node counters, zero on entry; cap: its node capacity; ops: the table
+// operands launch_sep_ops made, sep_ops_bytes long, 0 for other N).
+size_t sep_ops_bytes(int n, int precision, uint32_t families);
+hipError_t launch_sep_ops(int n, int precision, uint32_t families, const double* tab, void* out, hipStream_t s);
+hipError_t launch_pursuit_sep(int n, int precision, uint32_t families, const JobDev* jobs, LevelDev lv,
+                              const int32_t* count, int32_t* queue, int64_t cap, const double* tab, const void* ops,
+                              hipStream_t s);
 hipError_t launch_mp_fused(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t lg, int32_t n_atoms,
                            const double* tab, hipStream_t s);
 // Whole-level BF16 pursuit of a level of N = 8 or 16 (next: the level's
@@ -260,5 +283,6 @@ struct aqmp_dict {
     double* d_xg = nullptr;        // [n][n] <T_0[p], T_1[p']> (two families only)
     float* d_f32 = nullptr;        // [m_pad][k]
     uint16_t* d_bf16 = nullptr;    // [m_pad][k]
+    void* d_sep[2] = {nullptr, nullptr};   // operands of the factored correlation, by precision
   } lv[aqmp::kLevels];
 };

@@ -157,7 +157,8 @@ __global__ __launch_bounds__(256) void k_head_zero_u32(uint32_t* p, int64_t n, u
     p[i] = i == 0 ? v : 0u;
 }
 
-__global__ void k_init_counts(Counters* c, const int32_t* ntop) {
+static_assert(kLevels * kQueues <= 64, "one thread per counter");
+__global__ void k_init_counts(Counters* c, Queues* q, const int32_t* ntop) {
   const int i = threadIdx.x;
   if (i < kLevels) {
     c->count[i] = ntop[i];
@@ -165,12 +166,13 @@ __global__ void k_init_counts(Counters* c, const int32_t* ntop) {
   }
   if (i < 3) c->act[i] = 0;
   if (i == 0) c->scan_error = 0;
+  if (i < kLevels * kQueues) q->at[i / kQueues][(i % kQueues) * kQueuePad] = 0;
 }
 
 }  // namespace
 
-hipError_t launch_init_counts(Counters* c, const int32_t* ntop_dev, hipStream_t s) {
-  hipLaunchKernelGGL(k_init_counts, dim3(1), dim3(64), 0, s, c, ntop_dev);
+hipError_t launch_init_counts(Counters* c, Queues* q, const int32_t* ntop_dev, hipStream_t s) {
+  hipLaunchKernelGGL(k_init_counts, dim3(1), dim3(64), 0, s, c, q, ntop_dev);
   return hipGetLastError();
 }
 

@@ -1,0 +1,154 @@
+"""The whole-level pursuits with the factored correlation against the
+step-by-step form (``stepwise``: the unfactored correlation and a select
+launch per MP step).  Both re-score in FP64 in the same order and store the
+same FP32 residual, so trees, atoms, coefficients and norms are equal bit for
+bit; only the ranking that proposes candidates differs."""
+import sys
+
+import numpy as np
+import pytest
+
+from workloads import gradient_edges_image, piecewise_image, workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def A():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_09190_amd import aqmp
+    return aqmp
+
+
+@pytest.fixture(scope="module")
+def dics(A):
+    made = {}
+
+    def get(fam):
+        if fam not in made:
+            made[fam] = A.Dictionary(8, 64, families=fam)
+        return made[fam]
+    yield get
+    for d in made.values():
+        d.free()
+
+
+def _dev(img, f64=False):
+    import torch
+    t = torch.from_numpy(np.ascontiguousarray(img))
+    return t.to(torch.float64 if f64 else torch.float32).cuda()
+
+
+def _nodes(A, dic, imgs, params, jobs, prec, **kw):
+    code = A.Code(dic, imgs, params, jobs, precision=prec, schedule=kw.pop("schedule", 1), **kw)
+    e = code.export_nodes()
+    code.free()
+    return e
+
+
+def _same(a, b):
+    assert a.leaves.tobytes() == b.leaves.tobytes()
+    assert a.atom_idx.tobytes() == b.atom_idx.tobytes()
+    assert a.coef.tobytes() == b.coef.tobytes()
+
+
+def _both(A, dic, imgs, params, jobs, prec, **kw):
+    step = _nodes(A, dic, imgs, params, jobs, prec, stepwise=True, **kw)
+    whole = _nodes(A, dic, imgs, params, jobs, prec, **kw)
+    _say("nodes", len(whole.leaves), "atoms", len(whole.atom_idx))
+    _same(whole, step)
+    return whole
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("fam", [1, 2, 3])
+def test_matches_stepwise(A, dics, prec, fam):
+    """Both block sizes, an odd plane, FP64 samples, both split rules, one and
+    two families, k beyond one record window."""
+    chans = [_dev(piecewise_image(200, 331, seed=5)), _dev(gradient_edges_image(150, 97, seed=6), True)]
+    params = [dict(tol=0.02, max_atoms=32, n_min=32, n_max=64), dict(tol=0.01, max_atoms=12, n_min=32, n_max=64, split_rule="r2"),
+              dict(tol=0.004, max_atoms=70, n_min=32, n_max=32), dict(tol=0.6, tol_mode="abs", max_atoms=5, n_min=64, n_max=64)]
+    jobs = [(i, p) for p in range(len(params)) for i in range(2)]
+    _say("stepwise", prec, fam)
+    _both(A, dics(fam), chans, params, jobs, prec)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("scale", [1e-30, 1e-12, 1e15, 1e30])
+def test_sample_scales(A, dics, prec, scale):
+    """Planes far from the usual range: the ranking neither underflows nor
+    overflows, and the atoms are those of the plane at its usual scale (a
+    power of two times it, so every product scales exactly)."""
+    s = 2.0 ** round(np.log2(scale))
+    img = piecewise_image(64, 128, seed=8)
+    p = dict(tol=0.03, max_atoms=10, n_min=32, n_max=64)
+    ref = _nodes(A, dics(3), [_dev(img)], [p], [(0, 0)], prec)
+    got = _nodes(A, dics(3), [_dev(img * s)], [dict(p, tol=0.03 * s)], [(0, 0)], prec)
+    _say("scale", s)
+    assert got.atom_idx.tobytes() == ref.atom_idx.tobytes()
+    assert (got.coef == ref.coef * s).all()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_exact_ties(A, dics, prec):
+    """Planes of zeros and ones, where many atoms tie at a step and the FP64
+    re-score decides among all of them; a constant and an all-zero plane;
+    k = 0.  The reference is the FP32 step-by-step form: the BF16 one keeps
+    eight candidates by BF16 correlation, and more than eight atoms that tie
+    differ there by BF16 rounding alone."""
+    rng = np.random.default_rng(9)
+    dots = (rng.random((64, 64)) < 0.02).astype(np.float64)
+    chk = np.zeros((64, 64))
+    chk[::2, ::2] = 1.0
+    one = np.zeros((64, 64))
+    one[17, 40] = 1.0
+    planes = [_dev(dots), _dev(chk), _dev(one), _dev(np.full((64, 64), 0.37)), _dev(np.zeros((64, 64)))]
+    params = [dict(tol=1e-4, max_atoms=12, n_min=32, n_max=64), dict(tol=0.0, max_atoms=3, n_min=64, n_max=64),
+              dict(tol=0.01, max_atoms=0, n_min=32, n_max=64)]
+    jobs = [(i, p) for p in range(len(params)) for i in range(len(planes))]
+    want = _nodes(A, dics(3), planes, params, jobs, 0, stepwise=True)
+    _same(_nodes(A, dics(3), planes, params, jobs, prec), want)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("fam", [1, 3])
+def test_undefined_pixels(A, dics, prec, fam):
+    """A plane with an infinite and one with an undefined pixel: their blocks
+    stop as in the step-by-step form, and the other blocks are untouched."""
+    base = piecewise_image(128, 128, seed=11)
+    planes = []
+    for v in (np.inf, np.nan):
+        a = base.copy()
+        a[70, 30] = v
+        planes.append(_dev(a))
+    p = dict(tol=0.02, max_atoms=8, n_min=64, n_max=64)
+    step = _nodes(A, dics(fam), planes, [p], [(0, 0), (1, 0)], prec, stepwise=True)
+    whole = _nodes(A, dics(fam), planes, [p], [(0, 0), (1, 0)], prec)
+    assert (whole.leaves["n_atoms"] == step.leaves["n_atoms"]).all()
+    assert whole.atom_idx.tobytes() == step.atom_idx.tobytes()
+    np.testing.assert_array_equal(whole.coef, step.coef)
+    np.testing.assert_array_equal(whole.leaves["resid_sq"], step.leaves["resid_sq"])
+
+
+@pytest.mark.parametrize("prec,sched", [(1, 0), (1, 2), (0, 0), (0, 2)])
+def test_schedules_and_replays(A, dics, prec, sched):
+    """Every schedule gives the batched result, and replays on other planes
+    and back reproduce it (nodes are handed out by a counter)."""
+    w = workload("c1")
+    p = dict(w["params"][0], n_min=32)
+    a, b = _dev(w["channels"][0]), _dev(piecewise_image(512, 512, seed=21))
+    ref = _nodes(A, dics(3), [a, b], [p], [(0, 0), (1, 0)], prec, stepwise=True)
+    code = A.Code(dics(3), [a, b], [p], [(0, 0), (1, 0)], precision=prec, schedule=sched)
+    for i in range(4):
+        _same(code.export_nodes(), ref)
+        code.reencode([b, a])
+        code.export_nodes()
+        code.reencode([a, b])
+    code.free()
