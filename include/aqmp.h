@@ -122,9 +122,9 @@ enum { AQMP_SOLVER_DENSE = 0, AQMP_SOLVER_GRAM = 1, AQMP_SOLVER_OMP = 2 };   /* 
 typedef struct {
   int32_t precision;   /* AQMP_PREC_FP32: FP32 MFMA correlation;
                           AQMP_PREC_BF16: 16-bit MFMA, FP32 accumulate
-                          (BF16 operands, or in the whole-level pursuits of
-                          N = 32 and 64 every operand as the sum of two FP16
-                          values, which is nearer to FP32).
+                          (BF16 operands step by step; in the whole-level
+                          pursuits of N >= 8 every operand as the sum of two
+                          FP16 values, which is nearer to FP32).
                           Both re-score the AQMP_CANDIDATES best atoms in
                           FP64 and take the coefficient and the stop/split
                           test in FP64. */
@@ -146,8 +146,8 @@ typedef struct {
                           MP step per launch (correlation and select)
                           instead of the whole-level pursuits; same method,
                           for comparison. */
-  int32_t corr_variant;  /* tuning: 0 = library default (N >= 32: the
-                            whole-level pursuit, whose correlation is
+  int32_t corr_variant;  /* tuning: 0 = library default (the
+                            whole-level pursuits, whose correlation is
                             factored through the atoms' outer products);
                             2, 3 or 6 run the BF16 levels of N >= 32 step by
                             step with one family of correlation kernels

@@ -324,13 +324,17 @@ bool sep_level(const aqmp_code* c, int n) {
   return c->opt.precision != AQMP_PREC_BF16 || forced_variant(c, ilog2(n)) == 0;
 }
 
-// Levels that run without per-step launches: N <= kFusedMaxN in both forms
-// (dense FP64 pursuit), N = 16 in the BF16 form (whole-level MFMA pursuit),
-// N >= 32 with the factored correlation, and every level of the Gram and OMP
-// solvers.
+// Dense levels whose wave-sized pursuit runs on the matrix cores: N = 16,
+// unless step by step, and N = 8 of the BF16 form.
+bool sub_level(const aqmp_code* c, int n) {
+  if (c->opt.solver != AQMP_SOLVER_DENSE) return false;
+  return n == 16 ? !(c->opt.flags & AQMP_OPT_STEPWISE) : (n == 8 && c->opt.precision == AQMP_PREC_BF16);
+}
+
+// Levels that run without per-step launches: every level of the dense solver
+// but N >= 16 step by step, and every level of the Gram and OMP solvers.
 bool whole_level(const aqmp_code* c, int n) {
-  if (n <= kFusedMaxN || c->opt.solver != AQMP_SOLVER_DENSE || sep_level(c, n)) return true;
-  return n == 16 && c->opt.precision == AQMP_PREC_BF16 && !(c->opt.flags & AQMP_OPT_STEPWISE);
+  return n <= kFusedMaxN || c->opt.solver != AQMP_SOLVER_DENSE || sep_level(c, n) || sub_level(c, n);
 }
 
 int build_plan(aqmp_code* c) {
@@ -540,14 +544,11 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
       } else if (sep_level(c, n))
         AQMP_LAUNCH(launch_pursuit_sep(n, c->opt.precision, d->families, c->djobs, a.lv, count, c->dqueue[pi].at[l], pp.cap[l],
                                        D.d_tab, D.d_sep[c->opt.precision], s));
-      else if (n == 8 && c->opt.precision == AQMP_PREC_BF16)
-        AQMP_LAUNCH(launch_pursuit_bf16(8, c->djobs, a.lv, count, &cnt->next[l], pp.cap[l], D.m, d->nfam, D.d_tab,
-                                        D.d_tabT32, s));
-      else if (n <= kFusedMaxN)
-        AQMP_LAUNCH(launch_mp_fused(n, c->djobs, a.lv, count, l, D.m, D.d_tab, s));
+      else if (sub_level(c, n))
+        AQMP_LAUNCH(launch_pursuit_sub(n, c->opt.precision, d->families, c->djobs, a.lv, count, c->dqueue[pi].at[l],
+                                       pp.cap[l], D.d_tab, s));
       else
-        AQMP_LAUNCH(launch_pursuit_bf16(16, c->djobs, a.lv, count, &cnt->next[l], pp.cap[l], D.m, d->nfam, D.d_tab,
-                                        D.d_tabT32, s));
+        AQMP_LAUNCH(launch_mp_fused(n, c->djobs, a.lv, count, l, D.m, D.d_tab, s));
       if (l > pp.lg_lo && pp.cap[l - 1] > 0)
         AQMP_LAUNCH(launch_split_emit(c->djobs, (int32_t)c->jobs.size(), a.lv, count, level_at(c, l - 1, pp.base[l - 1]), pp.ntop[l - 1],
                                       &cnt->count[l - 1], l, pp.cap[l], wk.ss, &cnt->scan_error, s));

@@ -594,6 +594,7 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
 #pragma unroll
         for (int j = 0; j < VPL; ++j)
           mask = __builtin_amdgcn_alignbit(mask, __float_as_uint(thr - fabsf(val(j))), 31);
+        if (!(mx > 0.f && mx < __builtin_inff())) mask = 0u;   // undefined sums: nothing to compare
       }
       auto atom_of = [&](int w, int l, int bit) -> int {   // wave of the node, lane, bit of its mask
         const int j = VPL - 1 - bit, f = j / (4 * G::TT * G::TQ), i = (j / (4 * G::TT)) % G::TQ, tp = (j >> 2) % G::TT;

@@ -1,0 +1,642 @@
+// kernels_sub.hip - whole-level Matching Pursuit of the dense solver for small
+// blocks on the matrix cores: N = 8 and 16 of the BF16 form, N = 16 of the
+// FP32 form.  A wave runs several nodes side by side (slots of LPS lanes),
+// with no workgroup barrier; the residual stays in registers from the gather
+// to the last step.
+//
+// The correlation is the factored one of kernels_sep.hip: C_f = T_f R T_f^T
+// for every family f, first D1[y][q] = sum_x R[y][x] T[q][x], then C[p][q] =
+// sum_y T[p][y] D1[y][q], whose lane layout makes D1 the B operand of the
+// second product as it is.  FP16 halves (BF16 form): the value and its
+// remainder of one operand sit side by side in the 32-deep contraction of
+// v_mfma_f32_16x16x32_f16, so one instruction makes two of the three
+// products:
+//   N = 16: A = [R hi | R lo] against [T hi; T hi] and (DCT) [T lo; 0];
+//   N = 8:  two nodes fill the 16 rows, both families the 16 columns, and
+//           A = [R hi | R lo | R hi | 0] against [T hi; T hi; T lo; 0] makes
+//           all three products at once.
+// Selection as in kernels_sep.hip: every atom whose |c| is within 2^-12 ||r||
+// of the largest is re-scored in FP64.
+//
+// What bounds it: the instructions of a step (about 400 for a wave's nodes
+// together), then the longest pursuits.  On three 2048 x 2048 planes N = 16
+// (157 690 node-steps) takes 124 us and N = 8 (170 692) 89 us; with the
+// unfactored BF16 product (8 or 4 times the operations) in workgroups of 16
+// slots, which met three times a step, 254 and 115 us.  FP32 form, 1536 x
+// 1024 x 3: N = 16 96 us, 1 870 us step by step.
+//
+// The order of operations of the FP64 re-score, update and norms is fixed by
+// the patches (SubGeo): BF16 form a slot of 32 (N = 16) or 16 lanes with rows
+// of four pixels per lane; FP32 form k_select's and k_gather's, so that it
+// equals the step-by-step form bit for bit.
+#include "internal.h"
+#include "dev_common.h"
+
+namespace aqmp {
+
+namespace {
+
+typedef _Float16 sb_h8 __attribute__((ext_vector_type(8)));
+typedef float sb_f32x4 __attribute__((ext_vector_type(4)));
+
+template <int N_, int FAMS_, bool BF_>
+struct SubGeo {
+  static constexpr int N = N_, K = N * N, FAMS = FAMS_;
+  static constexpr bool BF = BF_;
+  static constexpr int NFAM = FAMS == 3 ? 2 : 1;
+  static constexpr int SN = BF ? (N == 16 ? 2 : 4) : 1;   // nodes per wave
+  static constexpr int LPS = 64 / SN;                     // lanes per slot
+  static constexpr int PC = BF ? 4 : 2;                   // patch: columns,
+  static constexpr int PR = K / LPS / PC;                 // rows of a lane
+  static constexpr int XQ = N / PC;                       // patches per row of patches
+  // values per lane and node: N = 16 four per family; N = 8 four (rows and
+  // columns of one family meet in half of the lanes)
+  static constexpr int VPL = N == 16 ? 4 * NFAM : 4;
+  // operand row in LDS (value half, remainder half, padding against bank
+  // conflicts), and bytes per node
+  static constexpr int ROWB = N == 16 ? 80 : 48;
+  static constexpr int NODEB = N * ROWB;
+  static constexpr float TS = BF ? 128.f : 1.f;           // see SepGeo::TS
+  static_assert(N == 16 || (N == 8 && BF), "block sizes");
+  static_assert(PR * PC * LPS == K && PR >= 1 && VPL <= 8, "patches");
+};
+
+__device__ inline uint32_t sb_split_hi(float a, float b) {
+  const auto p = __builtin_amdgcn_cvt_pkrtz(a, b);
+  uint32_t h;
+  __builtin_memcpy(&h, &p, 4);
+  return h;
+}
+// packed FP16 remainders of a pair (see sp_split2)
+__device__ inline uint32_t sb_split_lo(float a, float b, uint32_t h) {
+  uint32_t l;
+  __asm__("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(l) : "v"(h), "v"(a));
+  __asm__("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(l) : "v"(h), "v"(b));
+  return l;
+}
+
+// Table operands.  BF16 form: t1 the B operands of the first product, t2 the
+// A operands of the second; index 0 the products with [T hi; T hi] (N = 8:
+// all three), 1 the DCT's remainders.  FP32 form: t[f][r] = T_f[lane % 16][4 g + r].
+template <class G>
+struct SubOps {
+  sb_h8 t1[G::BF ? G::NFAM : 1], t1l[1], t2[G::BF ? (G::N == 8 ? 2 : G::NFAM) : 1], t2l[G::N == 8 ? 2 : 1];
+  float t[G::BF ? 1 : G::NFAM][4];
+  float sc[4];                                            // N = 16: Haar magnitudes of rows 4 g + r and the lane's column
+};
+
+template <class G>
+__device__ constexpr bool sub_haar(int f) { return G::FAMS == AQMP_HAAR || (G::FAMS == 3 && f == 1); }
+
+// tabs: the FP64 tables of the dictionary's families, [f][row][col].
+template <class G>
+__device__ inline void sub_load_ops(SubOps<G>& T, const double* tabs) {
+  constexpr int N = G::N, K = G::K;
+  const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+  // operand value: scaled DCT entry, or Haar entry (its sign for N = 16)
+  auto hi_lo = [](float v, _Float16& h, _Float16& l) {
+    h = (_Float16)v;
+    l = (_Float16)(v - (float)h);
+  };
+  if constexpr (!G::BF) {
+#pragma unroll
+    for (int f = 0; f < G::NFAM; ++f)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) T.t[f][r] = (float)tabs[f * K + m * N + 4 * g + r];
+  } else if constexpr (N == 16) {
+#pragma unroll
+    for (int f = 0; f < G::NFAM; ++f) {
+      const bool hr = sub_haar<G>(f);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        // first product: k = 8 g + j is pixel x = k % 16 (value, then remainder of R)
+        const double a = tabs[f * K + m * N + ((8 * g + j) & 15)];
+        // second: k-slot (g, j) is row y = 4 g + j % 4 (value, then remainder of D1)
+        const double b = tabs[f * K + m * N + 4 * g + (j & 3)];
+        if (hr) {
+          T.t1[f][j] = (_Float16)(a > 0.0 ? 1.f : (a < 0.0 ? -1.f : 0.f));
+          T.t2[f][j] = (_Float16)(b > 0.0 ? 1.f : (b < 0.0 ? -1.f : 0.f));
+        } else {
+          _Float16 h, l;
+          hi_lo((float)a * G::TS, h, l);
+          T.t1[f][j] = h;
+          T.t1l[0][j] = g < 2 ? l : (_Float16)0.f;
+          hi_lo((float)b * G::TS, h, l);
+          T.t2[f][j] = h;
+          T.t2l[0][j] = j < 4 ? l : (_Float16)0.f;
+        }
+      }
+      if (hr) {
+        auto mag = [&](int row) -> float {
+          int at = 0;
+          if (row > 0) {
+            const int top = 1 << (31 - __builtin_clz((unsigned)row));
+            at = (row - top) * (N / top);
+          }
+          return (float)tabs[f * K + row * N + at];
+        };
+        const float mq = mag(m) * (G::TS * G::TS);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) T.sc[r] = mag(4 * g + r) * mq;
+      }
+    }
+  } else {
+    // N = 8: column n = 8 f + q of the first product, row 8 f + p of the
+    // second; all entries scaled values (no sign form).  k-slots of the
+    // first: g = 0 (R hi) T hi, g = 1 (R lo) T hi, g = 2 (R hi) T lo, g = 3 zero;
+    // of the second, for the node of rows g / 2 == u: (g, j) is row
+    // y = 4 (g % 2) + j % 4 of D1's values, then remainders.
+    const int fc = m >> 3, c = m & 7;
+    const bool ok = fc < G::NFAM;
+    const double* tf = tabs + (ok ? fc : 0) * K + c * N;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      _Float16 h, l;
+      hi_lo(ok ? (float)tf[j] * G::TS : 0.f, h, l);
+      T.t1[0][j] = g < 2 ? h : (g == 2 ? l : (_Float16)0.f);
+      hi_lo(ok ? (float)tf[4 * (g & 1) + (j & 3)] * G::TS : 0.f, h, l);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        T.t2[u][j] = (g >> 1) == u ? h : (_Float16)0.f;
+        T.t2l[u][j] = (g >> 1) == u && j < 4 ? l : (_Float16)0.f;
+      }
+    }
+  }
+}
+
+// Correlations of the wave's nodes with all atoms, scaled by TS^2 and the
+// node's row scale: V[n][v], atom_of(lane, v).
+template <class G>
+__device__ inline void sub_correlate(const char* sR, const SubOps<G>& T, float (&V)[G::SN][G::VPL]) {
+  const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+  const sb_f32x4 z4{0.f, 0.f, 0.f, 0.f};
+  if constexpr (!G::BF) {
+    const sb_f32x4 rv = *(const sb_f32x4*)(sR + m * G::ROWB + 16 * g);
+    sb_f32x4 D[G::NFAM];
+#pragma unroll
+    for (int f = 0; f < G::NFAM; ++f) D[f] = z4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int f = 0; f < G::NFAM; ++f) D[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(rv[r], T.t[f][r], D[f], 0, 0, 0);
+    sb_f32x4 C[G::NFAM];
+#pragma unroll
+    for (int f = 0; f < G::NFAM; ++f) C[f] = z4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int f = 0; f < G::NFAM; ++f) C[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(T.t[f][r], D[f][r], C[f], 0, 0, 0);
+#pragma unroll
+    for (int f = 0; f < G::NFAM; ++f)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) V[0][4 * f + r] = C[f][r];
+  } else if constexpr (G::N == 16) {
+    sb_f32x4 D[G::SN][G::NFAM];
+#pragma unroll
+    for (int n = 0; n < G::SN; ++n) {
+      const sb_h8 a = *(const sb_h8*)(sR + n * G::NODEB + m * G::ROWB + 16 * g);
+#pragma unroll
+      for (int f = 0; f < G::NFAM; ++f) {
+        D[n][f] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, T.t1[f], z4, 0, 0, 0);
+        if (!sub_haar<G>(f)) D[n][f] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, T.t1l[0], D[n][f], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < G::SN; ++n)
+#pragma unroll
+      for (int f = 0; f < G::NFAM; ++f) {
+        const sb_f32x4 d = D[n][f];
+        uint32_t w[4];
+        w[0] = sb_split_hi(d[0], d[1]);
+        w[1] = sb_split_hi(d[2], d[3]);
+        w[2] = sb_split_lo(d[0], d[1], w[0]);
+        w[3] = sb_split_lo(d[2], d[3], w[1]);
+        sb_h8 b;
+        __builtin_memcpy(&b, w, 16);
+        sb_f32x4 c = __builtin_amdgcn_mfma_f32_16x16x32_f16(T.t2[f], b, z4, 0, 0, 0);
+        if (!sub_haar<G>(f)) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(T.t2l[0], b, c, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) V[n][4 * f + r] = sub_haar<G>(f) ? c[r] * T.sc[r] : c[r];
+      }
+  } else {
+    sb_f32x4 D[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {   // nodes 2 u and 2 u + 1: 16 rows
+      const sb_h8 a = *(const sb_h8*)(sR + 2 * u * G::NODEB + m * G::ROWB + (g == 1 ? 16 : 0));
+      D[u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, T.t1[0], z4, 0, 0, 0);
+    }
+    const bool on = (g >> 1) == (m >> 3);   // rows and columns of one family
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const sb_f32x4 d = D[u];
+      uint32_t w[4];
+      w[0] = sb_split_hi(d[0], d[1]);
+      w[1] = sb_split_hi(d[2], d[3]);
+      w[2] = sb_split_lo(d[0], d[1], w[0]);
+      w[3] = sb_split_lo(d[2], d[3], w[1]);
+      sb_h8 b;
+      __builtin_memcpy(&b, w, 16);
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        sb_f32x4 c = __builtin_amdgcn_mfma_f32_16x16x32_f16(T.t2[v], b, z4, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(T.t2l[v], b, c, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) V[2 * u + v][r] = on ? c[r] : 0.f;
+      }
+    }
+  }
+}
+
+// Atom of value v in lane l (see sub_correlate).
+template <class G>
+__device__ inline int sub_atom(int l, int v) {
+  const int m = l & 15, g = l >> 4;
+  if constexpr (G::N == 16) return (v >> 2) * G::K + m * 16 + 4 * g + (v & 3);
+  else return (m >> 3) * G::K + (m & 7) * 8 + 4 * (g & 1) + v;
+}
+
+// Sum over the lanes of a slot, a butterfly (every lane gets the same bits).
+template <class G>
+__device__ inline double sub_slot_sum(double v) {
+  if constexpr (G::LPS == 64) {
+    return wave_sum_f64(v);
+  } else {
+    if constexpr (G::LPS == 32) v = lane_pair_sum_f64<16>(v);
+    v += row_perm_f64<0x128>(v);   // row_ror:8
+    v += row_perm_f64<0x141>(v);   // row_half_mirror
+    v += row_perm_f64<0x4E>(v);    // quad_perm [2,3,0,1]
+    v += row_perm_f64<0xB1>(v);    // quad_perm [1,0,3,2]
+    return v;
+  }
+}
+
+template <class G>
+__device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelDev& lv,
+                                   const int32_t* __restrict__ count_ptr, int32_t* __restrict__ queue,
+                                   const double* __restrict__ tab) {
+  constexpr int N = G::N, K = G::K, SN = G::SN, LPS = G::LPS, PR = G::PR, PC = G::PC, VPL = G::VPL;
+  constexpr bool BF = G::BF;
+  constexpr int lg = N == 16 ? 4 : 3;
+  __shared__ __attribute__((aligned(16))) double sTab[G::NFAM][N][N];
+  __shared__ __attribute__((aligned(16))) char sRows[4][SN * G::NODEB];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  char* sR = sRows[wv];
+  for (int i = tid; i < G::NFAM * K; i += 256) (&sTab[0][0][0])[i] = tab[i];
+  for (int i = lane; i < SN * G::NODEB / 16; i += 64) ((uint4*)sR)[i] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  SubOps<G> T;
+  sub_load_ops<G>(T, &sTab[0][0][0]);
+  const int count = *count_ptr;
+  const double inv_n = 1.0 / N;
+  const int slot = lane / LPS, li = lane % LPS;
+  const int py = (li / G::XQ) * PR, px = (li % G::XQ) * PC;
+  char* sRow = sR + slot * G::NODEB;
+  // The first nodes are dealt out in order, the others by the queues.
+  const int q0 = (int)gridDim.x * 4 * SN, qk = (int)blockIdx.x % kQueues;
+  int node = ((int)blockIdx.x * 4 + wv) * SN + slot;
+  int ahead = 0;                       // the slot's next node (its first lane)
+  bool dry = node >= count, run = false, load = !dry;
+  int t = 0, kmax = 0, rec_i = 0;
+  double rec_c = 0.0, e = 0.0, eps2 = 0.0;
+  float sc = 1.f;
+  double rd[PR][PC];
+#pragma unroll
+  for (int i = 0; i < PR; ++i)
+#pragma unroll
+    for (int j = 0; j < PC; ++j) rd[i][j] = 0.0;
+
+  auto scale_of = [](double en) -> float {   // see k_pursuit_sep
+    const int ex = (int)((unsigned long long)__double_as_longlong(en) >> 52) - 1023;
+    int sh = ex >> 1;
+    if constexpr (BF) sh -= 7;
+    else if (ex >= -40 && ex < 80) return 1.f;
+    sh = sh < -120 ? -120 : (sh > 120 ? 120 : sh);
+    return __uint_as_float((uint32_t)(127 - sh) << 23);
+  };
+  auto put_rows = [&]() {
+#pragma unroll
+    for (int i = 0; i < PR; ++i) {
+      char* row = sRow + (py + i) * G::ROWB;
+      if constexpr (BF) {
+        float v[PC];
+#pragma unroll
+        for (int j = 0; j < PC; ++j) v[j] = (float)rd[i][j] * sc;
+        const uint32_t h0 = sb_split_hi(v[0], v[1]), h1 = sb_split_hi(v[2], v[3]);
+        *(uint2*)(row + 2 * px) = make_uint2(h0, h1);
+        *(uint2*)(row + 2 * N + 2 * px) = make_uint2(sb_split_lo(v[0], v[1], h0), sb_split_lo(v[2], v[3], h1));
+      } else {
+        *(float2*)(row + 4 * px) = make_float2((float)rd[i][0] * sc, (float)rd[i][1] * sc);
+      }
+    }
+  };
+
+  for (;;) {
+    // ---- slots without a node take their next one ----
+    if (__ballot(load) != 0ull) {
+      if (load) {
+        if (li == 0) ahead = atomicAdd(queue + qk * kQueuePad, 1);
+        const int jidx = lv.job[node];
+        const int bx = lv.x0[node], by = lv.y0[node];
+        const JobDev jl = jobs[jidx];
+        eps2 = jobs[jidx].eps2[lg];
+        kmax = jobs[jidx].k[lg];
+        if constexpr (BF) {
+          double pv[PR][PC];
+#pragma unroll
+          for (int i = 0; i < PR; ++i) job_pixels<PC>(jl, by + py + i, bx + px, pv[i]);
+          double ep = 0.0;
+#pragma unroll
+          for (int i = 0; i < PR; ++i) {
+            double ei = 0.0;
+#pragma unroll
+            for (int j = 0; j < PC; ++j) {
+              rd[i][j] = (double)(float)pv[i][j];
+              ei = fma(pv[i][j], pv[i][j], ei);
+            }
+            ep += ei;
+          }
+          e = sub_slot_sum<G>(ep);
+        } else {
+          // k_gather's layout: one pixel per thread of four waves
+          double gv[4], pv[PR][PC];
+#pragma unroll
+          for (int w = 0; w < 4; ++w) gv[w] = job_pixel(jl, by + 4 * w + (lane >> 4), bx + (lane & 15));
+#pragma unroll
+          for (int i = 0; i < PR; ++i) job_pixels<PC>(jl, by + py + i, bx + px, pv[i]);
+#pragma unroll
+          for (int i = 0; i < PR; ++i)
+#pragma unroll
+            for (int j = 0; j < PC; ++j) rd[i][j] = (double)(float)pv[i][j];
+          double s[4];
+#pragma unroll
+          for (int w = 0; w < 4; ++w) s[w] = wave_sum_f64(gv[w] * gv[w]);
+          e = (s[0] + s[1]) + (s[2] + s[3]);
+        }
+        t = 0;
+        uint8_t st = ST_RUN;
+        if (e < eps2)
+          st = ST_ACC;
+        else if (kmax <= 0)
+          st = ST_SPARSE;
+        else if (!(e > 0.0 && e < __builtin_inf()))   // a zero residual, or undefined pixels: nothing to select
+          st = ST_ZERO;
+        run = st == ST_RUN;
+        if (run) {
+          sc = scale_of(e);
+          put_rows();
+        } else if (li == 0) {
+          lv.e[node] = e;
+          lv.t[node] = 0;
+          lv.st[node] = st;
+        }
+      }
+    }
+    const unsigned long long runs = __ballot(run);
+    if (runs != 0ull) {
+      wave_sync();
+      // ---- correlations; per node the atoms within the window of its largest ----
+      float V[SN][VPL];
+      sub_correlate<G>(sR, T, V);
+      if constexpr (G::NFAM == 2) {
+        // the second family's constant atom equals the first's, which wins the tie
+        const bool dc1 = lane == (N == 16 ? 0 : 40);
+        constexpr int v1 = N == 16 ? 4 : 0;
+#pragma unroll
+        for (int n = 0; n < SN; ++n) V[n][v1] = dc1 ? 0.f : V[n][v1];
+      }
+      wave_sync();   // the rows are read before any slot writes new ones
+      const float win = __builtin_amdgcn_sqrtf((float)(e * ((double)sc * (double)sc))) * (1.0001f * 0x1p-12f * G::TS * G::TS);
+      unsigned long long lanes[SN];
+      uint32_t mask[SN], bits[SN];
+      bool more = false;
+      int cand = 0;
+#pragma unroll
+      for (int n = 0; n < SN; ++n) {
+        float m0 = 0.f;
+#pragma unroll
+        for (int v = 0; v < VPL; v += 2) m0 = fmaxf(fmaxf(fabsf(V[n][v]), fabsf(V[n][v + 1])), m0);
+        const float mx = wave_max_f32(m0);
+        const float wn = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(win), n * LPS));
+        const float thr = mx - wn;
+        uint32_t mk = 0u;
+#pragma unroll
+        for (int v = 0; v < VPL; ++v) mk = __builtin_amdgcn_alignbit(mk, __float_as_uint(thr - fabsf(V[n][v])), 31);
+        // a slot at rest, or infinite or undefined sums: nothing to compare
+        const bool alive = ((runs >> (n * LPS)) & 1ull) != 0ull && mx > 0.f && mx < __builtin_inff();
+        mask[n] = alive ? mk : 0u;
+        lanes[n] = __ballot(mask[n] != 0u);
+        // the first candidate; whether there are others
+        const int l = lanes[n] ? __builtin_ctzll(lanes[n]) : 0;
+        bits[n] = (uint32_t)__builtin_amdgcn_readlane((int)mask[n], l);
+        int at = -1;
+        if (lanes[n]) {
+          at = sub_atom<G>(l, VPL - 1 - __builtin_ctz(bits[n]));
+          bits[n] &= bits[n] - 1u;
+          if (bits[n] == 0u) lanes[n] &= lanes[n] - 1ull;
+          more = more || lanes[n] != 0ull;
+        }
+        cand = slot == n ? at : cand;
+      }
+      // ---- FP64 re-score of the slot's candidate ----
+      double tq[PC], tp[PR];
+      auto rows = [&](int a) {
+        const int f = a / K, q = (a % K) / N, p = a % N;
+#pragma unroll
+        for (int j = 0; j < PC; j += 2) {
+          const double2 v = *(const double2*)&sTab[f][q][px + j];
+          tq[j] = v.x;
+          tq[j + 1] = v.y;
+        }
+#pragma unroll
+        for (int i = 0; i < PR; ++i) tp[i] = sTab[f][p][py + i];
+      };
+      auto rescore = [&](int a) -> double {   // a >= 0
+        rows(a);
+        const bool dc = (a % K) == 0;
+        double part = 0.0;
+        if constexpr (BF) {
+          double dcp = 0.0;
+#pragma unroll
+          for (int i = 0; i < PR; ++i) {
+            const double sy = fma(rd[i][0], tq[0], rd[i][1] * tq[1]) + fma(rd[i][2], tq[2], rd[i][3] * tq[3]);
+            part = i == 0 ? tp[0] * sy : fma(tp[i], sy, part);
+            dcp += (rd[i][0] + rd[i][1]) + (rd[i][2] + rd[i][3]);
+          }
+          part = dc ? dcp * inv_n : part;
+        } else {
+          double dcp = 0.0;
+#pragma unroll
+          for (int i = 0; i < PR; ++i) {
+            double sr = 0.0, sd = 0.0;
+#pragma unroll
+            for (int j = 0; j < PC; ++j) {
+              sr = fma(rd[i][j], tq[j], sr);
+              sd += rd[i][j];
+            }
+            part = fma(tp[i], sr, part);
+            dcp += sd;
+          }
+          part = dc ? dcp * inv_n : part;
+        }
+        return sub_slot_sum<G>(part);
+      };
+      int atom = cand;
+      double coef = rescore(cand < 0 ? 0 : cand);
+      double mag = cand < 0 ? 0.0 : fabs(coef);
+      if (more) {
+        // the other atoms of the windows, lowest index on ties
+        while (more) {
+          more = false;
+          int at = -1;
+#pragma unroll
+          for (int n = 0; n < SN; ++n) {
+            int an = -1;
+            if (lanes[n]) {
+              const int l = __builtin_ctzll(lanes[n]);
+              if (bits[n] == 0u) bits[n] = (uint32_t)__builtin_amdgcn_readlane((int)mask[n], l);
+              an = sub_atom<G>(l, VPL - 1 - __builtin_ctz(bits[n]));
+              bits[n] &= bits[n] - 1u;
+              if (bits[n] == 0u) lanes[n] &= lanes[n] - 1ull;
+              more = more || lanes[n] != 0ull;
+            }
+            at = slot == n ? an : at;
+          }
+          const double c0 = rescore(at < 0 ? 0 : at), m0 = fabs(c0);
+          const bool take = at >= 0 && (m0 > mag || (m0 == mag && at < atom));
+          mag = take ? m0 : mag;
+          coef = take ? c0 : coef;
+          atom = take ? at : atom;
+        }
+        rows(atom < 0 ? 0 : atom);
+      }
+      // ---- rank-1 update, norm, record, stop test ----
+      uint8_t st = ST_RUN;
+      const bool zero = !(mag > 0.0);
+      const bool dc = (atom % K) == 0;
+      double en = 0.0;
+#pragma unroll
+      for (int i = 0; i < PR; ++i) {
+        double ei = 0.0;
+#pragma unroll
+        for (int j = 0; j < PC; ++j) {
+          const double phi = dc ? inv_n : tp[i] * tq[j];
+          const double rn = (double)(float)fma(-coef, phi, rd[i][j]);
+          rd[i][j] = zero ? rd[i][j] : rn;
+          ei = fma(rn, rn, ei);
+        }
+        en += ei;
+      }
+      en = sub_slot_sum<G>(en);
+      if (run) {
+        if (zero) {
+          st = ST_ZERO;
+        } else {
+          e = en;
+          if (li == (t & (LPS - 1))) {
+            rec_i = atom;
+            rec_c = coef;
+          }
+          ++t;
+          if (e < eps2)
+            st = ST_ACC;
+          else if (t >= kmax)
+            st = ST_SPARSE;
+          else if (!(e > 0.0))
+            st = ST_ZERO;
+          if (BF || st == ST_RUN) sc = scale_of(e);
+          if (st == ST_RUN) put_rows();
+          const int base = (t - 1) & ~(LPS - 1);   // first step held in the registers
+          if (st != ST_RUN || t - base == LPS) {
+            if (li < t - base) {
+              const size_t rs = (size_t)node * lv.kmax + base + li;
+              lv.rec_idx[rs] = rec_i;
+              lv.rec_coef[rs] = rec_c;
+            }
+          }
+        }
+        if (zero) {
+          const int base = t & ~(LPS - 1);
+          if (li < t - base) {
+            const size_t rs = (size_t)node * lv.kmax + base + li;
+            lv.rec_idx[rs] = rec_i;
+            lv.rec_coef[rs] = rec_c;
+          }
+        }
+        if (st != ST_RUN && li == 0) {
+          lv.e[node] = e;
+          lv.t[node] = t;
+          lv.st[node] = st;
+        }
+        run = st == ST_RUN;
+      }
+    }
+    // ---- the next node of the slots that ended ----
+    load = false;
+    if (__ballot(!run && !dry) != 0ull) {
+      const int idx = q0 + __shfl(ahead, lane & ~(LPS - 1), 64) * kQueues + qk;
+      if (!run && !dry) {
+        node = idx;
+        dry = idx >= count;
+        load = !dry;
+      }
+    }
+    if (__ballot(run || load) == 0ull) break;
+  }
+}
+
+template <int N, int FAMS>
+__global__ __launch_bounds__(256) void k_pursuit_bf16(const JobDev* __restrict__ jobs, LevelDev lv,
+                                                      const int32_t* __restrict__ count_ptr,
+                                                      int32_t* __restrict__ queue, const double* __restrict__ tab) {
+  pursuit_sub<SubGeo<N, FAMS, true>>(jobs, lv, count_ptr, queue, tab);
+}
+
+template <int FAMS>
+__global__ __launch_bounds__(256) void k_pursuit16_f32(const JobDev* __restrict__ jobs, LevelDev lv,
+                                                       const int32_t* __restrict__ count_ptr,
+                                                       int32_t* __restrict__ queue, const double* __restrict__ tab) {
+  pursuit_sub<SubGeo<16, FAMS, false>>(jobs, lv, count_ptr, queue, tab);
+}
+
+// As many workgroups as are resident at once, at most one per 4 SN nodes.
+template <class Kern>
+hipError_t launch_sub(Kern kern, int nodes_per_wg, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* queue,
+                      int64_t cap, const double* tab, hipStream_t s) {
+  int dev = 0, n_cus = 0, per_cu = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, 0) != hipSuccess || per_cu < 1) per_cu = 1;
+  int64_t wgs = (cap + nodes_per_wg - 1) / nodes_per_wg;
+  if (wgs > (int64_t)n_cus * per_cu) wgs = (int64_t)n_cus * per_cu;
+  if (wgs < 1) wgs = 1;
+  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(256), 0, s, jobs, lv, count, queue, tab);
+  return hipGetLastError();
+}
+
+template <int FAMS>
+hipError_t launch_sub_f(int n, int precision, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* queue,
+                        int64_t cap, const double* tab, hipStream_t s) {
+  if (precision == AQMP_PREC_BF16) {
+    if (n == 8) return launch_sub(k_pursuit_bf16<8, FAMS>, 4 * SubGeo<8, FAMS, true>::SN, jobs, lv, count, queue, cap, tab, s);
+    if (n == 16) return launch_sub(k_pursuit_bf16<16, FAMS>, 4 * SubGeo<16, FAMS, true>::SN, jobs, lv, count, queue, cap, tab, s);
+  } else if (n == 16) {
+    return launch_sub(k_pursuit16_f32<FAMS>, 4, jobs, lv, count, queue, cap, tab, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+hipError_t launch_pursuit_sub(int n, int precision, uint32_t families, const JobDev* jobs, LevelDev lv,
+                              const int32_t* count, int32_t* queue, int64_t cap, const double* tab, hipStream_t s) {
+  switch (families) {
+    case AQMP_DCT: return launch_sub_f<AQMP_DCT>(n, precision, jobs, lv, count, queue, cap, tab, s);
+    case AQMP_HAAR: return launch_sub_f<AQMP_HAAR>(n, precision, jobs, lv, count, queue, cap, tab, s);
+    case AQMP_DCT | AQMP_HAAR: return launch_sub_f<AQMP_DCT | AQMP_HAAR>(n, precision, jobs, lv, count, queue, cap, tab, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace aqmp

@@ -8,6 +8,8 @@ import sys
 import numpy as np
 import pytest
 
+from oracle import aqmp_oracle as O
+from tests import parity_util as PU
 from workloads import gradient_edges_image, piecewise_image, workload
 
 pytestmark = pytest.mark.gpu
@@ -152,3 +154,77 @@ def test_schedules_and_replays(A, dics, prec, sched):
         code.export_nodes()
         code.reencode([a, b])
     code.free()
+
+
+@pytest.mark.parametrize("fam", [1, 2, 3])
+def test_small_blocks_fp32_match_stepwise(A, dics, fam):
+    """N = 16 of the FP32 form: a node per wave, k across record windows."""
+    chans = [_dev(piecewise_image(75, 133, seed=15)), _dev(gradient_edges_image(40, 210, seed=16), True)]
+    params = [dict(tol=0.02, max_atoms=32, n_min=16, n_max=64), dict(tol=0.002, max_atoms=70, n_min=16, n_max=16),
+              dict(tol=0.03, max_atoms=7, n_min=8, n_max=16, split_rule="r2")]
+    jobs = [(i, p) for p in range(len(params)) for i in range(2)]
+    _both(A, dics(fam), chans, params, jobs, 0)
+
+
+@pytest.mark.parametrize("fam", [1, 2, 3])
+def test_small_blocks_bf16_match_fp32(A, dics, fam):
+    """N = 16 and 8 of the BF16 form (two and four nodes per wave) choose the
+    FP32 form's trees and atoms; the coefficients differ by the order of
+    FP64 sums and the FP32 roundings of the residual that it moves: at most
+    2^-24 of the plane's range per pixel and step, over a unit atom."""
+    chans = [_dev(piecewise_image(75, 133, seed=17)), _dev(gradient_edges_image(200, 150, seed=18), True)]
+    params = [dict(tol=0.02, max_atoms=32, n_min=8, n_max=16), dict(tol=0.006, max_atoms=40, n_min=8, n_max=8),
+              dict(tol=0.01, max_atoms=20, n_min=16, n_max=16, split_rule="r2"), dict(tol=0.2, tol_mode="abs", max_atoms=3, n_min=8, n_max=16)]
+    jobs = [(i, p) for p in range(len(params)) for i in range(2)]
+    want = _nodes(A, dics(fam), chans, params, jobs, 0, stepwise=True)
+    got = _nodes(A, dics(fam), chans, params, jobs, 1)
+    _say("nodes", len(got.leaves), "atoms", len(got.atom_idx))
+    for f in ("job", "x0", "y0", "n", "n_atoms", "flags"):
+        assert (got.leaves[f] == want.leaves[f]).all(), f
+    assert got.atom_idx.tobytes() == want.atom_idx.tobytes()
+    tol = 2.0 ** -24 * 16 * np.sqrt(40)          # N <= 16 pixels a side, 40 steps of independent roundings
+    assert np.abs(got.coef - want.coef).max() <= tol
+    assert np.abs(got.leaves["resid_sq"] - want.leaves["resid_sq"]).max() <= 16 * tol
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_small_blocks_edges(A, dics, prec):
+    """Small blocks that end at once or tie: zero and constant planes, k = 0,
+    exact ties of binary dots, one node."""
+    rng = np.random.default_rng(19)
+    dots = (rng.random((32, 48)) < 0.05).astype(np.float64)
+    planes = [dots, np.full((33, 17), 0.3), np.zeros((16, 16)), dots[:5, :7]]
+    params = [dict(tol=1e-4, max_atoms=10, n_min=8, n_max=16), dict(tol=0.0, max_atoms=3, n_min=16, n_max=16),
+              dict(tol=0.01, max_atoms=0, n_min=8, n_max=16), dict(tol=1e-5, max_atoms=20, n_min=8, n_max=8)]
+    jobs = [(i, p) for p in range(len(params)) for i in range(len(planes))]
+    got = _nodes(A, dics(3), [_dev(x) for x in planes], params, jobs, prec)
+    if prec == 0:
+        _same(got, _nodes(A, dics(3), [_dev(x) for x in planes], params, jobs, 0, stepwise=True))
+        return
+    # the BF16 form sums in another order, which decides exact ties: the oracle's tie rules
+    rep = PU.Report()
+    for j, (i, p) in enumerate(jobs):
+        on = O.encode_channel(planes[i].astype(np.float32).astype(np.float64), O.Params.from_dict(params[p]))
+        PU.compare_job(planes[i], on, PU.gpu_nodes_by_key(got, j), 2e-3, params[p]["n_max"], rep=rep)
+    _say(rep.summary())
+    assert rep.ok(), rep.summary()
+
+
+@pytest.mark.parametrize("prec,n", [(0, 16), (1, 16), (1, 8)])
+def test_small_blocks_undefined_pixels(A, dics, prec, n):
+    """A block with an infinite or undefined pixel selects nothing; the others
+    are those of the plane without it."""
+    good = piecewise_image(48, 32, seed=20)
+    bad = good.copy()
+    bad[3, 5], bad[40, 9] = np.inf, np.nan
+    p = dict(tol=0.01, max_atoms=9, n_min=n, n_max=n)
+    g = _nodes(A, dics(3), [_dev(good)], [p], [(0, 0)], prec)
+    b = _nodes(A, dics(3), [_dev(bad)], [p], [(0, 0)], prec)
+    for i in range(len(g.leaves)):
+        u, v = g.leaves[i], b.leaves[i]
+        assert (u["x0"], u["y0"]) == (v["x0"], v["y0"])
+        if not np.isfinite(bad[u["y0"]:u["y0"] + n, u["x0"]:u["x0"] + n]).all():
+            assert v["n_atoms"] == 0
+            continue
+        su, sv = slice(u["atom_off"], u["atom_off"] + u["n_atoms"]), slice(v["atom_off"], v["atom_off"] + v["n_atoms"])
+        assert (g.atom_idx[su] == b.atom_idx[sv]).all() and (g.coef[su] == b.coef[sv]).all()
