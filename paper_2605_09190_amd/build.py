@@ -19,7 +19,7 @@ OUT = os.path.join(HERE, "libaqmp.so")
 OBJ = os.path.join(ROOT, "_build")
 SOURCES = ["api.hip", "dict.hip", "encode.hip", "kernels_tree.hip", "kernels_mp.hip", "kernels_corr.hip",
            "kernels_fused.hip", "kernels_sep.hip",
-           "kernels_sub.hip", "kernels_gram.hip", "kernels_ssim.hip", "kernels_export.hip", "worklist.hip",
+           "kernels_sub.hip", "kernels_decode.hip", "kernels_gram.hip", "kernels_ssim.hip", "kernels_export.hip", "worklist.hip",
            "host_core.cpp"]
 ARCH = "gfx950"
 

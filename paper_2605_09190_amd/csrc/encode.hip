@@ -66,6 +66,7 @@ struct aqmp_code {
   aqmp::Counters* dcnt = nullptr;      // one per pass
   aqmp::Queues* dqueue = nullptr;      // one per pass
   int32_t* dntop = nullptr;            // [pass][kLevels]
+  int2* dranges = nullptr;             // [level][job]: the job's nodes within its pass
   int64_t cap_total[aqmp::kLevels] = {};
   int32_t kmax_total[aqmp::kLevels] = {};
   aqmp::LevelDev lv[aqmp::kLevels] = {};
@@ -433,6 +434,7 @@ int build_plan(aqmp_code* c) {
   }
   ALLOC(c->djobs, sizeof(JobDev) * nj);
   ALLOC(c->dcnt, sizeof(Counters) * c->passes.size());
+  ALLOC(c->dranges, sizeof(int2) * kLevels * nj);
   ALLOC(c->dqueue, sizeof(Queues) * c->passes.size());
   ALLOC(c->dntop, sizeof(int32_t) * kLevels * c->passes.size());
 #undef ALLOC
@@ -442,7 +444,8 @@ int build_plan(aqmp_code* c) {
     AQMP_HIP(hipMemsetAsync(wk.ss.ticket, 0, sizeof(int32_t) * 2, s));
   }
   AQMP_HIP(hipMemsetAsync(c->dcnt, 0, sizeof(Counters) * c->passes.size(), s));
-  // Static top-level node lists.
+  // Static top-level node lists, and the jobs' ranges in them.
+  std::vector<int2> ranges((size_t)kLevels * nj, int2{0, 0});
   std::vector<int32_t> ntop_all(kLevels * c->passes.size(), 0);
   for (size_t pi = 0; pi < c->passes.size(); ++pi) {
     const PassPlan& pp = c->passes[pi];
@@ -451,6 +454,11 @@ int build_plan(aqmp_code* c) {
       if (!pp.ntop[l]) continue;
       std::vector<int32_t> job, x0, y0;
       top_nodes(c, pp, l, job, x0, y0);
+      for (int32_t i = 0; i < (int32_t)job.size(); ++i) {
+        int2& r = ranges[(size_t)l * nj + job[i]];
+        if (i == 0 || job[i - 1] != job[i]) r.x = i;
+        r.y = i + 1;
+      }
       const int64_t b = pp.base[l];
       AQMP_HIP(hipMemcpyAsync(c->lv[l].job + b, job.data(), 4 * job.size(), hipMemcpyHostToDevice, s));
       AQMP_HIP(hipMemcpyAsync(c->lv[l].x0 + b, x0.data(), 4 * x0.size(), hipMemcpyHostToDevice, s));
@@ -459,6 +467,7 @@ int build_plan(aqmp_code* c) {
     }
   }
   AQMP_HIP(hipMemcpyAsync(c->dntop, ntop_all.data(), 4 * ntop_all.size(), hipMemcpyHostToDevice, s));
+  AQMP_HIP(hipMemcpyAsync(c->dranges, ranges.data(), sizeof(int2) * ranges.size(), hipMemcpyHostToDevice, s));
   AQMP_HIP(hipStreamSynchronize(s));
   AQMP_HIP(hipEventCreateWithFlags(&c->done, hipEventDisableTiming));
   if (c->opt.flags & AQMP_OPT_TIMING) {
@@ -551,7 +560,7 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
         AQMP_LAUNCH(launch_mp_fused(n, c->djobs, a.lv, count, l, D.m, D.d_tab, s));
       if (l > pp.lg_lo && pp.cap[l - 1] > 0)
         AQMP_LAUNCH(launch_split_emit(c->djobs, (int32_t)c->jobs.size(), a.lv, count, level_at(c, l - 1, pp.base[l - 1]), pp.ntop[l - 1],
-                                      &cnt->count[l - 1], l, pp.cap[l], wk.ss, &cnt->scan_error, s));
+                                      &cnt->count[l - 1], c->dranges + (size_t)(l - 1) * c->jobs.size(), l, pp.cap[l], wk.ss, &cnt->scan_error, s));
       if (le) AQMP_HIP(hipEventRecord(le->end, s));
       continue;
     }
@@ -578,7 +587,7 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
     }
     if (l > pp.lg_lo && pp.cap[l - 1] > 0)
       AQMP_LAUNCH(launch_split_emit(c->djobs, (int32_t)c->jobs.size(), a.lv, count, level_at(c, l - 1, pp.base[l - 1]), pp.ntop[l - 1],
-                                    &cnt->count[l - 1], l, pp.cap[l], wk.ss, &cnt->scan_error, s));
+                                    &cnt->count[l - 1], c->dranges + (size_t)(l - 1) * c->jobs.size(), l, pp.cap[l], wk.ss, &cnt->scan_error, s));
     if (le) AQMP_HIP(hipEventRecord(le->end, s));
   }
   return AQMP_OK;
@@ -1040,11 +1049,18 @@ int decode(const aqmp_dict* d, const aqmp_code* c, int job, double step, void* o
   size_t pi = 0;
   while (pi < c->passes.size() && !(job >= c->passes[pi].j0 && job < c->passes[pi].j1)) ++pi;
   const PassPlan& pp = c->passes[pi];
-  for (int l = pp.lg_hi; l >= pp.lg_lo; --l) {
-    if (pp.cap[l] == 0) continue;
-    AQMP_LAUNCH(launch_decode(1 << l, c->djobs, level_at(c, l, pp.base[l]), &c->dcnt[pi].count[l], job, d->nfam,
-                              d->lv[l].d_tab, step > 0.0 ? (double)(float)step : 0.0, out, dtype, row_stride, s));
-  }
+  const aqmp_image& im = c->imgs[c->jobs[job].image];
+  const aqmp_params& p = c->prm[c->jobs[job].params];
+  DecodeArgs a{};
+  a.jobs = c->djobs;
+  a.ranges = c->dranges;
+  a.n_jobs = (int32_t)c->jobs.size();
+  a.job = job;
+  a.lg_hi = ilog2(p.n_max);
+  a.lg_lo = ilog2(p.n_min);
+  for (int l = a.lg_lo; l <= a.lg_hi; ++l) a.lv[l] = DecodeLevel{level_at(c, l, pp.base[l]), d->lv[l].d_tab};
+  AQMP_LAUNCH(launch_decode(a, padded(im.w, p.n_max) * padded(im.h, p.n_max), step > 0.0 ? (double)(float)step : 0.0, out,
+                            dtype, row_stride, s));
   return AQMP_OK;
 }
 

@@ -178,9 +178,10 @@ hipError_t launch_compact(const int32_t* in_list, const int32_t* in_count, const
                           int32_t* out_list, int32_t* out_count, int32_t* clear_count, int64_t cap,
                           ScanState ss, int32_t* err, hipStream_t s);
 // Split test and child emission of one level.  A node whose job index is not
-// below n_jobs is not split and sets *err.
+// below n_jobs is not split and sets *err.  child_ranges, when given, receives
+// per job of the level the range of its children (their jobs keep their order).
 hipError_t launch_split_emit(const JobDev* jobs, int32_t n_jobs, LevelDev parent, const int32_t* parent_count,
-                             LevelDev child, int32_t child_ntop, int32_t* child_count,
+                             LevelDev child, int32_t child_ntop, int32_t* child_count, int2* child_ranges,
                              int32_t lg, int64_t cap, ScanState ss, int32_t* err, hipStream_t s);
 // ev0 / ev1, when given, are recorded by the dispatch itself at the kernel's
 // start and end (hipExtLaunchKernel), so their elapsed time is the kernel's
@@ -224,11 +225,23 @@ hipError_t launch_omp_pursuit(int n, const JobDev* jobs, LevelDev lv, const int3
 hipError_t launch_ssim(const aqmp_image& x, const aqmp_image& y, int mode, double c1, double c2, double* partial,
                        int* n_partial, hipStream_t s);
 int ssim_planes(const aqmp_image* x, const aqmp_image* y, int mode, double data_range, double* out, hipStream_t s);
+// Decode of one job: its levels (lg_hi .. lg_lo), their FP64 tables, and the
+// ranges of every job's nodes per level ([level][job]: first, end).
+struct DecodeLevel {
+  LevelDev lv;
+  const double* tab;
+};
+struct DecodeArgs {
+  DecodeLevel lv[kLevels];
+  const JobDev* jobs;
+  const int2* ranges;
+  int32_t n_jobs, job, lg_hi, lg_lo;
+};
 // step > 0: every coefficient is replaced by its quantised value
 // rint(c / step) * step first (the stream's coefficient format 1).
-hipError_t launch_decode(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t job,
-                         int32_t nfam, const double* tab, double step, void* out, int32_t dtype,
-                         int64_t row_stride, hipStream_t s);
+// blocks_px: pixels of the job's padded plane.
+hipError_t launch_decode(const DecodeArgs& a, int64_t blocks_px, double step, void* out, int32_t dtype, int64_t row_stride,
+                         hipStream_t s);
 
 // Device gather of a code's visited nodes in canonical order.  Sort key of a
 // node: global top-level block ordinal << kExportLowBits | Morton code of its

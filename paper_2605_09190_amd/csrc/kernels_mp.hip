@@ -1,7 +1,6 @@
 // kernels_mp.hip - per-node Matching Pursuit kernels: gathering a block into
-// its residual, the candidate re-score / coefficient / rank-1 update / norm
-// step of MP (Section 2.2, steps (b)-(c) and eq. (2)), and the decoder of
-// Algorithm 3.
+// its residual, and the candidate re-score / coefficient / rank-1 update /
+// norm step of MP (Section 2.2, steps (b)-(c) and eq. (2)).
 //
 // Layout: the residual of node slot i is r32[i * N*N + y*N + x] (row-major
 // pixels of the block; the correlation sums over pixels, so the dictionary
@@ -513,68 +512,6 @@ __global__ __launch_bounds__(64 * SelCfg<N>::WPN * SelCfg<N>::NPG, 2) void k_sel
   }
 }
 
-// ---------------------------------------------------------------------------
-// Decoder (Algorithm 3): every leaf of `job` at this level writes
-// sum_t c_t phi_{i_t} at its position.
-// ---------------------------------------------------------------------------
-template <int N>
-__global__ __launch_bounds__(256) void k_decode(const JobDev* jobs, LevelDev lv, const int32_t* count_ptr,
-                                                int32_t job, const double* tab, double step, void* out,
-                                                int32_t dtype, int64_t row_stride) {
-  using G = Geo<N>;
-  constexpr int K = G::K;
-  const int count = *count_ptr;
-  const int g = threadIdx.x / G::TPN, lt = threadIdx.x % G::TPN;
-  const double inv_n = 1.0 / N;
-  for (int base = blockIdx.x * G::NPW; base < count; base += gridDim.x * G::NPW) {
-    const int i = base + g;
-    if (i >= count) continue;
-    if (lv.job[i] != job || (lv.st[i] & ST_SPLIT)) continue;
-    int py, px;
-    patch_origin<N>(lt, py, px);
-    double acc[G::PH][G::PW];
-#pragma unroll
-    for (int dy = 0; dy < G::PH; ++dy)
-#pragma unroll
-      for (int dx = 0; dx < G::PW; ++dx) acc[dy][dx] = 0.0;
-    const int na = lv.t[i];
-    for (int s = 0; s < na; ++s) {
-      const size_t slot = (size_t)i * lv.kmax + s;
-      const int atom = lv.rec_idx[slot];
-      const double c0 = lv.rec_coef[slot];
-      const double coef = step > 0.0 ? rint(c0 / step) * step : c0;
-      const int f = atom / K, q = (atom % K) / N, p = atom % N;
-      const double* tf = tab + (size_t)f * K;
-      const bool dc = (p == 0 && q == 0);
-#pragma unroll
-      for (int dy = 0; dy < G::PH; ++dy) {
-        const double ty = tf[p * N + py + dy];
-#pragma unroll
-        for (int dx = 0; dx < G::PW; ++dx) {
-          const double phi = dc ? inv_n : ty * tf[q * N + px + dx];
-          acc[dy][dx] = fma(coef, phi, acc[dy][dx]);
-        }
-      }
-    }
-    // Pixels of the padding (past the image) are not written.
-    const int bx = lv.x0[i], by = lv.y0[i];
-    const int w = jobs[job].w, h = jobs[job].h;
-#pragma unroll
-    for (int dy = 0; dy < G::PH; ++dy) {
-      const int y = by + py + dy;
-      const int64_t row = (int64_t)y * row_stride + bx + px;
-#pragma unroll
-      for (int dx = 0; dx < G::PW; ++dx) {
-        if (y >= h || bx + px + dx >= w) continue;
-        if (dtype == AQMP_F64)
-          ((double*)out)[row + dx] = acc[dy][dx];
-        else
-          ((float*)out)[row + dx] = (float)acc[dy][dx];
-      }
-    }
-  }
-}
-
 template <int N>
 int grid_for(int per_cu) {
   return 256 * per_cu;
@@ -614,15 +551,6 @@ hipError_t launch_select(int n, const StepArgs& a, int64_t cap, hipStream_t s, h
     case 64: launch_select_n<64>(a, cap, s, ev0, ev1); break;
     default: return hipErrorInvalidValue;   // smaller levels run the fused pursuit
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_decode(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t job,
-                         int32_t nfam, const double* tab, double step, void* out, int32_t dtype, int64_t row_stride,
-                         hipStream_t s) {
-  (void)nfam;
-  AQMP_DISPATCH_N(n, hipLaunchKernelGGL(k_decode<NN>, dim3(grid_for<NN>(4)), dim3(256), 0, s, jobs, lv,
-                                        count, job, tab, step, out, dtype, row_stride));
   return hipGetLastError();
 }
 

@@ -56,6 +56,7 @@ __device__ void stable_scan(Op& op, ScanState ss, int32_t* err) {
     int pos = s_prefix + excl;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
+      if (base + j < n) op.mark(base + j, n, pos, f[j]);
       if (f[j]) op.emit(base + j, pos++);
     }
     if (tile == ntiles - 1 && tid == 0) op.total(s_prefix + agg);
@@ -91,6 +92,7 @@ struct CompactOp {
   __device__ int node(int i) const { return in_list ? in_list[i] : i; }
   __device__ int keep(int i) const { return st[node(i)] == ST_RUN ? 1 : 0; }
   __device__ void emit(int i, int pos) const { out_list[pos] = node(i); }
+  __device__ void mark(int, int, int, int) const {}
   __device__ void total(int t) const {
     *out_count = t;
     if (clear) *clear = 0;
@@ -106,8 +108,18 @@ struct SplitOp {
   LevelDev child;
   int32_t child_ntop;
   int32_t* child_count;
+  int2* child_ranges;       // per job, or null
   int32_t lg;
   __device__ int count() const { return *parent_count; }
+  // The nodes of a job are neighbours: top-level nodes are listed job by job
+  // and a stable scan emits the children in that order, so its first and
+  // last node, with the splits before them, give its children's range.
+  __device__ void mark(int i, int n, int pos, int kept) const {
+    if (!child_ranges) return;
+    const int jb = parent.job[i];
+    if (i == 0 || parent.job[i - 1] != jb) child_ranges[jb].x = child_ntop + 4 * pos;
+    if (i == n - 1 || parent.job[i + 1] != jb) child_ranges[jb].y = child_ntop + 4 * (pos + kept);
+  }
   // Algorithm 2: refine when N > N_min and the node failed the test of its
   // split rule; the node's own atoms are then discarded by the exporter.
   __device__ int keep(int i) const {
@@ -198,9 +210,9 @@ hipError_t launch_compact(const int32_t* in_list, const int32_t* in_count, const
 }
 
 hipError_t launch_split_emit(const JobDev* jobs, int32_t n_jobs, LevelDev parent, const int32_t* parent_count,
-                             LevelDev child, int32_t child_ntop, int32_t* child_count,
+                             LevelDev child, int32_t child_ntop, int32_t* child_count, int2* child_ranges,
                              int32_t lg, int64_t cap, ScanState ss, int32_t* err, hipStream_t s) {
-  SplitOp op{jobs, n_jobs, err, parent, parent_count, child, child_ntop, child_count, lg};
+  SplitOp op{jobs, n_jobs, err, parent, parent_count, child, child_ntop, child_count, child_ranges, lg};
   hipLaunchKernelGGL(k_split_emit, dim3(scan_blocks(cap)), dim3(256), 0, s, op, ss, err);
   return hipGetLastError();
 }

@@ -188,7 +188,7 @@ int worklist_split(const aqmp_params* prm, int n_prm, int n, const int32_t* node
   const int lg = ilog2(n);
   const ScanBlock b = scan_block_at(p, n_nodes);
   rc = run_scan(b, scan_bytes, n_nodes, s, who, [&](ScanBlock sb) {
-    return launch_split_emit(djobs, n_prm, parent, sb.hdr, child, child_base, child_count, lg, n_nodes, sb.ss,
+    return launch_split_emit(djobs, n_prm, parent, sb.hdr, child, child_base, child_count, nullptr, lg, n_nodes, sb.ss,
                              sb.hdr + 3, s);
   });
   dev_free(p, bytes);
