@@ -153,11 +153,12 @@ __device__ inline unsigned long long wave_max_u64(unsigned long long v) {
 }
 // Orders the LDS writes of a wave's lanes before its later LDS reads by
 // other lanes of the same wave (no workgroup barrier): the wave's LDS
-// operations complete before it goes on.
+// operations complete before it goes on (its loads and stores of global
+// memory need not: none of them is read by another lane).
 __device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Lane exchange with a permutation inside rows of 16 (every lane has a

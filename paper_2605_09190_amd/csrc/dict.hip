@@ -45,8 +45,7 @@ static uint16_t atom_bf16(const aqmp_dict::Level& L, int a, int y, int x) {
 }
 
 static void free_level(aqmp_dict::Level& L, uint32_t families) {
-  for (int prec = 0; prec < 2; ++prec)
-    if (L.d_sep[prec]) dev_free(L.d_sep[prec], sep_ops_bytes(L.n, prec, families));
+  if (L.d_sep) dev_free(L.d_sep, sep_ops_bytes(L.n, families));
   if (L.d_tab) dev_free(L.d_tab, sizeof(double) * L.h_tab.size());
   if (L.d_tabT32) dev_free(L.d_tabT32, sizeof(float) * L.h_tab.size());
   if (L.d_xg) dev_free(L.d_xg, sizeof(double) * L.k);
@@ -119,8 +118,8 @@ int dictionary_build(int n_min, int n_max, uint32_t families, hipStream_t s, aqm
     if (rc == AQMP_OK && !xg.empty()) rc = dev_alloc((void**)&L.d_xg, sizeof(double) * xg.size());
     if (rc == AQMP_OK) rc = dev_alloc((void**)&L.d_f32, sizeof(float) * a32.size());
     if (rc == AQMP_OK) rc = dev_alloc((void**)&L.d_bf16, sizeof(uint16_t) * a16.size());
-    for (int prec = 0; prec < 2 && rc == AQMP_OK; ++prec)
-      if (const size_t b = sep_ops_bytes(n, prec, families)) rc = dev_alloc(&L.d_sep[prec], b);
+    if (const size_t b = sep_ops_bytes(n, families))
+      if (rc == AQMP_OK) rc = dev_alloc(&L.d_sep, b);
     if (rc != AQMP_OK) {
       dictionary_free(d);
       return rc;
@@ -136,8 +135,7 @@ int dictionary_build(int n_min, int n_max, uint32_t families, hipStream_t s, aqm
       e = hipMemcpyAsync(L.d_tabT32, tT.data(), sizeof(float) * tT.size(), hipMemcpyHostToDevice, s);
     if (e == hipSuccess && L.d_xg)
       e = hipMemcpyAsync(L.d_xg, xg.data(), sizeof(double) * xg.size(), hipMemcpyHostToDevice, s);
-    for (int prec = 0; prec < 2 && e == hipSuccess; ++prec)
-      if (L.d_sep[prec]) e = launch_sep_ops(n, prec, families, L.d_tab, L.d_sep[prec], s);
+    if (e == hipSuccess && L.d_sep) e = launch_sep_ops(n, families, L.d_tab, L.d_xg, L.d_sep, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
       dictionary_free(d);

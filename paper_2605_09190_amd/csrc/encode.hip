@@ -551,8 +551,7 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
                                           wk.cbuf, s));
         if (se) AQMP_HIP(hipEventRecord(se->c, s));
       } else if (sep_level(c, n))
-        AQMP_LAUNCH(launch_pursuit_sep(n, c->opt.precision, d->families, c->djobs, a.lv, count, c->dqueue[pi].at[l], pp.cap[l],
-                                       D.d_tab, D.d_sep[c->opt.precision], s));
+        AQMP_LAUNCH(launch_pursuit_sep(n, d->families, c->djobs, a.lv, count, c->dqueue[pi].at[l], pp.cap[l], D.d_tab, D.d_sep, s));
       else if (sub_level(c, n))
         AQMP_LAUNCH(launch_pursuit_sub(n, c->opt.precision, d->families, c->djobs, a.lv, count, c->dqueue[pi].at[l],
                                        pp.cap[l], D.d_tab, s));

@@ -194,11 +194,10 @@ hipError_t launch_select(int n, const StepArgs& a, int64_t cap, hipStream_t s, h
 // correlation factored through the atoms' outer products (`queue`: the level's
 // node counters, zero on entry; cap: its node capacity; ops: the table
 // operands launch_sep_ops made, sep_ops_bytes long, 0 for other N).
-size_t sep_ops_bytes(int n, int precision, uint32_t families);
-hipError_t launch_sep_ops(int n, int precision, uint32_t families, const double* tab, void* out, hipStream_t s);
-hipError_t launch_pursuit_sep(int n, int precision, uint32_t families, const JobDev* jobs, LevelDev lv,
-                              const int32_t* count, int32_t* queue, int64_t cap, const double* tab, const void* ops,
-                              hipStream_t s);
+size_t sep_ops_bytes(int n, uint32_t families);
+hipError_t launch_sep_ops(int n, uint32_t families, const double* tab, const double* xg, void* out, hipStream_t s);
+hipError_t launch_pursuit_sep(int n, uint32_t families, const JobDev* jobs, LevelDev lv, const int32_t* count,
+                              int32_t* queue, int64_t cap, const double* tab, const void* ops, hipStream_t s);
 hipError_t launch_mp_fused(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t lg, int32_t n_atoms,
                            const double* tab, hipStream_t s);
 // Whole-level pursuit of the dense solver at N = 8 (BF16 form) and 16
@@ -295,6 +294,6 @@ struct aqmp_dict {
     double* d_xg = nullptr;        // [n][n] <T_0[p], T_1[p']> (two families only)
     float* d_f32 = nullptr;        // [m_pad][k]
     uint16_t* d_bf16 = nullptr;    // [m_pad][k]
-    void* d_sep[2] = {nullptr, nullptr};   // operands of the factored correlation, by precision
+    void* d_sep = nullptr;         // operands of the factored correlation (launch_sep_ops)
   } lv[aqmp::kLevels];
 };

@@ -7,41 +7,51 @@
 // same c_a = <r, phi_a> as in the step-by-step form, factored through the
 // atoms' outer-product shape (Section 2.1): atom (f, p, q) is T_f[p] (x)
 // T_f[q], so C_f = T_f R T_f^T holds c_a for every atom of family f, 8 N^3
-// operations per node and step for both families instead of the 4 N^4 of the
-// unfactored product.  It is made anew from the residual at every step, on
-// the matrix cores:
-//   BF16 form: every operand split into an FP16 value and an FP16 remainder,
-//     hi hi + hi lo + lo hi with FP32 accumulation (the Haar operands are
-//     exact signs, see SepOps).  Largest error over ||r|| against FP64 on
-//     smooth, edge, noise and pursued blocks: 1.2e-7, where BF16 atoms and
-//     residuals give 5.6e-4;
-//   FP32 form: FP32 operands and accumulation (1.5e-7; the unfactored FP32
-//     product 5.5e-7).
-// First product D1[y][q] = sum_x R[y][x] T[q][x], second D2[p][q] =
-// sum_y T[p][y] D1[y][q].  A wave owns whole columns q of both: the lane that
-// holds D1[16 ty + 4 g + r][q] (the matrix-core output layout, g = lane / 16)
-// needs exactly those values as B operand of the second product once its
-// k index is taken in the order (ty, g, r), so D1 never leaves the
-// registers; the table operands are laid out in that order once per kernel.
+// operations for both families instead of the 4 N^4 of the unfactored
+// product.  Matrix cores, every operand split into an FP16 value and an FP16
+// remainder, hi hi + hi lo + lo hi with FP32 accumulation (the Haar operands
+// are exact signs, see sep_make_ops).  First product D1[y][q] = sum_x R[y][x]
+// T[q][x], second D2[p][q] = sum_y T[p][y] D1[y][q].  A wave owns whole
+// columns q of both: the lane that holds D1[16 ty + 4 g + r][q] (the
+// matrix-core output layout, g = lane / 16) needs exactly those values as B
+// operand of the second product once its k index is taken in the order (ty,
+// g, r), so D1 never leaves the registers; the table operands and the rows of
+// R are laid out in that order, and one table serves both products.
+//
+// A step with atom (f, p, q) and coefficient c takes c phi from the residual,
+// so every correlation loses c <phi, phi'>: c for the atom itself, 0 for the
+// rest of its family (an orthonormal basis), c X[p][p'] X[q][q'] for the other
+// family, X the 1D products <T_0[p], T_1[p']>.  The correlations are therefore
+// carried in FP32 registers from step to step (2 operations per atom of one
+// family instead of 4 N per atom of both) and made anew from the residual
+// when its norm has halved, or after at most 64 steps.  Largest error over
+// ||r|| against FP64, whole pursuits on smooth, edge, texture, noise and dot
+// blocks: 2.0e-7; the unfactored product of every step has 3.7e-7 to 6.7e-7
+// with FP32 operands and 5.6e-4 with BF16 atoms and residuals.  Both forms
+// run this one kernel.
 //
 // Selection: the candidates are all atoms whose |c| is within 2 delta of the
-// largest, delta = 2^-13 ||r||.  Either form is within 2^-14.9 ||r|| of the
-// FP64 value in the worst case (per product the remainders' rounding and the
-// dropped lo lo term, 3 2^-22, and at most 192 FP32 additions, 192 2^-24, of
-// sum |T||R|, which Cauchy-Schwarz bounds by the norm): no other atom can be
-// the arg-max of the FP64 re-score or tie it.  One atom is left in 98% of the
-// steps of an ordinary image.
+// largest, delta = 2^-14 ||r'||, r' the residual of the last product.  A
+// fresh correlation is within 2^-14.9 ||r'|| of the FP64 value in the worst
+// case (per product the remainders' rounding and the dropped lo lo term, 3
+// 2^-22, and at most 192 FP32 additions, 192 2^-24, of sum |T||R|, which
+// Cauchy-Schwarz bounds by the norm), and a step adds at most 6 2^-24 ||r'||
+// (roundings of c, X, two products, the sum, and of the stored residual), 64
+// of them 2^-15.4 ||r'||: no other atom can be the arg-max of the FP64
+// re-score or tie it.  One atom is left in 98% of the steps of an ordinary
+// image.
 // The FP64 re-score, the rank-1 update and the norm use the same lane
 // patches and the same order of operations as k_select, and the initial
 // norm those of k_gather, so the trees, atoms, coefficients and norms are
 // those of the step-by-step form bit for bit.
 //
-// What bounds it: the chain of one node's step (two products, arg-max,
-// re-score, update), and the last long nodes of a level.  On three 2048 x
-// 2048 planes (36 432 node-steps at N = 64, 74 821 at N = 32) the levels take
-// 420 and 193 us; a correlation and a select launch per step took 2 510 and
-// 980 us, 32 (N = 64) or 16 times the operations and the residual through
-// memory at every step.
+// What bounds it: the chain of one node's step (re-score 1 460 cycles, update
+// of residual and correlations 1 060, arg-max 720, norm and stop test 700;
+// correlations anew 4 700, 1.9 times a node), and the last long nodes of a
+// level.  On three 2048 x 2048 planes (36 432 node-steps at N = 64, 74 821 at
+// N = 32) the levels take 280 and 112 us; with the correlations made anew at
+// every step 444 and 191 us, and with a correlation and a select launch per
+// step 2 510 and 980 us.
 #include "internal.h"
 #include "dev_common.h"
 
@@ -51,71 +61,48 @@ namespace {
 
 typedef _Float16 sp_h8 __attribute__((ext_vector_type(8)));
 typedef float sp_f32x4 __attribute__((ext_vector_type(4)));
+typedef float sp_f32x16 __attribute__((ext_vector_type(16)));
 
 // Geometry.  N = 64: the four waves of a workgroup share one node (16
 // columns q each), N = 32: a node per wave.  FAMS: family mask (AQMP_DCT |
-// AQMP_HAAR, DCT first), BF: BF16 form.
-template <int N_, int FAMS_, bool BF_>
+// AQMP_HAAR, DCT first).
+template <int N_, int FAMS_>
 struct SepGeo {
   static constexpr int N = N_, K = N * N, FAMS = FAMS_;
-  static constexpr bool BF = BF_;
   static constexpr int NFAM = FAMS == 3 ? 2 : 1;
   static constexpr int M = NFAM * K;
   static constexpr int WPN = N == 64 ? 4 : 1;          // waves per node
   static constexpr int NPG = 4 / WPN;                  // nodes per workgroup
   static constexpr int TT = N / 16;                    // 16-wide tiles of a side
   static constexpr int TQ = TT / WPN;                  // q tiles per wave
-  static constexpr int VPL = NFAM * TQ * TT * 4;       // correlations per lane
+  static constexpr int VPL = NFAM * 16;                // correlations per lane: 4 TQ TT of each family
   static constexpr int PW = N / 8, PH = N / 8;         // patch of a lane over the node's waves
   static constexpr int RPW = PH / WPN;                 // patch rows held by one wave
-  static constexpr int KS = N / 32;                    // BF16 k-steps (32) of a product
+  static constexpr int KS = N / 32;                    // k-steps (32) of a product
   // LDS rows of the residual, padded by 16 bytes: 16 consecutive rows read
   // at one column offset (16 bytes per lane) fall on all banks once.
-  static constexpr int ROWB = (BF ? 2 : 4) * N + 16;
-  static constexpr int HALFB = N * ROWB;               // BF16: hi rows, then lo rows
-  static constexpr int RBYTES = BF ? 2 * HALFB : HALFB;
+  static constexpr int ROWB = 2 * N + 16;
+  static constexpr int HALFB = N * ROWB;               // hi rows, then lo rows
+  static constexpr int RBYTES = 2 * HALFB;
   static_assert(RBYTES >= 4 * K, "the gather stages FP32 pixels in the residual buffer");
-  // Power of two on the DCT operands of the BF16 form (and on the Haar
-  // magnitudes): their FP16 remainders are then normal numbers.
-  static constexpr float TS = BF ? 128.f : 1.f;
-  static_assert(VPL <= 32, "one mask word per lane");
+  // Power of two on the DCT operands (and on the Haar magnitudes): their
+  // FP16 remainders are then normal numbers.
+  static constexpr float TS = 128.f;
+  static_assert(4 * TQ * TT == 16 && VPL <= 32, "one vector per family, one mask word per lane");
+  // Table operands, 16 bytes at a time: values of each family, then the DCT
+  // remainders; then the signs of the Haar table (bytes) and FP32 <T_0[p],
+  // T_1[p']> with its transpose.
+  static constexpr int NOPS = FAMS == 3 ? 3 : (FAMS == AQMP_HAAR ? 1 : 2);
+  static constexpr int EOPS = NOPS * TT * KS * 64;
+  static constexpr int SGNB = FAMS == AQMP_DCT ? 0 : K;   // bytes of signs
+  static constexpr size_t OFF_S = EOPS, OFF_X = OFF_S + SGNB / 16;
+  static constexpr size_t BYTES = 16 * OFF_X + (NFAM == 2 ? 8 * (size_t)K : 0);
+  static constexpr bool XLDS = NFAM == 2 && N == 32;     // that table in LDS (N = 64: 32 KB, no room beside a second workgroup)
 };
 
 // Whether family f of a dictionary is the Haar one.
 template <class G>
 __device__ constexpr bool sep_haar(int f) { return G::FAMS == AQMP_HAAR || (G::FAMS == 3 && f == 1); }
-
-// Table operands of a wave, in registers for the whole kernel.  A Haar row is
-// one magnitude times -1, 0 or 1: its operands are those signs, exact in BF16
-// (no remainder, two products instead of three), and the magnitudes of the
-// row and the column multiply the finished correlation.
-template <class G, bool BF = G::BF>
-struct SepOps;
-template <class G>
-struct SepOps<G, true> {
-  sp_h8 ah[G::NFAM][G::TQ][G::KS], bh[G::NFAM][G::TT][G::KS];   // T[q][x] (first product, B), T[p][y] (second, A)
-  sp_h8 al[1][G::TQ][G::KS], bl[1][G::TT][G::KS];               // DCT remainders
-  float sp0[G::TQ][4], sp[G::TQ][G::TT];                             // Haar magnitudes: p < 16 by row, then by p tile
-};
-template <class G>
-struct SepOps<G, false> {
-  sp_f32x4 a[1][G::TQ][G::TT], b[1][G::TT][G::TT];                  // DCT
-  uint2 ha[1][G::TQ][G::TT], hb[1][G::TT][G::TT];                   // Haar signs, BF16 pairs
-  float sp0[G::TQ][4], sp[G::TQ][G::TT];
-};
-
-__device__ inline sp_h8 sp_hi(const float (&v)[8]) {
-  sp_h8 h;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) h[j] = (_Float16)v[j];
-  return h;
-}
-__device__ inline sp_h8 sp_lo(const float (&v)[8], const sp_h8& h) {
-  sp_h8 l;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) l[j] = (_Float16)(v[j] - (float)h[j]);
-  return l;
-}
 
 // Two FP32 values -> packed FP16 halves and their packed remainders.  The
 // mixed-precision FMA takes FP16 sources and rounds its result to FP16 in
@@ -136,190 +123,125 @@ __device__ inline void sp_split2_scaled(float a, float b, float s, uint32_t& h, 
   __asm__("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(l) : "v"(b), "v"(s), "v"(h));
 }
 
-__device__ inline float sp_sign(double v) { return v > 0.0 ? 1.f : (v < 0.0 ? -1.f : 0.f); }
-__device__ inline uint2 sp_pack4(const float (&v)[4]) {   // exact in BF16
-  return make_uint2((__float_as_uint(v[0]) >> 16) | (__float_as_uint(v[1]) & 0xFFFF0000u),
-                    (__float_as_uint(v[2]) >> 16) | (__float_as_uint(v[3]) & 0xFFFF0000u));
-}
-__device__ inline float sp_unpack(const uint2& u, int r) {
-  const uint32_t w = r < 2 ? u.x : u.y;
-  return __uint_as_float((r & 1) ? (w & 0xFFFF0000u) : (w << 16));
-}
-
+// Writes the operands of one dictionary level (see SepGeo), made once with
+// the dictionary: word ((o TT + t) KS + ks) 64 + lane holds T[16 t + m][x] at
+// the eight pixels x of k-slots (ks, g, 0..7).  A Haar row is one magnitude
+// times -1, 0 or 1: its operands are those signs, exact in FP16 (no remainder,
+// two products instead of three), and the magnitudes of the row and the
+// column multiply the finished correlation.  xg: FP64 <T_0[p], T_1[p']>.
 template <class G>
-__device__ inline void sep_load_ops(SepOps<G>& T, const double* __restrict__ tab, int wq) {
+__device__ inline void sep_make_ops(const double* __restrict__ tab, const double* __restrict__ xg,
+                                    uint4* __restrict__ out) {
   constexpr int N = G::N;
-  const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
-#pragma unroll
-  for (int f = 0; f < G::NFAM; ++f) {
-    const double* tf = tab + (size_t)f * G::K;
-    auto entry = [&](int row, int col) -> float {
-      const double v = tf[row * N + col];
-      return sep_haar<G>(f) ? sp_sign(v) : (float)v * G::TS;
-    };
-    if constexpr (G::BF) {
-#pragma unroll
-      for (int i = 0; i < G::TQ; ++i)
-#pragma unroll
-        for (int ks = 0; ks < G::KS; ++ks) {
-          float v[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) v[j] = entry(16 * (wq * G::TQ + i) + m, 32 * ks + 8 * g + j);
-          T.ah[f][i][ks] = sp_hi(v);
-          if (!sep_haar<G>(f)) T.al[0][i][ks] = sp_lo(v, T.ah[f][i][ks]);
-        }
-#pragma unroll
-      for (int tp = 0; tp < G::TT; ++tp)
-#pragma unroll
-        for (int ks = 0; ks < G::KS; ++ks) {
-          float v[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) v[j] = entry(16 * tp + m, 32 * ks + 16 * (j >> 2) + 4 * g + (j & 3));
-          T.bh[f][tp][ks] = sp_hi(v);
-          if (!sep_haar<G>(f)) T.bl[0][tp][ks] = sp_lo(v, T.bh[f][tp][ks]);
-        }
-    } else {
-#pragma unroll
-      for (int i = 0; i < G::TQ; ++i)
-#pragma unroll
-        for (int c = 0; c < G::TT; ++c) {
-          float v[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v[r] = entry(16 * (wq * G::TQ + i) + m, 16 * c + 4 * g + r);
-          if (sep_haar<G>(f)) T.ha[0][i][c] = sp_pack4(v);
-          else T.a[0][i][c] = sp_f32x4{v[0], v[1], v[2], v[3]};
-        }
-#pragma unroll
-      for (int tp = 0; tp < G::TT; ++tp)
-#pragma unroll
-        for (int ty = 0; ty < G::TT; ++ty) {
-          float v[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v[r] = entry(16 * tp + m, 16 * ty + 4 * g + r);
-          if (sep_haar<G>(f)) T.hb[0][tp][ty] = sp_pack4(v);
-          else T.b[0][tp][ty] = sp_f32x4{v[0], v[1], v[2], v[3]};
-        }
+  const int tid = threadIdx.x;
+  for (int i = tid; i < G::EOPS; i += 256) {
+    const int lane = i & 63, m = lane & 15, g = lane >> 4;
+    const int ks = (i >> 6) % G::KS, t = (i >> 6) / G::KS % G::TT, o = (i >> 6) / (G::KS * G::TT);
+    const int f = o < G::NFAM ? o : 0;
+    const bool haar = sep_haar<G>(f);
+    const double* row = tab + (size_t)f * G::K + (16 * t + m) * N;
+    sp_h8 v;
+    for (int j = 0; j < 8; ++j) {
+      const double d = row[32 * ks + 16 * (j >> 2) + 4 * g + (j & 3)];
+      const float w = haar ? (d > 0.0 ? 1.f : (d < 0.0 ? -1.f : 0.f)) : (float)d * G::TS;
+      const _Float16 h = (_Float16)w;
+      v[j] = o < G::NFAM ? h : (_Float16)(w - (float)h);
     }
-    if (sep_haar<G>(f)) {
-      // a row's magnitude is its value at the first pixel of its support
-      auto mag = [&](int row) -> float {
-        int at = 0;
-        if (row > 0) {
-          const int top = 1 << (31 - __builtin_clz((unsigned)row));
-          at = (row - top) * (N / top);
-        }
-        return (float)tf[row * N + at];
-      };
-#pragma unroll
-      for (int i = 0; i < G::TQ; ++i) {
-        const float mq = mag(16 * (wq * G::TQ + i) + m);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) T.sp0[i][r] = mag(4 * g + r) * mq * (G::TS * G::TS);
-#pragma unroll
-        for (int tp = 1; tp < G::TT; ++tp) T.sp[i][tp] = mag(16 * tp) * mq * (G::TS * G::TS);   // one scale from row 16 up to the next power of two
-      }
+    __builtin_memcpy(&out[i], &v, 16);
+  }
+  if constexpr (G::SGNB > 0) {
+    const double* h = tab + (G::FAMS == 3 ? G::K : 0);
+    int8_t* sg = (int8_t*)(out + G::OFF_S);
+    for (int i = tid; i < G::K; i += 256) sg[i] = h[i] > 0.0 ? 1 : (h[i] < 0.0 ? -1 : 0);
+  }
+  if constexpr (G::NFAM == 2) {
+    float* x = (float*)(out + G::OFF_X);
+    for (int i = tid; i < G::K; i += 256) {
+      x[i] = (float)xg[i];
+      x[G::K + i] = (float)xg[(i % N) * N + i / N];
     }
   }
 }
 
+template <int N, int FAMS>
+__global__ __launch_bounds__(256) void k_sep_ops(const double* __restrict__ tab, const double* __restrict__ xg,
+                                                 uint4* __restrict__ out) {
+  sep_make_ops<SepGeo<N, FAMS>>(tab, xg, out);
+}
+
 // All correlations of the residual in sR with the wave's columns q:
-// C[f][i][tp][r] = c of atom (f, p = 16 tp + 4 g + r, q = 16 (TQ wq + i) + m).
+// C[f][4 (i TT + tp) + r] = c of atom (f, p = 16 tp + 4 g + r, q = 16 (TQ wq + i) + m).
+// ops: the table operands in LDS (in registers they would fill half of those
+// of the steps between two calls; from memory a call took 12 000 to 45 000
+// cycles, every workgroup reading the same lines).
 template <class G>
-__device__ inline void sep_correlate(const char* sR, const SepOps<G>& T, sp_f32x4 (&C)[G::NFAM][G::TQ][G::TT]) {
+__device__ inline void sep_correlate(const char* sR, const uint4* ops, int wq, const float (&mq)[G::TQ], const float (&mp0)[4],
+                                     const float (&mp)[G::TT], sp_f32x16 (&C)[G::NFAM]) {
   const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
-  sp_f32x4 D[G::NFAM][G::TQ][G::TT];
+  auto op = [&](int o, int t, int ks) -> sp_h8 { return *(const sp_h8*)&ops[((o * G::TT + t) * G::KS + ks) * 64 + lane]; };
+  const char* base = sR + m * G::ROWB + 16 * g;
 #pragma unroll
-  for (int f = 0; f < G::NFAM; ++f)
+  for (int f = 0; f < G::NFAM; ++f) {
+    constexpr int L = G::NOPS - 1;                       // the DCT's remainders
+    const bool haar = sep_haar<G>(f);                    // no remainders
+    sp_f32x4 D[G::TQ][G::TT], c[G::TQ][G::TT];
 #pragma unroll
     for (int i = 0; i < G::TQ; ++i)
 #pragma unroll
-      for (int t = 0; t < G::TT; ++t) D[f][i][t] = C[f][i][t] = sp_f32x4{0.f, 0.f, 0.f, 0.f};
-  const char* base = sR + m * G::ROWB + 16 * g;
-  if constexpr (G::BF) {
+      for (int t = 0; t < G::TT; ++t) D[i][t] = c[i][t] = sp_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ks = 0; ks < G::KS; ++ks)
+    for (int ks = 0; ks < G::KS; ++ks) {
+      sp_h8 a[G::TQ], al[G::TQ];
+#pragma unroll
+      for (int i = 0; i < G::TQ; ++i) {
+        a[i] = op(f, wq * G::TQ + i, ks);
+        if (!haar) al[i] = op(L, wq * G::TQ + i, ks);
+      }
 #pragma unroll
       for (int ty = 0; ty < G::TT; ++ty) {
         const sp_h8 rh = *(const sp_h8*)(base + 16 * ty * G::ROWB + 64 * ks);
         const sp_h8 rl = *(const sp_h8*)(base + G::HALFB + 16 * ty * G::ROWB + 64 * ks);
 #pragma unroll
-        for (int pr = 0; pr < 3; ++pr)
+        for (int i = 0; i < G::TQ; ++i) {
+          D[i][ty] = __builtin_amdgcn_mfma_f32_16x16x32_f16(rh, a[i], D[i][ty], 0, 0, 0);
+          if (!haar) D[i][ty] = __builtin_amdgcn_mfma_f32_16x16x32_f16(rh, al[i], D[i][ty], 0, 0, 0);
+          D[i][ty] = __builtin_amdgcn_mfma_f32_16x16x32_f16(rl, a[i], D[i][ty], 0, 0, 0);
+        }
+      }
+    }
 #pragma unroll
-          for (int f = 0; f < G::NFAM; ++f)
+    for (int ks = 0; ks < G::KS; ++ks) {
+      sp_h8 zh[G::TQ], zl[G::TQ];
 #pragma unroll
-            for (int i = 0; i < G::TQ; ++i) {
-              if (pr == 1 && sep_haar<G>(f)) continue;   // no remainder
-              D[f][i][ty] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pr == 2 ? rl : rh, pr == 1 ? T.al[0][i][ks] : T.ah[f][i][ks],
-                                                                    D[f][i][ty], 0, 0, 0);
-            }
+      for (int i = 0; i < G::TQ; ++i) {
+        uint32_t h[4], l[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const sp_f32x4& d = D[i][2 * ks + (j >> 1)];
+          sp_split2(d[2 * (j & 1)], d[2 * (j & 1) + 1], h[j], l[j]);
+        }
+        __builtin_memcpy(&zh[i], h, 16);
+        __builtin_memcpy(&zl[i], l, 16);
       }
 #pragma unroll
-    for (int f = 0; f < G::NFAM; ++f)
-#pragma unroll
-      for (int ks = 0; ks < G::KS; ++ks) {
-        sp_h8 zh[G::TQ], zl[G::TQ];
+      for (int tp = 0; tp < G::TT; ++tp) {
+        const sp_h8 b = op(f, tp, ks);
+        sp_h8 bl;
+        if (!haar) bl = op(L, tp, ks);
 #pragma unroll
         for (int i = 0; i < G::TQ; ++i) {
-          uint32_t h[4], l[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const sp_f32x4& d = D[f][i][2 * ks + (j >> 1)];
-            sp_split2(d[2 * (j & 1)], d[2 * (j & 1) + 1], h[j], l[j]);
-          }
-          __builtin_memcpy(&zh[i], h, 16);
-          __builtin_memcpy(&zl[i], l, 16);
+          c[i][tp] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b, zh[i], c[i][tp], 0, 0, 0);
+          if (!haar) c[i][tp] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bl, zh[i], c[i][tp], 0, 0, 0);
+          c[i][tp] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b, zl[i], c[i][tp], 0, 0, 0);
         }
-#pragma unroll
-        for (int pr = 0; pr < 3; ++pr)
-#pragma unroll
-          for (int tp = 0; tp < G::TT; ++tp)
-#pragma unroll
-            for (int i = 0; i < G::TQ; ++i) {
-              if (pr == 1 && sep_haar<G>(f)) continue;
-              C[f][i][tp] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pr == 1 ? T.bl[0][tp][ks] : T.bh[f][tp][ks],
-                                                                    pr == 2 ? zl[i] : zh[i], C[f][i][tp], 0, 0, 0);
-            }
       }
-  } else {
-#pragma unroll
-    for (int c = 0; c < G::TT; ++c)
-#pragma unroll
-      for (int ty = 0; ty < G::TT; ++ty) {
-        const sp_f32x4 rv = *(const sp_f32x4*)(base + 16 * ty * G::ROWB + 64 * c);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int f = 0; f < G::NFAM; ++f)
-#pragma unroll
-            for (int i = 0; i < G::TQ; ++i) {
-              const float tv = sep_haar<G>(f) ? sp_unpack(T.ha[0][i][c], r) : T.a[0][i][c][r];
-              D[f][i][ty] = __builtin_amdgcn_mfma_f32_16x16x4f32(rv[r], tv, D[f][i][ty], 0, 0, 0);
-            }
-      }
-#pragma unroll
-    for (int f = 0; f < G::NFAM; ++f)
-#pragma unroll
-      for (int ty = 0; ty < G::TT; ++ty)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int tp = 0; tp < G::TT; ++tp)
-#pragma unroll
-            for (int i = 0; i < G::TQ; ++i) {
-              const float tv = sep_haar<G>(f) ? sp_unpack(T.hb[0][tp][ty], r) : T.b[0][tp][ty][r];
-              C[f][i][tp] = __builtin_amdgcn_mfma_f32_16x16x4f32(tv, D[f][i][ty][r], C[f][i][tp], 0, 0, 0);
-            }
-  }
-#pragma unroll
-  for (int f = 0; f < G::NFAM; ++f)
-    if (sep_haar<G>(f)) {
-#pragma unroll
-      for (int i = 0; i < G::TQ; ++i)
-#pragma unroll
-        for (int tp = 0; tp < G::TT; ++tp)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) C[f][i][tp][r] *= tp == 0 ? T.sp0[i][r] : T.sp[i][tp];
     }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int i = j / (4 * G::TT), tp = (j >> 2) % G::TT, r = j & 3;
+      C[f][j] = haar ? c[i][tp][r] * ((tp == 0 ? mp0[r] : mp[tp]) * mq[i]) : c[i][tp][r];
+    }
+  }
 }
 
 // Orders a node's LDS writes before its other lanes' reads: a workgroup
@@ -336,49 +258,87 @@ __device__ inline void sep_sync() {
   }
 }
 
-// FP64 1D tables in LDS: the DCT as it is; a Haar row is one magnitude
-// times -1, 0 or 1 (exact products), kept as FP32 signs and one FP64
-// magnitude per scale (row 0, then rows [2^j, 2^(j+1))).
+// Tables in LDS: operands of the correlation; FP64 1D rows, the DCT as it
+// is, a Haar row one magnitude times -1, 0 or 1 (exact products), kept as
+// signs and one FP64 magnitude per scale (row 0, then rows [2^j, 2^(j+1))).
 template <class G>
 struct SepTab {
-  double dct[(G::FAMS & AQMP_DCT) ? G::K : 1];
-  float sgn[(G::FAMS & AQMP_HAAR) ? G::K : 1];
+  uint4 ops[G::EOPS];
+  double dct[(G::FAMS & AQMP_DCT) ? G::K + 2 * G::N : 1];   // rows N, N + 1: ones and 1/N, of the constant atom
+  uint4 sgn[G::SGNB ? G::SGNB / 16 : 1];
+  float x[G::XLDS ? 2 * G::K : 1];
   double mag[8];
 };
 
 __device__ inline int sep_haar_scale(int p) { return p == 0 ? 0 : 32 - __builtin_clz((unsigned)p); }
 
 template <class G>
-__device__ inline void sep_load_tab(SepTab<G>& S, const double* __restrict__ tab) {
+__device__ inline void sep_load_tab(SepTab<G>& S, const double* __restrict__ tab, const uint4* __restrict__ ops) {
   const int tid = threadIdx.x;
-  if constexpr ((G::FAMS & AQMP_DCT) != 0)
-    for (int i = tid; i < G::K; i += 256) S.dct[i] = tab[i];
-  if constexpr ((G::FAMS & AQMP_HAAR) != 0) {
-    const double* h = tab + (G::FAMS == 3 ? G::K : 0);
-    for (int i = tid; i < G::K; i += 256) S.sgn[i] = h[i] > 0.0 ? 1.f : (h[i] < 0.0 ? -1.f : 0.f);
+#pragma unroll 6
+  for (int i = tid; i < G::EOPS; i += 256) S.ops[i] = ops[i];
+  if constexpr ((G::FAMS & AQMP_DCT) != 0) {
+#pragma unroll 8
+    for (int i = tid; i < G::K / 2; i += 256) ((double2*)S.dct)[i] = ((const double2*)tab)[i];
+    if (tid < 2 * G::N) S.dct[G::K + tid] = tid < G::N ? 1.0 : 1.0 / G::N;
+  }
+  if constexpr (G::SGNB > 0) {
+    for (int i = tid; i < G::SGNB / 16; i += 256) S.sgn[i] = ops[G::OFF_S + i];
     // the first row of a scale starts at pixel 0
+    const double* h = tab + (G::FAMS == 3 ? G::K : 0);
     if (tid < 8) {
       const int row = tid == 0 ? 0 : 1 << (tid - 1);
       S.mag[tid] = row < G::N ? h[row * G::N] : 0.0;
     }
   }
+  if constexpr (G::XLDS)
+    for (int i = tid; i < G::K / 2; i += 256) ((uint4*)S.x)[i] = ops[G::OFF_X + i];
 }
 
-// CNT consecutive FP64 entries of row p of family f (uniform f, p).
-template <class G, int CNT>
-__device__ inline void sep_row(const SepTab<G>& S, int f, int p, int at, double (&v)[CNT]) {
-  const bool haar = G::FAMS == AQMP_HAAR || (G::FAMS == 3 && f == 1);
-  if (haar) {
+// The FP64 factors of atom `at` (uniform) over the lane's patch: tq at its
+// columns px.., tp at its rows py.. of the whole node's patch, ty at those of
+// its wave's rows.  The constant atom is 1/N times ones.
+template <class G>
+__device__ inline void sep_factors(const SepTab<G>& S, int at, int px, int py, int wq, double (&tq)[G::PW],
+                                   double (&tp)[G::PH], double (&ty)[G::RPW]) {
+  constexpr int N = G::N, K = G::K, PW = G::PW, PH = G::PH, RPW = G::RPW;
+  const int f = at / K, q = (at % K) / N, p = at % N;
+  const bool dc = p == 0 && q == 0;
+  if (G::FAMS == AQMP_HAAR || (G::FAMS == 3 && f == 1)) {
     if constexpr ((G::FAMS & AQMP_HAAR) != 0) {
-      const double mg = S.mag[sep_haar_scale(p)];
+      const double mg = G::FAMS == AQMP_HAAR && dc ? 1.0 : S.mag[sep_haar_scale(q)];
+      const double mh = G::FAMS == AQMP_HAAR && dc ? 1.0 / N : S.mag[sep_haar_scale(p)];
+      uint32_t w[PW / 4], v[PH / 4];
+      __builtin_memcpy(w, __builtin_assume_aligned((const char*)S.sgn + q * N + px, PW), PW);
+      __builtin_memcpy(v, __builtin_assume_aligned((const char*)S.sgn + p * N + py, PH), PH);
 #pragma unroll
-      for (int j = 0; j < CNT; ++j) v[j] = (double)S.sgn[p * G::N + at + j] * mg;
+      for (int j = 0; j < PW; ++j) tq[j] = (double)((int32_t)(w[j / 4] << (24 - 8 * (j % 4))) >> 24) * mg;
+#pragma unroll
+      for (int i = 0; i < PH; ++i) tp[i] = (double)((int32_t)(v[i / 4] << (24 - 8 * (i % 4))) >> 24) * mh;
+      if constexpr (G::WPN > 1) {
+        uint16_t u;
+        __builtin_memcpy(&u, __builtin_assume_aligned((const char*)S.sgn + p * N + py + wq * RPW, 2), 2);
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) ty[i] = (double)((int32_t)((uint32_t)u << (24 - 8 * i)) >> 24) * mh;
+      }
     }
   } else {
     if constexpr ((G::FAMS & AQMP_DCT) != 0) {
+      const double* rq = S.dct + (dc ? N : q) * N + px;
+      const double* rp = S.dct + (dc ? N + 1 : p) * N + py;
 #pragma unroll
-      for (int j = 0; j < CNT; ++j) v[j] = S.dct[p * G::N + at + j];
+      for (int j = 0; j < PW; ++j) tq[j] = rq[j];
+#pragma unroll
+      for (int i = 0; i < PH; ++i) tp[i] = rp[i];
+      if constexpr (G::WPN > 1) {
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) ty[i] = rp[wq * RPW + i];
+      }
     }
+  }
+  if constexpr (G::WPN == 1) {
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) ty[i] = tp[i];
   }
 }
 
@@ -389,43 +349,19 @@ __device__ inline double sep_bcast_f64(double d) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// The table operands of every thread of a workgroup, 16 bytes at a time in
-// thread order, made once with the dictionary (making them in the pursuit
-// took about 2 000 instructions per launch).
-template <class G>
-struct SepOpsBuf {
-  static constexpr int E = (int)((sizeof(SepOps<G>) + 15) / 16);
-  union U {
-    SepOps<G> ops;
-    uint4 w[E];
-    __device__ U() {}
-  };
-};
-
-template <int N, int FAMS, bool BF>
-__global__ __launch_bounds__(256) void k_sep_ops(const double* __restrict__ tab, uint4* __restrict__ out) {
-  using B = SepOpsBuf<SepGeo<N, FAMS, BF>>;
-  typename B::U u;
-#pragma unroll
-  for (int e = 0; e < B::E; ++e) u.w[e] = make_uint4(0u, 0u, 0u, 0u);
-  sep_load_ops<SepGeo<N, FAMS, BF>>(u.ops, tab, N == 64 ? (int)(threadIdx.x >> 6) : 0);
-#pragma unroll
-  for (int e = 0; e < B::E; ++e) out[e * 256 + threadIdx.x] = u.w[e];
-}
-
-template <int N, int FAMS, bool BF>
+template <int N, int FAMS>
 __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict__ jobs, LevelDev lv,
                                                         const int32_t* __restrict__ count_ptr,
                                                         int32_t* __restrict__ queue, int32_t lg,
                                                         const double* __restrict__ tab,
                                                         const uint4* __restrict__ ops) {
-  using G = SepGeo<N, FAMS, BF>;
+  using G = SepGeo<N, FAMS>;
   constexpr int K = G::K, WPN = G::WPN, NPG = G::NPG, PW = G::PW, PH = G::PH, RPW = G::RPW, VPL = G::VPL;
+  // Per node: operand rows of the residual; the gather's pixels; N = 64: row
+  // sums that the waves exchange and their masks (in turn, barriers between).
   __shared__ __attribute__((aligned(16))) char sRes[NPG][G::RBYTES];
   __shared__ __attribute__((aligned(16))) SepTab<G> sTab;
-  __shared__ __attribute__((aligned(16))) uint4 sTop[WPN > 1 ? 4 : 1];            // per wave: largest |c|, its atom, several candidates
-  __shared__ __attribute__((aligned(16))) double sPart[WPN > 1 ? 2 : 1][WPN > 1 ? PH : 1][WPN > 1 ? 64 : 1];
-  __shared__ uint32_t sMask[WPN > 1 ? 256 : 1];
+  __shared__ __attribute__((aligned(16))) uint4 sTop[2];   // per wave: largest |c|; its atom, with the top bit if there are others
   __shared__ double sRed[4];
   __shared__ int sNode[4];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -433,14 +369,30 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
   const int wq = WPN > 1 ? wv : 0;                       // wave within the node
   const int grp = WPN > 1 ? 0 : wv;                      // node slot of the workgroup
   char* sR = sRes[grp];
-  typename SepOpsBuf<G>::U opu;
+  double(*sPart)[PH][64] = (double(*)[PH][64])sR;        // two buffers, WPN > 1
+  uint32_t* sMask = (uint32_t*)(sR + 2 * sizeof(*sPart));
+  static_assert(WPN == 1 || 2 * sizeof(*sPart) + 1024 <= G::RBYTES, "exchange buffers");
+  // [f][p][p']: row p of family f against the other family
+  const float* gram = G::XLDS ? sTab.x : (const float*)(ops + G::OFF_X);
+  sep_load_tab<G>(sTab, tab, ops);
+  // Haar magnitudes of the lane's columns and rows: a row's is its value at
+  // the first pixel of its support
+  float mq[G::TQ] = {}, mp0[4] = {}, mp[G::TT] = {};
+  if constexpr (G::FAMS != AQMP_DCT) {
+    const double* h = tab + (G::FAMS == 3 ? K : 0);
+    auto mag = [&](int row) -> float {
+      const int top = row > 0 ? 1 << (31 - __builtin_clz((unsigned)row)) : N;
+      return (float)h[row * N + (row > 0 ? (row - top) * (N / top) : 0)];
+    };
 #pragma unroll
-  for (int i = 0; i < SepOpsBuf<G>::E; ++i) opu.w[i] = ops[i * 256 + tid];
-  const SepOps<G>& T = opu.ops;
-  sep_load_tab<G>(sTab, tab);
+    for (int i = 0; i < G::TQ; ++i) mq[i] = mag(16 * (wq * G::TQ + i) + (lane & 15)) * (G::TS * G::TS);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) mp0[r] = mag(4 * (lane >> 4) + r);
+#pragma unroll
+    for (int tp = 1; tp < G::TT; ++tp) mp[tp] = mag(16 * tp);   // one scale from row 16 up to the next power of two
+  }
   __syncthreads();
   const int count = *count_ptr;
-  const double inv_n = 1.0 / N;
   const int py = (lane >> 3) * PH + wq * RPW;            // first pixel of the lane's rows
   const int px = (lane & 7) * PW;
   // The first nodes are dealt out in order, the others by the queues: queue
@@ -474,7 +426,10 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
             st[(gy + dy) * N + gx + dx] = (float)v;
             ep += v * v;
           }
-        e = group_sum<256>(ep, sRed);
+        ep = wave_sum_f64(ep);                           // group_sum<256>'s order
+        if (lane == 0) sRed[wv] = ep;
+        sep_sync<WPN>();
+        e = (sRed[0] + sRed[1]) + (sRed[2] + sRed[3]);
       } else {
         constexpr int GP = 2;                            // 2 x 2 pixels per thread of four virtual waves
         double ev[4];
@@ -497,58 +452,45 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
               st[(gy + dy) * N + gx + dx] = (float)v;
               ev[vw] += v * v;
             }
-#pragma unroll
-          for (int off = 1; off < 64; off <<= 1) ev[vw] += __shfl_xor(ev[vw], off, 64);
+          ev[vw] = wave_sum_f64(ev[vw]);
         }
         e = (ev[0] + ev[1]) + (ev[2] + ev[3]);
       }
     }
     e = sep_bcast_f64(e);
-    sep_sync<WPN>();
-    float r[RPW][PW];
+    if constexpr (WPN == 1) sep_sync<WPN>();
+    double r[RPW][PW];                                   // FP32 values
 #pragma unroll
     for (int i = 0; i < RPW; ++i)
 #pragma unroll
-      for (int j = 0; j < PW; ++j) r[i][j] = ((const float*)sR)[(py + i) * N + px + j];
+      for (int j = 0; j < PW; ++j) r[i][j] = (double)((const float*)sR)[(py + i) * N + px + j];
     sep_sync<WPN>();
     // the node after this one: taken here, needed at the end
     int ahead = 0;
     if (WPN > 1 ? tid == 0 : lane == 0) ahead = atomicAdd(queue + qk * kQueuePad, 1);
-    // Scale of the operand rows, a power of two.  FP16 halves: ||r|| goes to
-    // [2^7, 2^8), so that the first product (at most 2^15) and the
-    // remainders stay inside FP16's range.  FP32: 1 unless the plane's
-    // values are far from the usual range.
+    // Scale of the operand rows, a power of two: ||r|| goes to [2^7, 2^8), so
+    // that the first product (at most 2^15) and the remainders stay inside
+    // FP16's range.
     auto scale_of = [](double en) -> float {
       const int ex = (int)((unsigned long long)__double_as_longlong(en) >> 52) - 1023;
-      int sh = ex >> 1;
-      if constexpr (BF) sh -= 7;
-      else if (ex >= -40 && ex < 80) return 1.f;
+      int sh = (ex >> 1) - 7;
       sh = sh < -120 ? -120 : (sh > 120 ? 120 : sh);
       return __uint_as_float((uint32_t)(127 - sh) << 23);
     };
-    float sc = scale_of(e);
-    auto put_rows = [&]() {                              // the lane's pixels into the operand rows
+    auto put_rows = [&](float sc) {                      // the lane's pixels into the operand rows
 #pragma unroll
       for (int i = 0; i < RPW; ++i) {
         char* row = sR + (py + i) * G::ROWB;
-        if constexpr (BF) {
-          uint32_t h[PW / 2], l[PW / 2];
+        uint32_t h[PW / 2], l[PW / 2];
 #pragma unroll
-          for (int j = 0; j < PW / 2; ++j) sp_split2_scaled(r[i][2 * j], r[i][2 * j + 1], sc, h[j], l[j]);
-          if constexpr (PW == 8) {
-            *(uint4*)(row + 2 * px) = make_uint4(h[0], h[1], h[2], h[3]);
-            *(uint4*)(row + G::HALFB + 2 * px) = make_uint4(l[0], l[1], l[2], l[3]);
-          } else {
-            *(uint2*)(row + 2 * px) = make_uint2(h[0], h[1]);
-            *(uint2*)(row + G::HALFB + 2 * px) = make_uint2(l[0], l[1]);
-          }
-        } else {
+        for (int j = 0; j < PW / 2; ++j) sp_split2_scaled((float)r[i][2 * j], (float)r[i][2 * j + 1], sc, h[j], l[j]);
+        // in the order of the k-slots: pixel x is value 4 ((x / 16) % 2) + x % 4
+        // of the slots (x / 32, (x / 4) % 4)
 #pragma unroll
-          for (int j = 0; j < PW; j += 4) {
-            sp_f32x4 v{r[i][j], r[i][j + 1], r[i][j + 2], r[i][j + 3]};
-            if (sc != 1.f) v *= sc;
-            *(sp_f32x4*)(row + 4 * (px + j)) = v;
-          }
+        for (int j = 0; j < PW; j += 4) {
+          char* at = row + 2 * (32 * (px >> 5) + 8 * ((px >> 2) & 3) + 4 * ((px >> 4) & 1) + 2 * j);
+          *(uint2*)at = make_uint2(h[j / 2], h[j / 2 + 1]);
+          *(uint2*)(at + G::HALFB) = make_uint2(l[j / 2], l[j / 2 + 1]);
         }
       }
     };
@@ -561,229 +503,234 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
     int rec_i = 0;
     double rec_c = 0.0;
     const size_t rec0 = (size_t)node * lv.kmax;
-    if (st == ST_RUN) put_rows();
-    sep_sync<WPN>();
+    sp_f32x16 C[G::NFAM];                                // correlations, times gain
+    float win = 0.f, mx = 0.f;
+    uint32_t mask = 0u;                                  // bit VPL - 1 - j: value j is within win of the wave's largest
+    uint32_t best = 0u;                                  // the wave's candidate, with the top bit if there are others or none
+    auto atom_of = [&](int w, int l, int bit) -> int {   // wave of the node, lane, bit of its mask
+      const int j = VPL - 1 - bit, f = j >> 4, i = (j & 15) / (4 * G::TT), tp = (j >> 2) % G::TT;
+      return f * K + (16 * (w * G::TQ + i) + (l & 15)) * N + 16 * tp + 4 * (l >> 4) + (j & 3);
+    };
+    // The wave's largest |c| and its atoms within the window, to the node's
+    // other waves.
+    auto top = [&]() {
+      if constexpr (G::NFAM == 2) {
+        // the second family's constant atom equals the first's, which wins the tie
+        if (wq == 0 && lane == 0) C[1][0] = 0.f;
+      }
+      auto val = [&](int j) -> float { return C[j >> 4][j & 15]; };
+      float m0 = 0.f, m1 = 0.f;
+#pragma unroll
+      for (int j = 0; j < VPL; j += 4) {
+        m0 = fmaxf(fmaxf(fabsf(val(j)), fabsf(val(j + 1))), m0);
+        m1 = fmaxf(fmaxf(fabsf(val(j + 2)), fabsf(val(j + 3))), m1);
+      }
+      mx = wave_max_f32(fmaxf(m0, m1));
+      // the sign of thr - |c| into the mask: two instructions per value
+      const float thr = mx - win;
+      mask = 0u;
+#pragma unroll
+      for (int j = 0; j < VPL; ++j)
+        mask = __builtin_amdgcn_alignbit(mask, __float_as_uint(thr - fabsf(val(j))), 31);
+      if (!(mx > 0.f && mx < __builtin_inff())) mask = 0u;   // undefined sums: nothing to compare
+      const unsigned long long near = __ballot(mask != 0u);
+      const bool others = __popcll(near) != 1 || __ballot((mask & (mask - 1u)) != 0u) != 0ull;
+      const int l = near ? __builtin_ctzll(near) : 0;
+      const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)mask, l);
+      best = (uint32_t)atom_of(wq, l, bits ? __builtin_ctz(bits) : 0) | (others ? 0x80000000u : 0u);
+      if constexpr (WPN > 1)
+        if (lane == 0) {
+          ((uint32_t*)sTop)[wv] = __float_as_uint(mx);
+          ((uint32_t*)sTop)[4 + wv] = best;
+        }
+    };
     while (st == ST_RUN) {
       if (!(e > 0.0 && e < __builtin_inf())) {           // a zero residual, or undefined pixels: nothing to select
         st = ST_ZERO;
         break;
       }
-      // ---- correlations; the wave's atoms within 2 delta of its largest ----
-      uint32_t mask = 0u;                                // bit VPL - 1 - j: value j is within
-      float mx;
-      const float win = __builtin_amdgcn_sqrtf((float)(e * ((double)sc * (double)sc))) * (1.0001f * 0x1p-12f * G::TS * G::TS);
-      {
-        sp_f32x4 C[G::NFAM][G::TQ][G::TT];
-        sep_correlate<G>(sR, T, C);
-        if constexpr (G::NFAM == 2) {
-          // the second family's constant atom equals the first's, which wins the tie
-          if (wq == 0 && lane == 0) C[1][0][0][0] = 0.f;
+      // ---- correlations from the residual ----
+      const float sc = scale_of(e);
+      sep_sync<WPN>();                                   // the sums of the last step are read
+      put_rows(sc);
+      sep_sync<WPN>();
+      sep_correlate<G>(sR, sTab.ops, wq, mq, mp0, mp, C);
+      const double gain = (double)sc * (double)(G::TS * G::TS);
+      win = __builtin_amdgcn_sqrtf((float)(e * ((double)sc * (double)sc))) * (1.0001f * 0x1p-13f * G::TS * G::TS);
+      top();
+      sep_sync<WPN>();
+      // They hold while ||r|| is at least half of what it is now, for at most
+      // 64 steps (and to the end of a window of records).
+      const double elim = fmax(eps2, 0.25 * e), emax = 4.0 * e;
+      const int tlim = min(kmax, (t & ~63) + 64);
+      for (;;) {
+        uint32_t pick = best;
+        if constexpr (WPN > 1) {
+          const uint4 a = sTop[0], b = sTop[1];
+          const float wm[4] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w)};
+          const uint32_t wb[4] = {b.x, b.y, b.z, b.w};
+          mx = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));
+          const float thr = mx - win;
+          uint32_t n = 0u;
+          pick = 0u;
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            pick = wm[w] >= thr ? wb[w] : pick;
+            n += wm[w] >= thr ? 1u : 0u;
+          }
+          pick = n == 1u ? pick : 0x80000000u;
         }
-        auto val = [&](int j) -> float {
-          return C[j / (4 * G::TT * G::TQ)][(j / (4 * G::TT)) % G::TQ][(j >> 2) % G::TT][j & 3];
+        pick = (uint32_t)__builtin_amdgcn_readfirstlane((int)pick);
+        // rows of the 1D Gram matrix for the update of the correlations (read
+        // ahead of the re-score that hides them)
+        sp_f32x4 gp[G::NFAM == 2 ? G::TT : 1];
+        float gq[G::NFAM == 2 ? G::TQ : 1];
+        auto gram_rows = [&](int at) {
+          if constexpr (G::NFAM == 2) {
+            const int f = at / K, q = (at % K) / N, p = at % N;
+            const float* x = gram + (size_t)f * K;
+#pragma unroll
+            for (int tp = 0; tp < G::TT; ++tp) gp[tp] = *(const sp_f32x4*)(x + p * N + 16 * tp + 4 * (lane >> 4));
+#pragma unroll
+            for (int i = 0; i < G::TQ; ++i) gq[i] = x[q * N + 16 * (wq * G::TQ + i) + (lane & 15)];
+          }
         };
-        float m0 = 0.f, m1 = 0.f;
+        // ---- FP64 re-score (k_select's patches and order of operations) ----
+        double tq[PW], tp8[PH], ty[RPW];
+        auto rescore = [&](int at) -> double {
+          sep_factors<G>(sTab, at, px, (lane >> 3) * PH, wq, tq, tp8, ty);
+          double all[PH], sr[RPW];
 #pragma unroll
-        for (int j = 0; j < VPL; j += 4) {
-          m0 = fmaxf(fmaxf(fabsf(val(j)), fabsf(val(j + 1))), m0);
-          m1 = fmaxf(fmaxf(fabsf(val(j + 2)), fabsf(val(j + 3))), m1);
-        }
-        mx = wave_max_f32(fmaxf(m0, m1));
-        // the sign of thr - |c| into the mask: two instructions per value
-        const float thr = mx - win;
+          for (int i = 0; i < RPW; ++i) {
+            sr[i] = 0.0;
 #pragma unroll
-        for (int j = 0; j < VPL; ++j)
-          mask = __builtin_amdgcn_alignbit(mask, __float_as_uint(thr - fabsf(val(j))), 31);
-        if (!(mx > 0.f && mx < __builtin_inff())) mask = 0u;   // undefined sums: nothing to compare
-      }
-      auto atom_of = [&](int w, int l, int bit) -> int {   // wave of the node, lane, bit of its mask
-        const int j = VPL - 1 - bit, f = j / (4 * G::TT * G::TQ), i = (j / (4 * G::TT)) % G::TQ, tp = (j >> 2) % G::TT;
-        return f * K + (16 * (w * G::TQ + i) + (l & 15)) * N + 16 * tp + 4 * (l >> 4) + (j & 3);
-      };
-      const unsigned long long near = __ballot(mask != 0u);
-      bool several = __popcll(near) != 1 || __ballot((mask & (mask - 1u)) != 0u) != 0ull;
-      int cand = 0;
-      {
-        const int l = near ? __builtin_ctzll(near) : 0;
-        const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)mask, l);
-        cand = atom_of(wq, l, bits ? __builtin_ctz(bits) : 0);
-      }
-      uint32_t wsel = 1u;                                // waves with a candidate
-      if constexpr (WPN > 1) {
-        if (lane == 0) sTop[wv] = make_uint4(__float_as_uint(mx), (uint32_t)cand, several ? 1u : 0u, 0u);
-        sep_sync<WPN>();
-        float wm[4];
-        uint32_t sev = 0u;
+            for (int j = 0; j < PW; ++j) sr[i] = fma(r[i][j], tq[j], sr[i]);
+          }
+          if constexpr (WPN > 1) {
+            // the row sums of the node's four waves
 #pragma unroll
-        for (int w = 0; w < 4; ++w) wm[w] = __uint_as_float(sTop[w].x);
-        mx = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));
-        const float thr = mx - win;
-        wsel = 0u;
+            for (int i = 0; i < RPW; ++i) sPart[par][wq * RPW + i][lane] = sr[i];
+            sep_sync<WPN>();
 #pragma unroll
-        for (int w = 0; w < 4; ++w) wsel |= wm[w] >= thr ? 1u << w : 0u;
-        wsel = (uint32_t)__builtin_amdgcn_readfirstlane((int)wsel);
-        const uint4 only = sTop[wsel ? __builtin_ctz(wsel) : 0];
-        cand = __builtin_amdgcn_readfirstlane((int)only.y);
-        sev = (uint32_t)__builtin_amdgcn_readfirstlane((int)only.z);
-        several = sev != 0u || (wsel & (wsel - 1u)) != 0u;
-        mx = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(mx)));
-      }
-      // ---- FP64 re-score (k_select's patches and order of operations) ----
-      double tq[PW], tp8[PH];
-      auto rescore = [&](int at) -> double {
-        const int f = at / K, q = (at % K) / N, p = at % N;
-        const bool dc = p == 0 && q == 0;
-        sep_row<G, PW>(sTab, f, q, px, tq);
-        sep_row<G, PH>(sTab, f, p, (lane >> 3) * PH, tp8);
-        double sr[RPW];
-#pragma unroll
-        for (int i = 0; i < RPW; ++i) {
-          sr[i] = 0.0;
-          if (dc) {
-#pragma unroll
-            for (int j = 0; j < PW; ++j) sr[i] += (double)r[i][j];
+            for (int i = 0; i < PH; ++i) all[i] = sPart[par][i][lane];
+            par ^= 1;
           } else {
 #pragma unroll
-            for (int j = 0; j < PW; ++j) sr[i] = fma((double)r[i][j], tq[j], sr[i]);
+            for (int i = 0; i < PH; ++i) all[i] = sr[i];
           }
-        }
-        double all[PH];
-        if constexpr (WPN > 1) {
-          // the row sums of the node's four waves
-#pragma unroll
-          for (int i = 0; i < RPW; ++i) sPart[par][wq * RPW + i][lane] = sr[i];
-          sep_sync<WPN>();
-#pragma unroll
-          for (int i = 0; i < PH; ++i) all[i] = sPart[par][i][lane];
-          par ^= 1;
-        } else {
-#pragma unroll
-          for (int i = 0; i < PH; ++i) all[i] = sr[i];
-        }
-        double part = 0.0;
-        if (dc) {
-#pragma unroll
-          for (int i = 0; i < PH; ++i) part += all[i];
-          part *= inv_n;
-        } else {
+          double part = 0.0;
 #pragma unroll
           for (int i = 0; i < PH; ++i) part = fma(tp8[i], all[i], part);
-        }
-        return wave_sum_f64(part);
-      };
-      int atom = -1;
-      double coef = 0.0, mag = -1.0;
-      if (!several && mx < __builtin_inff()) {
-        coef = rescore(cand);
-        mag = fabs(coef);
-        atom = cand;
-      } else if (mx < __builtin_inff()) {
-        // several atoms within the window: every one of them, lowest index on
-        // ties (a wave's mask is relative to its own largest: no fewer atoms)
-        if constexpr (WPN > 1) {
-          sMask[tid] = mask;
-          sep_sync<WPN>();
-        }
-        for (int w = 0; w < WPN; ++w) {
-          if (!((wsel >> w) & 1u)) continue;
-          const uint32_t mw = WPN > 1 ? sMask[64 * w + lane] : mask;
-          unsigned long long lanes = __ballot(mw != 0u);
-          while (lanes) {
-            const int l = __builtin_ctzll(lanes);
-            lanes &= lanes - 1ull;
-            uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)mw, l);
-            while (bits) {
-              const int bit = __builtin_ctz(bits);
-              bits &= bits - 1u;
-              const int at = atom_of(w, l, bit);
-              const double c0 = rescore(at), m0 = fabs(c0);
-              if (m0 > mag || (m0 == mag && at < atom)) {
-                mag = m0;
-                coef = c0;
-                atom = at;
+          return wave_sum_f64(part);
+        };
+        int atom = -1;
+        double coef = 0.0, mag = -1.0;
+        if (!(pick >> 31)) {
+          gram_rows((int)pick);
+          coef = rescore((int)pick);
+          mag = fabs(coef);
+          atom = (int)pick;
+        } else if (mx < __builtin_inff()) {
+          // several atoms within the window: every one of them, lowest index on
+          // ties (a wave's mask is relative to its own largest: no fewer atoms)
+          uint32_t wsel = 1u;                            // waves with a candidate
+          if constexpr (WPN > 1) {
+            sMask[tid] = mask;
+            wsel = 0u;
+            for (int w = 0; w < 4; ++w) wsel |= __uint_as_float(((const uint32_t*)sTop)[w]) >= mx - win ? 1u << w : 0u;
+            wsel = (uint32_t)__builtin_amdgcn_readfirstlane((int)wsel);
+            sep_sync<WPN>();
+          }
+          for (int w = 0; w < WPN; ++w) {
+            if (!((wsel >> w) & 1u)) continue;
+            const uint32_t mw = WPN > 1 ? sMask[64 * w + lane] : mask;
+            unsigned long long lanes = __ballot(mw != 0u);
+            while (lanes) {
+              const int l = __builtin_ctzll(lanes);
+              lanes &= lanes - 1ull;
+              uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)mw, l);
+              while (bits) {
+                const int bit = __builtin_ctz(bits);
+                bits &= bits - 1u;
+                const int at = atom_of(w, l, bit);
+                const double c0 = rescore(at), m0 = fabs(c0);
+                if (m0 > mag || (m0 == mag && at < atom)) {
+                  mag = m0;
+                  coef = c0;
+                  atom = at;
+                }
               }
             }
           }
-        }
-        if (atom >= 0) {
-          const int f = atom / K, q = (atom % K) / N, p = atom % N;
-          sep_row<G, PW>(sTab, f, q, px, tq);
-          sep_row<G, PH>(sTab, f, p, (lane >> 3) * PH, tp8);
-        }
-      }
-      if (atom < 0 || mag == 0.0) {
-        st = ST_ZERO;
-        break;
-      }
-      // ---- rank-1 update, norm, record, stop test ----
-      const bool dc = (atom % K) == 0;
-      double eh[RPW];
-      {
-        double ty[RPW];
-        if constexpr (WPN > 1) {
-#pragma unroll
-          for (int i = 0; i < RPW; ++i) {
-            double v = tp8[i];
-#pragma unroll
-            for (int w = 1; w < 4; ++w) v = wq == w ? tp8[w * RPW + i] : v;
-            ty[i] = v;
+          if (atom >= 0) {
+            gram_rows(atom);
+            sep_factors<G>(sTab, atom, px, (lane >> 3) * PH, wq, tq, tp8, ty);
           }
-        } else {
-#pragma unroll
-          for (int i = 0; i < RPW; ++i) ty[i] = tp8[i];
         }
-        if (dc) {
-#pragma unroll
-          for (int i = 0; i < RPW; ++i) ty[i] = inv_n;
-#pragma unroll
-          for (int j = 0; j < PW; ++j) tq[j] = 1.0;
+        if (atom < 0 || mag == 0.0) {
+          st = ST_ZERO;
+          break;
         }
+        // ---- rank-1 update, norm, record, stop test ----
+        double eh[RPW];
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
           eh[i] = 0.0;
 #pragma unroll
           for (int j = 0; j < PW; ++j) {
             const double phi = ty[i] * tq[j];
-            const float rn = (float)fma(-coef, phi, (double)r[i][j]);
+            const double rn = (double)(float)fma(-coef, phi, r[i][j]);
             r[i][j] = rn;
-            eh[i] = fma((double)rn, (double)rn, eh[i]);
+            eh[i] = fma(rn, rn, eh[i]);
           }
         }
-      }
-      if constexpr (BF) {
-        // scaled by the norm to come, e - c^2 but for the rounding of the residual
-        const double ep = fma(-coef, coef, e), lo = e * 0x1p-30;
-        sc = scale_of(ep > lo ? ep : lo);
-      }
-      put_rows();
-      double ew = 0.0;
-      if constexpr (WPN > 1) {
+        if constexpr (WPN > 1) {
 #pragma unroll
-        for (int i = 0; i < RPW; ++i) sPart[par][wq * RPW + i][lane] = eh[i];
-        sep_sync<WPN>();
-#pragma unroll
-        for (int i = 0; i < PH; ++i) ew += sPart[par][i][lane];
-        par ^= 1;
-      } else {
-        sep_sync<WPN>();
-#pragma unroll
-        for (int i = 0; i < PH; ++i) ew += eh[i];
-      }
-      e = wave_sum_f64(ew);
-      if constexpr (BF) {
-        const double es = e * ((double)sc * (double)sc);
-        if (!(es >= 0x1p8 && es < 0x1p18) && e > 0.0 && e < __builtin_inf()) {   // the guess was off: once more
-          sc = scale_of(e);
-          sep_sync<WPN>();
-          put_rows();
-          sep_sync<WPN>();
+          for (int i = 0; i < RPW; ++i) sPart[par][wq * RPW + i][lane] = eh[i];
         }
+        // ---- correlations of the new residual: the atom's own loses its
+        // coefficient, its family's others are orthogonal to it, those of the
+        // other family lose <phi, phi'> = X[p][p'] X[q][q'] times it ----
+        {
+          const int f = atom / K, q = (atom % K) / N, p = atom % N;
+          const float cs = (float)(coef * gain);
+          const float own = lane == (((p & 15) >> 2) << 4 | (q & 15)) ? cs : 0.f;
+          const int j = (((q >> 4) % G::TQ) * G::TT + (p >> 4)) * 4 + (p & 3);
+          auto update = [&](sp_f32x16& Cs, sp_f32x16& Co) {
+            if constexpr (G::NFAM == 2) {
+#pragma unroll
+              for (int i = 0; i < G::TQ; ++i) {
+                const float s = -(cs * gq[i]);
+#pragma unroll
+                for (int x = 0; x < 4 * G::TT; ++x)
+                  Co[i * 4 * G::TT + x] = fmaf(s, gp[x >> 2][x & 3], Co[i * 4 * G::TT + x]);
+              }
+            }
+            if (WPN == 1 || (q >> 4) / G::TQ == wq) Cs[j] -= own;
+          };
+          if (G::NFAM == 1 || f == 0) update(C[0], C[G::NFAM - 1]);
+          else update(C[G::NFAM - 1], C[0]);
+        }
+        top();
+        double ew = 0.0;
+        if constexpr (WPN > 1) {
+          sep_sync<WPN>();
+#pragma unroll
+          for (int i = 0; i < PH; ++i) ew += sPart[par][i][lane];
+          par ^= 1;
+        } else {
+#pragma unroll
+          for (int i = 0; i < PH; ++i) ew += eh[i];
+        }
+        e = wave_sum_f64(ew);
+        if (lane == (t & 63)) {
+          rec_i = atom;
+          rec_c = coef;
+        }
+        ++t;
+        if (!(e >= elim && e < emax && t < tlim)) break;
       }
-      if (lane == (t & 63)) {
-        rec_i = atom;
-        rec_c = coef;
-      }
-      ++t;
+      if (st != ST_RUN) break;
       if ((t & 63) == 0 && wq == 0) {
         lv.rec_idx[rec0 + t - 64 + lane] = rec_i;
         lv.rec_coef[rec0 + t - 64 + lane] = rec_c;
@@ -812,74 +759,63 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
   }
 }
 
-template <int N, int FAMS, bool BF>
+template <int N, int FAMS>
 hipError_t launch_sep_n(const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* queue, int64_t cap,
                         const double* tab, const void* ops, hipStream_t s) {
-  using G = SepGeo<N, FAMS, BF>;
+  using G = SepGeo<N, FAMS>;
   // Nodes come from a counter, so the grid is as many workgroups as are
   // resident at once (at most one per NPG nodes of the level).
   int dev = 0, n_cus = 0, per_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_pursuit_sep<N, FAMS, BF>, 256, 0) != hipSuccess || per_cu < 1)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_pursuit_sep<N, FAMS>, 256, 0) != hipSuccess || per_cu < 1)
     per_cu = 1;
   int64_t wgs = (cap + G::NPG - 1) / G::NPG;
   if (wgs > (int64_t)n_cus * per_cu) wgs = (int64_t)n_cus * per_cu;
   if (wgs < 1) wgs = 1;
-  hipLaunchKernelGGL((k_pursuit_sep<N, FAMS, BF>), dim3((unsigned)wgs), dim3(256), 0, s, jobs, lv, count, queue,
+  hipLaunchKernelGGL((k_pursuit_sep<N, FAMS>), dim3((unsigned)wgs), dim3(256), 0, s, jobs, lv, count, queue,
                      ilog2(N), tab, (const uint4*)ops);
   return hipGetLastError();
 }
 
-template <int N, int FAMS, bool BF>
-hipError_t launch_sep_ops_n(const double* tab, void* out, hipStream_t s) {
-  hipLaunchKernelGGL((k_sep_ops<N, FAMS, BF>), dim3(1), dim3(256), 0, s, tab, (uint4*)out);
+template <int N, int FAMS>
+hipError_t launch_sep_ops_n(const double* tab, const double* xg, void* out, hipStream_t s) {
+  hipLaunchKernelGGL((k_sep_ops<N, FAMS>), dim3(1), dim3(256), 0, s, tab, xg, (uint4*)out);
   return hipGetLastError();
 }
 
 }  // namespace
 
-// Calls CALL with NN, FF, BB set for a block size, family mask and precision.
-#define AQMP_SEP_F(NN_, CALL)                                                                              \
-  {                                                                                                        \
-    constexpr int NN = NN_;                                                                                \
-    if (precision == AQMP_PREC_BF16) {                                                                     \
-      constexpr bool BB = true;                                                                            \
-      switch (families) {                                                                                  \
-        case 1: { constexpr int FF = 1; CALL; }                                                            \
-        case 2: { constexpr int FF = 2; CALL; }                                                            \
-        case 3: { constexpr int FF = 3; CALL; }                                                            \
-      }                                                                                                    \
-    } else {                                                                                               \
-      constexpr bool BB = false;                                                                           \
-      switch (families) {                                                                                  \
-        case 1: { constexpr int FF = 1; CALL; }                                                            \
-        case 2: { constexpr int FF = 2; CALL; }                                                            \
-        case 3: { constexpr int FF = 3; CALL; }                                                            \
-      }                                                                                                    \
-    }                                                                                                      \
+// Runs CALL with NN, FF set for a block size and family mask.
+#define AQMP_SEP_F(NN_, CALL)                   \
+  {                                             \
+    constexpr int NN = NN_;                     \
+    switch (families) {                         \
+      case 1: { constexpr int FF = 1; CALL; }   \
+      case 2: { constexpr int FF = 2; CALL; }   \
+      case 3: { constexpr int FF = 3; CALL; }   \
+    }                                           \
   }
-#define AQMP_SEP(CALL)             \
-  switch (n) {                     \
+#define AQMP_SEP(CALL)                   \
+  switch (n) {                           \
     case 32: AQMP_SEP_F(32, CALL) break; \
     case 64: AQMP_SEP_F(64, CALL) break; \
   }
 
-size_t sep_ops_bytes(int n, int precision, uint32_t families) {
-  AQMP_SEP(return sizeof(uint4) * 256 * (size_t)(SepOpsBuf<SepGeo<NN, FF, BB>>::E))
+size_t sep_ops_bytes(int n, uint32_t families) {
+  AQMP_SEP(return (SepGeo<NN, FF>::BYTES))
   return 0;
 }
 
-hipError_t launch_sep_ops(int n, int precision, uint32_t families, const double* tab, void* out, hipStream_t s) {
-  AQMP_SEP(return (launch_sep_ops_n<NN, FF, BB>(tab, out, s)))
+hipError_t launch_sep_ops(int n, uint32_t families, const double* tab, const double* xg, void* out, hipStream_t s) {
+  AQMP_SEP(return (launch_sep_ops_n<NN, FF>(tab, xg, out, s)))
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_pursuit_sep(int n, int precision, uint32_t families, const JobDev* jobs, LevelDev lv,
-                              const int32_t* count, int32_t* queue, int64_t cap, const double* tab, const void* ops,
-                              hipStream_t s) {
-  AQMP_SEP(return (launch_sep_n<NN, FF, BB>(jobs, lv, count, queue, cap, tab, ops, s)))
+hipError_t launch_pursuit_sep(int n, uint32_t families, const JobDev* jobs, LevelDev lv, const int32_t* count,
+                              int32_t* queue, int64_t cap, const double* tab, const void* ops, hipStream_t s) {
+  AQMP_SEP(return (launch_sep_n<NN, FF>(jobs, lv, count, queue, cap, tab, ops, s)))
   return hipErrorInvalidValue;
 }
 

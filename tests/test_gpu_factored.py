@@ -120,6 +120,24 @@ def test_exact_ties(A, dics, prec):
 
 
 @pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("fam", [1, 2, 3])
+@pytest.mark.parametrize("n", [32, 64])
+def test_carried_correlations(A, dics, n, fam, prec):
+    """Pursuits past the steps that a product serves: 100 steps without a stop
+    on a noise block (its norm halves late), and a smooth one under a bright
+    mean, whose norm falls by orders of magnitude within them.  The reference
+    is the FP32 step-by-step form, a product per step."""
+    rng = np.random.default_rng(31)
+    y, x = np.mgrid[0:n, 0:n] / n
+    planes = [_dev(0.5 + 0.2 * rng.standard_normal((n, n))), _dev(0.9 + 0.05 * np.sin(5 * x + 2 * y) + 0.01 * y ** 3)]
+    p = dict(tol=1e-9, tol_mode="abs", max_atoms=100, n_min=n, n_max=n)
+    jobs = [(0, 0), (1, 0)]
+    want = _nodes(A, dics(fam), planes, [p], jobs, 0, stepwise=True)
+    _same(_nodes(A, dics(fam), planes, [p], jobs, prec), want)
+    assert (want.leaves["n_atoms"] == 100).all()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("fam", [1, 3])
 def test_undefined_pixels(A, dics, prec, fam):
     """A plane with an infinite and one with an undefined pixel: their blocks
