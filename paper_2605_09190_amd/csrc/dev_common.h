@@ -214,17 +214,19 @@ __device__ inline double wave_sum_f64(double d) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Largest of non-negative floats (or of any values by their order) over the wave.
-__device__ inline float wave_max_f32(float v) {
-#define AQMP_FMAXSTEP(C) v = fmaxf(v, __uint_as_float(row_perm_u32<C>(__float_as_uint(v))));
-  AQMP_FMAXSTEP(0xB1) AQMP_FMAXSTEP(0x4E) AQMP_FMAXSTEP(0x141) AQMP_FMAXSTEP(0x140)
-#undef AQMP_FMAXSTEP
+// Largest of non-negative floats over the wave, by their bits (which order
+// alike, and need no quieting of NaNs first).
+__device__ inline float wave_max_f32(float f) {
+  uint32_t v = __float_as_uint(f);
+#define AQMP_MAXSTEP(C) { const uint32_t o = row_perm_u32<C>(v); v = o > v ? o : v; }
+  AQMP_MAXSTEP(0xB1) AQMP_MAXSTEP(0x4E) AQMP_MAXSTEP(0x141) AQMP_MAXSTEP(0x140)
+#undef AQMP_MAXSTEP
   uint32_t p, q;
-  lane_pair_u32<16>(__float_as_uint(v), p, q);
-  v = fmaxf(__uint_as_float(p), __uint_as_float(q));
-  lane_pair_u32<32>(__float_as_uint(v), p, q);
-  v = fmaxf(__uint_as_float(p), __uint_as_float(q));
-  return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v)));
+  lane_pair_u32<16>(v, p, q);
+  v = p > q ? p : q;
+  lane_pair_u32<32>(v, p, q);
+  v = p > q ? p : q;
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)v));
 }
 
 }  // namespace aqmp

@@ -554,7 +554,7 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
         AQMP_LAUNCH(launch_pursuit_sep(n, d->families, c->djobs, a.lv, count, c->dqueue[pi].at[l], pp.cap[l], D.d_tab, D.d_sep, s));
       else if (sub_level(c, n))
         AQMP_LAUNCH(launch_pursuit_sub(n, c->opt.precision, d->families, c->djobs, a.lv, count, c->dqueue[pi].at[l],
-                                       pp.cap[l], D.d_tab, s));
+                                       pp.cap[l], D.d_tab, D.d_xg, s));
       else
         AQMP_LAUNCH(launch_mp_fused(n, c->djobs, a.lv, count, l, D.m, D.d_tab, s));
       if (l > pp.lg_lo && pp.cap[l - 1] > 0)

@@ -203,7 +203,8 @@ hipError_t launch_mp_fused(int n, const JobDev* jobs, LevelDev lv, const int32_t
 // Whole-level pursuit of the dense solver at N = 8 (BF16 form) and 16
 // (queue: the level's node counters, zero on entry; cap: its node capacity).
 hipError_t launch_pursuit_sub(int n, int precision, uint32_t families, const JobDev* jobs, LevelDev lv,
-                              const int32_t* count, int32_t* queue, int64_t cap, const double* tab, hipStream_t s);
+                              const int32_t* count, int32_t* queue, int64_t cap, const double* tab, const double* xg,
+                              hipStream_t s);
 // Gram and OMP forms (FP64).  For N >= 16 launch_gram_init writes the
 // correlations of every node of the level to cbuf ([node][nfam * n * n]) and
 // sets its ||y||^2 and first stop test; the pursuit launches then take each

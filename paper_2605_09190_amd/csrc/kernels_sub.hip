@@ -7,23 +7,30 @@
 // The correlation is the factored one of kernels_sep.hip: C_f = T_f R T_f^T
 // for every family f, first D1[y][q] = sum_x R[y][x] T[q][x], then C[p][q] =
 // sum_y T[p][y] D1[y][q], whose lane layout makes D1 the B operand of the
-// second product as it is.  FP16 halves (BF16 form): the value and its
-// remainder of one operand sit side by side in the 32-deep contraction of
+// second product as it is, and with FP16 halves: the value and its remainder
+// of one operand sit side by side in the 32-deep contraction of
 // v_mfma_f32_16x16x32_f16, so one instruction makes two of the three
 // products:
 //   N = 16: A = [R hi | R lo] against [T hi; T hi] and (DCT) [T lo; 0];
 //   N = 8:  two nodes fill the 16 rows, both families the 16 columns, and
 //           A = [R hi | R lo | R hi | 0] against [T hi; T hi; T lo; 0] makes
 //           all three products at once.
-// Selection as in kernels_sep.hip: every atom whose |c| is within 2^-12 ||r||
-// of the largest is re-scored in FP64.
+// N = 16 carries the correlations from step to step as kernels_sep.hip does,
+// until one of the wave's running nodes wants them anew (then all take them);
+// with four nodes to a wave N = 8 would want them at most steps.  Largest
+// error over ||r|| at N = 16, whole pursuits: 1.2e-7 (FP32 products of every
+// step 3.8e-7).  Selection as there, too: every atom whose |c| is within
+// 2^-13 ||r'|| of the largest is re-scored in FP64.
 //
-// What bounds it: the instructions of a step (about 400 for a wave's nodes
-// together), then the longest pursuits.  On three 2048 x 2048 planes N = 16
-// (157 690 node-steps) takes 124 us and N = 8 (170 692) 89 us; with the
-// unfactored BF16 product (8 or 4 times the operations) in workgroups of 16
-// slots, which met three times a step, 254 and 115 us.  FP32 form, 1536 x
-// 1024 x 3: N = 16 96 us, 1 870 us step by step.
+// What bounds it: the instructions of a step (about 400 for the two nodes of
+// a wave), then the longest pursuits.  On three 2048 x 2048 planes N = 16
+// (157 690 node-steps) takes 91 us and N = 8 (170 692) 77 us; with the N = 16
+// correlations made anew at every step, matrix-core results copied out of the
+// accumulator registers and the constant atom's sums beside the others' 124
+// and 88 us, with the unfactored BF16 product (8 or 4 times the operations)
+// in workgroups of 16 slots, which met three times a step, 254 and 115 us.
+// FP32 form, 1536 x 1024 x 3: N = 16 67 us (FP32 products at every step 97 us,
+// step by step 1 870 us).
 //
 // The order of operations of the FP64 re-score, update and norms is fixed by
 // the patches (SubGeo): BF16 form a slot of 32 (N = 16) or 16 lanes with rows
@@ -52,11 +59,14 @@ struct SubGeo {
   // values per lane and node: N = 16 four per family; N = 8 four (rows and
   // columns of one family meet in half of the lanes)
   static constexpr int VPL = N == 16 ? 4 * NFAM : 4;
+  // N = 16: correlations carried from step to step (N = 8: one of the four
+  // nodes of a wave would want them anew at most steps)
+  static constexpr bool CARRY = N == 16;
   // operand row in LDS (value half, remainder half, padding against bank
   // conflicts), and bytes per node
   static constexpr int ROWB = N == 16 ? 80 : 48;
   static constexpr int NODEB = N * ROWB;
-  static constexpr float TS = BF ? 128.f : 1.f;           // see SepGeo::TS
+  static constexpr float TS = 128.f;                      // see SepGeo::TS
   static_assert(N == 16 || (N == 8 && BF), "block sizes");
   static_assert(PR * PC * LPS == K && PR >= 1 && VPL <= 8, "patches");
 };
@@ -75,13 +85,12 @@ __device__ inline uint32_t sb_split_lo(float a, float b, uint32_t h) {
   return l;
 }
 
-// Table operands.  BF16 form: t1 the B operands of the first product, t2 the
-// A operands of the second; index 0 the products with [T hi; T hi] (N = 8:
-// all three), 1 the DCT's remainders.  FP32 form: t[f][r] = T_f[lane % 16][4 g + r].
+// Table operands: t1 the B operands of the first product, t2 the A operands of
+// the second; index 0 the products with [T hi; T hi] (N = 8: all three), 1 the
+// DCT's remainders.
 template <class G>
 struct SubOps {
-  sb_h8 t1[G::BF ? G::NFAM : 1], t1l[1], t2[G::BF ? (G::N == 8 ? 2 : G::NFAM) : 1], t2l[G::N == 8 ? 2 : 1];
-  float t[G::BF ? 1 : G::NFAM][4];
+  sb_h8 t1[G::N == 8 ? 1 : G::NFAM], t1l[1], t2[G::N == 8 ? 2 : G::NFAM], t2l[G::N == 8 ? 2 : 1];
   float sc[4];                                            // N = 16: Haar magnitudes of rows 4 g + r and the lane's column
 };
 
@@ -98,12 +107,7 @@ __device__ inline void sub_load_ops(SubOps<G>& T, const double* tabs) {
     h = (_Float16)v;
     l = (_Float16)(v - (float)h);
   };
-  if constexpr (!G::BF) {
-#pragma unroll
-    for (int f = 0; f < G::NFAM; ++f)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) T.t[f][r] = (float)tabs[f * K + m * N + 4 * g + r];
-  } else if constexpr (N == 16) {
+  if constexpr (N == 16) {
 #pragma unroll
     for (int f = 0; f < G::NFAM; ++f) {
       const bool hr = sub_haar<G>(f);
@@ -170,27 +174,7 @@ template <class G>
 __device__ inline void sub_correlate(const char* sR, const SubOps<G>& T, float (&V)[G::SN][G::VPL]) {
   const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
   const sb_f32x4 z4{0.f, 0.f, 0.f, 0.f};
-  if constexpr (!G::BF) {
-    const sb_f32x4 rv = *(const sb_f32x4*)(sR + m * G::ROWB + 16 * g);
-    sb_f32x4 D[G::NFAM];
-#pragma unroll
-    for (int f = 0; f < G::NFAM; ++f) D[f] = z4;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int f = 0; f < G::NFAM; ++f) D[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(rv[r], T.t[f][r], D[f], 0, 0, 0);
-    sb_f32x4 C[G::NFAM];
-#pragma unroll
-    for (int f = 0; f < G::NFAM; ++f) C[f] = z4;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int f = 0; f < G::NFAM; ++f) C[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(T.t[f][r], D[f][r], C[f], 0, 0, 0);
-#pragma unroll
-    for (int f = 0; f < G::NFAM; ++f)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) V[0][4 * f + r] = C[f][r];
-  } else if constexpr (G::N == 16) {
+  if constexpr (G::N == 16) {
     sb_f32x4 D[G::SN][G::NFAM];
 #pragma unroll
     for (int n = 0; n < G::SN; ++n) {
@@ -273,22 +257,35 @@ __device__ inline double sub_slot_sum(double v) {
 template <class G>
 __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelDev& lv,
                                    const int32_t* __restrict__ count_ptr, int32_t* __restrict__ queue,
-                                   const double* __restrict__ tab) {
+                                   const double* __restrict__ tab, const double* __restrict__ xg) {
   constexpr int N = G::N, K = G::K, SN = G::SN, LPS = G::LPS, PR = G::PR, PC = G::PC, VPL = G::VPL;
   constexpr bool BF = G::BF;
   constexpr int lg = N == 16 ? 4 : 3;
-  __shared__ __attribute__((aligned(16))) double sTab[G::NFAM][N][N];
+  // rows of the families' tables, then a row of ones and one of 1/N: the
+  // constant atom's factors
+  constexpr int ONES = G::NFAM * N;
+  __shared__ __attribute__((aligned(16))) double sTab[ONES + 2][N];
   __shared__ __attribute__((aligned(16))) char sRows[4][SN * G::NODEB];
+  // CARRY: FP32 <T_f[p], T_f'[p']> of the step's family f and each f'
+  __shared__ __attribute__((aligned(16))) float sX[G::CARRY ? G::NFAM : 1][G::NFAM][G::CARRY ? N : 1][G::CARRY ? N : 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   char* sR = sRows[wv];
-  for (int i = tid; i < G::NFAM * K; i += 256) (&sTab[0][0][0])[i] = tab[i];
+  for (int i = tid; i < G::NFAM * K; i += 256) (&sTab[0][0])[i] = tab[i];
+  if (tid < 2 * N) sTab[ONES + tid / N][tid % N] = tid < N ? 1.0 : 1.0 / N;
+  if constexpr (G::CARRY) {
+    for (int i = tid; i < G::NFAM * G::NFAM * K; i += 256) {
+      const int f = i / (G::NFAM * K), f2 = i / K % G::NFAM, a = i / N % N, b = i % N;
+      float v = a == b ? 1.f : 0.f;
+      if (f != f2) v = (float)(f == 0 ? xg[a * N + b] : xg[b * N + a]);
+      sX[f][f2][a][b] = v;
+    }
+  }
   for (int i = lane; i < SN * G::NODEB / 16; i += 64) ((uint4*)sR)[i] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
   SubOps<G> T;
-  sub_load_ops<G>(T, &sTab[0][0][0]);
+  sub_load_ops<G>(T, &sTab[0][0]);
   const int count = *count_ptr;
-  const double inv_n = 1.0 / N;
   const int slot = lane / LPS, li = lane % LPS;
   const int py = (li / G::XQ) * PR, px = (li % G::XQ) * PC;
   char* sRow = sR + slot * G::NODEB;
@@ -299,7 +296,16 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
   bool dry = node >= count, run = false, load = !dry;
   int t = 0, kmax = 0, rec_i = 0;
   double rec_c = 0.0, e = 0.0, eps2 = 0.0;
-  float sc = 1.f;
+  float sc = 1.f, win = 0.f;
+  // the carried correlations hold while e is in [elim, emax) and t < tlim
+  bool fresh = false;
+  double elim = 0.0, emax = 0.0;
+  int tlim = 0;
+  float V[SN][VPL];
+#pragma unroll
+  for (int n = 0; n < SN; ++n)
+#pragma unroll
+    for (int v = 0; v < VPL; ++v) V[n][v] = 0.f;
   double rd[PR][PC];
 #pragma unroll
   for (int i = 0; i < PR; ++i)
@@ -308,9 +314,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
 
   auto scale_of = [](double en) -> float {   // see k_pursuit_sep
     const int ex = (int)((unsigned long long)__double_as_longlong(en) >> 52) - 1023;
-    int sh = ex >> 1;
-    if constexpr (BF) sh -= 7;
-    else if (ex >= -40 && ex < 80) return 1.f;
+    int sh = (ex >> 1) - 7;
     sh = sh < -120 ? -120 : (sh > 120 ? 120 : sh);
     return __uint_as_float((uint32_t)(127 - sh) << 23);
   };
@@ -318,15 +322,17 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
 #pragma unroll
     for (int i = 0; i < PR; ++i) {
       char* row = sRow + (py + i) * G::ROWB;
-      if constexpr (BF) {
-        float v[PC];
+      float v[PC];
 #pragma unroll
-        for (int j = 0; j < PC; ++j) v[j] = (float)rd[i][j] * sc;
-        const uint32_t h0 = sb_split_hi(v[0], v[1]), h1 = sb_split_hi(v[2], v[3]);
+      for (int j = 0; j < PC; ++j) v[j] = (float)rd[i][j] * sc;
+      const uint32_t h0 = sb_split_hi(v[0], v[1]);
+      if constexpr (PC == 4) {
+        const uint32_t h1 = sb_split_hi(v[2], v[3]);
         *(uint2*)(row + 2 * px) = make_uint2(h0, h1);
         *(uint2*)(row + 2 * N + 2 * px) = make_uint2(sb_split_lo(v[0], v[1], h0), sb_split_lo(v[2], v[3], h1));
       } else {
-        *(float2*)(row + 4 * px) = make_float2((float)rd[i][0] * sc, (float)rd[i][1] * sc);
+        *(uint32_t*)(row + 2 * px) = h0;
+        *(uint32_t*)(row + 2 * N + 2 * px) = sb_split_lo(v[0], v[1], h0);
       }
     }
   };
@@ -382,10 +388,8 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
         else if (!(e > 0.0 && e < __builtin_inf()))   // a zero residual, or undefined pixels: nothing to select
           st = ST_ZERO;
         run = st == ST_RUN;
-        if (run) {
-          sc = scale_of(e);
-          put_rows();
-        } else if (li == 0) {
+        fresh = true;
+        if (!run && li == 0) {
           lv.e[node] = e;
           lv.t[node] = 0;
           lv.st[node] = st;
@@ -394,10 +398,20 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
     }
     const unsigned long long runs = __ballot(run);
     if (runs != 0ull) {
-      wave_sync();
-      // ---- correlations; per node the atoms within the window of its largest ----
-      float V[SN][VPL];
-      sub_correlate<G>(sR, T, V);
+      // ---- correlations, from the residual or carried ----
+      if (!G::CARRY || __ballot(run && fresh) != 0ull) {
+        if (run) {
+          sc = scale_of(e);
+          put_rows();
+          win = __builtin_amdgcn_sqrtf((float)(e * ((double)sc * (double)sc))) * (1.0001f * 0x1p-13f * G::TS * G::TS);
+          elim = fmax(eps2, 0.25 * e);
+          emax = 4.0 * e;
+          tlim = t + 64 < kmax ? t + 64 : kmax;
+        }
+        wave_sync();
+        sub_correlate<G>(sR, T, V);
+        wave_sync();   // the rows are read before any slot writes new ones
+      }
       if constexpr (G::NFAM == 2) {
         // the second family's constant atom equals the first's, which wins the tie
         const bool dc1 = lane == (N == 16 ? 0 : 40);
@@ -405,8 +419,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
 #pragma unroll
         for (int n = 0; n < SN; ++n) V[n][v1] = dc1 ? 0.f : V[n][v1];
       }
-      wave_sync();   // the rows are read before any slot writes new ones
-      const float win = __builtin_amdgcn_sqrtf((float)(e * ((double)sc * (double)sc))) * (1.0001f * 0x1p-12f * G::TS * G::TS);
+      // ---- per node the atoms within the window of its largest ----
       unsigned long long lanes[SN];
       uint32_t mask[SN], bits[SN];
       bool more = false;
@@ -442,42 +455,32 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
       double tq[PC], tp[PR];
       auto rows = [&](int a) {
         const int f = a / K, q = (a % K) / N, p = a % N;
+        const bool dc = (a % K) == 0;
+        const double* tr = &sTab[dc ? ONES : f * N + q][px];
+        const double* pr = &sTab[dc ? ONES + 1 : f * N + p][py];
 #pragma unroll
         for (int j = 0; j < PC; j += 2) {
-          const double2 v = *(const double2*)&sTab[f][q][px + j];
+          const double2 v = *(const double2*)(tr + j);
           tq[j] = v.x;
           tq[j + 1] = v.y;
         }
 #pragma unroll
-        for (int i = 0; i < PR; ++i) tp[i] = sTab[f][p][py + i];
+        for (int i = 0; i < PR; ++i) tp[i] = pr[i];
       };
       auto rescore = [&](int a) -> double {   // a >= 0
         rows(a);
-        const bool dc = (a % K) == 0;
         double part = 0.0;
-        if constexpr (BF) {
-          double dcp = 0.0;
 #pragma unroll
-          for (int i = 0; i < PR; ++i) {
-            const double sy = fma(rd[i][0], tq[0], rd[i][1] * tq[1]) + fma(rd[i][2], tq[2], rd[i][3] * tq[3]);
-            part = i == 0 ? tp[0] * sy : fma(tp[i], sy, part);
-            dcp += (rd[i][0] + rd[i][1]) + (rd[i][2] + rd[i][3]);
+        for (int i = 0; i < PR; ++i) {
+          double sy;
+          if constexpr (BF) {
+            sy = fma(rd[i][0], tq[0], rd[i][1] * tq[1]) + fma(rd[i][2], tq[2], rd[i][3] * tq[3]);
+          } else {
+            sy = 0.0;
+#pragma unroll
+            for (int j = 0; j < PC; ++j) sy = fma(rd[i][j], tq[j], sy);
           }
-          part = dc ? dcp * inv_n : part;
-        } else {
-          double dcp = 0.0;
-#pragma unroll
-          for (int i = 0; i < PR; ++i) {
-            double sr = 0.0, sd = 0.0;
-#pragma unroll
-            for (int j = 0; j < PC; ++j) {
-              sr = fma(rd[i][j], tq[j], sr);
-              sd += rd[i][j];
-            }
-            part = fma(tp[i], sr, part);
-            dcp += sd;
-          }
-          part = dc ? dcp * inv_n : part;
+          part = fma(tp[i], sy, part);   // (a product would be fused into the slot sum)
         }
         return sub_slot_sum<G>(part);
       };
@@ -513,19 +516,34 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
       // ---- rank-1 update, norm, record, stop test ----
       uint8_t st = ST_RUN;
       const bool zero = !(mag > 0.0);
-      const bool dc = (atom % K) == 0;
       double en = 0.0;
 #pragma unroll
       for (int i = 0; i < PR; ++i) {
         double ei = 0.0;
 #pragma unroll
         for (int j = 0; j < PC; ++j) {
-          const double phi = dc ? inv_n : tp[i] * tq[j];
-          const double rn = (double)(float)fma(-coef, phi, rd[i][j]);
-          rd[i][j] = zero ? rd[i][j] : rn;
+          const double rn = (double)(float)fma(-coef, tp[i] * tq[j], rd[i][j]);
+          rd[i][j] = rn;               // a slot with nothing to select ends here
           ei = fma(rn, rn, ei);
         }
         en += ei;
+      }
+      if constexpr (G::CARRY) {
+        // see k_pursuit_sep: c X[p][p'] X[q][q'] less, the own family's X the identity
+        const float cs = (float)(coef * ((double)sc * (double)(G::TS * G::TS)));
+#pragma unroll
+        for (int n = 0; n < SN; ++n) {
+          const int an = __builtin_amdgcn_readlane(atom < 0 ? 0 : atom, n * LPS);
+          const float cn = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(cs), n * LPS));
+          const int f = an / K, q = (an % K) / N, p = an % N;
+#pragma unroll
+          for (int f2 = 0; f2 < G::NFAM; ++f2) {
+            const float gq = -(cn * sX[f][f2][q][lane & 15]);
+            const sb_f32x4 gp = *(const sb_f32x4*)&sX[f][f2][p][4 * (lane >> 4)];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) V[n][4 * f2 + r] = fmaf(gq, gp[r], V[n][4 * f2 + r]);
+          }
+        }
       }
       en = sub_slot_sum<G>(en);
       if (run) {
@@ -544,8 +562,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
             st = ST_SPARSE;
           else if (!(e > 0.0))
             st = ST_ZERO;
-          if (BF || st == ST_RUN) sc = scale_of(e);
-          if (st == ST_RUN) put_rows();
+          fresh = !(e >= elim && e < emax && t < tlim);
           const int base = (t - 1) & ~(LPS - 1);   // first step held in the registers
           if (st != ST_RUN || t - base == LPS) {
             if (li < t - base) {
@@ -585,24 +602,27 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
   }
 }
 
+// (Four waves per SIMD: the matrix cores then write ordinary registers.)
 template <int N, int FAMS>
-__global__ __launch_bounds__(256) void k_pursuit_bf16(const JobDev* __restrict__ jobs, LevelDev lv,
+__global__ __launch_bounds__(256, 4) void k_pursuit_bf16(const JobDev* __restrict__ jobs, LevelDev lv,
                                                       const int32_t* __restrict__ count_ptr,
-                                                      int32_t* __restrict__ queue, const double* __restrict__ tab) {
-  pursuit_sub<SubGeo<N, FAMS, true>>(jobs, lv, count_ptr, queue, tab);
+                                                      int32_t* __restrict__ queue, const double* __restrict__ tab,
+                                                      const double* __restrict__ xg) {
+  pursuit_sub<SubGeo<N, FAMS, true>>(jobs, lv, count_ptr, queue, tab, xg);
 }
 
 template <int FAMS>
-__global__ __launch_bounds__(256) void k_pursuit16_f32(const JobDev* __restrict__ jobs, LevelDev lv,
+__global__ __launch_bounds__(256, 4) void k_pursuit16_f32(const JobDev* __restrict__ jobs, LevelDev lv,
                                                        const int32_t* __restrict__ count_ptr,
-                                                       int32_t* __restrict__ queue, const double* __restrict__ tab) {
-  pursuit_sub<SubGeo<16, FAMS, false>>(jobs, lv, count_ptr, queue, tab);
+                                                       int32_t* __restrict__ queue, const double* __restrict__ tab,
+                                                       const double* __restrict__ xg) {
+  pursuit_sub<SubGeo<16, FAMS, false>>(jobs, lv, count_ptr, queue, tab, xg);
 }
 
 // As many workgroups as are resident at once, at most one per 4 SN nodes.
 template <class Kern>
 hipError_t launch_sub(Kern kern, int nodes_per_wg, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* queue,
-                      int64_t cap, const double* tab, hipStream_t s) {
+                      int64_t cap, const double* tab, const double* xg, hipStream_t s) {
   int dev = 0, n_cus = 0, per_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -611,18 +631,18 @@ hipError_t launch_sub(Kern kern, int nodes_per_wg, const JobDev* jobs, LevelDev 
   int64_t wgs = (cap + nodes_per_wg - 1) / nodes_per_wg;
   if (wgs > (int64_t)n_cus * per_cu) wgs = (int64_t)n_cus * per_cu;
   if (wgs < 1) wgs = 1;
-  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(256), 0, s, jobs, lv, count, queue, tab);
+  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(256), 0, s, jobs, lv, count, queue, tab, xg);
   return hipGetLastError();
 }
 
 template <int FAMS>
 hipError_t launch_sub_f(int n, int precision, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* queue,
-                        int64_t cap, const double* tab, hipStream_t s) {
+                        int64_t cap, const double* tab, const double* xg, hipStream_t s) {
   if (precision == AQMP_PREC_BF16) {
-    if (n == 8) return launch_sub(k_pursuit_bf16<8, FAMS>, 4 * SubGeo<8, FAMS, true>::SN, jobs, lv, count, queue, cap, tab, s);
-    if (n == 16) return launch_sub(k_pursuit_bf16<16, FAMS>, 4 * SubGeo<16, FAMS, true>::SN, jobs, lv, count, queue, cap, tab, s);
+    if (n == 8) return launch_sub(k_pursuit_bf16<8, FAMS>, 4 * SubGeo<8, FAMS, true>::SN, jobs, lv, count, queue, cap, tab, xg, s);
+    if (n == 16) return launch_sub(k_pursuit_bf16<16, FAMS>, 4 * SubGeo<16, FAMS, true>::SN, jobs, lv, count, queue, cap, tab, xg, s);
   } else if (n == 16) {
-    return launch_sub(k_pursuit16_f32<FAMS>, 4, jobs, lv, count, queue, cap, tab, s);
+    return launch_sub(k_pursuit16_f32<FAMS>, 4, jobs, lv, count, queue, cap, tab, xg, s);
   }
   return hipErrorInvalidValue;
 }
@@ -630,11 +650,11 @@ hipError_t launch_sub_f(int n, int precision, const JobDev* jobs, LevelDev lv, c
 }  // namespace
 
 hipError_t launch_pursuit_sub(int n, int precision, uint32_t families, const JobDev* jobs, LevelDev lv,
-                              const int32_t* count, int32_t* queue, int64_t cap, const double* tab, hipStream_t s) {
+                              const int32_t* count, int32_t* queue, int64_t cap, const double* tab, const double* xg, hipStream_t s) {
   switch (families) {
-    case AQMP_DCT: return launch_sub_f<AQMP_DCT>(n, precision, jobs, lv, count, queue, cap, tab, s);
-    case AQMP_HAAR: return launch_sub_f<AQMP_HAAR>(n, precision, jobs, lv, count, queue, cap, tab, s);
-    case AQMP_DCT | AQMP_HAAR: return launch_sub_f<AQMP_DCT | AQMP_HAAR>(n, precision, jobs, lv, count, queue, cap, tab, s);
+    case AQMP_DCT: return launch_sub_f<AQMP_DCT>(n, precision, jobs, lv, count, queue, cap, tab, xg, s);
+    case AQMP_HAAR: return launch_sub_f<AQMP_HAAR>(n, precision, jobs, lv, count, queue, cap, tab, xg, s);
+    case AQMP_DCT | AQMP_HAAR: return launch_sub_f<AQMP_DCT | AQMP_HAAR>(n, precision, jobs, lv, count, queue, cap, tab, xg, s);
     default: return hipErrorInvalidValue;
   }
 }

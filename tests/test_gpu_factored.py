@@ -138,6 +138,44 @@ def test_carried_correlations(A, dics, n, fam, prec):
 
 
 @pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("fam", [1, 2, 3])
+def test_carried_correlations_16(A, dics, fam, prec):
+    """The same at N = 16, where a wave of the BF16 form carries two nodes that
+    want a product at different steps (a noise block beside smooth ones).  The
+    reference takes the FP64 arg-max over all atoms at every step and stores
+    the FP32 residual (the step-by-step form's eight FP32 keys miss it by
+    2.5e-8 ||r|| at one step of one block).  Coefficients: sums of 256 products
+    of pixels below 1 with atoms of unit norm, within 256 2^-53 16."""
+    rng = np.random.default_rng(32)
+    y, x = np.mgrid[0:64, 0:64] / 64
+    img = 0.9 + 0.05 * np.sin(5 * x + 2 * y) + 0.01 * y ** 3
+    img[::, 16:32] += 0.02 * rng.standard_normal((64, 16))
+    p = dict(tol=1e-4, tol_mode="abs", max_atoms=90, n_min=16, n_max=16)
+    got = _nodes(A, dics(fam), [_dev(img)], [p], [(0, 0)], prec)
+    tabs = [t for t, f in ((O.dct_matrix(16), 1), (O.haar_matrix(16), 2)) if fam & f]
+    ends = np.cumsum(got.leaves["n_atoms"])
+    _say("atoms", ends[-1], got.leaves["n_atoms"].max())
+    assert got.leaves["n_atoms"].max() > 64
+    for leaf, end in zip(got.leaves, ends):
+        na = int(leaf["n_atoms"])
+        r = img[leaf["y0"]:leaf["y0"] + 16, leaf["x0"]:leaf["x0"] + 16].astype(np.float32).astype(np.float64)
+        for t in range(na):
+            c = np.stack([t_ @ r @ t_.T for t_ in tabs])          # [f][p][q]
+            flat = np.abs(c.transpose(0, 2, 1)).ravel()            # f K + q N + p
+            if fam == 3:
+                flat[256] = 0.0                                    # the second constant atom
+            a = int(flat.argmax())
+            f, q, pp = a // 256, a % 256 // 16, a % 16
+            assert got.atom_idx[end - na + t] == a, (leaf["x0"], leaf["y0"], t)
+            coef = got.coef[end - na + t]
+            assert abs(coef - c[f, pp, q]) <= 256 * 2.0 ** -53 * 16
+            # the stored residual, of the encoder's own coefficient and as one
+            # rounding: Haar products fall on FP32's midpoints
+            phi = np.outer(tabs[f][pp], tabs[f][q]) if a else np.full((16, 16), 1 / 16)
+            r = (r - np.longdouble(coef) * phi).astype(np.float64).astype(np.float32).astype(np.float64)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("fam", [1, 3])
 def test_undefined_pixels(A, dics, prec, fam):
     """A plane with an infinite and one with an undefined pixel: their blocks
