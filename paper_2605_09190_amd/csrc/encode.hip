@@ -326,10 +326,10 @@ bool sep_level(const aqmp_code* c, int n) {
 }
 
 // Dense levels whose wave-sized pursuit runs on the matrix cores: N = 16,
-// unless step by step, and N = 8 of the BF16 form.
+// unless step by step, and N = 8.
 bool sub_level(const aqmp_code* c, int n) {
   if (c->opt.solver != AQMP_SOLVER_DENSE) return false;
-  return n == 16 ? !(c->opt.flags & AQMP_OPT_STEPWISE) : (n == 8 && c->opt.precision == AQMP_PREC_BF16);
+  return n == 16 ? !(c->opt.flags & AQMP_OPT_STEPWISE) : n == 8;
 }
 
 // Levels that run without per-step launches: every level of the dense solver
@@ -556,7 +556,7 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
         AQMP_LAUNCH(launch_pursuit_sub(n, c->opt.precision, d->families, c->djobs, a.lv, count, c->dqueue[pi].at[l],
                                        pp.cap[l], D.d_tab, D.d_xg, s));
       else
-        AQMP_LAUNCH(launch_mp_fused(n, c->djobs, a.lv, count, l, D.m, D.d_tab, s));
+        AQMP_LAUNCH(launch_mp_fused4(c->djobs, a.lv, count, l, D.m, D.d_tab, s));
       if (l > pp.lg_lo && pp.cap[l - 1] > 0)
         AQMP_LAUNCH(launch_split_emit(c->djobs, (int32_t)c->jobs.size(), a.lv, count, level_at(c, l - 1, pp.base[l - 1]), pp.ntop[l - 1],
                                       &cnt->count[l - 1], c->dranges + (size_t)(l - 1) * c->jobs.size(), l, pp.cap[l], wk.ss, &cnt->scan_error, s));

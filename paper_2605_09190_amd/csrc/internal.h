@@ -198,9 +198,9 @@ size_t sep_ops_bytes(int n, uint32_t families);
 hipError_t launch_sep_ops(int n, uint32_t families, const double* tab, const double* xg, void* out, hipStream_t s);
 hipError_t launch_pursuit_sep(int n, uint32_t families, const JobDev* jobs, LevelDev lv, const int32_t* count,
                               int32_t* queue, int64_t cap, const double* tab, const void* ops, hipStream_t s);
-hipError_t launch_mp_fused(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t lg, int32_t n_atoms,
-                           const double* tab, hipStream_t s);
-// Whole-level pursuit of the dense solver at N = 8 (BF16 form) and 16
+hipError_t launch_mp_fused4(const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t lg, int32_t n_atoms,
+                            const double* tab, hipStream_t s);
+// Whole-level pursuit of the dense solver at N = 8 and 16
 // (queue: the level's node counters, zero on entry; cap: its node capacity).
 hipError_t launch_pursuit_sub(int n, int precision, uint32_t families, const JobDev* jobs, LevelDev lv,
                               const int32_t* count, int32_t* queue, int64_t cap, const double* tab, const double* xg,

@@ -1,14 +1,13 @@
 // kernels_fused.hip - whole-level Matching Pursuit for the smallest blocks: the
-// dense FP64 pursuit (N <= 8 of the FP32 form, N = 4 of both).
+// dense FP64 pursuit of N = 4, both forms.
 //
-// For N <= 8 the dictionary (M <= 128 atoms of K <= 64 pixels) fits in LDS
-// even in FP64 (64 KB), while one MP step of one node is only K*M = 8192
-// multiply-adds: a batched correlation launch per step would be all launch
-// and latency.  Here one group of TPN = min(K, 64) lanes runs a node's whole
+// The dictionary (32 atoms of 16 pixels) fits in LDS in FP64, while one MP
+// step of one node is 512 multiply-adds: a batched correlation launch per
+// step would be all launch and latency.  Here 16 lanes run a node's whole
 // pursuit (Section 2.2 steps (a)-(d), eq. (2)) without leaving the kernel:
 //   r = unravel(block) (FP64, lane = pixel), stop test before every step;
 //   c_a = <r, phi_a> for every atom in FP64 (the plain definition, dense);
-//   i = argmax |c| (lowest index on ties), stop if max |c| = 0;
+//   i = argmax |c| (lowest index on ties), stop unless max |c| > 0;
 //   r <- r - c_i phi_i, ||r||^2, record (i, c_i).
 // The residual stays in registers; atoms are formed in LDS once per
 // workgroup from the FP64 1D tables (constant atom exactly 1/N).
@@ -108,7 +107,7 @@ __global__ __launch_bounds__(256) void k_mp_fused(const JobDev* __restrict__ job
         const double oc = __shfl_xor(bc, off, 64);
         if (om > bm || (om == bm && oi < bi)) { bm = om; bi = oi; bc = oc; }
       }
-      if (bm == 0.0) { st = ST_ZERO; break; }
+      if (!(bm > 0.0)) { st = ST_ZERO; break; }   // all zero, or undefined pixels
       r = fma(-bc, sD[lt * G::MMAX + bi], r);
       e = grp_sum<TPN>(r * r);
       if (valid && lt == 0) {
@@ -128,18 +127,9 @@ __global__ __launch_bounds__(256) void k_mp_fused(const JobDev* __restrict__ job
 
 }  // namespace
 
-hipError_t launch_mp_fused(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t lg, int32_t n_atoms,
-                           const double* tab, hipStream_t s) {
-  switch (n) {
-    case 4:
-      hipLaunchKernelGGL(k_mp_fused<4>, dim3(256 * 4), dim3(256), 0, s, jobs, lv, count, lg, n_atoms, tab);
-      break;
-    case 8:
-      hipLaunchKernelGGL(k_mp_fused<8>, dim3(256 * 2), dim3(256), 0, s, jobs, lv, count, lg, n_atoms, tab);
-      break;
-    default:
-      return hipErrorInvalidValue;
-  }
+hipError_t launch_mp_fused4(const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t lg, int32_t n_atoms,
+                            const double* tab, hipStream_t s) {
+  hipLaunchKernelGGL(k_mp_fused<4>, dim3(256 * 4), dim3(256), 0, s, jobs, lv, count, lg, n_atoms, tab);
   return hipGetLastError();
 }
 

@@ -1,6 +1,5 @@
 // kernels_sub.hip - whole-level Matching Pursuit of the dense solver for small
-// blocks on the matrix cores: N = 8 and 16 of the BF16 form, N = 16 of the
-// FP32 form.  A wave runs several nodes side by side (slots of LPS lanes),
+// blocks on the matrix cores: N = 8 and 16.  A wave runs several nodes side by side (slots of LPS lanes),
 // with no workgroup barrier; the residual stays in registers from the gather
 // to the last step.
 //
@@ -32,10 +31,22 @@
 // FP32 form, 1536 x 1024 x 3: N = 16 67 us (FP32 products at every step 97 us,
 // step by step 1 870 us).
 //
+// N = 8 of the FP32 form (k_mp_fused) keeps the residual and its coefficients
+// in FP64: the FP16 split only proposes the atoms, and a candidate's
+// coefficient is the plain sum over the 64 pixels, one after the other, as if
+// every atom had its own (c_a = <r, phi_a>, dense).  That chain of 64 FP64
+// fused multiply-adds is a third of the step; its operands want registers, so
+// two waves per SIMD measured best (70 us for the 476 nodes of a 512 x 512
+// plane, 83 us for 4 544; four per SIMD 89 and 92 us).  The dense FP64 product
+// with all atoms from LDS, a node per wave, took 78 and 215 us.
+//
 // The order of operations of the FP64 re-score, update and norms is fixed by
 // the patches (SubGeo): BF16 form a slot of 32 (N = 16) or 16 lanes with rows
 // of four pixels per lane; FP32 form k_select's and k_gather's, so that it
-// equals the step-by-step form bit for bit.
+// equals the step-by-step form bit for bit; its N = 8 the sums over lane =
+// pixel of the dense form.
+#include <type_traits>
+
 #include "internal.h"
 #include "dev_common.h"
 
@@ -46,10 +57,15 @@ namespace {
 typedef _Float16 sb_h8 __attribute__((ext_vector_type(8)));
 typedef float sb_f32x4 __attribute__((ext_vector_type(4)));
 
-template <int N_, int FAMS_, bool BF_>
+// The three forms: FP32 (N = 16), BF16 (N = 8 and 16), and the FP32 form's
+// exact one (N = 8), whose residual stays FP64.
+enum { SUB_F32, SUB_BF16, SUB_F64 };
+
+template <int N_, int FAMS_, int FORM_>
 struct SubGeo {
   static constexpr int N = N_, K = N * N, FAMS = FAMS_;
-  static constexpr bool BF = BF_;
+  static constexpr bool EXACT = FORM_ == SUB_F64;
+  static constexpr bool BF = FORM_ != SUB_F32;            // the BF16 form's patches
   static constexpr int NFAM = FAMS == 3 ? 2 : 1;
   static constexpr int SN = BF ? (N == 16 ? 2 : 4) : 1;   // nodes per wave
   static constexpr int LPS = 64 / SN;                     // lanes per slot
@@ -67,7 +83,7 @@ struct SubGeo {
   static constexpr int ROWB = N == 16 ? 80 : 48;
   static constexpr int NODEB = N * ROWB;
   static constexpr float TS = 128.f;                      // see SepGeo::TS
-  static_assert(N == 16 || (N == 8 && BF), "block sizes");
+  static_assert((N == 16 && !EXACT) || (N == 8 && BF), "block sizes");
   static_assert(PR * PC * LPS == K && PR >= 1 && VPL <= 8, "patches");
 };
 
@@ -245,6 +261,13 @@ __device__ inline double sub_slot_sum(double v) {
   if constexpr (G::LPS == 64) {
     return wave_sum_f64(v);
   } else {
+    if constexpr (G::EXACT) {            // pixels in the order of their bits
+      v += row_perm_f64<0xB1>(v);
+      v += row_perm_f64<0x4E>(v);
+      v += row_perm_f64<0x141>(v);
+      v += row_perm_f64<0x128>(v);
+      return v;
+    }
     if constexpr (G::LPS == 32) v = lane_pair_sum_f64<16>(v);
     v += row_perm_f64<0x128>(v);   // row_ror:8
     v += row_perm_f64<0x141>(v);   // row_half_mirror
@@ -259,7 +282,8 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
                                    const int32_t* __restrict__ count_ptr, int32_t* __restrict__ queue,
                                    const double* __restrict__ tab, const double* __restrict__ xg) {
   constexpr int N = G::N, K = G::K, SN = G::SN, LPS = G::LPS, PR = G::PR, PC = G::PC, VPL = G::VPL;
-  constexpr bool BF = G::BF;
+  constexpr bool BF = G::BF, EXACT = G::EXACT;
+  using Scale = std::conditional_t<EXACT, double, float>;
   constexpr int lg = N == 16 ? 4 : 3;
   // rows of the families' tables, then a row of ones and one of 1/N: the
   // constant atom's factors
@@ -268,6 +292,9 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
   __shared__ __attribute__((aligned(16))) char sRows[4][SN * G::NODEB];
   // CARRY: FP32 <T_f[p], T_f'[p']> of the step's family f and each f'
   __shared__ __attribute__((aligned(16))) float sX[G::CARRY ? G::NFAM : 1][G::NFAM][G::CARRY ? N : 1][G::CARRY ? N : 1];
+  // EXACT: the FP64 residuals, every slot's on banks of its own
+  constexpr int RP = K + 2;
+  __shared__ __attribute__((aligned(16))) double sPix[EXACT ? 4 : 1][EXACT ? SN * RP : 2];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   char* sR = sRows[wv];
@@ -296,7 +323,8 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
   bool dry = node >= count, run = false, load = !dry;
   int t = 0, kmax = 0, rec_i = 0;
   double rec_c = 0.0, e = 0.0, eps2 = 0.0;
-  float sc = 1.f, win = 0.f;
+  Scale sc = 1;
+  float win = 0.f;
   // the carried correlations hold while e is in [elim, emax) and t < tlim
   bool fresh = false;
   double elim = 0.0, emax = 0.0;
@@ -312,11 +340,25 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
 #pragma unroll
     for (int j = 0; j < PC; ++j) rd[i][j] = 0.0;
 
-  auto scale_of = [](double en) -> float {   // see k_pursuit_sep
+  auto scale_of = [](double en) -> Scale {   // see k_pursuit_sep
     const int ex = (int)((unsigned long long)__double_as_longlong(en) >> 52) - 1023;
     int sh = (ex >> 1) - 7;
+    if constexpr (EXACT) return __longlong_as_double((long long)(1023 - sh) << 52);
     sh = sh < -120 ? -120 : (sh > 120 ? 120 : sh);
     return __uint_as_float((uint32_t)(127 - sh) << 23);
+  };
+  // EXACT: ||r||^2 beyond what the ranking's scale can take (an FP64 plane's
+  // extremes): every atom is a candidate
+  auto beyond = [](double en) { return EXACT && !(en >= 0x1p-900 && en < 0x1p900); };
+  auto still = [&](double en) {              // nothing to select: a zero residual, or undefined pixels
+    if constexpr (!EXACT) return !(en > 0.0 && en < __builtin_inf());
+    bool any = false;
+#pragma unroll
+    for (int i = 0; i < PR; ++i)
+#pragma unroll
+      for (int j = 0; j < PC; ++j) any = any || rd[i][j] != 0.0;
+    const unsigned long long lanes = __ballot(any) >> (lane & ~(LPS - 1));
+    return !(en < __builtin_inf()) || (lanes & ((1ull << (LPS % 64)) - 1ull)) == 0ull;
   };
   auto put_rows = [&]() {
 #pragma unroll
@@ -324,7 +366,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
       char* row = sRow + (py + i) * G::ROWB;
       float v[PC];
 #pragma unroll
-      for (int j = 0; j < PC; ++j) v[j] = (float)rd[i][j] * sc;
+      for (int j = 0; j < PC; ++j) v[j] = EXACT ? (float)(rd[i][j] * (double)sc) : (float)rd[i][j] * (float)sc;
       const uint32_t h0 = sb_split_hi(v[0], v[1]);
       if constexpr (PC == 4) {
         const uint32_t h1 = sb_split_hi(v[2], v[3]);
@@ -335,6 +377,11 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
         *(uint32_t*)(row + 2 * N + 2 * px) = sb_split_lo(v[0], v[1], h0);
       }
     }
+  };
+
+  // EXACT: the first two levels of the norm's butterfly over the pixels
+  auto quad = [](const double (&v)[PC]) -> double {
+    return fma(v[0], v[0], v[1] * v[1]) + fma(v[PC - 2], v[PC - 2], v[PC - 1] * v[PC - 1]);
   };
 
   for (;;) {
@@ -357,10 +404,10 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
             double ei = 0.0;
 #pragma unroll
             for (int j = 0; j < PC; ++j) {
-              rd[i][j] = (double)(float)pv[i][j];
+              rd[i][j] = EXACT ? pv[i][j] : (double)(float)pv[i][j];
               ei = fma(pv[i][j], pv[i][j], ei);
             }
-            ep += ei;
+            ep += EXACT ? quad(pv[i]) : ei;
           }
           e = sub_slot_sum<G>(ep);
         } else {
@@ -385,7 +432,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
           st = ST_ACC;
         else if (kmax <= 0)
           st = ST_SPARSE;
-        else if (!(e > 0.0 && e < __builtin_inf()))   // a zero residual, or undefined pixels: nothing to select
+        else if (still(e))
           st = ST_ZERO;
         run = st == ST_RUN;
         fresh = true;
@@ -401,8 +448,13 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
       // ---- correlations, from the residual or carried ----
       if (!G::CARRY || __ballot(run && fresh) != 0ull) {
         if (run) {
-          sc = scale_of(e);
+          sc = beyond(e) ? 0 : scale_of(e);
           put_rows();
+          if constexpr (EXACT) {
+#pragma unroll
+            for (int j = 0; j < PC; j += 2)
+              *(double2*)&sPix[wv][slot * RP + N * py + px + j] = make_double2(rd[0][j], rd[0][j + 1]);
+          }
           win = __builtin_amdgcn_sqrtf((float)(e * ((double)sc * (double)sc))) * (1.0001f * 0x1p-13f * G::TS * G::TS);
           elim = fmax(eps2, 0.25 * e);
           emax = 4.0 * e;
@@ -420,6 +472,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
         for (int n = 0; n < SN; ++n) V[n][v1] = dc1 ? 0.f : V[n][v1];
       }
       // ---- per node the atoms within the window of its largest ----
+      const unsigned long long far = EXACT ? __ballot(run && beyond(e)) : 0ull;
       unsigned long long lanes[SN];
       uint32_t mask[SN], bits[SN];
       bool more = false;
@@ -436,8 +489,13 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
 #pragma unroll
         for (int v = 0; v < VPL; ++v) mk = __builtin_amdgcn_alignbit(mk, __float_as_uint(thr - fabsf(V[n][v])), 31);
         // a slot at rest, or infinite or undefined sums: nothing to compare
-        const bool alive = ((runs >> (n * LPS)) & 1ull) != 0ull && mx > 0.f && mx < __builtin_inff();
+        const bool on = ((runs >> (n * LPS)) & 1ull) != 0ull;
+        const bool alive = on && mx > 0.f && mx < __builtin_inff();
         mask[n] = alive ? mk : 0u;
+        if constexpr (EXACT) {
+          const int fm = (lane & 15) >> 3;
+          if ((far >> (n * LPS)) & 1ull) mask[n] = on && (lane >> 5) == fm && fm < G::NFAM ? (1u << VPL) - 1u : 0u;
+        }
         lanes[n] = __ballot(mask[n] != 0u);
         // the first candidate; whether there are others
         const int l = lanes[n] ? __builtin_ctzll(lanes[n]) : 0;
@@ -469,6 +527,31 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
       };
       auto rescore = [&](int a) -> double {   // a >= 0
         rows(a);
+        if constexpr (EXACT) {
+          // the plain sum over the pixels, one after the other
+          const int f = a / K, q = (a % K) / N, p = a % N;
+          const bool dc = (a % K) == 0;
+          const double* tr = sTab[dc ? ONES : f * N + q];
+          const double* pr = sTab[dc ? ONES + 1 : f * N + p];
+          double tx[N], c = 0.0;
+#pragma unroll
+          for (int x = 0; x < N; x += 2) {
+            const double2 v = *(const double2*)(tr + x);
+            tx[x] = v.x;
+            tx[x + 1] = v.y;
+          }
+#pragma unroll
+          for (int y = 0; y < N; ++y) {
+            const double ty = pr[y];
+#pragma unroll
+            for (int x = 0; x < N; x += 2) {
+              const double2 v = *(const double2*)&sPix[wv][slot * RP + N * y + x];
+              c = fma(v.x, ty * tx[x], c);
+              c = fma(v.y, ty * tx[x + 1], c);
+            }
+          }
+          return c;
+        }
         double part = 0.0;
 #pragma unroll
         for (int i = 0; i < PR; ++i) {
@@ -522,11 +605,12 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
         double ei = 0.0;
 #pragma unroll
         for (int j = 0; j < PC; ++j) {
-          const double rn = (double)(float)fma(-coef, tp[i] * tq[j], rd[i][j]);
+          const double rx = fma(-coef, tp[i] * tq[j], rd[i][j]);
+          const double rn = EXACT ? rx : (double)(float)rx;
           rd[i][j] = rn;               // a slot with nothing to select ends here
           ei = fma(rn, rn, ei);
         }
-        en += ei;
+        en += EXACT ? quad(rd[i]) : ei;
       }
       if constexpr (G::CARRY) {
         // see k_pursuit_sep: c X[p][p'] X[q][q'] less, the own family's X the identity
@@ -546,6 +630,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
         }
       }
       en = sub_slot_sum<G>(en);
+      const bool none = still(en);
       if (run) {
         if (zero) {
           st = ST_ZERO;
@@ -560,7 +645,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
             st = ST_ACC;
           else if (t >= kmax)
             st = ST_SPARSE;
-          else if (!(e > 0.0))
+          else if (EXACT ? none : !(e > 0.0))
             st = ST_ZERO;
           fresh = !(e >= elim && e < emax && t < tlim);
           const int base = (t - 1) & ~(LPS - 1);   // first step held in the registers
@@ -602,13 +687,13 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
   }
 }
 
-// (Four waves per SIMD: the matrix cores then write ordinary registers.)
+// (Four waves per SIMD, not any number: the matrix cores then write ordinary registers.)
 template <int N, int FAMS>
 __global__ __launch_bounds__(256, 4) void k_pursuit_bf16(const JobDev* __restrict__ jobs, LevelDev lv,
                                                       const int32_t* __restrict__ count_ptr,
                                                       int32_t* __restrict__ queue, const double* __restrict__ tab,
                                                       const double* __restrict__ xg) {
-  pursuit_sub<SubGeo<N, FAMS, true>>(jobs, lv, count_ptr, queue, tab, xg);
+  pursuit_sub<SubGeo<N, FAMS, SUB_BF16>>(jobs, lv, count_ptr, queue, tab, xg);
 }
 
 template <int FAMS>
@@ -616,7 +701,15 @@ __global__ __launch_bounds__(256, 4) void k_pursuit16_f32(const JobDev* __restri
                                                        const int32_t* __restrict__ count_ptr,
                                                        int32_t* __restrict__ queue, const double* __restrict__ tab,
                                                        const double* __restrict__ xg) {
-  pursuit_sub<SubGeo<16, FAMS, false>>(jobs, lv, count_ptr, queue, tab, xg);
+  pursuit_sub<SubGeo<16, FAMS, SUB_F32>>(jobs, lv, count_ptr, queue, tab, xg);
+}
+
+// (Two waves per SIMD: see the head.)
+template <int N, int FAMS>
+__global__ __launch_bounds__(256, 2) void k_mp_fused(const JobDev* __restrict__ jobs, LevelDev lv,
+                                                  const int32_t* __restrict__ count_ptr, int32_t* __restrict__ queue,
+                                                  const double* __restrict__ tab, const double* __restrict__ xg) {
+  pursuit_sub<SubGeo<N, FAMS, SUB_F64>>(jobs, lv, count_ptr, queue, tab, xg);
 }
 
 // As many workgroups as are resident at once, at most one per 4 SN nodes.
@@ -639,8 +732,10 @@ template <int FAMS>
 hipError_t launch_sub_f(int n, int precision, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* queue,
                         int64_t cap, const double* tab, const double* xg, hipStream_t s) {
   if (precision == AQMP_PREC_BF16) {
-    if (n == 8) return launch_sub(k_pursuit_bf16<8, FAMS>, 4 * SubGeo<8, FAMS, true>::SN, jobs, lv, count, queue, cap, tab, xg, s);
-    if (n == 16) return launch_sub(k_pursuit_bf16<16, FAMS>, 4 * SubGeo<16, FAMS, true>::SN, jobs, lv, count, queue, cap, tab, xg, s);
+    if (n == 8) return launch_sub(k_pursuit_bf16<8, FAMS>, 4 * SubGeo<8, FAMS, SUB_BF16>::SN, jobs, lv, count, queue, cap, tab, xg, s);
+    if (n == 16) return launch_sub(k_pursuit_bf16<16, FAMS>, 4 * SubGeo<16, FAMS, SUB_BF16>::SN, jobs, lv, count, queue, cap, tab, xg, s);
+  } else if (n == 8) {
+    return launch_sub(k_mp_fused<8, FAMS>, 4 * SubGeo<8, FAMS, SUB_F64>::SN, jobs, lv, count, queue, cap, tab, xg, s);
   } else if (n == 16) {
     return launch_sub(k_pursuit16_f32<FAMS>, 4, jobs, lv, count, queue, cap, tab, xg, s);
   }

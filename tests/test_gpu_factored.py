@@ -175,6 +175,36 @@ def test_carried_correlations_16(A, dics, fam, prec):
             r = (r - np.longdouble(coef) * phi).astype(np.float64).astype(np.float32).astype(np.float64)
 
 
+@pytest.mark.parametrize("fam", [1, 2, 3])
+@pytest.mark.parametrize("exp", [-560, -440, 0, 440, 500])
+def test_exact_form_8(A, dics, fam, exp):
+    """N = 8 of the FP32 form (FP64 residual, ranked by the FP16 split): the
+    atoms are arg-maxima of the oracle's dictionary at every scale of an FP64
+    plane, also where the norm underflows to zero or passes the ranking's
+    range; coefficients scale exactly with a power of two."""
+    img = piecewise_image(40, 64, seed=23)
+    dots = (np.random.default_rng(24).random((16, 64)) < 0.1).astype(np.float64)
+    img = np.concatenate([img, dots])
+    p = dict(tol=0.0, max_atoms=12, n_min=8, n_max=8)
+    s = 2.0 ** exp
+    got = _nodes(A, dics(fam), [_dev(img * s, True)], [p], [(0, 0)], 0)
+    _say("fam", fam, "2^", exp, "atoms", len(got.atom_idx))
+    dic = O.get_dict(8, fam)
+    at = 0
+    for leaf in got.leaves:
+        blk = img[leaf["y0"]:leaf["y0"] + 8, leaf["x0"]:leaf["x0"] + 8]
+        r, na = O.unravel(blk), int(leaf["n_atoms"])
+        tol = 64 * 2.0 ** -52 * np.linalg.norm(blk)   # 64 products, and the roundings of the residual
+        for t in range(na):
+            c = dic.D.T @ r
+            a = int(got.atom_idx[at + t])
+            assert abs(c[a]) >= np.abs(c).max() - tol, (leaf["x0"], leaf["y0"], t)
+            assert abs(got.coef[at + t] / s - c[a]) <= tol
+            r = r - got.coef[at + t] / s * dic.D[:, a]
+        assert na == 12 or np.linalg.norm(r) <= tol
+        at += na
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("fam", [1, 3])
 def test_undefined_pixels(A, dics, prec, fam):
