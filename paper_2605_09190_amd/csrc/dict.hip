@@ -57,6 +57,7 @@ static void free_level(aqmp_dict::Level& L, uint32_t families) {
 void dictionary_free(aqmp_dict* d) {
   if (!d) return;
   for (auto& L : d->lv) free_level(L, d->families);
+  for (auto& st : d->capture.idle) (void)hipStreamDestroy(st.second);
   delete d;
 }
 

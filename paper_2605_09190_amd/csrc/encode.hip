@@ -36,13 +36,6 @@ struct PassPlan {
   int lg_hi = 0, lg_lo = 0;
 };
 
-// A node copied back to the host, with its place in the canonical order.
-struct HostNode {
-  aqmp_leaf leaf;
-  const int32_t* idx;
-  const double* coef;
-};
-
 // Grow-only device (or pinned host) buffer of a code's result gather.
 struct DevBuf {
   void* p = nullptr;
@@ -106,22 +99,27 @@ struct aqmp_code {
   std::vector<LevelEv> lev;
   std::vector<StepEv> sev;
   size_t lev_pos = 0, sev_pos = 0;
-  // Every visited node of the last encode in canonical order, gathered on
-  // the device and copied back on the first read (stats, export, pack), kept
-  // until the next encode.
-  bool nodes_ok = false;
-  std::vector<aqmp::HostNode> nodes;   // records and atoms point into `pinned`
-  aqmp::DevBuf pinned;                 // page-locked host copy of ex_out
-  // Device side of the gather: segment and job tables (built once), keys,
-  // flat ids, scan and output buffers (grown as needed).
+  // What the last encode holds, counted on the device at the first read
+  // (stats, sizes, export, pack), and its nodes or leaves in canonical order,
+  // gathered there and copied back when first asked for; kept until the next
+  // encode.
+  bool totals_ok = false;
+  aqmp::ExportTotals totals{};
+  enum View { VIEW_NONE, VIEW_LEAVES, VIEW_NODES } view = VIEW_NONE;
+  int64_t view_n = 0, view_atoms = 0;
+  aqmp::DevBuf pinned;                 // page-locked host copy: node records, atom indices, coefficients
+  aqmp::DevBuf pinned_tot;             // and of the counters and totals
+  std::vector<hipEvent_t> ex_ev;       // ends of the copy's pieces
+  // Device side of the gather: segment and job tables (built once), and one
+  // buffer for keys, flat ids, scan and output (grown as needed).
   bool ex_ready = false;
   int ex_nseg = 0;
   int ex_end_bit = 0;
   int64_t ex_max_cap = 0;
   aqmp::ExportSeg* d_ex_segs = nullptr;
   aqmp::ExportJob* d_ex_jobs = nullptr;
-  // ex_out: node records, then atom indices, then coefficients (8-byte aligned)
-  aqmp::DevBuf ex_keys, ex_keys2, ex_vals, ex_vals2, ex_tot, ex_tmp, ex_t, ex_off, ex_out;
+  aqmp::ExportTotals* d_totals = nullptr;   // after the passes' counters
+  aqmp::DevBuf ex_buf;
 };
 
 namespace aqmp {
@@ -304,10 +302,10 @@ void free_code(aqmp_code* c) {
   for (auto& e : c->lev) destroy(e.start), destroy(e.end);
   for (auto& e : c->sev) destroy(e.a), destroy(e.b), destroy(e.c), destroy(e.d);
   for (auto& a : c->allocs) dev_free(a.p, a.bytes);
-  for (DevBuf* b : {&c->ex_keys, &c->ex_keys2, &c->ex_vals, &c->ex_vals2, &c->ex_tot, &c->ex_tmp, &c->ex_t,
-                    &c->ex_off, &c->ex_out})
-    if (b->p) dev_free(b->p, b->bytes);
-  if (c->pinned.p) (void)hipHostFree(c->pinned.p);
+  for (auto ev : c->ex_ev) destroy(ev);
+  if (c->ex_buf.p) dev_free(c->ex_buf.p, c->ex_buf.bytes);
+  for (DevBuf* b : {&c->pinned, &c->pinned_tot})
+    if (b->p) (void)hipHostFree(b->p);
   delete c;
 }
 
@@ -433,7 +431,9 @@ int build_plan(aqmp_code* c) {
     ALLOC(wk.ss.ticket, sizeof(int32_t) * 2);
   }
   ALLOC(c->djobs, sizeof(JobDev) * nj);
-  ALLOC(c->dcnt, sizeof(Counters) * c->passes.size());
+  static_assert(sizeof(Counters) % alignof(ExportTotals) == 0, "the totals follow the counters");
+  ALLOC(c->dcnt, sizeof(Counters) * c->passes.size() + sizeof(ExportTotals));
+  c->d_totals = (ExportTotals*)(c->dcnt + c->passes.size());
   ALLOC(c->dranges, sizeof(int2) * kLevels * nj);
   ALLOC(c->dqueue, sizeof(Queues) * c->passes.size());
   ALLOC(c->dntop, sizeof(int32_t) * kLevels * c->passes.size());
@@ -592,9 +592,40 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
   return AQMP_OK;
 }
 
+// A stream of the current device to capture on, and its return (after a
+// capture that failed it is destroyed instead).
+hipError_t take_stream(const aqmp_dict* d, hipStream_t* st) {
+  int dev = 0;
+  const hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  {
+    std::lock_guard<std::mutex> lock(d->capture.mu);
+    auto& idle = d->capture.idle;
+    for (size_t i = 0; i < idle.size(); ++i)
+      if (idle[i].first == dev) {
+        *st = idle[i].second;
+        idle.erase(idle.begin() + (long)i);
+        return hipSuccess;
+      }
+  }
+  return hipStreamCreateWithFlags(st, hipStreamNonBlocking);
+}
+void give_stream(const aqmp_dict* d, hipStream_t st, bool ok) {
+  int dev = 0;
+  if (ok && hipGetDevice(&dev) == hipSuccess) {
+    std::lock_guard<std::mutex> lock(d->capture.mu);
+    if (d->capture.idle.size() <= (size_t)kBranches) {
+      d->capture.idle.emplace_back(dev, st);
+      return;
+    }
+  }
+  (void)hipStreamDestroy(st);
+}
+
 int run(aqmp_code* c, hipStream_t s) {
   c->lev_pos = c->sev_pos = 0;
-  c->nodes_ok = false;
+  c->totals_ok = false;
+  c->view = aqmp_code::VIEW_NONE;
   // The job table goes to the device only when it differs from what is
   // there (a re-encode of the same images changes nothing in it).
   if (c->hjobs_dev.size() != c->hjobs.size() ||
@@ -609,10 +640,10 @@ int run(aqmp_code* c, hipStream_t s) {
       // Capture on a private stream (the caller's may be the null stream,
       // which cannot be captured); the graph is launched on the caller's.
       hipStream_t cs = nullptr;
-      AQMP_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
+      AQMP_HIP(take_stream(c->dict, &cs));
       hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
       if (e != hipSuccess) {
-        (void)hipStreamDestroy(cs);
+        give_stream(c->dict, cs, false);
         AQMP_FAIL(AQMP_E_HIP, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
       }
       int rc = AQMP_OK;
@@ -631,7 +662,7 @@ int run(aqmp_code* c, hipStream_t s) {
         }
         for (size_t pi = 0; pi < c->passes.size() && e == hipSuccess && rc == AQMP_OK; ++pi) {
           hipStream_t bs = nullptr;
-          e = hipStreamCreateWithFlags(&bs, hipStreamNonBlocking);
+          e = take_stream(c->dict, &bs);
           if (e != hipSuccess) break;
           br.push_back(bs);
           e = hipStreamWaitEvent(bs, fork, 0);
@@ -652,9 +683,10 @@ int run(aqmp_code* c, hipStream_t s) {
       }
       hipGraph_t g = nullptr;
       e = hipStreamEndCapture(cs, &g);
-      for (auto bs : br) (void)hipStreamDestroy(bs);
+      const bool clean = rc == AQMP_OK && e == hipSuccess;
+      for (auto bs : br) give_stream(c->dict, bs, clean);
       for (auto ev : evs) (void)hipEventDestroy(ev);
-      (void)hipStreamDestroy(cs);
+      give_stream(c->dict, cs, clean);
       if (rc != AQMP_OK) {
         if (g) (void)hipGraphDestroy(g);
         return rc;
@@ -712,6 +744,7 @@ int export_tables(aqmp_code* c) {
       sg.L = level_at(c, l, pp.base[l]);
       sg.count = &c->dcnt[pi].count[l];
       sg.lg = l;
+      sg.cap = (int32_t)pp.cap[l];
       sg.flat_base = (uint32_t)flat;
       segs.push_back(sg);
       flat += (uint64_t)pp.cap[l];
@@ -741,112 +774,153 @@ int export_tables(aqmp_code* c) {
     if (rc1 != AQMP_OK) return rc1;
     const int rc2 = alloc(c, (void**)&c->d_ex_jobs, sizeof(ExportJob) * jx.size());
     if (rc2 != AQMP_OK) return rc2;
-    AQMP_HIP(hipMemcpy(c->d_ex_segs, segs.data(), sizeof(ExportSeg) * segs.size(), hipMemcpyHostToDevice));
-    AQMP_HIP(hipMemcpy(c->d_ex_jobs, jx.data(), sizeof(ExportJob) * jx.size(), hipMemcpyHostToDevice));
-    int rc = ensure(c->ex_keys, sizeof(unsigned long long) * flat);
-    if (rc == AQMP_OK) rc = ensure(c->ex_vals, sizeof(uint32_t) * flat);
-    if (rc == AQMP_OK) rc = ensure(c->ex_tot, 2 * sizeof(unsigned long long));
-    if (rc != AQMP_OK) return rc;
+    // (the copies read pageable memory, which is done when they return)
+    AQMP_HIP(hipMemcpyAsync(c->d_ex_segs, segs.data(), sizeof(ExportSeg) * segs.size(), hipMemcpyHostToDevice, c->stream));
+    AQMP_HIP(hipMemcpyAsync(c->d_ex_jobs, jx.data(), sizeof(ExportJob) * jx.size(), hipMemcpyHostToDevice, c->stream));
+    AQMP_HIP(hipStreamSynchronize(c->stream));
   }
   c->ex_ready = true;
   return AQMP_OK;
 }
 
-#define AQMP_ENSURE(buf, bytes)                 \
-  do {                                          \
-    const int rc_ = ensure((buf), (bytes));     \
-    if (rc_ != AQMP_OK) return rc_;             \
-  } while (0)
-
-// Gathers every visited node on the device in canonical order (job, top-level
-// block in raster order, then depth-first: Morton order of the corner, the
-// larger node first) and copies three dense arrays back: node records, atom
-// indices, coefficients.
-int collect_all(aqmp_code* c) {
+// What the code holds, by block size: one pass over the nodes' counts and
+// states, one copy back, one wait.
+int totals(const aqmp_code* cc) {
+  aqmp_code* c = const_cast<aqmp_code*>(cc);   // the cache is not part of the code's observable state
+  if (c->totals_ok) return AQMP_OK;
   hipStream_t s = c->stream;
+  if (!c->ex_ready) {
+    const int rc = export_tables(c);
+    if (rc != AQMP_OK) return rc;
+  }
+  const size_t np = c->passes.size(), bytes = sizeof(Counters) * np + sizeof(ExportTotals);
+  {
+    const int rc = ensure_pinned(c->pinned_tot, bytes);
+    if (rc != AQMP_OK) return rc;
+  }
+  AQMP_HIP(hipMemsetAsync(c->d_totals, 0, sizeof(ExportTotals), s));
+  AQMP_HIP(launch_export_stats(c->d_ex_segs, c->ex_nseg, c->ex_max_cap, c->d_totals, s));
+  AQMP_HIP(hipMemcpyAsync(c->pinned_tot.p, c->dcnt, bytes, hipMemcpyDeviceToHost, s));
   AQMP_HIP(hipStreamSynchronize(s));
-  std::vector<Counters> cnt(c->passes.size());
-  AQMP_HIP(hipMemcpy(cnt.data(), c->dcnt, sizeof(Counters) * cnt.size(), hipMemcpyDeviceToHost));
-  for (size_t pi = 0; pi < cnt.size(); ++pi) {
+  const Counters* cnt = (const Counters*)c->pinned_tot.p;
+  for (size_t pi = 0; pi < np; ++pi) {
     if (cnt[pi].scan_error) AQMP_FAIL(AQMP_E_HIP, "aqmp_encode: a device scan exceeded its bounded wait");
     for (int l = 0; l < kLevels; ++l)
       if (cnt[pi].count[l] > c->passes[pi].cap[l])
         AQMP_FAIL(AQMP_E_HIP, "aqmp_encode: level count exceeds its capacity");
   }
-  c->nodes.clear();
-  if (!c->ex_ready) {
-    const int rc = export_tables(c);
-    if (rc != AQMP_OK) return rc;
-  }
-  if (c->ex_nseg == 0) return AQMP_OK;
-  auto* keys = (unsigned long long*)c->ex_keys.p;
-  auto* vals = (uint32_t*)c->ex_vals.p;
-  auto* tot = (unsigned long long*)c->ex_tot.p;
-  AQMP_HIP(hipMemsetAsync(tot, 0, 2 * sizeof(unsigned long long), s));
-  AQMP_HIP(launch_export_keys(c->d_ex_segs, c->ex_nseg, c->ex_max_cap, c->d_ex_jobs, keys, vals, tot, s));
-  unsigned long long ht[2] = {0, 0};
-  AQMP_HIP(hipMemcpyAsync(ht, tot, sizeof(ht), hipMemcpyDeviceToHost, s));
-  AQMP_HIP(hipStreamSynchronize(s));
-  const int64_t n = (int64_t)ht[0], na = (int64_t)ht[1];
-  if (n == 0) return AQMP_OK;
-  AQMP_ENSURE(c->ex_keys2, sizeof(unsigned long long) * n);
-  AQMP_ENSURE(c->ex_vals2, sizeof(uint32_t) * n);
-  AQMP_ENSURE(c->ex_t, sizeof(int64_t) * n);
-  AQMP_ENSURE(c->ex_off, sizeof(int64_t) * n);
-  auto* keys2 = (unsigned long long*)c->ex_keys2.p;
-  auto* vals2 = (uint32_t*)c->ex_vals2.p;
-  auto* tcount = (int64_t*)c->ex_t.p;
-  auto* off = (int64_t*)c->ex_off.p;
-  size_t sort_bytes = 0, scan_bytes = 0;
-  AQMP_HIP(export_sort(nullptr, sort_bytes, keys, keys2, vals, vals2, n, c->ex_end_bit, s));
-  AQMP_HIP(export_scan(nullptr, scan_bytes, tcount, off, n, s));
-  AQMP_ENSURE(c->ex_tmp, std::max(sort_bytes, scan_bytes));
-  sort_bytes = scan_bytes = c->ex_tmp.bytes;
-  AQMP_HIP(export_sort(c->ex_tmp.p, sort_bytes, keys, keys2, vals, vals2, n, c->ex_end_bit, s));
-  AQMP_HIP(launch_export_counts(c->d_ex_segs, c->ex_nseg, vals2, n, tcount, s));
-  AQMP_HIP(export_scan(c->ex_tmp.p, scan_bytes, tcount, off, n, s));
-  // one output block, one copy into page-locked memory
-  const size_t idx_at = sizeof(aqmp_leaf) * n;
-  const size_t coef_at = idx_at + (sizeof(int32_t) * na + 7) / 8 * 8;
-  const size_t total = coef_at + sizeof(double) * na;
-  AQMP_ENSURE(c->ex_out, total);
-  {
-    const int rc = ensure_pinned(c->pinned, total);
-    if (rc != AQMP_OK) return rc;
-  }
-  char* dout = (char*)c->ex_out.p;
-  AQMP_HIP(launch_export_write(c->d_ex_segs, c->ex_nseg, vals2, off, n, (aqmp_leaf*)dout, (int32_t*)(dout + idx_at),
-                               (double*)(dout + coef_at), s));
-  AQMP_HIP(hipMemcpyAsync(c->pinned.p, dout, total, hipMemcpyDeviceToHost, s));
-  AQMP_HIP(hipStreamSynchronize(s));
-  const char* hout = (const char*)c->pinned.p;
-  const aqmp_leaf* rec = (const aqmp_leaf*)hout;
-  const int32_t* idx = (const int32_t*)(hout + idx_at);
-  const double* coef = (const double*)(hout + coef_at);
-  c->nodes.resize(n);
-  for (int64_t i = 0; i < n; ++i) {
-    HostNode& h = c->nodes[i];
-    h.leaf = rec[i];
-    h.idx = idx + h.leaf.atom_off;
-    h.coef = coef + h.leaf.atom_off;
-  }
+  std::memcpy(&c->totals, cnt + np, sizeof(ExportTotals));
+  c->totals_ok = true;
   return AQMP_OK;
 }
 
-#undef AQMP_ENSURE
-
-// The code's visited nodes (or leaves) in canonical order; the device copy is
-// made once per encode.
-int collect(const aqmp_code* cc, bool leaves_only, std::vector<HostNode>& out) {
-  aqmp_code* c = const_cast<aqmp_code*>(cc);   // the cache is not part of the code's observable state
-  if (!c->nodes_ok) {
-    const int rc = collect_all(c);
-    if (rc != AQMP_OK) return rc;
-    c->nodes_ok = true;
+// Nodes and atoms of a view (the totals are known).
+void view_size(const aqmp_code* c, bool leaves_only, int64_t& n, int64_t& na) {
+  n = na = 0;
+  for (int l = 0; l < kLevels; ++l) {
+    n += (int64_t)(leaves_only ? c->totals.leaves[l] : c->totals.nodes[l]);
+    na += (int64_t)(leaves_only ? c->totals.emitted[l] : c->totals.iters[l]);
   }
-  out.clear();
-  for (const auto& h : c->nodes)
-    if (!(leaves_only && (h.leaf.flags & 1))) out.push_back(h);
+}
+
+// Where a view's arrays lie in its block of memory.
+struct ViewLayout {
+  size_t idx_at, coef_at, total;
+  ViewLayout(int64_t n, int64_t na)
+      : idx_at(sizeof(aqmp_leaf) * (size_t)n), coef_at(idx_at + (sizeof(int32_t) * (size_t)na + 7) / 8 * 8),
+        total(coef_at + sizeof(double) * (size_t)na) {}
+};
+
+// Gathers the visited nodes (or the leaves) on the device in canonical order
+// (job, top-level block in raster order, then depth-first: Morton order of the
+// corner, the larger node first) and copies three dense arrays back: node
+// records, atom indices, coefficients.  done(b, e) is called for every piece
+// [b, e) of the block once it is in c->pinned, in order, while the next pieces
+// are on their way.
+template <class F>
+int collect(const aqmp_code* cc, bool leaves_only, F&& done) {
+  aqmp_code* c = const_cast<aqmp_code*>(cc);   // the cache is not part of the code's observable state
+  {
+    const int rc = totals(c);
+    if (rc != AQMP_OK) return rc;
+  }
+  int64_t n, na;
+  view_size(c, leaves_only, n, na);
+  const ViewLayout at(n, na);
+  const auto want = leaves_only ? aqmp_code::VIEW_LEAVES : aqmp_code::VIEW_NODES;
+  c->view_n = n;
+  c->view_atoms = na;
+  if (n == 0) return AQMP_OK;
+  if (c->view == want) {
+    done((size_t)0, at.total);
+    return AQMP_OK;
+  }
+  c->view = aqmp_code::VIEW_NONE;
+  hipStream_t s = c->stream;
+  size_t sort_bytes = 0, scan_bytes = 0;
+  AQMP_HIP(export_sort(nullptr, sort_bytes, nullptr, nullptr, nullptr, nullptr, n, c->ex_end_bit, s));
+  AQMP_HIP(export_scan(nullptr, scan_bytes, nullptr, nullptr, n, s));
+  // Small results are written to the host's memory by the gather itself: 36
+  // against 43 us for 64 leaves and 768 atoms.  Larger ones are copied in
+  // pieces, 430 against 630 us for 37 749 leaves and 616 284 atoms (8.9 MB).
+  const bool direct = at.total <= (size_t)1 << 18;
+  size_t need = 0;
+  auto part = [&](size_t bytes) {
+    const size_t o = need;
+    need += (bytes + 255) / 256 * 256;
+    return o;
+  };
+  const size_t o_keys = part(8 * (size_t)n), o_keys2 = part(8 * (size_t)n), o_vals = part(4 * (size_t)n),
+               o_vals2 = part(4 * (size_t)n), o_t = part(8 * (size_t)n), o_off = part(8 * (size_t)n),
+               o_tmp = part(std::max(sort_bytes, scan_bytes)), o_out = part(direct ? 0 : at.total);
+  {
+    int rc = ensure(c->ex_buf, need);
+    if (rc == AQMP_OK) rc = ensure_pinned(c->pinned, at.total);
+    if (rc != AQMP_OK) return rc;
+  }
+  char* b = (char*)c->ex_buf.p;
+  auto* keys = (unsigned long long*)(b + o_keys);
+  auto* keys2 = (unsigned long long*)(b + o_keys2);
+  auto* vals = (uint32_t*)(b + o_vals);
+  auto* vals2 = (uint32_t*)(b + o_vals2);
+  auto* tcount = (int64_t*)(b + o_t);
+  auto* off = (int64_t*)(b + o_off);
+  char* out = direct ? (char*)c->pinned.p : b + o_out;
+  AQMP_HIP(hipMemsetAsync(&c->d_totals->next, 0, sizeof(c->d_totals->next), s));
+  AQMP_HIP(launch_export_keys(c->d_ex_segs, c->ex_nseg, c->ex_max_cap, c->d_ex_jobs, leaves_only, keys, vals,
+                              &c->d_totals->next, s));
+  AQMP_HIP(export_sort(b + o_tmp, sort_bytes, keys, keys2, vals, vals2, n, c->ex_end_bit, s));
+  AQMP_HIP(launch_export_counts(c->d_ex_segs, c->ex_nseg, vals2, n, tcount, s));
+  AQMP_HIP(export_scan(b + o_tmp, scan_bytes, tcount, off, n, s));
+  AQMP_HIP(launch_export_write(c->d_ex_segs, c->ex_nseg, vals2, off, n, (aqmp_leaf*)out, (int32_t*)(out + at.idx_at),
+                               (double*)(out + at.coef_at), s));
+  if (direct) {
+    AQMP_HIP(hipStreamSynchronize(s));
+    done((size_t)0, at.total);
+  } else {
+    // one copy into page-locked memory, in pieces
+    constexpr size_t kPieces = 8;
+    const size_t step = std::max<size_t>((at.total / kPieces + 4095) / 4096 * 4096, (size_t)1 << 19);
+    std::vector<size_t> ends;
+    for (size_t p = 0; p < at.total; p += step) {
+      const size_t e = std::min(at.total, p + step);
+      AQMP_HIP(hipMemcpyAsync((char*)c->pinned.p + p, out + p, e - p, hipMemcpyDeviceToHost, s));
+      if (c->ex_ev.size() <= ends.size()) {
+        hipEvent_t ev = nullptr;
+        AQMP_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+        c->ex_ev.push_back(ev);
+      }
+      AQMP_HIP(hipEventRecord(c->ex_ev[ends.size()], s));
+      ends.push_back(e);
+    }
+    size_t p = 0;
+    for (size_t i = 0; i < ends.size(); ++i) {
+      AQMP_HIP(hipEventSynchronize(c->ex_ev[i]));
+      done(p, ends[i]);
+      p = ends[i];
+    }
+  }
+  c->view = want;
   return AQMP_OK;
 }
 
@@ -902,19 +976,15 @@ void code_free(aqmp_code* c) { free_code(c); }
 
 int code_stats(const aqmp_code* c, aqmp_stats* s) {
   if (!c || !s) AQMP_FAIL(AQMP_E_INVALID, "aqmp_code_stats: null argument");
-  std::vector<HostNode> nodes;
-  const int rc = collect(c, false, nodes);
+  const int rc = totals(c);
   if (rc != AQMP_OK) return rc;
   std::memset(s, 0, sizeof(*s));
-  for (const auto& h : nodes) {
-    const int l = ilog2(h.leaf.n);
-    s->nodes[l]++;
-    s->iters_level[l] += h.leaf.n_atoms;
-    s->iters_executed += h.leaf.n_atoms;
-    if (!(h.leaf.flags & 1)) {
-      s->leaves[l]++;
-      s->iters_emitted += h.leaf.n_atoms;
-    }
+  for (int l = 0; l < kLevels; ++l) {
+    s->nodes[l] = (int64_t)c->totals.nodes[l];
+    s->leaves[l] = (int64_t)c->totals.leaves[l];
+    s->iters_level[l] = (int64_t)c->totals.iters[l];
+    s->iters_executed += (int64_t)c->totals.iters[l];
+    s->iters_emitted += (int64_t)c->totals.emitted[l];
   }
   s->steps_launched = c->steps_launched;
   return AQMP_OK;
@@ -954,24 +1024,24 @@ int code_sizes(const aqmp_code* c, int64_t* n_leaves, int64_t* n_atoms) {
 int code_export(const aqmp_code* c, bool leaves_only, aqmp_leaf* leaves, int32_t* atom_idx, double* coef,
                 int64_t cap_leaves, int64_t cap_atoms) {
   if (!c || !leaves || !atom_idx || !coef) AQMP_FAIL(AQMP_E_INVALID, "aqmp_code_export: null argument");
-  std::vector<HostNode> nodes;
-  const int rc = collect(c, leaves_only, nodes);
+  int rc = totals(c);
   if (rc != AQMP_OK) return rc;
-  int64_t na = 0;
-  for (const auto& h : nodes) na += h.leaf.n_atoms;
-  if ((int64_t)nodes.size() > cap_leaves || na > cap_atoms)
-    AQMP_FAIL(AQMP_E_CAPACITY, "aqmp_code_export: need " + std::to_string(nodes.size()) + " records and " +
-                                   std::to_string(na) + " atoms");
-  int64_t off = 0;
-  for (size_t i = 0; i < nodes.size(); ++i) {
-    aqmp_leaf L = nodes[i].leaf;
-    L.atom_off = off;
-    std::memcpy(atom_idx + off, nodes[i].idx, sizeof(int32_t) * L.n_atoms);
-    std::memcpy(coef + off, nodes[i].coef, sizeof(double) * L.n_atoms);
-    off += L.n_atoms;
-    leaves[i] = L;
-  }
-  return AQMP_OK;
+  int64_t n, na;
+  view_size(c, leaves_only, n, na);
+  if (n > cap_leaves || na > cap_atoms)
+    AQMP_FAIL(AQMP_E_CAPACITY, "aqmp_code_export: need " + std::to_string(n) + " records and " + std::to_string(na) +
+                                   " atoms");
+  const ViewLayout at(n, na);
+  return collect(c, leaves_only, [&](size_t b, size_t e) {
+    // the piece's share of each array
+    auto put = [&](void* dst, size_t from, size_t bytes) {
+      const size_t lo = std::max(b, from), hi = std::min(e, from + bytes);
+      if (lo < hi) std::memcpy((char*)dst + (lo - from), (const char*)c->pinned.p + lo, hi - lo);
+    };
+    put(leaves, 0, sizeof(aqmp_leaf) * (size_t)n);
+    put(atom_idx, at.idx_at, sizeof(int32_t) * (size_t)na);
+    put(coef, at.coef_at, sizeof(double) * (size_t)na);
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -997,20 +1067,24 @@ int code_pack(const aqmp_code* c, const int32_t* jobs, int n_jobs, int level, do
     if (im.w != im0.w || im.h != im0.h || p.n_min != p0.n_min || p.n_max != p0.n_max)
       AQMP_FAIL(AQMP_E_INVALID, "aqmp_code_pack: the channels of a stream need one size and one block range");
   }
-  std::vector<HostNode> nodes;
-  const int rc = collect(c, false, nodes);
+  const int rc = collect(c, false, [](size_t, size_t) {});
   if (rc != AQMP_OK) return rc;
+  const int64_t n = c->view_n;
+  const ViewLayout at(n, c->view_atoms);
+  const aqmp_leaf* rec = (const aqmp_leaf*)c->pinned.p;
+  const int32_t* idx = (const int32_t*)((const char*)c->pinned.p + at.idx_at);
+  const double* coef = (const double*)((const char*)c->pinned.p + at.coef_at);
   std::vector<std::vector<StreamNode>> sn(n_jobs);
   std::vector<StreamChannel> ch(n_jobs);
   for (int i = 0; i < n_jobs; ++i) {
     // the job's nodes are contiguous in the canonical order
-    auto lo = std::lower_bound(nodes.begin(), nodes.end(), jobs[i],
-                               [](const HostNode& a, int32_t j) { return a.leaf.job < j; });
-    auto hi = std::lower_bound(lo, nodes.end(), jobs[i] + 1,
-                               [](const HostNode& a, int32_t j) { return a.leaf.job < j; });
+    auto first = [&](int32_t job) {
+      return std::lower_bound(rec, rec + n, job, [](const aqmp_leaf& a, int32_t j) { return a.job < j; });
+    };
+    const aqmp_leaf *lo = first(jobs[i]), *hi = first(jobs[i] + 1);
     sn[i].reserve((size_t)(hi - lo));
     for (auto it = lo; it != hi; ++it)
-      sn[i].push_back(StreamNode{it->leaf.n, (it->leaf.flags & 1) != 0, it->leaf.n_atoms, it->idx, it->coef});
+      sn[i].push_back(StreamNode{it->n, (it->flags & 1) != 0, it->n_atoms, idx + it->atom_off, coef + it->atom_off});
     ch[i] = StreamChannel{sn[i].data(), sn[i].size()};
   }
   const StreamHeader hd{(int)c->dict->families, (uint32_t)im0.w, (uint32_t)im0.h, p0.n_min, p0.n_max};

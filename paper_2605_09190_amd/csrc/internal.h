@@ -7,6 +7,8 @@
 #include <stdint.h>
 
 #include <string>
+#include <mutex>
+#include <utility>
 #include <vector>
 
 #include "aqmp.h"
@@ -252,15 +254,22 @@ struct ExportSeg {          // one level of one pass
   LevelDev L;               // offset by the pass base
   const int32_t* count;     // nodes present (device)
   int32_t lg;
+  int32_t cap;              // its node slots
   uint32_t flat_base;       // first flat node id of the segment
+};
+// What a code holds, by block size, and the slot counter of the key pass.
+struct ExportTotals {
+  unsigned long long nodes[kLevels], leaves[kLevels], iters[kLevels], emitted[kLevels];
+  unsigned long long next;
 };
 struct ExportJob {
   long long top_base;       // global ordinal of the job's first top-level block
   int32_t nm;               // N_max of the job
   int32_t cols;             // top-level blocks per row of the padded plane
 };
-hipError_t launch_export_keys(const ExportSeg* segs, int nseg, int64_t max_cap, const ExportJob* jx,
-                              unsigned long long* keys, uint32_t* vals, unsigned long long* totals, hipStream_t s);
+hipError_t launch_export_stats(const ExportSeg* segs, int nseg, int64_t max_cap, ExportTotals* tot, hipStream_t s);
+hipError_t launch_export_keys(const ExportSeg* segs, int nseg, int64_t max_cap, const ExportJob* jx, bool leaves_only,
+                              unsigned long long* keys, uint32_t* vals, unsigned long long* next, hipStream_t s);
 hipError_t export_sort(void* tmp, size_t& tmp_bytes, unsigned long long* keys, unsigned long long* keys_out,
                        uint32_t* vals, uint32_t* vals_out, int64_t n, int end_bit, hipStream_t s);
 hipError_t export_scan(void* tmp, size_t& tmp_bytes, const int64_t* in, int64_t* out, int64_t n, hipStream_t s);
@@ -283,6 +292,14 @@ int corr_grid(int n, int precision);
 
 // Opaque public handles.
 struct aqmp_dict {
+  // Streams that capture the graphs of the dictionary's codes: making one takes
+  // 460 us, ten times the rest of a capture.  At most kBranches + 1 idle ones
+  // are kept (with their device), and given back with the dictionary.
+  struct CaptureStreams {
+    std::mutex mu;
+    std::vector<std::pair<int, hipStream_t>> idle;
+  };
+  mutable CaptureStreams capture;
   int n_min, n_max;
   uint32_t families;
   int nfam;

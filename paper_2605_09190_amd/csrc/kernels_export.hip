@@ -5,7 +5,9 @@
 // a top-level block is the order of (Morton code of the node's corner,
 // larger node first), so one radix sort of a 64-bit key per node gives it.
 // The host then reads three dense arrays (node records, atom indices,
-// coefficients) instead of every level's fixed-stride record slots.
+// coefficients) instead of every level's fixed-stride record slots; of the
+// leaves alone where the caller asks for those (their atoms are about two
+// thirds of all).
 #include <algorithm>
 
 #include <rocprim/device/device_radix_sort.hpp>
@@ -39,20 +41,49 @@ __device__ inline int seg_of(const ExportSeg* segs, int nseg, uint32_t fid) {
   return lo;
 }
 
-// One key and one flat id per visited node, appended in any order (the sort
-// fixes the order); totals[0] counts nodes, totals[1] their MP iterations.
-__global__ __launch_bounds__(256) void k_export_keys(const ExportSeg* segs, const ExportJob* jx,
-                                                     unsigned long long* keys, uint32_t* vals,
-                                                     unsigned long long* totals) {
+// Nodes, leaves, their MP iterations and those of the leaves, per block size:
+// a sum per workgroup, then one atomic each.
+__global__ __launch_bounds__(256) void k_export_stats(const ExportSeg* segs, ExportTotals* tot) {
   const ExportSeg sg = segs[blockIdx.y];
-  const int count = *sg.count;
+  const int count = min(*sg.count, sg.cap);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  unsigned long long v[3] = {0, 0, 0};                   // leaves, iterations, iterations of leaves
+  for (int i = blockIdx.x * 256 + (int)threadIdx.x; i < count; i += gridDim.x * 256) {
+    const int t = sg.L.t[i];
+    const bool leaf = !(sg.L.st[i] & ST_SPLIT);
+    v[0] += leaf ? 1 : 0;
+    v[1] += t;
+    v[2] += leaf ? t : 0;
+  }
+  __shared__ unsigned long long part[4][3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v[k] += __shfl_xor(v[k], d, 64);
+    if (lane == 0) part[w][k] = v[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < 3 && (int)blockIdx.x * 256 < count) {
+    const int k = threadIdx.x;
+    const unsigned long long sum = part[0][k] + part[1][k] + part[2][k] + part[3][k];
+    atomicAdd(k == 0 ? &tot->leaves[sg.lg] : (k == 1 ? &tot->iters[sg.lg] : &tot->emitted[sg.lg]), sum);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 64) atomicAdd(&tot->nodes[sg.lg], (unsigned long long)count);
+}
+
+// One key and one flat id per visited node (or leaf), appended in any order
+// (the sort fixes the order); *next is zero on entry.
+__global__ __launch_bounds__(256) void k_export_keys(const ExportSeg* segs, const ExportJob* jx, int leaves_only,
+                                                     unsigned long long* keys, uint32_t* vals,
+                                                     unsigned long long* next) {
+  const ExportSeg sg = segs[blockIdx.y];
+  const int count = min(*sg.count, sg.cap);
   const int lane = threadIdx.x & 63;
   const unsigned long long below = (1ull << lane) - 1ull;
   for (int base = blockIdx.x * 256; base < count; base += gridDim.x * 256) {
     const int i = base + (int)threadIdx.x;
-    const bool v = i < count;
+    const bool v = i < count && !(leaves_only && (sg.L.st[i] & ST_SPLIT));
     unsigned long long key = 0;
-    int t = 0;
     if (v) {
       const int job = sg.L.job[i];
       const ExportJob j = jx[job];
@@ -61,18 +92,11 @@ __global__ __launch_bounds__(256) void k_export_keys(const ExportSeg* segs, cons
       key = ((unsigned long long)top << kExportLowBits) |
             ((unsigned long long)corner_morton((uint32_t)(x0 % j.nm), (uint32_t)(y0 % j.nm)) << 3) |
             (unsigned long long)(7 - sg.lg);
-      t = sg.L.t[i];
     }
     const unsigned long long m = __ballot(v);
     const int rank = __popcll(m & below);
-    int tsum = t;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) tsum += __shfl_xor(tsum, d, 64);
     unsigned long long slot = 0;
-    if (lane == 0 && m) {
-      slot = atomicAdd(&totals[0], (unsigned long long)__popcll(m));
-      atomicAdd(&totals[1], (unsigned long long)tsum);
-    }
+    if (lane == 0 && m) slot = atomicAdd(next, (unsigned long long)__popcll(m));
     slot = __shfl(slot, 0, 64);
     if (v) {
       keys[slot + rank] = key;
@@ -130,11 +154,18 @@ int grid_1d(int64_t items, int per_block) {
 
 }  // namespace
 
-hipError_t launch_export_keys(const ExportSeg* segs, int nseg, int64_t max_cap, const ExportJob* jx,
-                              unsigned long long* keys, uint32_t* vals, unsigned long long* totals, hipStream_t s) {
+hipError_t launch_export_stats(const ExportSeg* segs, int nseg, int64_t max_cap, ExportTotals* tot, hipStream_t s) {
+  if (nseg <= 0) return hipSuccess;
+  const dim3 grid(std::min(grid_1d(max_cap, 1024), 64), nseg);
+  hipLaunchKernelGGL(k_export_stats, grid, dim3(256), 0, s, segs, tot);
+  return hipGetLastError();
+}
+
+hipError_t launch_export_keys(const ExportSeg* segs, int nseg, int64_t max_cap, const ExportJob* jx, bool leaves_only,
+                              unsigned long long* keys, uint32_t* vals, unsigned long long* next, hipStream_t s) {
   if (nseg <= 0) return hipSuccess;
   const dim3 grid(grid_1d(max_cap, 256), nseg);
-  hipLaunchKernelGGL(k_export_keys, grid, dim3(256), 0, s, segs, jx, keys, vals, totals);
+  hipLaunchKernelGGL(k_export_keys, grid, dim3(256), 0, s, segs, jx, leaves_only ? 1 : 0, keys, vals, next);
   return hipGetLastError();
 }
 
