@@ -134,6 +134,27 @@ struct Counters {
 struct Queues {
   int32_t at[kLevels][kQueues * kQueuePad];
 };
+// The next node of a worker that takes from queue qk, the first q0 nodes
+// having been dealt out; when its queue is empty, one of another that is not
+// (qk then names that one).  `count` or more: none is left.
+__device__ inline int next_node(int32_t* queue, int& qk, int q0, int count) {
+  int node = q0 + atomicAdd(queue + qk * kQueuePad, 1) * kQueues + qk;
+  if (node < count) return node;
+  int at[kQueues];
+#pragma unroll
+  for (int k = 1; k < kQueues; ++k)
+    at[k] = __hip_atomic_load(queue + (qk + k) % kQueues * kQueuePad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int own = qk;
+#pragma unroll
+  for (int k = 1; k < kQueues; ++k) {
+    const int q = (own + k) % kQueues;
+    if (node >= count && q0 + at[k] * kQueues + q < count) {
+      node = q0 + atomicAdd(queue + q * kQueuePad, 1) * kQueues + q;
+      qk = q;
+    }
+  }
+  return node;
+}
 
 // Look-back scan bookkeeping: one 64-bit word per tile plus two counters.
 // The last block of every scan launch restores it to zero.
@@ -212,14 +233,14 @@ hipError_t launch_pursuit_sub(int n, int precision, uint32_t families, const Job
 // sets its ||y||^2 and first stop test; the pursuit launches then take each
 // node through its whole MP (Gram updates) or OMP (least-squares refits);
 // for N <= 8 the pursuit launch does everything.  `next` is a zero-
-// initialised work counter the pursuits hand out nodes from.
+// initialised work counter, `queue` the level's node counters, zero on entry.
 hipError_t launch_gram_init(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t lg, int32_t nfam,
                             const double* tab, double* cbuf, hipStream_t s);
 hipError_t launch_gram_pursuit(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* next, int32_t lg,
                                int32_t nfam, const double* tab, const double* xg, const double* cbuf, hipStream_t s);
 // kmax: the largest k among the level's jobs (at most kOmpMaxAtoms); it
 // sizes the factor in LDS.
-hipError_t launch_omp_pursuit(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* next, int32_t lg,
+hipError_t launch_omp_pursuit(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* queue, int32_t lg,
                               int32_t nfam, const double* tab, const double* xg, const double* cbuf, int32_t kmax,
                               hipStream_t s);
 // SSIM partials: one FP64 per workgroup (window7) or five plane sums per

@@ -49,7 +49,7 @@
 // of residual and correlations 1 060, arg-max 720, norm and stop test 700;
 // correlations anew 4 700, 1.9 times a node), and the last long nodes of a
 // level.  On three 2048 x 2048 planes (36 432 node-steps at N = 64, 74 821 at
-// N = 32) the levels take 280 and 112 us; with the correlations made anew at
+// N = 32) the levels take 241 and 86 us; with the correlations made anew at
 // every step 444 and 191 us, and with a correlation and a select launch per
 // step 2 510 and 980 us.
 #include "internal.h"
@@ -397,7 +397,8 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
   const int px = (lane & 7) * PW;
   // The first nodes are dealt out in order, the others by the queues: queue
   // k holds every kQueues-th node after the first ones.
-  const int q0 = (int)gridDim.x * NPG, qk = (int)blockIdx.x % kQueues;
+  const int q0 = (int)gridDim.x * NPG;
+  int qk = (int)blockIdx.x % kQueues;
   int par = 0;                                           // sPart buffer in use
   int node = (int)blockIdx.x * NPG + grp;
   while (node < count) {
@@ -465,9 +466,6 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
 #pragma unroll
       for (int j = 0; j < PW; ++j) r[i][j] = (double)((const float*)sR)[(py + i) * N + px + j];
     sep_sync<WPN>();
-    // the node after this one: taken here, needed at the end
-    int ahead = 0;
-    if (WPN > 1 ? tid == 0 : lane == 0) ahead = atomicAdd(queue + qk * kQueuePad, 1);
     // Scale of the operand rows, a power of two: ||r|| goes to [2^7, 2^8), so
     // that the first product (at most 2^15) and the remainders stay inside
     // FP16's range.
@@ -740,6 +738,17 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
       else if (t >= kmax)
         st = ST_SPARSE;
     }
+    // The next node, not before this one is done: nodes differ in length by
+    // the whole pursuit (taken with this node's gather, N = 64 took 277 instead
+    // of 243 us on three 2048 x 2048 planes, N = 32 106 instead of 86).  N = 64
+    // also empties the other queues (search round 575 -> 549 us); with a node
+    // per wave or slot the look at them costs more than it evens out.
+    int ahead = 0;
+    if constexpr (WPN > 1) {
+      if (tid == 0) ahead = next_node(queue, qk, q0, count);
+    } else {
+      if (lane == 0) ahead = q0 + atomicAdd(queue + qk * kQueuePad, 1) * kQueues + qk;
+    }
     if (wq == 0) {
       if (lane < (t & 63)) {
         lv.rec_idx[rec0 + (t & ~63) + lane] = rec_i;
@@ -752,7 +761,7 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
       }
     }
     // The next node, through LDS so that every lane takes the same value.
-    if (WPN > 1 ? tid == 0 : lane == 0) sNode[grp] = q0 + ahead * kQueues + qk;
+    if (WPN > 1 ? tid == 0 : lane == 0) sNode[grp] = ahead;
     sep_sync<WPN>();
     node = __builtin_amdgcn_readfirstlane(sNode[grp]);
     sep_sync<WPN>();

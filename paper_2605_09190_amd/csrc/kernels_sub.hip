@@ -23,12 +23,12 @@
 //
 // What bounds it: the instructions of a step (about 400 for the two nodes of
 // a wave), then the longest pursuits.  On three 2048 x 2048 planes N = 16
-// (157 690 node-steps) takes 91 us and N = 8 (170 692) 77 us; with the N = 16
+// (157 690 node-steps) takes 86 us and N = 8 (170 692) 74 us; with the N = 16
 // correlations made anew at every step, matrix-core results copied out of the
 // accumulator registers and the constant atom's sums beside the others' 124
 // and 88 us, with the unfactored BF16 product (8 or 4 times the operations)
 // in workgroups of 16 slots, which met three times a step, 254 and 115 us.
-// FP32 form, 1536 x 1024 x 3: N = 16 67 us (FP32 products at every step 97 us,
+// FP32 form, 1536 x 1024 x 3: N = 16 63 us (FP32 products at every step 97 us,
 // step by step 1 870 us).
 //
 // N = 8 of the FP32 form (k_mp_fused) keeps the residual and its coefficients
@@ -388,7 +388,6 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
     // ---- slots without a node take their next one ----
     if (__ballot(load) != 0ull) {
       if (load) {
-        if (li == 0) ahead = atomicAdd(queue + qk * kQueuePad, 1);
         const int jidx = lv.job[node];
         const int bx = lv.x0[node], by = lv.y0[node];
         const JobDev jl = jobs[jidx];
@@ -676,6 +675,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
     // ---- the next node of the slots that ended ----
     load = false;
     if (__ballot(!run && !dry) != 0ull) {
+      if (!run && !dry && li == 0) ahead = atomicAdd(queue + qk * kQueuePad, 1);   // (not before: see k_pursuit_sep)
       const int idx = q0 + __shfl(ahead, lane & ~(LPS - 1), 64) * kQueues + qk;
       if (!run && !dry) {
         node = idx;
