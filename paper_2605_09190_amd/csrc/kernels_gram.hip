@@ -552,8 +552,15 @@ __global__ __launch_bounds__(256) void k_gram_small(const JobDev* __restrict__ j
 //     Kronecker delta (the selected atoms' own correlations are exactly zero,
 //     r being orthogonal to them), across families the X products.
 // One workgroup per node at every N (the per-step solves are small and
-// serial), nodes handed out from a counter.  c0 = D^T y comes from
+// serial), nodes handed out from queues.  c0 = D^T y comes from
 // k_gram_init for N >= 16 and is computed here for N <= 8.
+// What bounds it: the chain of a step (5 300 cycles at N = 8: arg-max 640,
+// Gram entries and w 1 170, root, quotients and the new row 1 650, refresh
+// 1 600), of which a CU holds as many as the factors leave room for.  Three
+// 1024 x 1024 planes, k = 32, N = 64 / 32 / 16 / 8: 187 / 145 / 135 / 129 us;
+// 204 / 212 / 168 / 176 us with loops over single selections, each waiting
+// for its loads, and thousands of workgroups starting on one counter (20 to
+// 25 us of every node's start).
 // ---------------------------------------------------------------------------
 template <int N, int NFAM>
 struct OmpGeo {
@@ -599,9 +606,9 @@ struct OmpGeo {
 
 template <int N, int NFAM>
 __global__ __launch_bounds__((OmpGeo<N, NFAM>::NT)) void k_omp(const JobDev* __restrict__ jobs, LevelDev lv,
-                                             const int32_t* __restrict__ count_ptr, int32_t* next, int32_t lg,
+                                             const int32_t* __restrict__ count_ptr, int32_t* queue, int32_t lg,
                                              const double* __restrict__ tab, const double* __restrict__ xg,
-                                             const double* __restrict__ cbuf, int kcap) {
+                                             const double* __restrict__ cbuf, int k8) {
   using G = OmpGeo<N, NFAM>;
   constexpr int K = G::K, M = G::M, APT = G::APT, AF = G::AF;
   constexpr bool SMALL = G::SMALL;
@@ -610,15 +617,20 @@ __global__ __launch_bounds__((OmpGeo<N, NFAM>::NT)) void k_omp(const JobDev* __r
   __shared__ double sX[NX][NX + 1];                    // X[p][p'] = <T_0[p], T_1[p']>
   __shared__ double sT[SMALL ? NFAM : 1][SMALL ? K : 1];
   __shared__ double sY[SMALL ? K : 1];
-  // L = chol(G_SS)^-1, lower triangular, kcap x (kcap + 1) doubles sized at
-  // launch by the largest k of the level (smaller k: more workgroups per CU)
+  // L = chol(G_SS)^-1, lower triangular, k8 rows of k8 + 1 doubles, sized at
+  // launch by the largest k of the level, rounded up to eights (smaller k:
+  // more workgroups per CU).  Rows are zero past the diagonal, and rows not
+  // written yet hold finite values, so that its products run over whole
+  // blocks of eight, their loads in flight together: the terms past the end
+  // are exact zeros.
   extern __shared__ double sLdyn[];
-  const int ldl = kcap + 1;
+  const int ldl = k8 + 1;
   __shared__ int sS[KC];                               // selected atoms in order
   __shared__ double sXc[KC], sG[KC], sW[KC];           // x_S, g, w
   // the selected atoms split by family, in selection order: p | q << 8 and x
-  __shared__ int sPQ[NFAM][KC];
-  __shared__ double sXF[NFAM][KC];
+  // (zeros behind the last: the refresh takes both in eights)
+  __shared__ int sPQ[NFAM][KC + 8];
+  __shared__ double sXF[NFAM][KC + 8];
   __shared__ int sNF[NFAM];
   __shared__ double sBc[2][8];                         // per-wave best c
   __shared__ int sBi[2][8];
@@ -630,16 +642,22 @@ __global__ __launch_bounds__((OmpGeo<N, NFAM>::NT)) void k_omp(const JobDev* __r
     for (int i = tid; i < K; i += G::NT) sX[i / N][i % N] = xg[i];
   if constexpr (SMALL)
     for (int i = tid; i < NFAM * K; i += G::NT) (&sT[0][0])[i] = tab[i];
+  for (int i = tid; i < k8 * ldl; i += G::NT) sLdyn[i] = 0.0;
   __syncthreads();
   const int count = *count_ptr;
   const int pa = tid % N;                              // p of the thread's atom (N <= 8)
   int ph = 0, np = 0;
-  for (;;) {
-    if (tid == 0) sNode[np] = atomicAdd(next, 1);
-    __syncthreads();
-    const int node = sNode[np];
-    np ^= 1;
-    if (node >= count) break;
+  // The first nodes are dealt out in order, the others by the queues (see
+  // k_pursuit_sep).
+  const int qk = (int)blockIdx.x % kQueues;
+  int node = (int)blockIdx.x;
+  for (; node < count; node = sNode[np], np ^= 1) {
+    if constexpr (NFAM == 2)
+      for (int i = tid; i < NFAM * (KC + 8); i += G::NT) {
+        (&sPQ[0][0])[i] = 0;
+        (&sXF[0][0])[i] = 0.0;
+      }
+    __syncthreads();   // the lists are the wave's that fills them
     const JobDev& jb = jobs[lv.job[node]];
     const double eps2 = jb.eps2[lg];
     const int kmax = jb.k[lg];
@@ -745,12 +763,35 @@ __global__ __launch_bounds__((OmpGeo<N, NFAM>::NT)) void k_omp(const JobDev* __r
         }
         sG[lane] = g;
         wave_sync();
+        const double* lrow = sLdyn + (lane < k8 ? lane : k8 - 1) * ldl;
         double wr = 0.0;
-        if (act) {
-#pragma unroll 4
-          for (int cc = 0; cc <= lane; ++cc) wr = fma(sLdyn[lane * ldl + cc], sG[cc], wr);
+        for (int c8 = 0; c8 < t; c8 += 8) {
+          double lv8[8], g8[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            lv8[i] = lrow[c8 + i];
+            g8[i] = sG[c8 + i];
+          }
+#pragma unroll
+          for (int i = 0; i < 8; ++i) wr = fma(lv8[i], g8[i], wr);
         }
+        wr = act ? wr : 0.0;
         sW[lane] = wr;
+        wave_sync();
+        // w L: the first eight rows beside the norm and its root, the others behind
+        const double* lcol = sLdyn + (lane < k8 ? lane : k8 - 1);
+        auto wl = [&](int r8, double acc) -> double {
+          double lv8[8], w8[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            lv8[i] = lcol[(r8 + i) * ldl];
+            w8[i] = sW[r8 + i];
+          }
+#pragma unroll
+          for (int i = 0; i < 8; ++i) acc = fma(w8[i], lv8[i], acc);
+          return acc;
+        };
+        double acc = wl(0, 0.0);
         const double s1 = wave_sum_f64(wr * wr);
         const double d2 = 1.0 - s1;
         const bool dep = !(d2 > 1e-24);   // chosen atom (numerically) in the span of the selected ones
@@ -760,21 +801,16 @@ __global__ __launch_bounds__((OmpGeo<N, NFAM>::NT)) void k_omp(const JobDev* __r
           const double invd = 1.0 / d;
           const double zt = bc / d;
           enew = fma(-zt, zt, e);
-          wave_sync();
           double lr = invd, dx = zt * invd, xn = dx;
+          for (int r8 = 8; r8 < t; r8 += 8) acc = wl(r8, acc);
           if (act) {
-            double acc = 0.0;
-#pragma unroll 4
-            for (int r = lane; r < t; ++r) acc = fma(sW[r], sLdyn[r * ldl + lane], acc);
             lr = -acc * invd;
             dx = zt * lr;
             xn = sXc[lane] + dx;
           }
           const bool in = lane <= t;
-          if (in) {
-            sLdyn[t * ldl + lane] = lr;
-            sXc[lane] = xn;
-          }
+          if (lane < k8) sLdyn[t * ldl + lane] = in ? lr : 0.0;
+          if (in) sXc[lane] = xn;
           if (lane == 0) {
             sS[t] = bi;
           }
@@ -787,9 +823,10 @@ __global__ __launch_bounds__((OmpGeo<N, NFAM>::NT)) void k_omp(const JobDev* __r
               sPQ[f][rk] = (as % N) | (((as % K) / N) << 8);
               sXF[f][rk] = SMALL ? xn : dx;
             }
+            const int n0 = __popcll(m0), n1 = __popcll(m1);
             if (lane == 0) {
-              sNF[0] = __popcll(m0);
-              sNF[1] = __popcll(m1);
+              sNF[0] = n0;
+              sNF[1] = n1;
             }
           }
         }
@@ -824,12 +861,18 @@ __global__ __launch_bounds__((OmpGeo<N, NFAM>::NT)) void k_omp(const JobDev* __r
         if (tid < K) {
 #pragma unroll
           for (int fs = 0; fs < 2; ++fs) {
-            const int fa = 1 - fs;
-            for (int k = 0; k < sNF[fs]; ++k) {
-              const int pq = sPQ[fs][k];
-              const int ps = pq & 255, qs = pq >> 8;
-              const double g = fs == 0 ? sX[ps][pa] * sX[qs][qa] : sX[pa][ps] * sX[qa][qs];
-              c[fa] = fma(-sXF[fs][k], g, c[fa]);
+            const int ns = sNF[fs];
+            for (int k0 = 0; k0 < ns; k0 += 4) {   // four at a time: the loads together
+              double g[4], x[4];
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const int pq = sPQ[fs][k0 + i];
+                const int ps = pq & 255, qs = pq >> 8;
+                g[i] = fs == 0 ? sX[ps][pa] * sX[qs][qa] : sX[pa][ps] * sX[qa][qs];
+                x[i] = sXF[fs][k0 + i];
+              }
+#pragma unroll
+              for (int i = 0; i < 4; ++i) c[1 - fs] = fma(-x[i], g[i], c[1 - fs]);
             }
           }
         }
@@ -842,27 +885,36 @@ __global__ __launch_bounds__((OmpGeo<N, NFAM>::NT)) void k_omp(const JobDev* __r
         const int lk = lane >> 4, li = lane & 15;
 #pragma unroll
         for (int fs = 0; fs < 2; ++fs) {
-          const int ns = sNF[fs];
-          const int fa = 1 - fs;   // the family whose atoms change
-          for (int kb = 0; kb < ns; kb += 4) {
-            const int k = kb + lk;
-            const bool ok = k < ns;
-            const int pq = ok ? sPQ[fs][k] : 0;
-            const double xs = ok ? sXF[fs][k] : 0.0;
-            const int ps = pq & 255, qs = pq >> 8;
+          const int ns = sNF[fs], fa = 1 - fs;   // fa: the family whose atoms change
+          for (int kb = 0; kb < ns; kb += 8) {
+            // eight selections: two updates whose operands load together
+            double xs[2], av[2][TPW], bv[2][TPW];
 #pragma unroll
-            for (int i = 0; i < TPW; ++i) {
-              const int tt = wv * TPW + i, tp = tt / NT16, tq = tt % NT16;
-              // family-1 atoms: X[ps][p] X[qs][q]; family-0 atoms: X[p][ps] X[q][qs]
-              const double av = -xs * (fs == 0 ? sX[ps][16 * tp + li] : sX[16 * tp + li][ps]);
-              const double bv = fs == 0 ? sX[qs][16 * tq + li] : sX[16 * tq + li][qs];
-              const int j0 = fa * G::AF + 4 * i;
-              d4 cv = d4{c[j0], c[j0 + 1], c[j0 + 2], c[j0 + 3]};
-              cv = mfma64(av, bv, cv);
-              c[j0] = cv[0];
-              c[j0 + 1] = cv[1];
-              c[j0 + 2] = cv[2];
-              c[j0 + 3] = cv[3];
+            for (int u = 0; u < 2; ++u) {
+              const int pq = sPQ[fs][kb + 4 * u + lk];
+              xs[u] = sXF[fs][kb + 4 * u + lk];
+              const int ps = pq & 255, qs = pq >> 8;
+#pragma unroll
+              for (int i = 0; i < TPW; ++i) {
+                const int tt = wv * TPW + i, tp = tt / NT16, tq = tt % NT16;
+                // family-1 atoms: X[ps][p] X[qs][q]; family-0 atoms: X[p][ps] X[q][qs]
+                av[u][i] = fs == 0 ? sX[ps][16 * tp + li] : sX[16 * tp + li][ps];
+                bv[u][i] = fs == 0 ? sX[qs][16 * tq + li] : sX[16 * tq + li][qs];
+              }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              if (kb + 4 * u >= ns) continue;
+#pragma unroll
+              for (int i = 0; i < TPW; ++i) {
+                const int j0 = fa * G::AF + 4 * i;
+                d4 cv = d4{c[j0], c[j0 + 1], c[j0 + 2], c[j0 + 3]};
+                cv = mfma64(-xs[u] * av[u][i], bv[u][i], cv);
+                c[j0] = cv[0];
+                c[j0 + 1] = cv[1];
+                c[j0 + 2] = cv[2];
+                c[j0 + 3] = cv[3];
+              }
             }
           }
         }
@@ -879,7 +931,9 @@ __global__ __launch_bounds__((OmpGeo<N, NFAM>::NT)) void k_omp(const JobDev* __r
       lv.e[node] = e;
       lv.t[node] = t;
       lv.st[node] = st;
+      sNode[np] = (int)gridDim.x + atomicAdd(queue + qk * kQueuePad, 1) * kQueues + qk;
     }
+    __syncthreads();   // the next node; sS, sXc are read
   }
 }
 
@@ -940,18 +994,18 @@ hipError_t launch_gram_pursuit(int n, const JobDev* jobs, LevelDev lv, const int
   return hipGetLastError();
 }
 
-hipError_t launch_omp_pursuit(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* next, int32_t lg,
+hipError_t launch_omp_pursuit(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* queue, int32_t lg,
                               int32_t nfam, const double* tab, const double* xg, const double* cbuf, int32_t kmax,
                               hipStream_t s) {
   if (nfam == 2 && !xg) return hipErrorInvalidValue;
   if (nfam != 1 && nfam != 2) return hipErrorInvalidValue;
   if (kmax > kOmpMaxAtoms) return hipErrorInvalidValue;
-  const int kcap = kmax < 1 ? 1 : kmax;
+  const int k8 = kmax < 1 ? 8 : (kmax + 7) / 8 * 8;
   int dev = 0, n_cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
-  const size_t smem = sizeof(double) * (size_t)kcap * (kcap + 1);
+  const size_t smem = sizeof(double) * (size_t)k8 * (k8 + 1);
   // Nodes come from a counter, so the grid is as many workgroups as fit on
   // the device at once (registers and LDS decide; more would only start
   // after the work is gone).
@@ -963,7 +1017,7 @@ hipError_t launch_omp_pursuit(int n, const JobDev* jobs, LevelDev lv, const int3
         per_cu < 1)                                                                                            \
       per_cu = 1;                                                                                              \
     hipLaunchKernelGGL((k_omp<NN, FF>), dim3(n_cus * per_cu), dim3(OmpGeo<NN, FF>::NT), smem, s, jobs, lv,  \
-                       count, next, lg, tab, xg, cbuf, kcap);                                                  \
+                       count, queue, lg, tab, xg, cbuf, k8);                                                  \
   }
 #define AQMP_OMP(NN)             \
   case NN:                       \
