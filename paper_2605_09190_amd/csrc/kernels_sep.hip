@@ -108,12 +108,14 @@ __device__ constexpr bool sep_haar(int f) { return G::FAMS == AQMP_HAAR || (G::F
 // mixed-precision FMA takes FP16 sources and rounds its result to FP16 in
 // place, so a value costs one and a half instructions here (BF16 needs
 // three: no such FMA exists for it).  op_sel_hi marks an FP16 source, op_sel
-// its upper half.
+// its upper half.  The remainders are matrix-core operands: two wait states
+// after their last write, which the compiler does not add behind inline
+// assembly.
 __device__ inline void sp_split2(float a, float b, uint32_t& h, uint32_t& l) {
   const auto p = __builtin_amdgcn_cvt_pkrtz(a, b);
   __builtin_memcpy(&h, &p, 4);
   __asm__("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(l) : "v"(h), "v"(a));
-  __asm__("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(l) : "v"(h), "v"(b));
+  __asm__("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\ts_nop 1" : "+v"(l) : "v"(h), "v"(b));
 }
 // The same for a * s and b * s (s a power of two).
 __device__ inline void sp_split2_scaled(float a, float b, float s, uint32_t& h, uint32_t& l) {

@@ -93,11 +93,11 @@ __device__ inline uint32_t sb_split_hi(float a, float b) {
   __builtin_memcpy(&h, &p, 4);
   return h;
 }
-// packed FP16 remainders of a pair (see sp_split2)
+// packed FP16 remainders of a pair (see sp_split2, also for the wait states)
 __device__ inline uint32_t sb_split_lo(float a, float b, uint32_t h) {
   uint32_t l;
   __asm__("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(l) : "v"(h), "v"(a));
-  __asm__("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(l) : "v"(h), "v"(b));
+  __asm__("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\ts_nop 1" : "+v"(l) : "v"(h), "v"(b));
   return l;
 }
 
