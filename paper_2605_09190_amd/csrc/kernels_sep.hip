@@ -694,22 +694,23 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
         {
           const int f = atom / K, q = (atom % K) / N, p = atom % N;
           const float cs = (float)(coef * gain);
-          const float own = lane == (((p & 15) >> 2) << 4 | (q & 15)) ? cs : 0.f;
+          const float own = lane == (((p & 15) >> 2) << 4 | (q & 15)) && (WPN == 1 || (q >> 4) / G::TQ == wq) ? cs : 0.f;
           const int j = (((q >> 4) % G::TQ) * G::TT + (p >> 4)) * 4 + (p & 3);
-          auto update = [&](sp_f32x16& Cs, sp_f32x16& Co) {
-            if constexpr (G::NFAM == 2) {
+          // (no branch on the family, whose joins copied all of them: the atom's
+          // own family takes zero times the products)
+          if constexpr (G::NFAM == 2) {
+#pragma unroll
+            for (int f2 = 0; f2 < 2; ++f2)
 #pragma unroll
               for (int i = 0; i < G::TQ; ++i) {
-                const float s = -(cs * gq[i]);
+                const float s = f2 != f ? -(cs * gq[i]) : 0.f;
 #pragma unroll
                 for (int x = 0; x < 4 * G::TT; ++x)
-                  Co[i * 4 * G::TT + x] = fmaf(s, gp[x >> 2][x & 3], Co[i * 4 * G::TT + x]);
+                  C[f2][i * 4 * G::TT + x] = fmaf(s, gp[x >> 2][x & 3], C[f2][i * 4 * G::TT + x]);
               }
-            }
-            if (WPN == 1 || (q >> 4) / G::TQ == wq) Cs[j] -= own;
-          };
-          if (G::NFAM == 1 || f == 0) update(C[0], C[G::NFAM - 1]);
-          else update(C[G::NFAM - 1], C[0]);
+          }
+#pragma unroll
+          for (int f2 = 0; f2 < G::NFAM; ++f2) C[f2][j] -= f2 == f ? own : 0.f;
         }
         top();
         double ew = 0.0;
