@@ -202,9 +202,10 @@ def solver_roofline(A, dic, imgs, w, solver, sched, steps, warmup):
     """Dominant kernel of a labelled solver, timed live with the library's HIP
     events (a separate encode issued on the stream, like the headline's).
 
-    Gram: the initial correlations of the largest blocks, k_gram_init<N>,
-    8 N^3 flop per node (two N^3 products per family, FMA = 2 flop) on the
-    FP64 matrix cores.  OMP: its pursuit k_omp<N>, whose correlation refresh
+    Gram: the pursuit of the largest blocks, k_gram_pursuit<N>: the initial
+    correlations, 8 N^3 flop per node (two N^3 products per family, FMA = 2
+    flop) on the FP64 matrix cores, and 2 N^2 per step for the update of the
+    other family's.  OMP: its pursuit k_omp<N>, whose correlation refresh
     after step s costs s * N^2 FMA (each selected atom updates the N^2 atoms
     of the other family), i.e. N^2 T (T - 1) flop for a node of T atoms, on
     the FP64 vector units."""
@@ -215,12 +216,10 @@ def solver_roofline(A, dic, imgs, w, solver, sched, steps, warmup):
     n = 1 << lg
     fam = 2
     if solver == A.SOLVER_GRAM:
-        flops = 8.0 * n ** 3 * st["nodes"][lg]
-        ms = tm["corr_ms"][lg]
-        name, bound = f"k_gram_init<{n}, {fam}>", "mfma"
-        other = dict(kernel=f"k_gram_pursuit<{n}, {fam}>", ms=round(tm["select_ms"][lg], 4),
-                     flops=2.0 * n * n * st["iters_level"][lg])
-        other["frac"] = round(other["flops"] / (other["ms"] * 1e-3) / 1e12 / PEAK_FP64_TFLOPS, 4)
+        flops = 8.0 * n ** 3 * st["nodes"][lg] + 2.0 * n * n * st["iters_level"][lg]
+        ms = tm["select_ms"][lg]
+        name, bound = f"k_gram_pursuit<{n}, {fam}>", "mfma"
+        other = dict(steps=int(st["iters_level"][lg]))
     else:
         exp = code_t.export_nodes()
         t = exp.leaves["n_atoms"][exp.leaves["n"] == n].astype(np.float64)

@@ -220,8 +220,8 @@ typedef struct {
  * launches on the stream. */
 typedef struct {
   double corr_ms[7];        /* correlation + top-R key launches of the levels
-                               that run step by step (Gram and OMP solvers,
-                               N >= 16: the initial-correlation launch)     */
+                               that run step by step (OMP solver, N >= 16:
+                               the initial-correlation launch)              */
   double select_ms[7];      /* re-score / update / norm launches (Gram and
                                OMP solvers, N >= 16: the pursuit launch)    */
   double level_ms[7];       /* whole level: gather .. split/emit            */

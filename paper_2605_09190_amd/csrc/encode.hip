@@ -382,7 +382,7 @@ int build_plan(aqmp_code* c) {
       max_r[wi] = std::max(max_r[wi], pp.cap[l] * n * n);
       max_keys[wi] = std::max(max_keys[wi], pp.cap[l] * (D.m_pad / corr_atom_tile((int)n)) * kTopR);
       max_cap[wi] = std::max(max_cap[wi], pp.cap[l]);
-      if (c->opt.solver != AQMP_SOLVER_DENSE && n > kFusedMaxN)
+      if (c->opt.solver == AQMP_SOLVER_OMP && n > kFusedMaxN)
         max_cbuf[wi] = std::max(max_cbuf[wi], pp.cap[l] * D.m);
       c->steps_launched += pp.kmax[l];
     }
@@ -540,15 +540,15 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
       if (c->opt.solver != AQMP_SOLVER_DENSE) {
         const aqmp_code::StepEv* se = timing && n > kFusedMaxN ? &c->sev[c->sev_pos++] : nullptr;
         if (se) AQMP_HIP(hipEventRecord(se->a, s));
-        if (n > kFusedMaxN)
+        if (n > kFusedMaxN && c->opt.solver == AQMP_SOLVER_OMP)
           AQMP_LAUNCH(launch_gram_init(n, c->djobs, a.lv, count, l, d->nfam, D.d_tab, wk.cbuf, s));
         if (se) AQMP_HIP(hipEventRecord(se->b, s));
         if (c->opt.solver == AQMP_SOLVER_OMP)
           AQMP_LAUNCH(launch_omp_pursuit(n, c->djobs, a.lv, count, c->dqueue[pi].at[l], l, d->nfam, D.d_tab, D.d_xg,
                                          wk.cbuf, pp.kmax[l], s));
         else
-          AQMP_LAUNCH(launch_gram_pursuit(n, c->djobs, a.lv, count, &cnt->next[l], l, d->nfam, D.d_tab, D.d_xg,
-                                          wk.cbuf, s));
+          AQMP_LAUNCH(launch_gram_pursuit(n, c->djobs, a.lv, count, c->dqueue[pi].at[l], l, d->nfam, pp.cap[l], D.d_tab,
+                                          D.d_xg, s));
         if (se) AQMP_HIP(hipEventRecord(se->c, s));
       } else if (sep_level(c, n))
         AQMP_LAUNCH(launch_pursuit_sep(n, d->families, c->djobs, a.lv, count, c->dqueue[pi].at[l], pp.cap[l], D.d_tab, D.d_sep, s));

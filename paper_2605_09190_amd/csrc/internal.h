@@ -228,16 +228,16 @@ hipError_t launch_mp_fused4(const JobDev* jobs, LevelDev lv, const int32_t* coun
 hipError_t launch_pursuit_sub(int n, int precision, uint32_t families, const JobDev* jobs, LevelDev lv,
                               const int32_t* count, int32_t* queue, int64_t cap, const double* tab, const double* xg,
                               hipStream_t s);
-// Gram and OMP forms (FP64).  For N >= 16 launch_gram_init writes the
-// correlations of every node of the level to cbuf ([node][nfam * n * n]) and
-// sets its ||y||^2 and first stop test; the pursuit launches then take each
-// node through its whole MP (Gram updates) or OMP (least-squares refits);
-// for N <= 8 the pursuit launch does everything.  `next` is a zero-
-// initialised work counter, `queue` the level's node counters, zero on entry.
+// Gram and OMP forms (FP64).  launch_gram_pursuit takes each node of the level
+// through its whole MP (Gram updates).  launch_omp_pursuit does so for OMP
+// (least-squares refits) with, for N >= 16, the initial correlations that
+// launch_gram_init wrote to cbuf ([node][nfam * n * n]) before it, together
+// with each node's ||y||^2 and first stop test.  `queue`: the level's node
+// counters, zero on entry; cap: its node capacity.
 hipError_t launch_gram_init(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t lg, int32_t nfam,
                             const double* tab, double* cbuf, hipStream_t s);
-hipError_t launch_gram_pursuit(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* next, int32_t lg,
-                               int32_t nfam, const double* tab, const double* xg, const double* cbuf, hipStream_t s);
+hipError_t launch_gram_pursuit(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* queue, int32_t lg,
+                               int32_t nfam, int64_t cap, const double* tab, const double* xg, hipStream_t s);
 // kmax: the largest k among the level's jobs (at most kOmpMaxAtoms); it
 // sizes the factor in LDS.
 hipError_t launch_omp_pursuit(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* queue, int32_t lg,

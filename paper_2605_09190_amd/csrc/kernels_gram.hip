@@ -19,13 +19,15 @@
 // FMAs, the residual itself is never formed, and the constant atoms (exactly
 // 1/N) are handled exactly.
 //
-// k_gram_init: gather, ||y||^2, the first stop test, and the correlations of
-// every node as two FP64 matrix-core products per family (Z^T = Y^T T_f^T,
-// then C^T = T_f Z^T), written to a per-node buffer.  N / 16 waves per node,
+// k_gram_pursuit: a node's whole MP in one launch: the initial correlations as
+// two FP64 matrix-core products per family (Z^T = Y^T T_f^T, then C^T = T_f
+// Z^T), then the pursuit (selection with the lowest index on ties, records,
+// stop test of eq. (2)) with the correlations held in registers.
+// k_gram_init: gather, ||y||^2, the first stop test and the same products,
+// written to a per-node buffer for the OMP kernel.  N / 16 waves per node,
 // each owning one 16-wide strip of the row index p.
-// k_gram_pursuit: the whole pursuit of every node (selection with the lowest
-// index on ties, records, stop test of eq. (2)) with the correlations held
-// in registers: one wave per node for N <= 32, four for N = 64.
+#include <type_traits>
+
 #include "internal.h"
 #include "dev_common.h"
 
@@ -179,15 +181,83 @@ __global__ __launch_bounds__(256) void k_gram_init(const JobDev* __restrict__ jo
   }
 }
 
+// Geometry of the whole-node pursuit: one wave per node for N <= 32, four for
+// N = 64, each owning 16-wide strips of the row index q (SW of them) with the
+// correlations in the matrix cores' output layout: value 4 (s T + tp) + r of
+// a lane is atom (q = 16 (WPN s.. + s) + lane / 16 + 4 r, p = 16 tp + lane % 16).
 template <int N, int NFAM>
 struct PurGeo {
   static constexpr int K = N * N;
   static constexpr int M = NFAM * K;
-  static constexpr int TPN = N == 64 ? 256 : 64;   // threads per node
-  static constexpr int WPN = TPN / 64;
-  static constexpr int APT = M / TPN;              // atoms per thread
-  static constexpr int NPW = 256 / TPN;            // nodes per workgroup
+  static constexpr int WPN = N == 64 ? 4 : 1;      // waves per node
+  static constexpr int NPW = 4 / WPN;              // nodes per workgroup
+  static constexpr int T = N / 16;
+  static constexpr int SW = T / WPN;               // strips per wave
+  static constexpr int AF = 4 * SW * T;            // correlations per lane and family
+  static constexpr int G = AF / 4 * NFAM;          // groups of four
+  static constexpr int KS = N / 4;
 };
+// CNT pixels of column x, rows y0, y0 + dy, ..
+template <int CNT>
+__device__ inline void job_column(const JobDev& jb, int y0, int dy, int x, double (&v)[CNT]) {
+  const int xx = x < jb.w ? x : jb.w - 1;
+  int64_t at[CNT];
+#pragma unroll
+  for (int i = 0; i < CNT; ++i) {
+    const int y = y0 + i * dy;
+    at[i] = (int64_t)(y < jb.h ? y : jb.h - 1) * jb.row_stride + xx;
+  }
+  if (jb.dtype == AQMP_F64) {
+    const gmem_f64* p = (const gmem_f64*)jb.img;
+#pragma unroll
+    for (int i = 0; i < CNT; ++i) v[i] = p[at[i]];
+  } else {
+    const gmem_f32* p = (const gmem_f32*)jb.img;
+#pragma unroll
+    for (int i = 0; i < CNT; ++i) v[i] = (double)p[at[i]];
+  }
+}
+template <int A>
+struct DVec;
+template <>
+struct DVec<16> {
+  typedef double type __attribute__((ext_vector_type(16)));
+};
+template <>
+struct DVec<4> {
+  typedef double type __attribute__((ext_vector_type(4)));
+};
+
+// Larger of |a| and b >= 0 (no quieting of NaNs first).  Neither a matrix-core
+// result may go in nor a lane exchange follow directly: the compiler adds no
+// wait states around inline assembly.
+__device__ inline double max_abs(double a, double b) {
+  double r;
+  __asm__("v_max_f64 %0, |%1|, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+// Largest of non-negative doubles over the wave, without NaNs, uniform.
+__device__ inline double wave_max_f64(double d) {
+  d = fmax(d, row_perm_f64<0xB1>(d));
+  d = fmax(d, row_perm_f64<0x4E>(d));
+  d = fmax(d, row_perm_f64<0x141>(d));
+  d = fmax(d, row_perm_f64<0x140>(d));
+  auto pair = [](double v, auto x) -> double {
+    constexpr int X = decltype(x)::value;
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    uint32_t p0, q0, p1, q1;
+    lane_pair_u32<X>((uint32_t)u, p0, q0);
+    lane_pair_u32<X>((uint32_t)(u >> 32), p1, q1);
+    return fmax(__longlong_as_double((long long)(((unsigned long long)p1 << 32) | p0)),
+                __longlong_as_double((long long)(((unsigned long long)q1 << 32) | q0)));
+  };
+  d = pair(d, std::integral_constant<int, 16>());
+  d = pair(d, std::integral_constant<int, 32>());
+  const unsigned long long w = (unsigned long long)__double_as_longlong(d);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)w);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(w >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 
 // Best atom of a wave: largest |c|, lowest atom index among equal
 // magnitudes; the result is uniform across the wave.  |c| is non-negative,
@@ -236,151 +306,347 @@ __device__ inline void lane_best(const double (&c)[A], double& bc, int& bj) {
   bj = ix[0];
 }
 
+// The whole pursuit of every node: gather, ||y||^2, first stop test, the
+// initial correlations (the two products of k_gram_init, in its order), then
+// the steps, everything in registers and LDS.  Z^T takes the place of the
+// pixels, so that N = 64 fits two workgroups to a CU beside X.
+//
+// What bounds it: N = 64 the FP64 products (2.1 MFLOP a node, 82 us for 3 072
+// nodes at the matrix cores' FP64 rate) beside the chain of a node's steps,
+// smaller blocks that chain.  Three 2048 x 2048 planes, N = 64 / 32 / 16:
+// 261 / 95 / 77 us; 323 / 123 / 82 us with the correlations through memory
+// (200 MB at N = 64) between two launches and a compare and three selects per
+// correlation for the arg-max.
 template <int N, int NFAM>
-__global__ __launch_bounds__(256) void k_gram_pursuit(const JobDev* __restrict__ jobs, LevelDev lv,
-                                                      const int32_t* __restrict__ count_ptr, int32_t* next, int32_t lg,
-                                                      const double* __restrict__ xg, const double* __restrict__ cbuf) {
-  using G = PurGeo<N, NFAM>;
-  constexpr int K = G::K, M = G::M, TPN = G::TPN, WPN = G::WPN, APT = G::APT, NPW = G::NPW;
-  constexpr int AF = APT / NFAM;          // atoms per thread per family
-  constexpr int RW = 64;                  // records held in registers between flushes
+__global__ __launch_bounds__(256, 2) void k_gram_pursuit(const JobDev* __restrict__ jobs, LevelDev lv,
+                                                         const int32_t* __restrict__ count_ptr,
+                                                         int32_t* __restrict__ queue, int32_t lg,
+                                                         const double* __restrict__ tab,
+                                                         const double* __restrict__ xg) {
+  using P = PurGeo<N, NFAM>;
+  constexpr int K = P::K, WPN = P::WPN, NPW = P::NPW, T = P::T, SW = P::SW, AF = P::AF, G = P::G, KS = P::KS;
   constexpr int NX = NFAM == 2 ? N : 1;
+  using CV = typename DVec<AF>::type;
   __shared__ double sX[NX][NX + 1];       // X[p][p'] = <T_0[p], T_1[p']>
-  __shared__ double sBc[2][4];            // per-wave best, double-buffered (N = 64)
-  __shared__ int sBi[2][4];
-  __shared__ int sNode[2];                // node handed to the workgroup (N = 64), double-buffered
+  __shared__ double sYZ[NPW][K];          // pixels, then Z^T of a family
+  __shared__ double sRed[4][2];
+  __shared__ __attribute__((aligned(16))) double sBc[2][4];   // per-wave best, double-buffered (N = 64)
+  __shared__ __attribute__((aligned(16))) int sBi[2][4];
+  __shared__ int sNode[2][4];             // next node, double-buffered
   const int tid = threadIdx.x, lane = tid & 63;
-  const int tn = tid % TPN, wn = tn >> 6;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wn = WPN > 1 ? wv : 0, grp = WPN > 1 ? 0 : wv;
+  const int li = lane & 15, lk = lane >> 4;
+  double* yz = sYZ[grp];
+  auto sync = [&]() {
+    if constexpr (WPN > 1) __syncthreads();
+    else wave_sync();
+  };
+  double tr[NFAM][SW][KS];
+#pragma unroll
+  for (int f = 0; f < NFAM; ++f)
+#pragma unroll
+    for (int s = 0; s < SW; ++s)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) tr[f][s][ks] = tab[(size_t)f * K + (16 * (wn * SW + s) + li) * N + 4 * ks + lk];
   if constexpr (NFAM == 2)
     for (int i = tid; i < K; i += 256) sX[i / N][i % N] = xg[i];
   __syncthreads();
   const int count = *count_ptr;
-  // This thread's atoms: a = tn + TPN j.  TPN is a multiple of N, so p_a =
-  // tn mod N for every j, q_a = (tn / N + (TPN / N) j) mod N and the family
-  // is j / AF.
-  const int pa = tn % N;
-  const int qb = tn / N;
+  const int q0 = (int)gridDim.x * NPW, qk = (int)blockIdx.x % kQueues;
   int ph = 0, np = 0;
-  // Nodes are handed out one at a time from a counter: their pursuits differ
-  // in length by up to k steps, and neighbouring node indices (the same
-  // block in the channels of one image) tend to be long together.
-  for (;;) {
-    // N = 64: one thread fetches, the workgroup reads the value after the
-    // barrier.  Smaller blocks (one wave per node, short pursuits): a fixed
-    // grid-stride assignment, since a fetch per node would cost more than
-    // the imbalance it removes.
-    int node;
-    if constexpr (NPW == 1) {
-      if (tid == 0) sNode[np] = atomicAdd(next, 1);
-      __syncthreads();
-      node = sNode[np];
-      np ^= 1;
+  int node = (int)blockIdx.x * NPW + grp;
+  while (node < count) {
+    const int jidx = lv.job[node];
+    const int bx = lv.x0[node], by = lv.y0[node];
+    const JobDev jb = jobs[jidx];
+    const double eps2 = jobs[jidx].eps2[lg];
+    const int kmax = __builtin_amdgcn_readfirstlane(jobs[jidx].k[lg]);
+    // ---- gather; ||y||^2 and the sum in k_gram_init's lanes and order ----
+    double e, sum;
+    if constexpr (N == 32) {
+      double ev[2] = {0.0, 0.0}, sv[2] = {0.0, 0.0};   // its two waves
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        double pv[K / 128];
+        job_column(jb, by + (64 * v + lane) / N, 128 / N, bx + lane % N, pv);
+#pragma unroll
+        for (int i0 = 0; i0 < K / 128; ++i0) {
+          const int i = 128 * i0 + 64 * v + lane;
+          yz[sw<N>(i / N, i % N)] = pv[i0];
+          ev[v] = fma(pv[i0], pv[i0], ev[v]);
+          sv[v] += pv[i0];
+        }
+        ev[v] = wave_sum_f64(ev[v]);
+        sv[v] = wave_sum_f64(sv[v]);
+      }
+      e = ev[0] + ev[1];
+      sum = sv[0] + sv[1];
     } else {
-      node = (blockIdx.x + gridDim.x * np) * NPW + (tid >> 6);
-      ++np;
+      constexpr int TPN = 64 * WPN;
+      const int tn = WPN > 1 ? tid : lane;
+      double ee = 0.0, ss = 0.0, pv[K / TPN];
+      job_column(jb, by + tn / N, TPN / N, bx + tn % N, pv);
+#pragma unroll
+      for (int i0 = 0; i0 < K / TPN; ++i0) {
+        const int i = TPN * i0 + tn;
+        yz[sw<N>(i / N, i % N)] = pv[i0];
+        ee = fma(pv[i0], pv[i0], ee);
+        ss += pv[i0];
+      }
+      e = wave_sum_f64(ee);
+      sum = wave_sum_f64(ss);
+      if constexpr (WPN > 1) {
+        if (lane == 0) {
+          sRed[wv][0] = e;
+          sRed[wv][1] = sum;
+        }
+      }
     }
-    if (node >= count) break;
-    const JobDev& jb = jobs[lv.job[node]];
-    const double eps2 = jb.eps2[lg];
-    const int kmax = jb.k[lg];
-    double e = lv.e[node];
-    uint8_t st = lv.st[node];
+    sync();
+    if constexpr (WPN > 1) {
+      e = sRed[0][0];
+      sum = sRed[0][1];
+#pragma unroll
+      for (int q = 1; q < WPN; ++q) {
+        e += sRed[q][0];
+        sum += sRed[q][1];
+      }
+    }
+    uint8_t st = ST_RUN;
+    if (e < eps2)
+      st = ST_ACC;
+    else if (kmax <= 0)
+      st = ST_SPARSE;
+    CV c[NFAM];
+    if (st == ST_RUN) {
+      // Z^T[x][p] = sum_y Y[y][x] T_f[p][y], p in the wave's strips
+      d4 z[NFAM][SW][T];
+#pragma unroll
+      for (int f = 0; f < NFAM; ++f)
+#pragma unroll
+        for (int s = 0; s < SW; ++s)
+#pragma unroll
+          for (int tx = 0; tx < T; ++tx) z[f][s][tx] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int tx = 0; tx < T; ++tx) {
+          const double yv = yz[sw<N>(4 * ks + lk, 16 * tx + li)];
+#pragma unroll
+          for (int f = 0; f < NFAM; ++f)
+#pragma unroll
+            for (int s = 0; s < SW; ++s) z[f][s][tx] = mfma64(yv, tr[f][s][ks], z[f][s][tx]);
+        }
+#pragma unroll
+      for (int f = 0; f < NFAM; ++f) {
+        sync();   // the pixels, or the other family's Z^T, are read
+#pragma unroll
+        for (int s = 0; s < SW; ++s)
+#pragma unroll
+          for (int tx = 0; tx < T; ++tx)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) yz[sw<N>(16 * tx + lk + 4 * r, 16 * (wn * SW + s) + li)] = z[f][s][tx][r];
+        sync();
+        // C^T[q][p] = sum_x T_f[q][x] Z^T[x][p], q in the wave's strips
+        d4 a[SW][T];
+#pragma unroll
+        for (int s = 0; s < SW; ++s)
+#pragma unroll
+          for (int tp = 0; tp < T; ++tp) a[s][tp] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int tp = 0; tp < T; ++tp) {
+            const double zv = yz[sw<N>(4 * ks + lk, 16 * tp + li)];
+#pragma unroll
+            for (int s = 0; s < SW; ++s) a[s][tp] = mfma64(tr[f][s][ks], zv, a[s][tp]);
+          }
+#pragma unroll
+        for (int j = 0; j < AF; ++j)   // (an ordinary instruction between the matrix cores and max_abs)
+          c[f][j] = __builtin_canonicalize(a[j / (4 * T)][(j >> 2) % T][j & 3]);
+        // the constant atom (p = q = 0) is exactly 1/N
+        if (wn == 0 && lane == 0) c[f][0] = sum / N;
+      }
+    }
+    // The largest |c| is found by FP64 maxima; undefined pixels (or a norm
+    // that overflows) by the order of the bits, where a NaN is the largest.
+    const bool odd = !(e < __builtin_inf());
     int t = 0;
     int rec_i = 0;
     double rec_c = 0.0;
-    double c[APT];
-    const double* cn = cbuf + (size_t)node * M;
-#pragma unroll
-    for (int j = 0; j < APT; ++j) c[j] = cn[tn + TPN * j];
     const size_t rec0 = (size_t)node * lv.kmax;
+    auto atom_of = [&](int f, int j, int w, int l) -> int {
+      return f * K + (16 * (w * SW + j / (4 * T)) + (l >> 4) + 4 * (j & 3)) * N + 16 * ((j >> 2) % T) + (l & 15);
+    };
     while (st == ST_RUN) {
-      // this thread's best (ascending j is ascending atom index)
+      // ---- the wave's arg-max |c|, lowest atom index on ties ----
+      if constexpr (NFAM == 2) {
+        // the second family's constant atom equals the first's, which wins the
+        // tie (and with which it goes to zero)
+        if (wn == 0 && lane == 0) c[1][0] = 0.0;
+      }
+      int bi = 0x7fffffff, at = 0, L = 0;            // atom; its place f AF + j and lane
+      bool one = !odd;
+      if (!odd) {
+        double m0 = 0.0, m1 = 0.0;
+#pragma unroll
+        for (int f = 0; f < NFAM; ++f)
+#pragma unroll
+          for (int j = 0; j < AF; j += 2) {
+            m0 = max_abs(c[f][j], m0);
+            m1 = max_abs(c[f][j + 1], m1);
+          }
+        const double m = wave_max_f64(max_abs(m0, m1));
+        // the sign of |c| - m, two instructions per value: bit V - 1 - j is 0
+        // where value j is the largest
+        constexpr int V = NFAM * AF;
+        uint32_t less = ~0u;
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+          const double d = fabs(c[j / AF][j % AF]) - m;
+          less = __builtin_amdgcn_alignbit(less, (uint32_t)((unsigned long long)__double_as_longlong(d) >> 32), 31);
+        }
+        const uint32_t is = ~less;
+        const unsigned long long hit = __ballot(is != 0u);
+        L = hit ? __builtin_ctzll(hit) : 0;
+        const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)is, L);
+        one = __popcll(hit) == 1 && __popc(bits) == 1;
+        at = V - 1 - (bits ? __builtin_ctz(bits) : 0);
+        bi = atom_of(at / AF, at % AF, wn, L);
+      }
+      if (!one) {
+        // ties, or undefined values: the largest by bits, then the lowest atom
+        unsigned long long mb = 0ull;
+        int best = 0x7fffffff;
+#pragma unroll
+        for (int f = 0; f < NFAM; ++f)
+#pragma unroll 1
+          for (int j = 0; j < AF; ++j) {
+            const unsigned long long u = (unsigned long long)__double_as_longlong(fabs(c[f][j]));
+            mb = u > mb ? u : mb;
+          }
+        const unsigned long long m = wave_max_u64(mb);
+#pragma unroll
+        for (int f = 0; f < NFAM; ++f)
+#pragma unroll 1
+          for (int j = 0; j < AF; ++j) {
+            const int a = atom_of(f, j, wn, lane);
+            if ((unsigned long long)__double_as_longlong(fabs(c[f][j])) == m && a < best) best = a;
+          }
+        bi = best;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const int o = __shfl_xor(bi, off, 64);
+          bi = o < bi ? o : bi;
+        }
+        bi = __builtin_amdgcn_readfirstlane(bi);
+        const int q = (bi % K) / N, p = bi % N;
+        at = bi / K * AF + 4 * (((q >> 4) % SW) * T + (p >> 4)) + ((q & 15) >> 2);
+        L = (q & 3) * 16 + (p & 15);
+      }
+      at = __builtin_amdgcn_readfirstlane(at);
+      L = __builtin_amdgcn_readfirstlane(L);
       double bc;
-      int bj;
-      lane_best(c, bc, bj);
-      int bi = tn + TPN * bj;
-      wave_best(bc, bi, bc, bi);
+      {
+        double v;
+        if (NFAM == 1 || at < AF) v = c[0][at % AF];
+        else v = c[NFAM - 1][at % AF];
+        const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+        const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)u, L);
+        const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), L);
+        bc = __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+      }
+      int ow = 0;                                    // the wave that holds the atom
       if constexpr (WPN > 1) {
         if (lane == 0) {
-          sBc[ph][wn] = bc;
-          sBi[ph][wn] = bi;
+          sBc[ph][wv] = bc;
+          sBi[ph][wv] = bi;
         }
         __syncthreads();
-        bc = sBc[ph][0];
-        bi = sBi[ph][0];
+        const double2 b01 = *(const double2*)&sBc[ph][0], b23 = *(const double2*)&sBc[ph][2];
+        const int4 bj = *(const int4*)&sBi[ph][0];
+        const double wb[4] = {b01.x, b01.y, b23.x, b23.y};
+        const int wi[4] = {bj.x, bj.y, bj.z, bj.w};
+        bc = wb[0];
+        bi = wi[0];
 #pragma unroll
         for (int q = 1; q < WPN; ++q) {
-          const double oc = sBc[ph][q];
-          const int oi = sBi[ph][q];
-          if (fabs(oc) > fabs(bc) || (fabs(oc) == fabs(bc) && oi < bi)) {
-            bc = oc;
-            bi = oi;
-          }
+          const bool take = fabs(wb[q]) > fabs(bc) || (fabs(wb[q]) == fabs(bc) && wi[q] < bi);
+          bc = take ? wb[q] : bc;
+          bi = take ? wi[q] : bi;
         }
+        bi = __builtin_amdgcn_readfirstlane(bi);
+        ow = (bi % K) / N / (16 * SW);
         ph ^= 1;
       }
       if (bc == 0.0) {
         st = ST_ZERO;
         break;
       }
-      if (tn == t % RW) {
+      if (lane == t % 64) {
         rec_i = bi;
         rec_c = bc;
       }
-      // c_a <- c_a - c_i <phi_a, phi_i>.  Across families the Gram entry is
-      // X[p_a][p_i] X[q_a][q_i] (or its transpose), exact for the constant
-      // atoms.  Within the chosen atom's family it is a Kronecker delta, so
-      // only c_i changes, to zero: c_j += z s_j with z = -c_i on the thread
-      // holding it (0 elsewhere) and s_j = [j = j_i] a scalar 0 or 1 gives
-      // exactly 0 there and leaves every other value unchanged, at one FMA
-      // per atom.
-      const int fi = bi / K, pi = bi % N, qi = (bi % K) / N;
-      const double z = (tn == bi % TPN) ? -bc : 0.0;
-      const int jsel = __builtin_amdgcn_readfirstlane(bi / TPN);
+      // c_a <- c_a - c_i <phi_a, phi_i>: zero for the atom itself, nothing for
+      // the rest of its family, X[p_a][p_i] X[q_a][q_i] (or its transpose)
+      // for the other family, exact for the constant atoms.
+      const int pi = bi % N, qi = (bi % K) / N;
+      // (No branch on the family, whose joins copied all of them: the atom's
+      // own family takes zero times the products.)
+      const bool first = NFAM == 1 || bi < K;
+      const bool own = (WPN == 1 || ow == wn) && lane == L;
+#pragma unroll
+      for (int f = 0; f < NFAM; ++f) {
+        const double v = c[f][at % AF];
+        c[f][at % AF] = own && first == (f == 0) ? 0.0 : v;
+      }
       if constexpr (NFAM == 2) {
-        if (fi == 0) {
-          const double bv = -bc * sX[pi][pa];
+        double bv[T], xq[SW][4];
 #pragma unroll
-          for (int j = 0; j < AF; ++j) c[j] = fma(z, j == jsel ? 1.0 : 0.0, c[j]);
+        for (int tp = 0; tp < T; ++tp) bv[tp] = -bc * (first ? sX[pi][16 * tp + li] : sX[16 * tp + li][pi]);
 #pragma unroll
-          for (int j = AF; j < APT; ++j) {
-            const int qa = (qb + (TPN / N) * j) % N;
-            c[j] = fma(bv, sX[qi][qa], c[j]);
-          }
-        } else {
-          const double bv = -bc * sX[pa][pi];
+        for (int s = 0; s < SW; ++s)
 #pragma unroll
-          for (int j = 0; j < AF; ++j) {
-            const int qa = (qb + (TPN / N) * j) % N;
-            c[j] = fma(bv, sX[qa][qi], c[j]);
+          for (int r = 0; r < 4; ++r) {
+            const int q = 16 * (wn * SW + s) + lk + 4 * r;
+            xq[s][r] = first ? sX[qi][q] : sX[q][qi];
           }
 #pragma unroll
-          for (int j = AF; j < APT; ++j) c[j] = fma(z, j == jsel ? 1.0 : 0.0, c[j]);
+        for (int f = 0; f < 2; ++f) {
+          double bf[T];
+#pragma unroll
+          for (int tp = 0; tp < T; ++tp) bf[tp] = first == (f == 1) ? bv[tp] : 0.0;
+#pragma unroll
+          for (int j = 0; j < AF; ++j) c[f][j] = fma(bf[(j >> 2) % T], xq[j / (4 * T)][j & 3], c[f][j]);
         }
-      } else {
-#pragma unroll
-        for (int j = 0; j < APT; ++j) c[j] = fma(z, j == jsel ? 1.0 : 0.0, c[j]);
       }
       e = fma(-bc, bc, e);
       ++t;
-      if (t % RW == 0 && tn < RW) {
-        lv.rec_idx[rec0 + (t - RW) + tn] = rec_i;
-        lv.rec_coef[rec0 + (t - RW) + tn] = rec_c;
+      if (t % 64 == 0 && wn == 0) {
+        lv.rec_idx[rec0 + (t - 64) + lane] = rec_i;
+        lv.rec_coef[rec0 + (t - 64) + lane] = rec_c;
       }
       if (e < eps2)
         st = ST_ACC;
       else if (t >= kmax)
         st = ST_SPARSE;
     }
-    if (tn < t % RW) {
-      lv.rec_idx[rec0 + (t - t % RW) + tn] = rec_i;
-      lv.rec_coef[rec0 + (t - t % RW) + tn] = rec_c;
+    if (WPN > 1 ? tid == 0 : lane == 0) sNode[np][grp] = q0 + atomicAdd(queue + qk * kQueuePad, 1) * kQueues + qk;
+    if (wn == 0) {
+      if (lane < t % 64) {
+        lv.rec_idx[rec0 + (t - t % 64) + lane] = rec_i;
+        lv.rec_coef[rec0 + (t - t % 64) + lane] = rec_c;
+      }
+      if (lane == 0) {
+        lv.e[node] = e;
+        lv.t[node] = t;
+        lv.st[node] = st;
+      }
     }
-    if (tn == 0) {
-      lv.e[node] = e;
-      lv.t[node] = t;
-      lv.st[node] = st;
-    }
+    sync();   // the next node; yz is read
+    node = __builtin_amdgcn_readfirstlane(sNode[np][grp]);
+    np ^= 1;
   }
 }
 
@@ -960,10 +1226,14 @@ hipError_t launch_gram_init(int n, const JobDev* jobs, LevelDev lv, const int32_
   return hipGetLastError();
 }
 
-hipError_t launch_gram_pursuit(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* next, int32_t lg,
-                               int32_t nfam, const double* tab, const double* xg, const double* cbuf, hipStream_t s) {
+hipError_t launch_gram_pursuit(int n, const JobDev* jobs, LevelDev lv, const int32_t* count, int32_t* queue, int32_t lg,
+                               int32_t nfam, int64_t cap, const double* tab, const double* xg, hipStream_t s) {
   if (nfam == 2 && !xg) return hipErrorInvalidValue;
   if (nfam != 1 && nfam != 2) return hipErrorInvalidValue;
+  int dev = 0, n_cus = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
 #define AQMP_GSMALL(NN, GRID)                                                                                  \
   case NN:                                                                                                     \
     if (nfam == 2)                                                                                             \
@@ -971,26 +1241,37 @@ hipError_t launch_gram_pursuit(int n, const JobDev* jobs, LevelDev lv, const int
     else                                                                                                       \
       hipLaunchKernelGGL((k_gram_small<NN, 1>), dim3(GRID), dim3(256), 0, s, jobs, lv, count, lg, tab, xg);   \
     break;
-#define AQMP_GPUR(NN, GRID)                                                                                    \
-  case NN:                                                                                                     \
-    if (nfam == 2)                                                                                             \
-      hipLaunchKernelGGL((k_gram_pursuit<NN, 2>), dim3(GRID), dim3(256), 0, s, jobs, lv, count, next, lg, xg, \
-                         cbuf);                                                                                \
-    else                                                                                                       \
-      hipLaunchKernelGGL((k_gram_pursuit<NN, 1>), dim3(GRID), dim3(256), 0, s, jobs, lv, count, next, lg, xg, \
-                         cbuf);                                                                                \
+#define AQMP_GPUR_F(NN, FF)                                                                                 \
+  {                                                                                                         \
+    int per_cu = 0;                                                                                         \
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_gram_pursuit<NN, FF>, 256, 0) != hipSuccess || \
+        per_cu < 1)                                                                                         \
+      per_cu = 1;                                                                                           \
+    int64_t wgs = (cap + PurGeo<NN, FF>::NPW - 1) / PurGeo<NN, FF>::NPW;                                    \
+    if (wgs > (int64_t)n_cus * per_cu) wgs = (int64_t)n_cus * per_cu;                                       \
+    if (wgs < 1) wgs = 1;                                                                                   \
+    hipLaunchKernelGGL((k_gram_pursuit<NN, FF>), dim3((unsigned)wgs), dim3(256), 0, s, jobs, lv, count, queue, lg, \
+                       tab, xg);                                                                            \
+  }
+#define AQMP_GPUR(NN)    \
+  case NN:               \
+    if (nfam == 2)       \
+      AQMP_GPUR_F(NN, 2) \
+    else                 \
+      AQMP_GPUR_F(NN, 1) \
     break;
   switch (n) {
     AQMP_GSMALL(4, 1024)
     AQMP_GSMALL(8, 2048)
-    AQMP_GPUR(16, 2048)
-    AQMP_GPUR(32, 2048)
-    AQMP_GPUR(64, 1024)
+    AQMP_GPUR(16)
+    AQMP_GPUR(32)
+    AQMP_GPUR(64)
     default:
       return hipErrorInvalidValue;
   }
 #undef AQMP_GSMALL
 #undef AQMP_GPUR
+#undef AQMP_GPUR_F
   return hipGetLastError();
 }
 

@@ -1,5 +1,6 @@
 """The OMP kernel at the edges of its blocks of eight selections, and with more
-nodes than workers (nodes come from queues), against the oracle."""
+nodes than workers (nodes come from queues), against the oracle; the Gram
+kernel's arg-max among exact ties and undefined values."""
 import numpy as np
 import pytest
 
@@ -32,3 +33,43 @@ def test_omp_more_nodes_than_workers(A, dic, n):
     rep = _run(A, dic, [img], [p], [(0, 0)], 1, dtype="f64", blocks_per_job=[sample])
     _say(rep.summary())
     assert rep.ok(), rep.summary()
+
+
+@pytest.mark.parametrize("n", [16, 32, 64])
+@pytest.mark.parametrize("fam", [1, 2, 3])
+def test_gram_ties_and_undefined_pixels(A, n, fam):
+    """One pixel per block, where whole rows of atoms have one correlation up
+    to rounding: an atom with the largest is taken first.  A plane with an
+    undefined pixel goes on until k in its block (undefined correlations are
+    the largest) and leaves the other blocks alone."""
+    import torch
+    d = A.Dictionary(16, 64, families=fam)
+    one = np.zeros((64, 64))
+    one[::n, ::n] = 1.0                       # one pixel of every block
+    nan = piecewise_image(64, 128, seed=43)
+    nan[5, 7] = np.nan
+    clean = piecewise_image(64, 128, seed=43)
+    imgs = [torch.from_numpy(a).cuda() for a in (one, nan, clean)]
+    p = dict(tol=1e-3, max_atoms=6, n_min=n, n_max=n)
+    code = A.Code(d, imgs, [p], [(0, 0), (1, 0), (2, 0)], schedule=1, solver=A.SOLVER_GRAM)
+    e = code.export_nodes()
+    code.free()
+    d.free()
+    print("n", n, "fam", fam, "nodes", len(e.leaves), flush=True)
+    dd = O.get_dict(n, fam).D if n < 64 else None
+    for leaf in e.leaves:
+        at = int(leaf["atom_off"])
+        if leaf["job"] == 0 and dd is not None:
+            c = np.abs(dd.T[:, 0])            # the pixel's values of every atom
+            first = int(e.atom_idx[at])
+            assert c[first] >= c.max() * (1 - 2.0 ** -50)
+        if leaf["job"] == 1 and leaf["x0"] == 0 and leaf["y0"] == 0:
+            assert leaf["n_atoms"] == 6 and np.isnan(leaf["resid_sq"])
+    by = {(int(x["job"]), int(x["x0"]), int(x["y0"])): x for x in e.leaves}
+    for (j, x0, y0), leaf in by.items():
+        if j == 1 and (x0, y0) != (0, 0):
+            other = by[(2, x0, y0)]
+            na = int(leaf["n_atoms"])
+            assert na == int(other["n_atoms"]) and leaf["resid_sq"] == other["resid_sq"]
+            a, b = int(leaf["atom_off"]), int(other["atom_off"])
+            assert (e.atom_idx[a:a + na] == e.atom_idx[b:b + na]).all() and (e.coef[a:a + na] == e.coef[b:b + na]).all()
