@@ -651,59 +651,38 @@ __global__ __launch_bounds__(256, 2) void k_gram_pursuit(const JobDev* __restric
 }
 
 // ---------------------------------------------------------------------------
-// Small blocks (N = 4, 8): one group of K = N^2 lanes per node (a whole wave
-// at N = 8, a row of 16 lanes at N = 4), lane = pixel for the gather and
-// lane = (p, q) for the atoms, one atom per family per lane.  The
+// Small blocks.  N = 4: a row of 16 lanes per node, lane = pixel for the
+// gather and lane = (p, q) for the atoms, one atom per family per lane.  The
 // correlations come from the separable sum sum_y T_f[p][y] sum_x T_f[q][x]
 // Y[y][x]; the pursuit then runs on the Gram updates as above.  Selection
-// reductions stay inside the group (DPP row operations; the wave-wide form
-// at N = 8): the largest |c|, then the lowest atom index among the lanes
-// holding it, then that lane's c.
+// reductions are DPP operations inside the row: the largest |c|, then the
+// lowest atom index among the lanes holding it, then that lane's c.
 // ---------------------------------------------------------------------------
-template <int LPN>
-__device__ inline unsigned long long grp_max_u64(unsigned long long v) {
-  if constexpr (LPN == 64) {
-    return wave_max_u64(v);
-  } else {
-    static_assert(LPN == 16, "groups of 16 or 64 lanes");
+__device__ inline unsigned long long row_max_u64(unsigned long long v) {
 #define AQMP_GMAX(C) { const unsigned long long o = dpp_u64<C, 0xF>(v); v = o > v ? o : v; }
-    AQMP_GMAX(0xB1) AQMP_GMAX(0x4E) AQMP_GMAX(0x141) AQMP_GMAX(0x140)
+  AQMP_GMAX(0xB1) AQMP_GMAX(0x4E) AQMP_GMAX(0x141) AQMP_GMAX(0x140)
 #undef AQMP_GMAX
-    return v;
-  }
+  return v;
 }
-template <int LPN>
-__device__ inline double grp_sum_f64(double d) {
-  if constexpr (LPN == 64) {
-    return wave_sum_f64(d);
-  } else {
-#define AQMP_GSUM(C) { d += __longlong_as_double((long long)dpp_u64<C, 0xF>((unsigned long long)__double_as_longlong(d))); }
-    AQMP_GSUM(0xB1) AQMP_GSUM(0x4E) AQMP_GSUM(0x141) AQMP_GSUM(0x140)
-#undef AQMP_GSUM
-    return d;
-  }
+__device__ inline double row_sum_f64(double d) {
+  d += row_perm_f64<0xB1>(d);
+  d += row_perm_f64<0x4E>(d);
+  d += row_perm_f64<0x141>(d);
+  d += row_perm_f64<0x140>(d);
+  return d;
 }
-// Minimum of non-negative 32-bit values over the group (lanes that a row
-// operation leaves without a source keep their own value).
-template <int CTRL, int RM>
-__device__ inline int dpp_keep(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, RM, 0xF, false); }
-template <int LPN>
-__device__ inline int grp_min_i32(int v) {
-#define AQMP_GMIN(C, RM) { const int o = dpp_keep<C, RM>(v); v = o < v ? o : v; }
-  AQMP_GMIN(0xB1, 0xF) AQMP_GMIN(0x4E, 0xF) AQMP_GMIN(0x141, 0xF) AQMP_GMIN(0x140, 0xF)
-  if constexpr (LPN == 64) {
-    AQMP_GMIN(0x142, 0xA) AQMP_GMIN(0x143, 0xC)
-    v = __builtin_amdgcn_readlane(v, 63);
-  }
+__device__ inline int row_min_i32(int v) {
+#define AQMP_GMIN(C) { const int o = (int)row_perm_u32<C>((uint32_t)v); v = o < v ? o : v; }
+  AQMP_GMIN(0xB1) AQMP_GMIN(0x4E) AQMP_GMIN(0x141) AQMP_GMIN(0x140)
 #undef AQMP_GMIN
   return v;
 }
 
-template <int N, int NFAM>
-__global__ __launch_bounds__(256) void k_gram_small(const JobDev* __restrict__ jobs, LevelDev lv,
-                                                    const int32_t* __restrict__ count_ptr, int32_t lg,
-                                                    const double* __restrict__ tab, const double* __restrict__ xg) {
-  constexpr int K = N * N;
+template <int NFAM>
+__global__ __launch_bounds__(256) void k_gram4(const JobDev* __restrict__ jobs, LevelDev lv,
+                                               const int32_t* __restrict__ count_ptr, const double* __restrict__ tab,
+                                               const double* __restrict__ xg) {
+  constexpr int N = 4, K = N * N, lg = 2;
   constexpr int LPN = K;                 // lanes per node
   constexpr int GPW = 64 / LPN;          // nodes per wave
   constexpr int NG = 4 * GPW;            // nodes per workgroup
@@ -726,8 +705,8 @@ __global__ __launch_bounds__(256) void k_gram_small(const JobDev* __restrict__ j
     const double v = job_pixel(jb, lv.y0[node] + qa, lv.x0[node] + pa);   // pixel (lt / N, lt % N)
     sY[grp][lt] = v;
     __builtin_amdgcn_wave_barrier();     // group-private: the wave's own writes are seen by its reads
-    double e = grp_sum_f64<LPN>(v * v);
-    const double s = grp_sum_f64<LPN>(v);
+    double e = row_sum_f64(v * v);
+    const double s = row_sum_f64(v);
     uint8_t st = ST_RUN;
     if (e < eps2)
       st = ST_ACC;
@@ -759,13 +738,13 @@ __global__ __launch_bounds__(256) void k_gram_small(const JobDev* __restrict__ j
         bi = take ? K + lt : bi;
       }
       const unsigned long long mb = (unsigned long long)__double_as_longlong(fabs(bc));
-      const unsigned long long m = grp_max_u64<LPN>(mb);
-      bi = grp_min_i32<LPN>(mb == m ? bi : 0x7fffffff);
+      const unsigned long long m = row_max_u64(mb);
+      bi = row_min_i32(mb == m ? bi : 0x7fffffff);
       if (m == 0ull) {
         st = ST_ZERO;
         break;
       }
-      bc = grp_sum_f64<LPN>((lt == bi % K) ? (bi >= K ? c[NFAM - 1] : c[0]) : 0.0);
+      bc = row_sum_f64((lt == bi % K) ? (bi >= K ? c[NFAM - 1] : c[0]) : 0.0);
       if (lt == t % LPN) {
         rec_i = bi;
         rec_c = bc;
@@ -801,6 +780,222 @@ __global__ __launch_bounds__(256) void k_gram_small(const JobDev* __restrict__ j
       lv.t[node] = t;
       lv.st[node] = st;
     }
+  }
+}
+
+// N = 8: four nodes per wave, 16 lanes each.  Lane li of a node holds pixels
+// (li / 2, 4 (li % 2) ..) and, of each family, atoms q = li / 2, p = 4 (li %
+// 2) + r, r = 0..3, so that a reduction over a node is four row operations
+// for all four nodes at once.  The sums and the updates are those of
+// a lane per pixel.  A slot whose node has ended takes its next one
+// from the queues.
+// What bounds it: the instructions of a step (about 200 for four nodes; 130
+// for one node with a lane per pixel).  11 152 nodes, 170 692 steps: 44 us,
+// 74 us with a wave per node and a lane per pixel.
+template <int NFAM>
+__global__ __launch_bounds__(256) void k_gram8(const JobDev* __restrict__ jobs, LevelDev lv,
+                                               const int32_t* __restrict__ count_ptr, int32_t* __restrict__ queue,
+                                               const double* __restrict__ tab, const double* __restrict__ xg) {
+  constexpr int N = 8, K = 64, LPS = 16, SN = 4, lg = 3;
+  constexpr int YP = K + 2;               // doubles of a node's pixels (a node's on banks of its own)
+  __shared__ __attribute__((aligned(16))) double sT[NFAM][N][N];    // T_f[p][y]
+  __shared__ __attribute__((aligned(16))) double sTt[NFAM][N][N];   // and by [y][p]
+  __shared__ __attribute__((aligned(16))) double sX[2][N][N];       // [f][p][p']: row p of family f against the other
+  __shared__ __attribute__((aligned(16))) double sY[4][SN * YP];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  for (int i = tid; i < NFAM * K; i += 256) {
+    const double v = tab[i];
+    const int f = i / K, pp = i % K / N, y = i % N;
+    sT[f][pp][y] = v;
+    sTt[f][y][pp] = v;
+  }
+  if constexpr (NFAM == 2)
+    if (tid < K) {
+      const double v = xg[tid];
+      sX[0][tid / N][tid % N] = v;
+      sX[1][tid % N][tid / N] = v;
+    }
+  __syncthreads();
+  const int count = *count_ptr;
+  const int slot = lane / LPS, li = lane % LPS, q = li >> 1, p0 = 4 * (li & 1);
+  double* ys = sY[wv] + slot * YP;
+  const int q0 = (int)gridDim.x * 4 * SN, qk = (int)blockIdx.x % kQueues;
+  int node = ((int)blockIdx.x * 4 + wv) * SN + slot;
+  bool dry = node >= count, run = false, load = !dry;
+  int t = 0, kmax = 0, rec_i = 0;
+  double rec_c = 0.0, e = 0.0, eps2 = 0.0;
+  double c[NFAM][4];
+#pragma unroll
+  for (int f = 0; f < NFAM; ++f)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) c[f][r] = 0.0;
+  auto slot_sum = [](double v) -> double {   // pixels in the order of their bits
+    v += row_perm_f64<0xB1>(v);
+    v += row_perm_f64<0x4E>(v);
+    v += row_perm_f64<0x141>(v);
+    v += row_perm_f64<0x128>(v);
+    return v;
+  };
+  for (;;) {
+    if (__ballot(load) != 0ull) {
+      if (load) {
+        const int jidx = lv.job[node];
+        const int bx = lv.x0[node], by = lv.y0[node];
+        const JobDev jl = jobs[jidx];
+        eps2 = jobs[jidx].eps2[lg];
+        kmax = jobs[jidx].k[lg];
+        double v[4];
+        job_pixels<4>(jl, by + q, bx + p0, v);
+#pragma unroll
+        for (int j = 0; j < 4; j += 2) *(double2*)&ys[q * N + p0 + j] = make_double2(v[j], v[j + 1]);
+        // of each pair of squares one is rounded by itself: the odd pixels' in
+        // the left half of a row, the even pixels' in the right one
+        const bool rh = p0 != 0;
+        const double a0 = rh ? v[1] : v[0], a1 = rh ? v[0] : v[1], a2 = rh ? v[3] : v[2], a3 = rh ? v[2] : v[3];
+        e = slot_sum(fma(a0, a0, a1 * a1) + fma(a2, a2, a3 * a3));
+        const double s = slot_sum((v[0] + v[1]) + (v[2] + v[3]));
+        t = 0;
+        uint8_t st = ST_RUN;
+        if (e < eps2)
+          st = ST_ACC;
+        else if (kmax <= 0)
+          st = ST_SPARSE;
+        run = st == ST_RUN;
+        if (!run && li == 0) {
+          lv.e[node] = e;
+          lv.t[node] = 0;
+          lv.st[node] = st;
+        }
+        wave_sync();   // the node's pixels, read by its other lanes
+        if (run) {
+          // sum_y T_f[p][y] sum_x T_f[q][x] Y[y][x]
+          double tq[NFAM][N];
+#pragma unroll
+          for (int f = 0; f < NFAM; ++f)
+#pragma unroll
+            for (int x = 0; x < N; ++x) tq[f][x] = sT[f][q][x];
+#pragma unroll
+          for (int f = 0; f < NFAM; ++f)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) c[f][r] = 0.0;
+#pragma unroll 2
+          for (int y = 0; y < N; ++y) {
+            double px[N];
+#pragma unroll
+            for (int x = 0; x < N; ++x) px[x] = ys[y * N + x];
+#pragma unroll
+            for (int f = 0; f < NFAM; ++f) {
+              double u = 0.0;
+#pragma unroll
+              for (int x = 0; x < N; ++x) u = fma(tq[f][x], px[x], u);
+#pragma unroll
+              for (int r = 0; r < 4; ++r) c[f][r] = fma(sTt[f][y][p0 + r], u, c[f][r]);
+            }
+          }
+          if (li == 0)
+#pragma unroll
+            for (int f = 0; f < NFAM; ++f) c[f][0] = s / N;
+        }
+        wave_sync();   // read before another node's pixels come
+      }
+    }
+    if (__ballot(run) != 0ull) {
+      // the larger of a lane's two families (the first on a tie), then the
+      // largest by bits, the lowest atom among equals
+      double bc[4];
+      int bf[4];
+      unsigned long long mb = 0ull;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        bc[r] = c[0][r];
+        bf[r] = 0;
+        if constexpr (NFAM == 2) {
+          const bool take = fabs(c[1][r]) > fabs(c[0][r]);
+          bc[r] = take ? c[1][r] : c[0][r];
+          bf[r] = take ? K : 0;
+        }
+        const unsigned long long u = (unsigned long long)__double_as_longlong(fabs(bc[r]));
+        mb = u > mb ? u : mb;
+      }
+      const unsigned long long m = row_max_u64(mb);
+      int bi = 0x7fffffff;
+#pragma unroll
+      for (int r = 3; r >= 0; --r) {
+        const int a = bf[r] + q * N + p0 + r;
+        if ((unsigned long long)__double_as_longlong(fabs(bc[r])) == m && a < bi) bi = a;
+      }
+      bi = row_min_i32(bi);
+      const bool zero = m == 0ull;
+      const int fi = NFAM == 2 && bi >= K ? 1 : 0, pi = bi % N, qi = bi % K / N;
+      const bool mine = qi == q && (pi & 4) == p0;
+      double v = 0.0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v = mine && (pi & 3) == r ? (fi ? c[NFAM - 1][r] : c[0][r]) : v;
+      const double b = slot_sum(v);
+      // same family: only the atom's own changes (to zero); the other: X products
+      double g[4] = {0.0, 0.0, 0.0, 0.0};
+      if constexpr (NFAM == 2) {
+        const double xq = sX[fi][qi & 7][q];
+        const double2 x0 = *(const double2*)&sX[fi][pi][p0], x1 = *(const double2*)&sX[fi][pi][p0 + 2];
+        g[0] = x0.x * xq;
+        g[1] = x0.y * xq;
+        g[2] = x1.x * xq;
+        g[3] = x1.y * xq;
+      }
+      if (run && !zero) {
+        if (li == (t & 15)) {
+          rec_i = bi;
+          rec_c = b;
+        }
+#pragma unroll
+        for (int f = 0; f < NFAM; ++f) {
+          const double nb = fi == f ? 0.0 : -b;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            double w = c[f][r];
+            if constexpr (NFAM == 2) w = fma(nb, g[r], w);
+            c[f][r] = fi == f && mine && (pi & 3) == r ? 0.0 : w;
+          }
+        }
+        e = fma(-b, b, e);
+        ++t;
+      }
+      if (run) {
+        uint8_t st = ST_RUN;
+        if (zero)
+          st = ST_ZERO;
+        else if (e < eps2)
+          st = ST_ACC;
+        else if (t >= kmax)
+          st = ST_SPARSE;
+        // records of the last up to 16 steps
+        const int base = zero ? t & ~15 : (t - 1) & ~15;
+        if ((st != ST_RUN || t - base == 16) && li < t - base) {
+          const size_t rs = (size_t)node * lv.kmax + base + li;
+          lv.rec_idx[rs] = rec_i;
+          lv.rec_coef[rs] = rec_c;
+        }
+        if (st != ST_RUN && li == 0) {
+          lv.e[node] = e;
+          lv.t[node] = t;
+          lv.st[node] = st;
+        }
+        run = st == ST_RUN;
+      }
+    }
+    // ---- the next node of the slots that ended ----
+    load = false;
+    if (__ballot(!run && !dry) != 0ull) {
+      int ahead = 0;
+      if (!run && !dry && li == 0) ahead = atomicAdd(queue + qk * kQueuePad, 1);
+      const int idx = q0 + __shfl(ahead, lane & ~(LPS - 1), 64) * kQueues + qk;
+      if (!run && !dry) {
+        node = idx;
+        dry = idx >= count;
+        load = !dry;
+      }
+    }
+    if (__ballot(run || load) == 0ull) break;
   }
 }
 
@@ -1234,13 +1429,16 @@ hipError_t launch_gram_pursuit(int n, const JobDev* jobs, LevelDev lv, const int
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
-#define AQMP_GSMALL(NN, GRID)                                                                                  \
-  case NN:                                                                                                     \
-    if (nfam == 2)                                                                                             \
-      hipLaunchKernelGGL((k_gram_small<NN, 2>), dim3(GRID), dim3(256), 0, s, jobs, lv, count, lg, tab, xg);   \
-    else                                                                                                       \
-      hipLaunchKernelGGL((k_gram_small<NN, 1>), dim3(GRID), dim3(256), 0, s, jobs, lv, count, lg, tab, xg);   \
-    break;
+#define AQMP_GSMALL(KERN, WGS, ...)                                                       \
+  {                                                                                       \
+    int64_t wgs = (cap + 15) / 16;   /* sixteen nodes per workgroup */                    \
+    if (wgs > (int64_t)n_cus * (WGS)) wgs = (int64_t)n_cus * (WGS);                       \
+    if (wgs < 1) wgs = 1;                                                                 \
+    if (nfam == 2)                                                                        \
+      hipLaunchKernelGGL((KERN<2>), dim3((unsigned)wgs), dim3(256), 0, s, __VA_ARGS__);   \
+    else                                                                                  \
+      hipLaunchKernelGGL((KERN<1>), dim3((unsigned)wgs), dim3(256), 0, s, __VA_ARGS__);   \
+  }
 #define AQMP_GPUR_F(NN, FF)                                                                                 \
   {                                                                                                         \
     int per_cu = 0;                                                                                         \
@@ -1261,8 +1459,13 @@ hipError_t launch_gram_pursuit(int n, const JobDev* jobs, LevelDev lv, const int
       AQMP_GPUR_F(NN, 1) \
     break;
   switch (n) {
-    AQMP_GSMALL(4, 1024)
-    AQMP_GSMALL(8, 2048)
+    // four waves per SIMD of 16-lane slots, at most a slot per node
+    case 4:
+      AQMP_GSMALL(k_gram4, 4, jobs, lv, count, tab, xg)
+      break;
+    case 8:
+      AQMP_GSMALL(k_gram8, 4, jobs, lv, count, queue, tab, xg)
+      break;
     AQMP_GPUR(16)
     AQMP_GPUR(32)
     AQMP_GPUR(64)

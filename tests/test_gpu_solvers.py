@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from oracle import aqmp_oracle as O
+from tests.test_gpu_gram import _run as _run_gram
 from tests.test_gpu_omp import A, _run, _say, dic   # noqa: F401  (fixtures and the parity helper)
 from workloads import piecewise_image
 
@@ -73,3 +74,25 @@ def test_gram_ties_and_undefined_pixels(A, n, fam):
             assert na == int(other["n_atoms"]) and leaf["resid_sq"] == other["resid_sq"]
             a, b = int(leaf["atom_off"]), int(other["atom_off"])
             assert (e.atom_idx[a:a + na] == e.atom_idx[b:b + na]).all() and (e.coef[a:a + na] == e.coef[b:b + na]).all()
+
+
+@pytest.mark.parametrize("fam", [1, 2, 3])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_gram_nodes_of_8(A, fam, dtype):
+    """N = 8 of the Gram form, four nodes to a wave: more nodes than slots
+    (16 384 on 256 CUs), a last wave with one node, step limits at the edges
+    of the records' 16, blocks that end before the first step."""
+    d = A.Dictionary(8, 8, families=fam)
+    big = piecewise_image(1032, 1040, seed=51)          # 129 x 130 = 16 770 nodes
+    small = np.ascontiguousarray(piecewise_image(64, 136, seed=52)[:8])   # 17 nodes, two of them zero
+    small[:, 8:24] = 0
+    imgs = [big, small, small, small, small]
+    params = [dict(tol=0.02, max_atoms=k, n_min=8, n_max=8) for k in (9, 16, 17, 33, 1)]
+    tops = O.top_blocks(1032, 1040, 8)
+    rng = np.random.default_rng(53)
+    sample = [tops[i] for i in sorted(rng.choice(len(tops), size=24, replace=False))] + [tops[-1]]
+    rep = _run_gram(A, d, imgs, params, [(i, i) for i in range(5)], 1, dtype=dtype, families=fam,
+                    blocks_per_job=[sample, None, None, None, None])
+    d.free()
+    _say("gram 8", fam, dtype, rep.summary())
+    assert rep.ok(), rep.summary()
