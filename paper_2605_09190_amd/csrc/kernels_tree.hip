@@ -9,6 +9,27 @@ namespace aqmp {
 
 namespace {
 
+// Completion count of a look-back scan by `blocks` blocks; the last one to
+// finish clears the tile words and the tickets for the next launch.
+__device__ void scan_done(ScanState ss, int ntiles, int blocks) {
+  __shared__ int s_last;
+  const int tid = threadIdx.x;
+  __syncthreads();
+  if (tid == 0) {
+    __threadfence();
+    const int done = atomicAdd(&ss.ticket[1], 1);
+    s_last = (done == blocks - 1);
+  }
+  __syncthreads();
+  if (s_last) {
+    for (int i = tid; i < ntiles && i < ss.ntiles_max; i += blockDim.x) ss.tiles[i] = 0ull;
+    if (tid == 0) {
+      ss.ticket[0] = 0;
+      ss.ticket[1] = 0;
+    }
+  }
+}
+
 // One launch = one stable scan over op.count() items with 0/1 keep flags.
 // Blocks take tiles in ticket order, so a block only ever waits on tiles
 // owned by blocks that started before it.  Every wait is bounded; when a
@@ -17,7 +38,7 @@ namespace {
 // to finish clears the tile words and the tickets for the next launch.
 template <class Op>
 __device__ void stable_scan(Op& op, ScanState ss, int32_t* err) {
-  __shared__ int s_tile, s_prefix, s_last;
+  __shared__ int s_tile, s_prefix;
   __shared__ int s_wsum[4];
   const int tid = threadIdx.x;
   if (tid == 0) s_tile = atomicAdd(&ss.ticket[0], 1);
@@ -56,29 +77,13 @@ __device__ void stable_scan(Op& op, ScanState ss, int32_t* err) {
     int pos = s_prefix + excl;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if (base + j < n) op.mark(base + j, n, pos, f[j]);
       if (f[j]) op.emit(base + j, pos++);
     }
     if (tile == ntiles - 1 && tid == 0) op.total(s_prefix + agg);
   } else if (tile == 0 && tid == 0) {
     op.total(0);   // n == 0: nothing kept
   }
-  // Completion count; the last block resets the shared scan state.
-  __syncthreads();
-  if (tid == 0) {
-    __threadfence();
-    const int done = atomicAdd(&ss.ticket[1], 1);
-    s_last = (done == (int)gridDim.x - 1);
-  }
-  __syncthreads();
-  if (s_last) {
-    const int used = ntiles > (int)gridDim.x ? ntiles : (int)gridDim.x;
-    for (int i = tid; i < used && i < ss.ntiles_max; i += blockDim.x) ss.tiles[i] = 0ull;
-    if (tid == 0) {
-      ss.ticket[0] = 0;
-      ss.ticket[1] = 0;
-    }
-  }
+  scan_done(ss, ntiles, (int)gridDim.x);
 }
 
 struct CompactOp {
@@ -92,12 +97,15 @@ struct CompactOp {
   __device__ int node(int i) const { return in_list ? in_list[i] : i; }
   __device__ int keep(int i) const { return st[node(i)] == ST_RUN ? 1 : 0; }
   __device__ void emit(int i, int pos) const { out_list[pos] = node(i); }
-  __device__ void mark(int, int, int, int) const {}
   __device__ void total(int t) const {
     *out_count = t;
     if (clear) *clear = 0;
   }
 };
+
+__global__ __launch_bounds__(256) void k_compact(CompactOp op, ScanState ss, int32_t* err) {
+  stable_scan(op, ss, err);
+}
 
 struct SplitOp {
   const JobDev* jobs;
@@ -110,57 +118,104 @@ struct SplitOp {
   int32_t* child_count;
   int2* child_ranges;       // per job, or null
   int32_t lg;
-  __device__ int count() const { return *parent_count; }
-  // The nodes of a job are neighbours: top-level nodes are listed job by job
-  // and a stable scan emits the children in that order, so its first and
-  // last node, with the splits before them, give its children's range.
-  __device__ void mark(int i, int n, int pos, int kept) const {
-    if (!child_ranges) return;
-    const int jb = parent.job[i];
-    if (i == 0 || parent.job[i - 1] != jb) child_ranges[jb].x = child_ntop + 4 * pos;
-    if (i == n - 1 || parent.job[i + 1] != jb) child_ranges[jb].y = child_ntop + 4 * (pos + kept);
-  }
   // Algorithm 2: refine when N > N_min and the node failed the test of its
   // split rule; the node's own atoms are then discarded by the exporter.
-  __device__ int keep(int i) const {
-    const int jb = parent.job[i];
-    if ((unsigned)jb >= (unsigned)n_jobs) {
-      atomicExch(bad, 1);
-      return 0;
-    }
+  __device__ bool split(int jb, double e, int t) const {
+    if ((unsigned)jb >= (unsigned)n_jobs) return false;
     const JobDev& j = jobs[jb];
-    const int n = 1 << lg;
-    int s = 0;
-    if (n > j.n_min) {
-      if (j.split_rule == AQMP_SPLIT_R1)
-        s = parent.e[i] >= j.eps2[lg];
-      else
-        s = parent.t[i] >= j.k[lg];
-    }
-    if (s) parent.st[i] = (uint8_t)(parent.st[i] | ST_SPLIT);
-    return s;
+    const int n_min = j.n_min, rule = j.split_rule, k = j.k[lg];
+    const double eps2 = j.eps2[lg];
+    return (1 << lg) > n_min && (rule == AQMP_SPLIT_R1 ? e >= eps2 : t >= k);
   }
-  // Children are the four quadrants of the original block, TL, TR, BL, BR.
-  __device__ void emit(int i, int pos) const {
-    const int h = 1 << (lg - 1);
-    const int jb = parent.job[i], x = parent.x0[i], y = parent.y0[i];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int c = child_ntop + 4 * pos + q;
-      child.job[c] = jb;
-      child.x0[c] = x + (q & 1) * h;
-      child.y0[c] = y + (q >> 1) * h;
-    }
-  }
-  __device__ void total(int t) const { *child_count = child_ntop + 4 * t; }
 };
 
-__global__ __launch_bounds__(256) void k_compact(CompactOp op, ScanState ss, int32_t* err) {
-  stable_scan(op, ss, err);
-}
-
-__global__ __launch_bounds__(256) void k_split_emit(SplitOp op, ScanState ss, int32_t* err) {
-  stable_scan(op, ss, err);
+// The split test of a level's nodes and its children, in the nodes' order:
+// child 4 p + q is quadrant q (TL, TR, BL, BR) of the p-th split node.  One
+// node per thread, 1024 per workgroup (tile).
+// What bounds it: the chain of loads (each from the far cache, since other
+// XCDs wrote the nodes) and the look-back from tile to tile.  So a node's
+// values are all loaded before any is used, a tile that is alone takes no
+// ticket, and the workgroups past the level's last tile (the grid covers its
+// capacity) leave before the tickets.  Mean of a launch, with four nodes per
+// thread, one value at a time, and tickets for every workgroup before: one
+// tile 7.1 -> 4.4 us; 3072, 5136 and 12 892 nodes 12.9 -> 7.6 us; 6144 to
+// 64 352 nodes 19.8 -> 8.7 us.  (Splits of earlier tiles counted by reading
+// their nodes again, no look-back: 7.3 us for the middle ones, 9.0 for the
+// last.)
+__global__ __launch_bounds__(kScanTile) void k_split_emit(SplitOp op, ScanState ss, int32_t* err) {
+  constexpr int NW = kScanTile / 64;
+  __shared__ int s_tile, s_prefix;
+  __shared__ int s_own[NW];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int n = *op.parent_count;
+  const int ntiles = (n + kScanTile - 1) / kScanTile;
+  int tile = (int)blockIdx.x;
+  if (tile >= ntiles) {   // the grid covers the level's capacity
+    if (tile == 0 && tid == 0) *op.child_count = op.child_ntop;
+    return;
+  }
+  if (ntiles > 1) {   // the ntiles blocks that are left share the tickets
+    if (tid == 0) s_tile = atomicAdd(&ss.ticket[0], 1);
+    __syncthreads();
+    tile = s_tile;
+  }
+  const int i = tile * kScanTile + tid;
+  const bool in = i < n;
+  int jb = -1, jprev = -1, jnext = -1, x = 0, y = 0, t = 0;
+  double e = 0.0;
+  uint8_t st = 0;
+  if (in) {
+    jb = op.parent.job[i];
+    e = op.parent.e[i];
+    t = op.parent.t[i];
+    x = op.parent.x0[i];
+    y = op.parent.y0[i];
+    st = op.parent.st[i];
+    if (op.child_ranges) {
+      if (i > 0) jprev = op.parent.job[i - 1];
+      if (i < n - 1) jnext = op.parent.job[i + 1];
+    }
+  }
+  const bool keep = in && op.split(jb, e, t);
+  if (in && (unsigned)jb >= (unsigned)op.n_jobs) atomicExch(op.bad, 1);
+  if (keep) op.parent.st[i] = (uint8_t)(st | ST_SPLIT);
+  const unsigned long long mask = __ballot(keep);
+  if (lane == 0) s_own[wv] = __popcll(mask);
+  __syncthreads();
+  int pre = 0, agg = 0, pos = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    pos += w < wv ? s_own[w] : 0;
+    agg += s_own[w];
+  }
+  if (ntiles > 1) {
+    if (wv == 0) {
+      const int p = lookback_wave(ss.tiles, tile, agg, err);
+      if (lane == 0) s_prefix = p;
+    }
+    __syncthreads();
+    pre = s_prefix;
+  }
+  pos += pre + __popcll(mask & ((1ull << lane) - 1ull));
+  if (in && op.child_ranges && (unsigned)jb < (unsigned)op.n_jobs) {
+    // The nodes of a job are neighbours: top-level nodes are listed job by
+    // job and children come in their parents' order, so its first and last
+    // node, with the splits before them, give its children's range.
+    if (i == 0 || jprev != jb) op.child_ranges[jb].x = op.child_ntop + 4 * pos;
+    if (i == n - 1 || jnext != jb) op.child_ranges[jb].y = op.child_ntop + 4 * (pos + (keep ? 1 : 0));
+  }
+  if (keep) {
+    const int h = 1 << (op.lg - 1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int c = op.child_ntop + 4 * pos + q;
+      op.child.job[c] = jb;
+      op.child.x0[c] = x + (q & 1) * h;
+      op.child.y0[c] = y + (q >> 1) * h;
+    }
+  }
+  if (tile == ntiles - 1 && tid == 0) *op.child_count = op.child_ntop + 4 * (pre + agg);
+  if (ntiles > 1) scan_done(ss, ntiles, ntiles);
 }
 
 // Word 0 = v, words 1 .. n-1 = 0: one thread per word.
@@ -213,7 +268,7 @@ hipError_t launch_split_emit(const JobDev* jobs, int32_t n_jobs, LevelDev parent
                              LevelDev child, int32_t child_ntop, int32_t* child_count, int2* child_ranges,
                              int32_t lg, int64_t cap, ScanState ss, int32_t* err, hipStream_t s) {
   SplitOp op{jobs, n_jobs, err, parent, parent_count, child, child_ntop, child_count, child_ranges, lg};
-  hipLaunchKernelGGL(k_split_emit, dim3(scan_blocks(cap)), dim3(256), 0, s, op, ss, err);
+  hipLaunchKernelGGL(k_split_emit, dim3(scan_blocks(cap)), dim3(kScanTile), 0, s, op, ss, err);
   return hipGetLastError();
 }
 
