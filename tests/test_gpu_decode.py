@@ -106,3 +106,19 @@ def test_decode_after_a_shallower_reencode(A, dic):
         for j in range(2):
             _check(A, code, dic, j, (128, 192), torch.float64, 4)
     code.free()
+
+
+@pytest.mark.parametrize("n", [16, 32, 64])
+@pytest.mark.parametrize("k", [1, 3, 4, 5, 64, 65, 130])
+def test_decode_of_list_lengths(A, dic, n, k):
+    """Lists around the four atoms in flight and the 64 records of a wave.  The
+    plane is noise: every list has k atoms, and partial sums stay below 2, so
+    that 130 terms of three roundings differ by less than 1e-13."""
+    import torch
+    img = np.random.default_rng(46).random((n + 3, 2 * n - 1))
+    p = dict(tol=1e-6, max_atoms=k, n_min=n, n_max=n)
+    code = A.Code(dic, [_dev(img, True)], [p], [(0, 0)], precision=1, schedule=1)
+    assert (code.export().leaves["n_atoms"] == k).all()
+    for dtype, pad in ((torch.float32, 4), (torch.float64, 1)):
+        _check(A, code, dic, 0, img.shape, dtype, pad)
+    code.free()
