@@ -120,14 +120,16 @@ enum { AQMP_OPT_TIMING = 1, AQMP_OPT_STEPWISE = 2 };   /* aqmp_options.flags */
 enum { AQMP_SOLVER_DENSE = 0, AQMP_SOLVER_GRAM = 1, AQMP_SOLVER_OMP = 2 };   /* aqmp_options.solver */
 
 typedef struct {
-  int32_t precision;   /* AQMP_PREC_FP32: FP32 MFMA correlation;
-                          AQMP_PREC_BF16: 16-bit MFMA, FP32 accumulate
-                          (BF16 operands step by step; in the whole-level
-                          pursuits of N >= 8 every operand as the sum of two
-                          FP16 values, which is nearer to FP32).
-                          Both re-score the AQMP_CANDIDATES best atoms in
-                          FP64 and take the coefficient and the stop/split
-                          test in FP64. */
+  int32_t precision;   /* The correlation's operands, FP32 accumulation:
+                          step by step AQMP_PREC_FP32: FP32 MFMA,
+                          AQMP_PREC_BF16: BF16 MFMA; in the whole-level
+                          pursuits of N >= 8 every operand of either form is
+                          the sum of two FP16 values (error below that of the
+                          FP32 products).  The candidates (step by step the
+                          AQMP_CANDIDATES best atoms, else every atom within
+                          the correlation's error bound of the best) are
+                          re-scored in FP64, and the coefficient and the
+                          stop/split test are FP64. */
   int32_t schedule;    /* AQMP_SCHED_PLAIN: jobs one after another,
                           stream-ordered launches;
                           AQMP_SCHED_BATCHED: every job in one pass,
@@ -164,9 +166,8 @@ typedef struct {
                           correlations of y as separable products
                           T_f Y T_f^T, then per step c <- c - c_i G[:, i]
                           and ||r||^2 <- ||r||^2 - c_i^2, all in FP64
-                          (precision and corr_variant do not apply; levels
-                          with N <= 8 run the dense FP64 pursuit as in the
-                          dense solver).  A labelled variant: the paper
+                          (precision and corr_variant do not apply).  A
+                          labelled variant: the paper
                           states the dense correlation.
                           AQMP_SOLVER_OMP: Orthogonal Matching Pursuit, the
                           solver the authors' implementation ran (Section

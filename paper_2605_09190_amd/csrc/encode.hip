@@ -4,22 +4,26 @@
 //
 // Launch sequence of one pass (a set of jobs coded together):
 //   init counts; for each block size N from the largest to the smallest:
+//     one launch runs every node of the level from the gather to its last
+//     step (see whole_level; the OMP form of N >= 16 has one before it for
+//     the first correlations);
+//     split test, stable scan, emit the children into the next level.
+// The step-by-step form of a level (AQMP_OPT_STEPWISE, or a correlation
+// family chosen for it) is instead:
 //     gather the level's nodes -> residuals, norms, first stop test;
 //     compact the running nodes into the active list;
 //     k_N times: correlation + top-R keys (MFMA), select/update (FP64)
-//                that appends the still-running nodes to the next list;
-//     split test, stable scan, emit the children into the next level.
+//                that appends the still-running nodes to the next list.
 // All data-dependent counts live in device memory: kernels read them and
 // idle when there is no work, so the sequence is fixed and can be captured
-// once as a graph.  The batched schedule runs every job in one pass (one
-// launch per MP step for every image, channel and parameter set); the plain
+// once as a graph.  The batched schedule runs every job in one pass (the
+// launches of a level serve every image, channel and parameter set); the plain
 // schedule runs one pass per job, stream-ordered without a graph.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
 #include <vector>
-
 
 #include "host_core.h"
 #include "host_util.h"
@@ -536,7 +540,7 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
     const aqmp_code::LevelEv* le = timing ? &c->lev[c->lev_pos++] : nullptr;
     if (le) AQMP_HIP(hipEventRecord(le->start, s));
     if (whole_level(c, n)) {
-      // Small blocks: each node's whole pursuit in one launch.
+      // Each node's whole pursuit in one launch.
       if (c->opt.solver != AQMP_SOLVER_DENSE) {
         const aqmp_code::StepEv* se = timing && n > kFusedMaxN ? &c->sev[c->sev_pos++] : nullptr;
         if (se) AQMP_HIP(hipEventRecord(se->a, s));

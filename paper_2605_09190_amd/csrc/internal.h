@@ -124,7 +124,7 @@ struct Counters {
   int32_t count[kLevels];   // nodes present at each level
   int32_t act[3];           // active-list lengths (rotating: in, out, cleared)
   int32_t scan_error;       // set if a bounded scan wait ran out
-  int32_t next[kLevels];    // work counter of the dynamically scheduled kernels per level
+  int32_t pad;
 };
 
 // Work counters of the pursuits whose nodes are taken by many small workers:

@@ -1,5 +1,6 @@
 // kernels_gram.hip - Matching Pursuit through the Gram matrix (exact
-// reformulation of Section 2.2, FP64 throughout), for N = 16, 32, 64.
+// reformulation of Section 2.2, FP64 throughout), and Orthogonal Matching
+// Pursuit in the same space.
 //
 // Every atom of D_N is an outer product of two rows of a 1D orthonormal table
 // (Section 2.1), so

@@ -1,7 +1,7 @@
 // kernels_sub.hip - whole-level Matching Pursuit of the dense solver for small
-// blocks on the matrix cores: N = 8 and 16.  A wave runs several nodes side by side (slots of LPS lanes),
-// with no workgroup barrier; the residual stays in registers from the gather
-// to the last step.
+// blocks on the matrix cores: N = 8 and 16.  A wave runs several nodes side by
+// side (slots of LPS lanes), with no workgroup barrier; the residual stays in
+// registers from the gather to the last step.
 //
 // The correlation is the factored one of kernels_sep.hip: C_f = T_f R T_f^T
 // for every family f, first D1[y][q] = sum_x R[y][x] T[q][x], then C[p][q] =

@@ -227,10 +227,7 @@ __global__ __launch_bounds__(256) void k_head_zero_u32(uint32_t* p, int64_t n, u
 static_assert(kLevels * kQueues <= 64, "one thread per counter");
 __global__ void k_init_counts(Counters* c, Queues* q, const int32_t* ntop) {
   const int i = threadIdx.x;
-  if (i < kLevels) {
-    c->count[i] = ntop[i];
-    c->next[i] = 0;
-  }
+  if (i < kLevels) c->count[i] = ntop[i];
   if (i < 3) c->act[i] = 0;
   if (i == 0) c->scan_error = 0;
   if (i < kLevels * kQueues) q->at[i / kQueues][(i % kQueues) * kQueuePad] = 0;
