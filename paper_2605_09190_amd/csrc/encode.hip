@@ -861,9 +861,18 @@ int collect(const aqmp_code* cc, bool leaves_only, F&& done) {
   }
   c->view = aqmp_code::VIEW_NONE;
   hipStream_t s = c->stream;
+  // Few nodes are put in order by one workgroup (see k_export_order), one launch
+  // instead of six: a 64 x 64 tile's pass 155 -> 146 us, a 512 x 512 plane's
+  // (1 900 leaves) 1 068 -> 993.  2048 is where its sort fills one workgroup and
+  // its time (21 us) comes near that of the other launches (26 us).
+  int64_t visited = 0;
+  for (int l = 0; l < kLevels; ++l) visited += (int64_t)c->totals.nodes[l];
+  const bool one_group = n <= kOrderMax && visited <= kOrderVisited && c->ex_nseg <= kOrderSegs;
   size_t sort_bytes = 0, scan_bytes = 0;
-  AQMP_HIP(export_sort(nullptr, sort_bytes, nullptr, nullptr, nullptr, nullptr, n, c->ex_end_bit, s));
-  AQMP_HIP(export_scan(nullptr, scan_bytes, nullptr, nullptr, n, s));
+  if (!one_group) {
+    AQMP_HIP(export_sort(nullptr, sort_bytes, nullptr, nullptr, nullptr, nullptr, n, c->ex_end_bit, s));
+    AQMP_HIP(export_scan(nullptr, scan_bytes, nullptr, nullptr, n, s));
+  }
   // Small results are written to the host's memory by the gather itself: 36
   // against 43 us for 64 leaves and 768 atoms.  Larger ones are copied in
   // pieces, 430 against 630 us for 37 749 leaves and 616 284 atoms (8.9 MB).
@@ -890,12 +899,16 @@ int collect(const aqmp_code* cc, bool leaves_only, F&& done) {
   auto* tcount = (int64_t*)(b + o_t);
   auto* off = (int64_t*)(b + o_off);
   char* out = direct ? (char*)c->pinned.p : b + o_out;
-  AQMP_HIP(hipMemsetAsync(&c->d_totals->next, 0, sizeof(c->d_totals->next), s));
-  AQMP_HIP(launch_export_keys(c->d_ex_segs, c->ex_nseg, c->ex_max_cap, c->d_ex_jobs, leaves_only, keys, vals,
-                              &c->d_totals->next, s));
-  AQMP_HIP(export_sort(b + o_tmp, sort_bytes, keys, keys2, vals, vals2, n, c->ex_end_bit, s));
-  AQMP_HIP(launch_export_counts(c->d_ex_segs, c->ex_nseg, vals2, n, tcount, s));
-  AQMP_HIP(export_scan(b + o_tmp, scan_bytes, tcount, off, n, s));
+  if (one_group) {
+    AQMP_HIP(launch_export_order(c->d_ex_segs, c->ex_nseg, c->d_ex_jobs, leaves_only, visited, n, vals2, off, s));
+  } else {
+    AQMP_HIP(hipMemsetAsync(&c->d_totals->next, 0, sizeof(c->d_totals->next), s));
+    AQMP_HIP(launch_export_keys(c->d_ex_segs, c->ex_nseg, c->ex_max_cap, c->d_ex_jobs, leaves_only, keys, vals,
+                                &c->d_totals->next, s));
+    AQMP_HIP(export_sort(b + o_tmp, sort_bytes, keys, keys2, vals, vals2, n, c->ex_end_bit, s));
+    AQMP_HIP(launch_export_counts(c->d_ex_segs, c->ex_nseg, vals2, n, tcount, s));
+    AQMP_HIP(export_scan(b + o_tmp, scan_bytes, tcount, off, n, s));
+  }
   AQMP_HIP(launch_export_write(c->d_ex_segs, c->ex_nseg, vals2, off, n, (aqmp_leaf*)out, (int32_t*)(out + at.idx_at),
                                (double*)(out + at.coef_at), s));
   if (direct) {

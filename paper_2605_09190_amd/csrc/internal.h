@@ -296,6 +296,12 @@ hipError_t export_sort(void* tmp, size_t& tmp_bytes, unsigned long long* keys, u
 hipError_t export_scan(void* tmp, size_t& tmp_bytes, const int64_t* in, int64_t* out, int64_t n, hipStream_t s);
 hipError_t launch_export_counts(const ExportSeg* segs, int nseg, const uint32_t* vals, int64_t n, int64_t* t_out,
                                 hipStream_t s);
+// The keys, the sort, the counts and the scan in one launch, for n <= kOrderMax
+// of at most kOrderVisited nodes in at most kOrderSegs segments.
+constexpr int kOrderBits = 11, kOrderMax = 1 << kOrderBits, kOrderVisited = 4096, kOrderSegs = 64;
+static_assert(kExportLowBits + 12 + kOrderBits <= 64, "a key of up to 4096 top-level blocks and a place");
+hipError_t launch_export_order(const ExportSeg* segs, int nseg, const ExportJob* jx, bool leaves_only, int64_t visited,
+                               int64_t n, uint32_t* vals, int64_t* off, hipStream_t s);
 hipError_t launch_export_write(const ExportSeg* segs, int nseg, const uint32_t* vals, const int64_t* off, int64_t n,
                                aqmp_leaf* out, int32_t* idx, double* coef, hipStream_t s);
 

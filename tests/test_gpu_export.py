@@ -174,3 +174,55 @@ def test_export_capacity_error_writes_nothing(A, dic):
     e = code.export()
     assert len(e.leaves) == nl and len(e.atom_idx) == na
     code.free()
+
+
+@pytest.mark.parametrize("blocks", [1, 63, 64, 65, 127, 128, 129, 1025, 2047, 2048, 2049])
+def test_order_of_few_nodes(blocks):
+    """Node counts around what one workgroup puts in order (up to 2048) and
+    around its powers of two: blocks of 8 in two jobs, one of them a single
+    row; leaves in job and raster order, atoms one after the other."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_09190_amd import aqmp
+    rng = np.random.default_rng(60)
+    cols = min(blocks, 33)
+    rows, rest = blocks // cols, blocks % cols
+    shapes = [(8 * rows, 8 * cols)] + ([(8, 8 * rest)] if rest else [])
+    imgs = [torch.from_numpy(rng.random(sh)).cuda() for sh in shapes]
+    print("blocks", blocks, shapes, flush=True)
+    d = aqmp.Dictionary(8, 8)
+    p = dict(tol=0.25, max_atoms=5, n_min=8, n_max=8)
+    code = aqmp.Code(d, imgs, [p], [(i, 0) for i in range(len(imgs))], precision=1, schedule=1)
+    e = code.export()
+    code.free()
+    d.free()
+    assert len(e.leaves) == blocks
+    want = [(j, 8 * x, 8 * y) for j, sh in enumerate(shapes) for y in range(sh[0] // 8) for x in range(sh[1] // 8)]
+    assert [(int(r["job"]), int(r["x0"]), int(r["y0"])) for r in e.leaves] == want
+    off = np.concatenate([[0], np.cumsum(e.leaves["n_atoms"])])
+    assert (e.leaves["atom_off"] == off[:-1]).all() and len(e.atom_idx) == off[-1]
+
+
+@pytest.mark.parametrize("jobs", [12, 13, 40])
+def test_order_of_many_segments(jobs):
+    """Job by job, every job has a segment per level: 60, 65 and 200 of them,
+    either side of the 64 that one workgroup takes, against one pass."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_09190_amd import aqmp
+    img = torch.from_numpy(np.random.default_rng(61).random((64, 64))).cuda()
+    img[:32] = 0.5
+    d = aqmp.Dictionary(4, 64)
+    p = dict(tol=0.05, max_atoms=6, n_min=4, n_max=64)
+    got = []
+    for sched in (0, 1):
+        code = aqmp.Code(d, [img], [dict(p, max_atoms=1 + i % 7) for i in range(jobs)], [(0, i) for i in range(jobs)],
+                         precision=1, schedule=sched)
+        print("jobs", jobs, "schedule", sched, flush=True)
+        got.append((code.export(), code.export_nodes()))
+        code.free()
+    d.free()
+    for a, b in zip(got[0], got[1]):
+        assert (a.leaves == b.leaves).all() and (a.atom_idx == b.atom_idx).all() and (a.coef == b.coef).all()
