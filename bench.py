@@ -95,7 +95,7 @@ def timed_encodes(code, imgs, steps):
     torch.cuda.synchronize()
     sec = (time.perf_counter() - t0) / steps
     st = code.stats()
-    st = dict(st, iters_level=[v * steps for v in st["iters_level"]])
+    st = dict(st, iters_level=[v * steps for v in st["iters_level"]], nodes=[v * steps for v in st["nodes"]])
     return tot, st, sec
 
 
@@ -245,27 +245,28 @@ def select_bytes(n, precision):
     return 8 * k + (2 * k if precision == 1 else 0) + tiles * 8 * 8 + 12
 
 
-def factored_flops(n, precision):
-    """Matrix-core operations of one node-iteration with the correlation
-    factored through the atoms' outer products (T R T^T per family, two
-    products of 2 N^3): FP32 one product each; BF16 form three 16-bit
-    products each for the DCT (value and remainder) and two for the Haar."""
-    return (8 if precision == 0 else 20) * n ** 3
+def factored_flops(n, nodes, steps):
+    """Operations that the whole-level pursuits of N >= 32 cannot do without:
+    per node its first correlations, factored through the atoms' outer
+    products (T R T^T per family, two products of 2 N^3, as three 16-bit
+    products each for the DCT and two for the Haar: 20 N^3), and per step 2
+    N^2 to carry the other family's correlations.  Correlations made anew in
+    between are not counted, nor is the FP64 re-score and update."""
+    return 20 * n ** 3 * nodes + 2 * n * n * steps
 
 
-def whole_level_roofline(n, stats, timing, precision):
-    """The largest level run as one launch: its matrix-core operations over
-    the level's time (gather, re-score, update and split test included)."""
+def whole_level_roofline(n, stats, timing):
+    """A level of N >= 32 run as one launch: its operations (factored_flops)
+    over the level's time (gather, re-score, update and split test included),
+    against the 16-bit matrix peak, in either form."""
     lg = n.bit_length() - 1
-    peak = PEAK_BF16_TFLOPS if precision == 1 else PEAK_FP32_TFLOPS
     ms = timing["level_ms"][lg]
-    flops = factored_flops(n, precision)
-    ach = flops * stats["iters_level"][lg] / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
-    return dict(bound="latency", achieved=round(ach, 2), peak=peak, unit="TFLOP/s", frac=round(ach / peak, 4),
-                traffic=None, kernel=f"k_pursuit_sep<{n}>", level_ms=round(ms, 4), flops_per_unit=flops,
-                units=int(stats["iters_level"][lg]),
-                unfactored_equivalent_tflops=round(4.0 * n ** 4 * stats["iters_level"][lg] / (ms * 1e-3) / 1e12, 1)
-                if ms > 0 else 0.0)
+    nodes, steps = int(stats["nodes"][lg]), int(stats["iters_level"][lg])
+    flops = factored_flops(n, nodes, steps)
+    ach = flops / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
+    return dict(bound="latency", achieved=round(ach, 2), peak=PEAK_BF16_TFLOPS, unit="TFLOP/s",
+                frac=round(ach / PEAK_BF16_TFLOPS, 4), traffic=None, kernel=f"k_pursuit_sep<{n}>", level_ms=round(ms, 4),
+                flops=flops, nodes=nodes, units=steps)
 
 
 def roofline(stats, timing, precision, kernel_name=None, workload=None):
@@ -273,11 +274,11 @@ def roofline(stats, timing, precision, kernel_name=None, workload=None):
     work per node-iteration is 2*K*M = 4 N^4 flops (every atom correlated with
     the residual); one launch processes the nodes active in that MP step.
     Each level also reports the select/update step against HBM bandwidth.
-    Where the largest level runs as one launch, the factored form of the
-    correlation is what is counted (whole_level_roofline)."""
+    Where the largest level runs as one launch, what its factored form needs
+    is counted (whole_level_roofline)."""
     lg = max(l for l in range(7) if stats["iters_level"][l] > 0)
     n = 1 << lg
-    whole = whole_level_roofline(n, stats, timing, precision) if n >= 32 and timing["corr_ms"][lg] == 0 else None
+    whole = whole_level_roofline(n, stats, timing) if n >= 32 and timing["corr_ms"][lg] == 0 else None
     flops = 4.0 * n ** 4 * stats["iters_level"][lg]
     ms = timing["corr_ms"][lg]
     steps = timing["steps"][lg]
@@ -301,14 +302,13 @@ def roofline(stats, timing, precision, kernel_name=None, workload=None):
                                           select_gbs=round(gbs, 1), select_hbm_frac=round(gbs / PEAK_HBM_GBS, 4),
                                           select_traffic=(measured_traffic(f"k_select<{nn}>", workload)
                                                           if precision == 1 else None))
-    # Levels run as one launch (N = 8, 16 in the BF16 form: MFMA pursuits;
-    # otherwise N <= 8: dense FP64 pursuit): the whole level's time against
-    # the flops of the method's per-step correlation, 4 N^4 per node-iteration.
+    # Levels of N <= 16 run as one launch: the whole level's time against the
+    # flops of the method's per-step correlation, 4 N^4 per node-iteration.
     for l in range(7):
         if stats["iters_level"][l] and timing["corr_ms"][l] == 0 and timing["level_ms"][l] > 0:
             nn = 1 << l
             if nn >= 32:
-                per_level[str(nn)] = dict(whole_level_roofline(nn, stats, timing, precision), kernel="whole-level pursuit")
+                per_level[str(nn)] = dict(whole_level_roofline(nn, stats, timing), kernel="whole-level pursuit")
                 continue
             bf16 = precision == 1 and nn in (8, 16)
             pk = peak if bf16 else PEAK_FP64_TFLOPS
@@ -641,10 +641,10 @@ def main():
     torch.cuda._sleep(1000)
     torch.cuda.synchronize()
     roof = roofline(st_t, tm_t, A.PREC_BF16, head_kernel, workload=args.workload)
-    roof["timing"] = ("HIP start/stop events recorded by each correlation and select dispatch itself "
-                      "(hipExtLaunchKernelGGL) in the same launch sequence issued on the stream (events cannot be "
-                      "timed inside a graph); in a kernel trace of this command these are the dispatches "
-                      "between the two spin_kernel markers")
+    roof["timing"] = ("HIP events around every level (and, step by step, recorded by each correlation and select "
+                      "dispatch itself) in the same launch sequence issued on the stream (events cannot be timed "
+                      "inside a graph); in a kernel trace of this command these are the dispatches between the two "
+                      "spin_kernel markers")
     code_t.free()
     log(f"bf16 batched (stream, timed): {sec_t * 1e3:.3f} ms/step, {roof['kernel']} {roof['achieved']} TFLOP/s")
     mark("headline_event_timed_encodes")

@@ -862,9 +862,9 @@ int collect(const aqmp_code* cc, bool leaves_only, F&& done) {
   c->view = aqmp_code::VIEW_NONE;
   hipStream_t s = c->stream;
   // Few nodes are put in order by one workgroup (see k_export_order), one launch
-  // instead of six: a 64 x 64 tile's pass 155 -> 146 us, a 512 x 512 plane's
-  // (1 900 leaves) 1 068 -> 993.  2048 is where its sort fills one workgroup and
-  // its time (21 us) comes near that of the other launches (26 us).
+  // instead of six.  An export of 64, 512, 1024 and 2048 leaves takes 24, 28, 33
+  // and 44 us, 36, 38, 42 and 58 with the launches; with 2048 its sort fills
+  // one workgroup.
   int64_t visited = 0;
   for (int l = 0; l < kLevels; ++l) visited += (int64_t)c->totals.nodes[l];
   const bool one_group = n <= kOrderMax && visited <= kOrderVisited && c->ex_nseg <= kOrderSegs;

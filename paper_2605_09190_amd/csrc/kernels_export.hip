@@ -128,9 +128,9 @@ __global__ __launch_bounds__(256) void k_export_counts(const ExportSeg* segs, in
 // blocks are small and a key leaves room for a place.
 // What bounds it: three dependent loads, then the LDS traffic of the sort (28
 // passes over 128 places, 66 over 2048; with the places in an array of their
-// own a third more, 26 us instead of 21).  84 nodes 8.6 us, 2 500 nodes with
-// 1 900 leaves 21 us; keys, radix sort, counts and scan as launches of their
-// own 15 and 26 us, and five more launches.
+// own a third more, 26 us instead of 21).  64 of 84 nodes 8.6 us, 847 of 1 108
+// 21 us; keys, radix sort, counts and scan as launches of their own 15 and 26
+// us, and five more launches.
 __global__ __launch_bounds__(1024) void k_export_order(const ExportSeg* segs, int nseg, const ExportJob* jx,
                                                        int leaves_only, int visited, int n, int size, uint32_t* vals,
                                                        int64_t* off) {
