@@ -108,6 +108,7 @@ struct aqmp_code {
   // gathered there and copied back when first asked for; kept until the next
   // encode.
   bool totals_ok = false;
+  bool totals_added = false;   // the totals on the device were added to since the encode
   aqmp::ExportTotals totals{};
   enum View { VIEW_NONE, VIEW_LEAVES, VIEW_NODES } view = VIEW_NONE;
   int64_t view_n = 0, view_atoms = 0;
@@ -518,7 +519,7 @@ int enqueue_pass(aqmp_code* c, size_t pi, hipStream_t s) {
   aqmp_code::Work& wk = c->work[pi % c->work.size()];
   Counters* cnt = c->dcnt + pi;
   const aqmp_dict* d = c->dict;
-  AQMP_LAUNCH(launch_init_counts(cnt, c->dqueue + pi, c->dntop + pi * kLevels, s));
+  AQMP_LAUNCH(launch_init_counts(cnt, c->dqueue + pi, c->d_totals, c->dntop + pi * kLevels, s));
   for (int l = pp.lg_hi; l >= pp.lg_lo; --l) {
     if (pp.cap[l] == 0) continue;
     const int n = 1 << l;
@@ -708,6 +709,7 @@ int run(aqmp_code* c, hipStream_t s) {
   }
   c->stream = s;
   AQMP_HIP(hipEventRecord(c->done, s));
+  c->totals_added = false;   // cleared with the counters
   return AQMP_OK;
 }
 
@@ -802,7 +804,9 @@ int totals(const aqmp_code* cc) {
     const int rc = ensure_pinned(c->pinned_tot, bytes);
     if (rc != AQMP_OK) return rc;
   }
-  AQMP_HIP(hipMemsetAsync(c->d_totals, 0, sizeof(ExportTotals), s));
+  // the encode has cleared the totals (a read that failed may have added to them)
+  if (c->totals_added) AQMP_HIP(hipMemsetAsync(c->d_totals, 0, sizeof(ExportTotals), s));
+  c->totals_added = true;
   AQMP_HIP(launch_export_stats(c->d_ex_segs, c->ex_nseg, c->ex_max_cap, c->d_totals, s));
   AQMP_HIP(hipMemcpyAsync(c->pinned_tot.p, c->dcnt, bytes, hipMemcpyDeviceToHost, s));
   AQMP_HIP(hipStreamSynchronize(s));

@@ -193,7 +193,9 @@ struct StepArgs {
 // ---------------------------------------------------------------------------
 // Launch wrappers (defined in the kernel translation units).
 // ---------------------------------------------------------------------------
-hipError_t launch_init_counts(Counters* c, Queues* q, const int32_t* ntop_dev, hipStream_t s);
+struct ExportTotals;
+// Sets a pass's counters and queues, and clears the code's totals.
+hipError_t launch_init_counts(Counters* c, Queues* q, ExportTotals* tot, const int32_t* ntop_dev, hipStream_t s);
 // p[0] = v and p[1 .. n-1] = 0, by a fill kernel.
 hipError_t launch_head_zero_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_gather(int n, const StepArgs& a, const int32_t* count, hipStream_t s);

@@ -225,18 +225,20 @@ __global__ __launch_bounds__(256) void k_head_zero_u32(uint32_t* p, int64_t n, u
 }
 
 static_assert(kLevels * kQueues <= 64, "one thread per counter");
-__global__ void k_init_counts(Counters* c, Queues* q, const int32_t* ntop) {
+static_assert(sizeof(ExportTotals) <= 64 * 8, "one thread per total");
+__global__ void k_init_counts(Counters* c, Queues* q, ExportTotals* tot, const int32_t* ntop) {
   const int i = threadIdx.x;
   if (i < kLevels) c->count[i] = ntop[i];
   if (i < 3) c->act[i] = 0;
   if (i == 0) c->scan_error = 0;
+  if (i < (int)(sizeof(ExportTotals) / 8)) ((unsigned long long*)tot)[i] = 0ull;
   if (i < kLevels * kQueues) q->at[i / kQueues][(i % kQueues) * kQueuePad] = 0;
 }
 
 }  // namespace
 
-hipError_t launch_init_counts(Counters* c, Queues* q, const int32_t* ntop_dev, hipStream_t s) {
-  hipLaunchKernelGGL(k_init_counts, dim3(1), dim3(64), 0, s, c, q, ntop_dev);
+hipError_t launch_init_counts(Counters* c, Queues* q, ExportTotals* tot, const int32_t* ntop_dev, hipStream_t s) {
+  hipLaunchKernelGGL(k_init_counts, dim3(1), dim3(64), 0, s, c, q, tot, ntop_dev);
   return hipGetLastError();
 }
 
