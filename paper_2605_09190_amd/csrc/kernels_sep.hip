@@ -468,22 +468,32 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
 #pragma unroll
       for (int j = 0; j < PW; ++j) r[i][j] = (double)((const float*)sR)[(py + i) * N + px + j];
     sep_sync<WPN>();
-    // Scale of the operand rows, a power of two: ||r|| goes to [2^7, 2^8), so
-    // that the first product (at most 2^15) and the remainders stay inside
-    // FP16's range.
-    auto scale_of = [](double en) -> float {
+    // Scale 2^-sh of the operand rows: ||r|| goes to [2^7, 2^8), so that the
+    // first product (at most 2^15) and the remainders stay inside FP16's
+    // range.  The norm of FP32 pixels can lie beyond FP32's range: what is
+    // past 120 of sh, either way, goes to the pixels in FP64.
+    auto scale_of = [](double en) -> int {
       const int ex = (int)((unsigned long long)__double_as_longlong(en) >> 52) - 1023;
-      int sh = (ex >> 1) - 7;
-      sh = sh < -120 ? -120 : (sh > 120 ? 120 : sh);
-      return __uint_as_float((uint32_t)(127 - sh) << 23);
+      return (ex >> 1) - 7;
     };
-    auto put_rows = [&](float sc) {                      // the lane's pixels into the operand rows
+    auto pow2 = [](int x) -> double { return __longlong_as_double((long long)(1023 + x) << 52); };
+    auto put_rows = [&](int sh) {                        // the lane's pixels into the operand rows
+      const int s0 = sh < -120 ? -120 : (sh > 120 ? 120 : sh);
+      const float sc = __uint_as_float((uint32_t)(127 - s0) << 23);
+      const bool far = s0 != sh;                         // uniform
 #pragma unroll
       for (int i = 0; i < RPW; ++i) {
         char* row = sR + (py + i) * G::ROWB;
         uint32_t h[PW / 2], l[PW / 2];
+        float v[PW];
 #pragma unroll
-        for (int j = 0; j < PW / 2; ++j) sp_split2_scaled((float)r[i][2 * j], (float)r[i][2 * j + 1], sc, h[j], l[j]);
+        for (int j = 0; j < PW; ++j) v[j] = (float)r[i][j];
+        if (far) {
+#pragma unroll
+          for (int j = 0; j < PW; ++j) v[j] = (float)(r[i][j] * pow2(s0 - sh));
+        }
+#pragma unroll
+        for (int j = 0; j < PW / 2; ++j) sp_split2_scaled(v[2 * j], v[2 * j + 1], sc, h[j], l[j]);
         // in the order of the k-slots: pixel x is value 4 ((x / 16) % 2) + x % 4
         // of the slots (x / 32, (x / 4) % 4)
 #pragma unroll
@@ -550,13 +560,13 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
         break;
       }
       // ---- correlations from the residual ----
-      const float sc = scale_of(e);
+      const int sh = scale_of(e);
       sep_sync<WPN>();                                   // the sums of the last step are read
-      put_rows(sc);
+      put_rows(sh);
       sep_sync<WPN>();
       sep_correlate<G>(sR, sTab.ops, wq, mq, mp0, mp, C);
-      const double gain = (double)sc * (double)(G::TS * G::TS);
-      win = __builtin_amdgcn_sqrtf((float)(e * ((double)sc * (double)sc))) * (1.0001f * 0x1p-13f * G::TS * G::TS);
+      const double gain = pow2(-sh) * (double)(G::TS * G::TS);
+      win = __builtin_amdgcn_sqrtf((float)(e * pow2(-sh) * pow2(-sh))) * (1.0001f * 0x1p-13f * G::TS * G::TS);
       top();
       sep_sync<WPN>();
       // They hold while ||r|| is at least half of what it is now, for at most
