@@ -45,8 +45,6 @@
 // of four pixels per lane; FP32 form k_select's and k_gather's, so that it
 // equals the step-by-step form bit for bit; its N = 8 the sums over lane =
 // pixel of the dense form.
-#include <type_traits>
-
 #include "internal.h"
 #include "dev_common.h"
 
@@ -283,7 +281,6 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
                                    const double* __restrict__ tab, const double* __restrict__ xg) {
   constexpr int N = G::N, K = G::K, SN = G::SN, LPS = G::LPS, PR = G::PR, PC = G::PC, VPL = G::VPL;
   constexpr bool BF = G::BF, EXACT = G::EXACT;
-  using Scale = std::conditional_t<EXACT, double, float>;
   constexpr int lg = N == 16 ? 4 : 3;
   // rows of the families' tables, then a row of ones and one of 1/N: the
   // constant atom's factors
@@ -323,7 +320,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
   bool dry = node >= count, run = false, load = !dry;
   int t = 0, kmax = 0, rec_i = 0;
   double rec_c = 0.0, e = 0.0, eps2 = 0.0;
-  Scale sc = 1;
+  double sc = 1.0;
   float win = 0.f;
   // the carried correlations hold while e is in [elim, emax) and t < tlim
   bool fresh = false;
@@ -340,12 +337,11 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
 #pragma unroll
     for (int j = 0; j < PC; ++j) rd[i][j] = 0.0;
 
-  auto scale_of = [](double en) -> Scale {   // see k_pursuit_sep
+  // see k_pursuit_sep; FP64, so that no norm of FP32 pixels is out of its range
+  auto scale_of = [](double en) -> double {
     const int ex = (int)((unsigned long long)__double_as_longlong(en) >> 52) - 1023;
-    int sh = (ex >> 1) - 7;
-    if constexpr (EXACT) return __longlong_as_double((long long)(1023 - sh) << 52);
-    sh = sh < -120 ? -120 : (sh > 120 ? 120 : sh);
-    return __uint_as_float((uint32_t)(127 - sh) << 23);
+    const int sh = (ex >> 1) - 7;
+    return __longlong_as_double((long long)(1023 - sh) << 52);
   };
   // EXACT: ||r||^2 beyond what the ranking's scale can take (an FP64 plane's
   // extremes): every atom is a candidate
@@ -360,13 +356,27 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
     const unsigned long long lanes = __ballot(any) >> (lane & ~(LPS - 1));
     return !(en < __builtin_inf()) || (lanes & ((1ull << (LPS % 64)) - 1ull)) == 0ull;
   };
+  // Some pixel of the slot's node, finite in FP64, is not in FP32.
+  auto past_f32 = [&]() {
+    bool any = false;
+#pragma unroll
+    for (int i = 0; i < PR; ++i)
+#pragma unroll
+      for (int j = 0; j < PC; ++j) any = any || !(fabs(rd[i][j]) < __builtin_inf());
+    const unsigned long long lanes = __ballot(any) >> (lane & ~(LPS - 1));
+    return (lanes & ((1ull << (LPS % 64)) - 1ull)) != 0ull;
+  };
+  // N = 8: two nodes meet in the second product, each masked from the other by
+  // zeros of the table, which hide finite values only.  So no row of a slot is
+  // ever infinite or undefined: such a node selects nothing, and what is put is
+  // scaled by its norm.
   auto put_rows = [&]() {
 #pragma unroll
     for (int i = 0; i < PR; ++i) {
       char* row = sRow + (py + i) * G::ROWB;
       float v[PC];
 #pragma unroll
-      for (int j = 0; j < PC; ++j) v[j] = EXACT ? (float)(rd[i][j] * (double)sc) : (float)rd[i][j] * (float)sc;
+      for (int j = 0; j < PC; ++j) v[j] = (float)(rd[i][j] * sc);
       const uint32_t h0 = sb_split_hi(v[0], v[1]);
       if constexpr (PC == 4) {
         const uint32_t h1 = sb_split_hi(v[2], v[3]);
@@ -433,6 +443,9 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
           st = ST_SPARSE;
         else if (still(e))
           st = ST_ZERO;
+        if constexpr (N == 8 && !EXACT) {
+          if (past_f32() && st == ST_RUN) st = ST_ZERO;
+        }
         run = st == ST_RUN;
         fresh = true;
         if (!run && li == 0) {
@@ -447,14 +460,14 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
       // ---- correlations, from the residual or carried ----
       if (!G::CARRY || __ballot(run && fresh) != 0ull) {
         if (run) {
-          sc = beyond(e) ? 0 : scale_of(e);
+          sc = beyond(e) ? 0.0 : scale_of(e);
           put_rows();
           if constexpr (EXACT) {
 #pragma unroll
             for (int j = 0; j < PC; j += 2)
               *(double2*)&sPix[wv][slot * RP + N * py + px + j] = make_double2(rd[0][j], rd[0][j + 1]);
           }
-          win = __builtin_amdgcn_sqrtf((float)(e * ((double)sc * (double)sc))) * (1.0001f * 0x1p-13f * G::TS * G::TS);
+          win = __builtin_amdgcn_sqrtf((float)(e * sc * sc)) * (1.0001f * 0x1p-13f * G::TS * G::TS);
           elim = fmax(eps2, 0.25 * e);
           emax = 4.0 * e;
           tlim = t + 64 < kmax ? t + 64 : kmax;
@@ -613,7 +626,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
       }
       if constexpr (G::CARRY) {
         // see k_pursuit_sep: c X[p][p'] X[q][q'] less, the own family's X the identity
-        const float cs = (float)(coef * ((double)sc * (double)(G::TS * G::TS)));
+        const float cs = (float)(coef * (sc * (double)(G::TS * G::TS)));
 #pragma unroll
         for (int n = 0; n < SN; ++n) {
           const int an = __builtin_amdgcn_readlane(atom < 0 ? 0 : atom, n * LPS);
@@ -644,7 +657,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
             st = ST_ACC;
           else if (t >= kmax)
             st = ST_SPARSE;
-          else if (EXACT ? none : !(e > 0.0))
+          else if (none)
             st = ST_ZERO;
           fresh = !(e >= elim && e < emax && t < tlim);
           const int base = (t - 1) & ~(LPS - 1);   // first step held in the registers
