@@ -114,7 +114,6 @@ struct aqmp_code {
   int64_t view_n = 0, view_atoms = 0;
   aqmp::DevBuf pinned;                 // page-locked host copy: node records, atom indices, coefficients
   aqmp::DevBuf pinned_tot;             // and of the counters and totals
-  std::vector<hipEvent_t> ex_ev;       // ends of the copy's pieces
   // Device side of the gather: segment and job tables (built once), and one
   // buffer for keys, flat ids, scan and output (grown as needed).
   bool ex_ready = false;
@@ -307,7 +306,6 @@ void free_code(aqmp_code* c) {
   for (auto& e : c->lev) destroy(e.start), destroy(e.end);
   for (auto& e : c->sev) destroy(e.a), destroy(e.b), destroy(e.c), destroy(e.d);
   for (auto& a : c->allocs) dev_free(a.p, a.bytes);
-  for (auto ev : c->ex_ev) destroy(ev);
   if (c->ex_buf.p) dev_free(c->ex_buf.p, c->ex_buf.bytes);
   for (DevBuf* b : {&c->pinned, &c->pinned_tot})
     if (b->p) (void)hipHostFree(b->p);
@@ -841,12 +839,9 @@ struct ViewLayout {
 
 // Gathers the visited nodes (or the leaves) on the device in canonical order
 // (job, top-level block in raster order, then depth-first: Morton order of the
-// corner, the larger node first) and copies three dense arrays back: node
-// records, atom indices, coefficients.  done(b, e) is called for every piece
-// [b, e) of the block once it is in c->pinned, in order, while the next pieces
-// are on their way.
-template <class F>
-int collect(const aqmp_code* cc, bool leaves_only, F&& done) {
+// corner, the larger node first) and copies three dense arrays to c->pinned:
+// node records, atom indices, coefficients.
+int collect(const aqmp_code* cc, bool leaves_only) {
   aqmp_code* c = const_cast<aqmp_code*>(cc);   // the cache is not part of the code's observable state
   {
     const int rc = totals(c);
@@ -859,10 +854,7 @@ int collect(const aqmp_code* cc, bool leaves_only, F&& done) {
   c->view_n = n;
   c->view_atoms = na;
   if (n == 0) return AQMP_OK;
-  if (c->view == want) {
-    done((size_t)0, at.total);
-    return AQMP_OK;
-  }
+  if (c->view == want) return AQMP_OK;
   c->view = aqmp_code::VIEW_NONE;
   hipStream_t s = c->stream;
   // Few nodes are put in order by one workgroup (see k_export_order), one launch
@@ -877,9 +869,8 @@ int collect(const aqmp_code* cc, bool leaves_only, F&& done) {
     AQMP_HIP(export_sort(nullptr, sort_bytes, nullptr, nullptr, nullptr, nullptr, n, c->ex_end_bit, s));
     AQMP_HIP(export_scan(nullptr, scan_bytes, nullptr, nullptr, n, s));
   }
-  // Small results are written to the host's memory by the gather itself: 36
-  // against 43 us for 64 leaves and 768 atoms.  Larger ones are copied in
-  // pieces, 430 against 630 us for 37 749 leaves and 616 284 atoms (8.9 MB).
+  // Small results are written to the host's memory by the gather itself, larger
+  // ones copied there.
   const bool direct = at.total <= (size_t)1 << 18;
   size_t need = 0;
   auto part = [&](size_t bytes) {
@@ -915,32 +906,8 @@ int collect(const aqmp_code* cc, bool leaves_only, F&& done) {
   }
   AQMP_HIP(launch_export_write(c->d_ex_segs, c->ex_nseg, vals2, off, n, (aqmp_leaf*)out, (int32_t*)(out + at.idx_at),
                                (double*)(out + at.coef_at), s));
-  if (direct) {
-    AQMP_HIP(hipStreamSynchronize(s));
-    done((size_t)0, at.total);
-  } else {
-    // one copy into page-locked memory, in pieces
-    constexpr size_t kPieces = 8;
-    const size_t step = std::max<size_t>((at.total / kPieces + 4095) / 4096 * 4096, (size_t)1 << 19);
-    std::vector<size_t> ends;
-    for (size_t p = 0; p < at.total; p += step) {
-      const size_t e = std::min(at.total, p + step);
-      AQMP_HIP(hipMemcpyAsync((char*)c->pinned.p + p, out + p, e - p, hipMemcpyDeviceToHost, s));
-      if (c->ex_ev.size() <= ends.size()) {
-        hipEvent_t ev = nullptr;
-        AQMP_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-        c->ex_ev.push_back(ev);
-      }
-      AQMP_HIP(hipEventRecord(c->ex_ev[ends.size()], s));
-      ends.push_back(e);
-    }
-    size_t p = 0;
-    for (size_t i = 0; i < ends.size(); ++i) {
-      AQMP_HIP(hipEventSynchronize(c->ex_ev[i]));
-      done(p, ends[i]);
-      p = ends[i];
-    }
-  }
+  if (!direct) AQMP_HIP(hipMemcpyAsync(c->pinned.p, out, at.total, hipMemcpyDeviceToHost, s));
+  AQMP_HIP(hipStreamSynchronize(s));
   c->view = want;
   return AQMP_OK;
 }
@@ -1053,16 +1020,14 @@ int code_export(const aqmp_code* c, bool leaves_only, aqmp_leaf* leaves, int32_t
     AQMP_FAIL(AQMP_E_CAPACITY, "aqmp_code_export: need " + std::to_string(n) + " records and " + std::to_string(na) +
                                    " atoms");
   const ViewLayout at(n, na);
-  return collect(c, leaves_only, [&](size_t b, size_t e) {
-    // the piece's share of each array
-    auto put = [&](void* dst, size_t from, size_t bytes) {
-      const size_t lo = std::max(b, from), hi = std::min(e, from + bytes);
-      if (lo < hi) std::memcpy((char*)dst + (lo - from), (const char*)c->pinned.p + lo, hi - lo);
-    };
-    put(leaves, 0, sizeof(aqmp_leaf) * (size_t)n);
-    put(atom_idx, at.idx_at, sizeof(int32_t) * (size_t)na);
-    put(coef, at.coef_at, sizeof(double) * (size_t)na);
-  });
+  // nothing below fails: the caller's buffers are written whole or not at all
+  rc = collect(c, leaves_only);
+  if (rc != AQMP_OK) return rc;
+  const char* from = (const char*)c->pinned.p;
+  std::memcpy(leaves, from, sizeof(aqmp_leaf) * (size_t)n);
+  std::memcpy(atom_idx, from + at.idx_at, sizeof(int32_t) * (size_t)na);
+  std::memcpy(coef, from + at.coef_at, sizeof(double) * (size_t)na);
+  return AQMP_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -1088,7 +1053,7 @@ int code_pack(const aqmp_code* c, const int32_t* jobs, int n_jobs, int level, do
     if (im.w != im0.w || im.h != im0.h || p.n_min != p0.n_min || p.n_max != p0.n_max)
       AQMP_FAIL(AQMP_E_INVALID, "aqmp_code_pack: the channels of a stream need one size and one block range");
   }
-  const int rc = collect(c, false, [](size_t, size_t) {});
+  const int rc = collect(c, false);
   if (rc != AQMP_OK) return rc;
   const int64_t n = c->view_n;
   const ViewLayout at(n, c->view_atoms);
