@@ -104,14 +104,14 @@ struct aqmp_code {
   std::vector<StepEv> sev;
   size_t lev_pos = 0, sev_pos = 0;
   // What the last encode holds, counted on the device at the first read
-  // (stats, sizes, export, pack), and its nodes or leaves in canonical order,
-  // gathered there and copied back when first asked for; kept until the next
-  // encode.
+  // (stats, sizes, export, pack), and its leaves or all its nodes in canonical
+  // order, gathered there when first asked for; kept until the next encode.
+  // All nodes hold the leaves too, so they take the leaves' place for good.
   bool totals_ok = false;
   bool totals_added = false;   // the totals on the device were added to since the encode
   aqmp::ExportTotals totals{};
   enum View { VIEW_NONE, VIEW_LEAVES, VIEW_NODES } view = VIEW_NONE;
-  int64_t view_n = 0, view_atoms = 0;
+  int64_t view_n = 0, view_atoms = 0;  // records and atoms of the view
   aqmp::DevBuf pinned;                 // page-locked host copy: node records, atom indices, coefficients
   aqmp::DevBuf pinned_tot;             // and of the counters and totals
   // Device side of the gather: segment and job tables (built once), and one
@@ -839,8 +839,9 @@ struct ViewLayout {
 
 // Gathers the visited nodes (or the leaves) on the device in canonical order
 // (job, top-level block in raster order, then depth-first: Morton order of the
-// corner, the larger node first) and copies three dense arrays to c->pinned:
-// node records, atom indices, coefficients.
+// corner, the larger node first) into three dense arrays in c->pinned: node
+// records, atom indices, coefficients.  Where the leaves are asked for and all
+// nodes are there, those stay (see code_export).
 int collect(const aqmp_code* cc, bool leaves_only) {
   aqmp_code* c = const_cast<aqmp_code*>(cc);   // the cache is not part of the code's observable state
   {
@@ -851,10 +852,7 @@ int collect(const aqmp_code* cc, bool leaves_only) {
   view_size(c, leaves_only, n, na);
   const ViewLayout at(n, na);
   const auto want = leaves_only ? aqmp_code::VIEW_LEAVES : aqmp_code::VIEW_NODES;
-  c->view_n = n;
-  c->view_atoms = na;
-  if (n == 0) return AQMP_OK;
-  if (c->view == want) return AQMP_OK;
+  if (n == 0 || c->view == want || c->view == aqmp_code::VIEW_NODES) return AQMP_OK;
   c->view = aqmp_code::VIEW_NONE;
   hipStream_t s = c->stream;
   // Few nodes are put in order by one workgroup (see k_export_order), one launch
@@ -908,6 +906,8 @@ int collect(const aqmp_code* cc, bool leaves_only) {
   AQMP_HIP(launch_export_write(c->d_ex_segs, c->ex_nseg, vals2, off, n, (aqmp_leaf*)out, (int32_t*)(out + at.idx_at),
                                (double*)(out + at.coef_at), s));
   AQMP_HIP(hipStreamSynchronize(s));
+  c->view_n = n;
+  c->view_atoms = na;
   c->view = want;
   return AQMP_OK;
 }
@@ -1019,14 +1019,31 @@ int code_export(const aqmp_code* c, bool leaves_only, aqmp_leaf* leaves, int32_t
   if (n > cap_leaves || na > cap_atoms)
     AQMP_FAIL(AQMP_E_CAPACITY, "aqmp_code_export: need " + std::to_string(n) + " records and " + std::to_string(na) +
                                    " atoms");
-  const ViewLayout at(n, na);
-  // nothing below fails: the caller's buffers are written whole or not at all
   rc = collect(c, leaves_only);
   if (rc != AQMP_OK) return rc;
+  // Nothing below fails: the caller's buffers are written whole or not at all.
+  const ViewLayout at(c->view_n, c->view_atoms);
   const char* from = (const char*)c->pinned.p;
-  std::memcpy(leaves, from, sizeof(aqmp_leaf) * (size_t)n);
-  std::memcpy(atom_idx, from + at.idx_at, sizeof(int32_t) * (size_t)na);
-  std::memcpy(coef, from + at.coef_at, sizeof(double) * (size_t)na);
+  const aqmp_leaf* rec = (const aqmp_leaf*)from;
+  const int32_t* idx = (const int32_t*)(from + at.idx_at);
+  const double* cf = (const double*)(from + at.coef_at);
+  if (n == c->view_n) {   // the view is what was asked for
+    std::memcpy(leaves, rec, sizeof(aqmp_leaf) * (size_t)n);
+    std::memcpy(atom_idx, idx, sizeof(int32_t) * (size_t)na);
+    std::memcpy(coef, cf, sizeof(double) * (size_t)na);
+    return AQMP_OK;
+  }
+  int64_t off = 0;
+  for (int64_t i = 0; i < c->view_n; ++i) {   // the leaves of all nodes
+    if (rec[i].flags & 1) continue;
+    const int64_t from_atom = rec[i].atom_off;
+    const size_t k = (size_t)rec[i].n_atoms;
+    *leaves = rec[i];
+    (leaves++)->atom_off = off;
+    std::memcpy(atom_idx + off, idx + from_atom, sizeof(int32_t) * k);
+    std::memcpy(coef + off, cf + from_atom, sizeof(double) * k);
+    off += (int64_t)k;
+  }
   return AQMP_OK;
 }
 

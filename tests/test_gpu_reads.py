@@ -82,6 +82,39 @@ dic.free()
 print("done", flush=True)
 '''
 
+AGAIN = COMMON + r'''
+def waits(f):
+    seen.value = 0
+    r = f()
+    return seen.value, r
+def same(a, b):
+    return all(x.tobytes() == y.tobytes() for x, y in ((a.leaves, b.leaves), (a.atom_idx, b.atom_idx), (a.coef, b.coef)))
+for h, w in ((96, 64), (512, 512)):
+    img, code = code_of(h, w)
+    leaves = code.export()
+    assert leaves.leaves["atom_off"][-1] + leaves.leaves["n_atoms"][-1] == len(leaves.coef)
+    n0, nodes = waits(code.export_nodes)
+    packed = code.pack([0], level=-1)
+    print("nodes", len(nodes.leaves), "leaves", len(leaves.leaves), "waits of the first reading of all", n0, flush=True)
+    assert len(nodes.leaves) > len(leaves.leaves) and n0 >= 1     # a stale count would hide the others
+    reads = [code.export, code.export_nodes, code.export, lambda: code.pack([0], level=-1), code.export, code.sizes, code.stats]
+    for start in (None, code.export_nodes, code.export):
+        if start:                                                  # another encode, read in another order
+            code.reencode([img])
+            start()
+            code.export_nodes()
+        for k, f in enumerate(reads):
+            n, r = waits(f)
+            assert n == 0, (h, k, n)
+            if isinstance(r, A.Export):
+                assert same(r, nodes if f == code.export_nodes else leaves), (h, k)
+            elif isinstance(r, bytes):
+                assert r == packed
+    code.free()
+dic.free()
+print("done", flush=True)
+'''
+
 
 @pytest.fixture(scope="module")
 def shim(tmp_path_factory):
@@ -106,3 +139,9 @@ def test_failed_wait_leaves_buffers_untouched(shim):
     keep their bytes, of a result that the gather writes to host memory and of
     one that is copied (several MB)."""
     _child(FAILING, shim)
+
+
+def test_nodes_serve_every_later_read(shim):
+    """Once all nodes of an encode are read, leaves, nodes, streams, sizes and
+    statistics of it need the device no more, in any order, and are the same."""
+    _child(AGAIN, shim)
