@@ -229,9 +229,10 @@ struct DVec<4> {
   typedef double type __attribute__((ext_vector_type(4)));
 };
 
-// Larger of |a| and b >= 0 (no quieting of NaNs first).  Neither a matrix-core
-// result may go in nor a lane exchange follow directly: the compiler adds no
-// wait states around inline assembly.
+// Larger of |a| and b >= 0 (no quieting of NaNs first).  A matrix-core result
+// may not go in: the compiler adds no wait states before inline assembly that
+// reads one.  (It does before a lane exchange that reads the result of inline
+// assembly; the one here does not rely on that.)
 __device__ inline double max_abs(double a, double b) {
   double r;
   __asm__("v_max_f64 %0, |%1|, %2" : "=v"(r) : "v"(a), "v"(b));
@@ -498,7 +499,8 @@ __global__ __launch_bounds__(256, 2) void k_gram_pursuit(const JobDev* __restric
             m0 = max_abs(c[f][j], m0);
             m1 = max_abs(c[f][j + 1], m1);
           }
-        const double m = wave_max_f64(max_abs(m0, m1));
+        // (an ordinary instruction between max_abs and the lane exchanges)
+        const double m = wave_max_f64(__builtin_canonicalize(max_abs(m0, m1)));
         // the sign of |c| - m, two instructions per value: bit V - 1 - j is 0
         // where value j is the largest
         constexpr int V = NFAM * AF;
