@@ -246,17 +246,21 @@ def select_bytes(n, precision):
 
 
 def factored_flops(n, nodes, steps):
-    """Operations that the whole-level pursuits of N >= 32 cannot do without:
-    per node its first correlations, factored through the atoms' outer
-    products (T R T^T per family, two products of 2 N^3, as three 16-bit
-    products each for the DCT and two for the Haar: 20 N^3), and per step 2
-    N^2 to carry the other family's correlations.  Correlations made anew in
-    between are not counted, nor is the FP64 re-score and update."""
+    """Operations that the whole-level pursuits of N >= 8 cannot do without,
+    for two families.  N >= 16: per node its first correlations, factored
+    through the atoms' outer products (T R T^T per family, two products of 2
+    N^3, as three 16-bit products each for the DCT and two for the Haar: 20
+    N^3), and per step 2 N^2 to carry the other family's correlations.
+    Correlations made anew in between are not counted.  N = 8 makes them at
+    every step, in three products for either family: 24 N^3.  The FP64
+    re-score and update are not counted."""
+    if n == 8:
+        return 24 * n ** 3 * steps
     return 20 * n ** 3 * nodes + 2 * n * n * steps
 
 
 def whole_level_roofline(n, stats, timing):
-    """A level of N >= 32 run as one launch: its operations (factored_flops)
+    """A level of N >= 8 run as one launch: its operations (factored_flops)
     over the level's time (gather, re-score, update and split test included),
     against the 16-bit matrix peak, in either form."""
     lg = n.bit_length() - 1
@@ -267,6 +271,15 @@ def whole_level_roofline(n, stats, timing):
     return dict(bound="latency", achieved=round(ach, 2), peak=PEAK_BF16_TFLOPS, unit="TFLOP/s",
                 frac=round(ach / PEAK_BF16_TFLOPS, 4), traffic=None, kernel=f"k_pursuit_sep<{n}>", level_ms=round(ms, 4),
                 flops=flops, nodes=nodes, units=steps)
+
+
+def largest_level_figures(roof):
+    """A roofline's figures of the largest level of the FP32 form under names
+    that say what they are a fraction of: the level's time and the 16-bit
+    matrix peak where it runs as one launch, else the FP32 correlation."""
+    if roof["bound"] == "latency":
+        return dict(level_tflops=roof["achieved"], level_frac_16bit_peak=roof["frac"])
+    return dict(corr_tflops=roof["achieved"], corr_frac_fp32_peak=roof["frac"])
 
 
 def roofline(stats, timing, precision, kernel_name=None, workload=None):
@@ -302,12 +315,13 @@ def roofline(stats, timing, precision, kernel_name=None, workload=None):
                                           select_gbs=round(gbs, 1), select_hbm_frac=round(gbs / PEAK_HBM_GBS, 4),
                                           select_traffic=(measured_traffic(f"k_select<{nn}>", workload)
                                                           if precision == 1 else None))
-    # Levels of N <= 16 run as one launch: the whole level's time against the
-    # flops of the method's per-step correlation, 4 N^4 per node-iteration.
+    # Levels that ran as one launch: N >= 8 against what their factored form
+    # needs; N = 4, and any level whose nodes are not known, against the method's
+    # per-step correlation, 4 N^4 per node-iteration.
     for l in range(7):
         if stats["iters_level"][l] and timing["corr_ms"][l] == 0 and timing["level_ms"][l] > 0:
             nn = 1 << l
-            if nn >= 32:
+            if nn >= 32 or (nn >= 8 and "nodes" in stats):
                 per_level[str(nn)] = dict(whole_level_roofline(nn, stats, timing), kernel="whole-level pursuit")
                 continue
             bf16 = precision == 1 and nn in (8, 16)
@@ -474,7 +488,7 @@ def form_compare(A, w, steps, warmup, fp32_steps, label):
                bf16_batched=dict(value=round(npx / sec / 1e6, 3), unit="Mpixel/s", ms_per_step=round(sec * 1e3, 3),
                                  steps=steps, mp_iters_per_s=round(st["iters_executed"] / sec, 1),
                                  leaves=int(sum(st["leaves"])), iters_executed=int(st["iters_executed"]),
-                                 per_level={k: {kk: v[kk] for kk in ("frac", "tflops", "corr_ms", "select_ms",
+                                 per_level={k: {kk: v[kk] for kk in ("frac", "tflops", "achieved", "corr_ms", "select_ms",
                                                                       "level_ms", "select_gbs") if kk in v}
                                             for k, v in roof["per_level"].items()}))
     if fp32_steps > 0:
@@ -677,8 +691,10 @@ def main():
         roof3 = roofline(st3, code3.timing(), A.PREC_FP32, lambda n: A.corr_kernel(n, A.PREC_FP32))
         fp32 = dict(value=round(npx / sec3 / 1e6, 3), ms_per_step=round(sec3 * 1e3, 3), steps=args.fp32_steps,
                     mp_iters_per_s=round(st3["iters_executed"] / sec3, 1), psnr_db=[round(p, 4) for p in psnr_f],
-                    corr_tflops=roof3["achieved"], corr_frac_fp32_peak=roof3["frac"],
-                    leaves=int(sum(st3["leaves"])))
+                    **largest_level_figures(roof3),
+                    leaves=int(sum(st3["leaves"])),
+                    form="FP32 form, jobs one after another.  Its whole levels rank atoms by the same FP16 pairs as "
+                         "the headline's, so the two differ in schedule and in the small blocks' FP64 sums")
         code3.free()
         log(f"fp32 plain: {sec3 * 1e3:.3f} ms/step")
         mark("fp32_plain_form")
@@ -784,8 +800,8 @@ def main():
         "dtype": "bf16",
         "data": "synthetic",
         "config": {"workload": w["name"], "jobs": len(w["jobs"]), "pixels_per_step": npx,
-                   "form": "batched: all jobs in one HIP graph, 16-bit MFMA correlation factored through the "
-                           "atoms' outer products, FP64 re-score"},
+                   "form": "batched: all jobs in one HIP graph, MFMA correlation of FP16 pairs (value and "
+                           "remainder) factored through the atoms' outer products, FP64 re-score"},
         "mp_iters_per_s": round(stats["iters_executed"] / sec, 1),
         "mp_iters_executed": int(stats["iters_executed"]),
         "mp_iters_emitted": int(stats["iters_emitted"]),
