@@ -47,29 +47,6 @@ __device__ inline double group_sum(double v, double* scratch) {
   return v;
 }
 
-// Same for an array of CNT doubles (each element reduced independently).
-template <int TPN, int CNT>
-__device__ inline void group_sum_n(double (&v)[CNT], double* scratch) {
-  constexpr int W = TPN < 64 ? TPN : 64;
-#pragma unroll
-  for (int c = 0; c < CNT; ++c) {
-#pragma unroll
-    for (int off = 1; off < W; off <<= 1) v[c] += __shfl_xor(v[c], off, 64);
-  }
-  if constexpr (TPN > 64) {
-    const int w = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-      for (int c = 0; c < CNT; ++c) scratch[c * 4 + w] = v[c];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < CNT; ++c)
-      v[c] = (scratch[c * 4 + 0] + scratch[c * 4 + 1]) + (scratch[c * 4 + 2] + scratch[c * 4 + 3]);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Decoupled look-back for stable single-pass prefix sums.  A tile word holds a
 // flag in its top two bits (1: tile aggregate published, 2: inclusive prefix

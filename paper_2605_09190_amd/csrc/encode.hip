@@ -75,7 +75,7 @@ struct aqmp_code {
     uint16_t* r16 = nullptr;
     unsigned long long* keys = nullptr;
     int32_t* act[2] = {nullptr, nullptr};
-    double* cbuf = nullptr;          // Gram form: FP64 correlations [node][M]
+    double* cbuf = nullptr;          // OMP: first correlations, FP64, [node][M]
     aqmp::ScanState ss{};
   };
   std::vector<Work> work;            // indexed by pass % work.size()
@@ -91,7 +91,8 @@ struct aqmp_code {
   // Timing events (AQMP_OPT_TIMING): per level of every pass a start/end
   // pair; per MP step the start and end of the correlation (a, b) and of the
   // select/update launch (c, d), recorded by the dispatches themselves.  The
-  // Gram and OMP solvers' levels use a, b, c around their two launches.
+  // Gram and OMP levels of N >= 16 use a, b, c: the pursuit between b and c,
+  // OMP's first correlations between a and b.
   struct LevelEv {
     int lg;
     hipEvent_t start, end;
@@ -482,8 +483,7 @@ int build_plan(aqmp_code* c) {
         AQMP_HIP(hipEventCreate(&le.end));
         c->lev.push_back(le);
         if (whole_level(c, 1 << l)) {
-          // Gram and OMP levels with N >= 16: one event triple around the
-          // initial-correlation and pursuit launches.
+          // Gram and OMP levels of N >= 16: one event triple (see StepEv).
           if (c->opt.solver != AQMP_SOLVER_DENSE && (1 << l) > kFusedMaxN) {
             aqmp_code::StepEv se{l, nullptr, nullptr, nullptr, nullptr};
             AQMP_HIP(hipEventCreate(&se.a));

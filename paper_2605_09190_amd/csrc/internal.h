@@ -29,7 +29,7 @@ constexpr int kLevels = 7;        // log2(N) for N = 1 .. 64
 constexpr int kCand = AQMP_CANDIDATES;
 constexpr int kTopR = 8;          // keys kept per node per atom tile
 constexpr int kScanTile = 1024;   // items per block of the stable scans
-constexpr int kFusedMaxN = 8;     // levels up to this size run the fused per-node pursuit
+constexpr int kFusedMaxN = 8;     // levels up to this size run as one launch in every form
 constexpr int kBranches = 4;      // parallel graph branches of the concurrent schedule
 constexpr int kOmpMaxAtoms = AQMP_OMP_MAX_ATOMS;   // OMP: selected atoms per node (LDS factor size)
 constexpr int kQueues = 8, kQueuePad = 32;   // node queues of a level and the words between them
@@ -307,8 +307,8 @@ hipError_t launch_export_order(const ExportSeg* segs, int nseg, const ExportJob*
 hipError_t launch_export_write(const ExportSeg* segs, int nseg, const uint32_t* vals, const int64_t* off, int64_t n,
                                aqmp_leaf* out, int32_t* idx, double* coef, hipStream_t s);
 
-// Name of the correlation kernel launch_corr runs (or the fused pursuit for
-// n <= kFusedMaxN); "" when the combination is invalid.
+// Name of the correlation kernel launch_corr runs (or the whole-level pursuit
+// for n <= kFusedMaxN); "" when the combination is invalid.
 const char* corr_kernel_name(int n, int precision, int variant);
 // The BF16 correlation variants the library has: 0 (default), 2, 3, 6.
 inline bool corr_variant_valid(int v) { return v == 0 || v == 2 || v == 3 || v == 6; }

@@ -25,17 +25,19 @@
 // carried in FP32 registers from step to step (2 operations per atom of one
 // family instead of 4 N per atom of both) and made anew from the residual
 // when its norm has halved, or after at most 64 steps.  Largest error over
-// ||r|| against FP64, whole pursuits on smooth, edge, texture, noise and dot
-// blocks: 2.0e-7; the unfactored product of every step has 3.7e-7 to 6.7e-7
-// with FP32 operands and 5.6e-4 with BF16 atoms and residuals.  Both forms
-// run this one kernel.
+// ||r|| against FP64, whole pursuits over blocks of 35 planes (51 to 1 822
+// pixels wide, k to 40), every FP32 sum taken one term after the other: 7.3e-7
+// at N = 32, 6.2e-7 at N = 64; the unfactored product of every step has 2.5e-6
+// and 2.3e-6 with FP32 operands (and, summed in blocks, 5.6e-4 with BF16 atoms
+// and residuals).  Both forms run this one kernel.
 //
 // Selection: the candidates are all atoms whose |c| is within 2 delta of the
 // largest, delta = 2^-14 ||r'||, r' the residual of the last product.  A
 // fresh correlation is within 2^-14.9 ||r'|| of the FP64 value in the worst
-// case (per product the remainders' rounding and the dropped lo lo term, 3
-// 2^-22, and at most 192 FP32 additions, 192 2^-24, of sum |T||R|, which
-// Cauchy-Schwarz bounds by the norm), and a step adds at most 6 2^-24 ||r'||
+// case (the remainders' rounding and the dropped lo lo term, 3 2^-22 in the
+// first product and 5 2^-22 in the second, whose operand is split by
+// truncation, and at most 192 FP32 additions in either, 192 2^-24, of sum
+// |T||R|, which Cauchy-Schwarz bounds by the norm), and a step adds at most 6 2^-24 ||r'||
 // (roundings of c, X, two products, the sum, and of the stored residual), 64
 // of them 2^-15.4 ||r'||: no other atom can be the arg-max of the FP64
 // re-score or tie it.  One atom is left in 98% of the steps of an ordinary

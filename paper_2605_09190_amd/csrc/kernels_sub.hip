@@ -17,9 +17,11 @@
 // N = 16 carries the correlations from step to step as kernels_sep.hip does,
 // until one of the wave's running nodes wants them anew (then all take them);
 // with four nodes to a wave N = 8 would want them at most steps.  Largest
-// error over ||r|| at N = 16, whole pursuits: 1.2e-7 (FP32 products of every
-// step 3.8e-7).  Selection as there, too: every atom whose |c| is within
-// 2^-13 ||r'|| of the largest is re-scored in FP64.
+// error over ||r|| (as measured there): N = 16 5.3e-7, FP32 products of every
+// step 2.2e-6; N = 8 3.5e-7.  Selection as there, too: every atom whose |c| is
+// within 2^-13 ||r'|| of the largest is re-scored in FP64 (the bound holds with
+// room: 48 FP32 additions at most per product instead of 192, and 5 2^-22 for
+// the split of either).
 //
 // What bounds it: the instructions of a step (about 400 for the two nodes of
 // a wave), then the longest pursuits.  On three 2048 x 2048 planes N = 16
