@@ -261,6 +261,23 @@ __device__ inline double wave_max_f64(double d) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+__device__ inline int row_min_i32(int v) {
+#define AQMP_GMIN(C) { const int o = (int)row_perm_u32<C>((uint32_t)v); v = o < v ? o : v; }
+  AQMP_GMIN(0xB1) AQMP_GMIN(0x4E) AQMP_GMIN(0x141) AQMP_GMIN(0x140)
+#undef AQMP_GMIN
+  return v;
+}
+// Smallest of the wave, uniform.
+__device__ inline int wave_min_i32(int v) {
+  v = row_min_i32(v);
+  uint32_t p, q;
+  lane_pair_u32<16>((uint32_t)v, p, q);
+  v = (int)p < (int)q ? (int)p : (int)q;
+  lane_pair_u32<32>((uint32_t)v, p, q);
+  v = (int)p < (int)q ? (int)p : (int)q;
+  return __builtin_amdgcn_readfirstlane(v);
+}
+
 // Best atom of a wave: largest |c|, lowest atom index among equal
 // magnitudes; the result is uniform across the wave.  |c| is non-negative,
 // so its bit pattern orders like its value.
@@ -474,6 +491,7 @@ __global__ __launch_bounds__(256, 2) void k_gram_pursuit(const JobDev* __restric
     // The largest |c| is found by FP64 maxima; undefined pixels (or a norm
     // that overflows) by the order of the bits, where a NaN is the largest.
     const bool odd = !(e < __builtin_inf());
+    constexpr int V = NFAM * AF;
     int t = 0;
     int rec_i = 0;
     double rec_c = 0.0;
@@ -489,6 +507,7 @@ __global__ __launch_bounds__(256, 2) void k_gram_pursuit(const JobDev* __restric
         if (wn == 0 && lane == 0) c[1][0] = 0.0;
       }
       int bi = 0x7fffffff, at = 0, L = 0;            // atom; its place f AF + j and lane
+      uint32_t is = 0u;                              // bit V - 1 - j: value j is the wave's largest
       bool one = !odd;
       if (!odd) {
         double m0 = 0.0, m1 = 0.0;
@@ -503,14 +522,13 @@ __global__ __launch_bounds__(256, 2) void k_gram_pursuit(const JobDev* __restric
         const double m = wave_max_f64(__builtin_canonicalize(max_abs(m0, m1)));
         // the sign of |c| - m, two instructions per value: bit V - 1 - j is 0
         // where value j is the largest
-        constexpr int V = NFAM * AF;
         uint32_t less = ~0u;
 #pragma unroll
         for (int j = 0; j < V; ++j) {
           const double d = fabs(c[j / AF][j % AF]) - m;
           less = __builtin_amdgcn_alignbit(less, (uint32_t)((unsigned long long)__double_as_longlong(d) >> 32), 31);
         }
-        const uint32_t is = ~less;
+        is = ~less;
         const unsigned long long hit = __ballot(is != 0u);
         L = hit ? __builtin_ctzll(hit) : 0;
         const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)is, L);
@@ -519,31 +537,35 @@ __global__ __launch_bounds__(256, 2) void k_gram_pursuit(const JobDev* __restric
         bi = atom_of(at / AF, at % AF, wn, L);
       }
       if (!one) {
-        // ties, or undefined values: the largest by bits, then the lowest atom
-        unsigned long long mb = 0ull;
+        // Ties (Haar atoms on replicated rows or binary planes tie at most
+        // steps), or undefined values: the lowest atom of those that are the
+        // largest, undefined values by their bits.
         int best = 0x7fffffff;
-#pragma unroll
-        for (int f = 0; f < NFAM; ++f)
-#pragma unroll 1
-          for (int j = 0; j < AF; ++j) {
-            const unsigned long long u = (unsigned long long)__double_as_longlong(fabs(c[f][j]));
-            mb = u > mb ? u : mb;
+        if (!odd) {
+          for (uint32_t u = is; __ballot(u != 0u) != 0ull; u &= u - 1u) {
+            const int j = V - 1 - (u ? __builtin_ctz(u) : 0);
+            const int a = atom_of(j / AF, j % AF, wn, lane);
+            best = u != 0u && a < best ? a : best;
           }
-        const unsigned long long m = wave_max_u64(mb);
+        } else {
+          unsigned long long mb = 0ull;
 #pragma unroll
-        for (int f = 0; f < NFAM; ++f)
+          for (int f = 0; f < NFAM; ++f)
 #pragma unroll 1
-          for (int j = 0; j < AF; ++j) {
-            const int a = atom_of(f, j, wn, lane);
-            if ((unsigned long long)__double_as_longlong(fabs(c[f][j])) == m && a < best) best = a;
-          }
-        bi = best;
+            for (int j = 0; j < AF; ++j) {
+              const unsigned long long u = (unsigned long long)__double_as_longlong(fabs(c[f][j]));
+              mb = u > mb ? u : mb;
+            }
+          const unsigned long long m = wave_max_u64(mb);
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const int o = __shfl_xor(bi, off, 64);
-          bi = o < bi ? o : bi;
+          for (int f = 0; f < NFAM; ++f)
+#pragma unroll 1
+            for (int j = 0; j < AF; ++j) {
+              const int a = atom_of(f, j, wn, lane);
+              if ((unsigned long long)__double_as_longlong(fabs(c[f][j])) == m && a < best) best = a;
+            }
         }
-        bi = __builtin_amdgcn_readfirstlane(bi);
+        bi = wave_min_i32(best);
         const int q = (bi % K) / N, p = bi % N;
         at = bi / K * AF + 4 * (((q >> 4) % SW) * T + (p >> 4)) + ((q & 15) >> 2);
         L = (q & 3) * 16 + (p & 15);
@@ -673,12 +695,6 @@ __device__ inline double row_sum_f64(double d) {
   d += row_perm_f64<0x141>(d);
   d += row_perm_f64<0x140>(d);
   return d;
-}
-__device__ inline int row_min_i32(int v) {
-#define AQMP_GMIN(C) { const int o = (int)row_perm_u32<C>((uint32_t)v); v = o < v ? o : v; }
-  AQMP_GMIN(0xB1) AQMP_GMIN(0x4E) AQMP_GMIN(0x141) AQMP_GMIN(0x140)
-#undef AQMP_GMIN
-  return v;
 }
 
 template <int NFAM>
