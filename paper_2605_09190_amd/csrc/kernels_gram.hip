@@ -676,12 +676,13 @@ __global__ __launch_bounds__(256, 2) void k_gram_pursuit(const JobDev* __restric
 }
 
 // ---------------------------------------------------------------------------
-// Small blocks.  N = 4: a row of 16 lanes per node, lane = pixel for the
-// gather and lane = (p, q) for the atoms, one atom per family per lane.  The
-// correlations come from the separable sum sum_y T_f[p][y] sum_x T_f[q][x]
-// Y[y][x]; the pursuit then runs on the Gram updates as above.  Selection
-// reductions are DPP operations inside the row: the largest |c|, then the
-// lowest atom index among the lanes holding it, then that lane's c.
+// Small blocks.  N = 4, and few nodes of N = 8: K = N^2 lanes per node (a row
+// of 16, or the wave), lane = pixel for the gather and lane = (p, q) for the
+// atoms, one atom per family per lane.  The correlations come from the
+// separable sum sum_y T_f[p][y] sum_x T_f[q][x] Y[y][x]; the pursuit then runs
+// on the Gram updates as above.  Selection reductions are lane exchanges: the
+// largest |c|, then the lowest atom index among the lanes holding it, then
+// that lane's c.
 // ---------------------------------------------------------------------------
 __device__ inline unsigned long long row_max_u64(unsigned long long v) {
 #define AQMP_GMAX(C) { const unsigned long long o = dpp_u64<C, 0xF>(v); v = o > v ? o : v; }
@@ -697,35 +698,29 @@ __device__ inline double row_sum_f64(double d) {
   return d;
 }
 
-template <int NFAM>
-__global__ __launch_bounds__(256) void k_gram4(const JobDev* __restrict__ jobs, LevelDev lv,
-                                               const int32_t* __restrict__ count_ptr, const double* __restrict__ tab,
-                                               const double* __restrict__ xg) {
-  constexpr int N = 4, K = N * N, lg = 2;
-  constexpr int LPN = K;                 // lanes per node
-  constexpr int GPW = 64 / LPN;          // nodes per wave
-  constexpr int NG = 4 * GPW;            // nodes per workgroup
-  constexpr int NX = NFAM == 2 ? N : 1;
-  __shared__ double sT[NFAM][K];         // T_f[p][y] at [f][p N + y]
-  __shared__ double sX[NX][NX + 1];      // X[p][p'] = <T_0[p], T_1[p']>
-  __shared__ double sY[NG][K];           // the node's pixels (group-private)
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int grp = (tid >> 6) * GPW + lane / LPN, lt = lane % LPN;
-  for (int i = tid; i < NFAM * K; i += 256) (&sT[0][0])[i] = tab[i];
-  if constexpr (NFAM == 2)
-    for (int i = tid; i < K; i += 256) sX[i / N][i % N] = xg[i];
-  __syncthreads();
-  const int count = *count_ptr;
+// The nodes node, node + step, .. of the lane's group; sT: T_f[p][y] at
+// [f][p N + y]; ys: K doubles of the group's own; cross(f, p, q): <phi, phi'>
+// of atom (f, p, q) with the lane's atom of the other family.
+template <int N, int NFAM, class Cross>
+__device__ inline void gram_pixels(const JobDev* __restrict__ jobs, const LevelDev& lv, int node, int step, int count,
+                                   const double* sT, double* ys, Cross cross) {
+  constexpr int K = N * N, lg = N == 4 ? 2 : 3;
+  static_assert(K == 16 || K == 64, "a row of lanes or a wave");
+  const int lt = (int)threadIdx.x % K;
   const int pa = lt % N, qa = lt / N;    // this lane's atoms f K + lt
-  for (int node = blockIdx.x * NG + grp; node < count; node += gridDim.x * NG) {
+  auto sum = [](double v) -> double {
+    if constexpr (K == 64) return wave_sum_f64(v);
+    else return row_sum_f64(v);
+  };
+  for (; node < count; node += step) {
     const JobDev& jb = jobs[lv.job[node]];
     const double eps2 = jb.eps2[lg];
     const int kmax = jb.k[lg];
     const double v = job_pixel(jb, lv.y0[node] + qa, lv.x0[node] + pa);   // pixel (lt / N, lt % N)
-    sY[grp][lt] = v;
+    ys[lt] = v;
     __builtin_amdgcn_wave_barrier();     // group-private: the wave's own writes are seen by its reads
-    double e = row_sum_f64(v * v);
-    const double s = row_sum_f64(v);
+    double e = sum(v * v);
+    const double s = sum(v);
     uint8_t st = ST_RUN;
     if (e < eps2)
       st = ST_ACC;
@@ -735,16 +730,16 @@ __global__ __launch_bounds__(256) void k_gram4(const JobDev* __restrict__ jobs, 
 #pragma unroll
     for (int f = 0; f < NFAM; ++f) {
       double acc = 0.0;
-#pragma unroll
+#pragma unroll 4
       for (int y = 0; y < N; ++y) {
         double u = 0.0;
 #pragma unroll
-        for (int x = 0; x < N; ++x) u = fma(sT[f][qa * N + x], sY[grp][y * N + x], u);
-        acc = fma(sT[f][pa * N + y], u, acc);
+        for (int x = 0; x < N; ++x) u = fma(sT[f * K + qa * N + x], ys[y * N + x], u);
+        acc = fma(sT[f * K + pa * N + y], u, acc);
       }
       c[f] = lt == 0 ? s / N : acc;
     }
-    __builtin_amdgcn_wave_barrier();     // sY is rewritten by the next node
+    __builtin_amdgcn_wave_barrier();     // ys is rewritten by the next node
     int t = 0, rec_i = 0;
     double rec_c = 0.0;
     const size_t rec0 = (size_t)node * lv.kmax;
@@ -757,14 +752,20 @@ __global__ __launch_bounds__(256) void k_gram4(const JobDev* __restrict__ jobs, 
         bi = take ? K + lt : bi;
       }
       const unsigned long long mb = (unsigned long long)__double_as_longlong(fabs(bc));
-      const unsigned long long m = row_max_u64(mb);
-      bi = row_min_i32(mb == m ? bi : 0x7fffffff);
+      unsigned long long m;
+      if constexpr (K == 64) {
+        m = wave_max_u64(mb);
+        bi = wave_min_i32(mb == m ? bi : 0x7fffffff);
+      } else {
+        m = row_max_u64(mb);
+        bi = row_min_i32(mb == m ? bi : 0x7fffffff);
+      }
       if (m == 0ull) {
         st = ST_ZERO;
         break;
       }
-      bc = row_sum_f64((lt == bi % K) ? (bi >= K ? c[NFAM - 1] : c[0]) : 0.0);
-      if (lt == t % LPN) {
+      bc = sum((lt == bi % K) ? (bi >= K ? c[NFAM - 1] : c[0]) : 0.0);
+      if (lt == t % K) {
         rec_i = bi;
         rec_c = bc;
       }
@@ -772,27 +773,25 @@ __global__ __launch_bounds__(256) void k_gram4(const JobDev* __restrict__ jobs, 
       // same family: only c_i changes (to zero); other family: X products
 #pragma unroll
       for (int f = 0; f < NFAM; ++f) {
-        if (f == fi) {
+        if (f == fi)
           c[f] = (lt == bi % K) ? 0.0 : c[f];
-        } else if constexpr (NFAM == 2) {
-          const double g = fi ? sX[pa][pi] * sX[qa][qi] : sX[pi][pa] * sX[qi][qa];
-          c[f] = fma(-bc, g, c[f]);
-        }
+        else if constexpr (NFAM == 2)
+          c[f] = fma(-bc, cross(fi, pi, qi), c[f]);
       }
       e = fma(-bc, bc, e);
       ++t;
-      if (t % LPN == 0) {
-        lv.rec_idx[rec0 + (t - LPN) + lt] = rec_i;
-        lv.rec_coef[rec0 + (t - LPN) + lt] = rec_c;
+      if (t % K == 0) {
+        lv.rec_idx[rec0 + (t - K) + lt] = rec_i;
+        lv.rec_coef[rec0 + (t - K) + lt] = rec_c;
       }
       if (e < eps2)
         st = ST_ACC;
       else if (t >= kmax)
         st = ST_SPARSE;
     }
-    if (lt < t % LPN) {
-      lv.rec_idx[rec0 + (t - t % LPN) + lt] = rec_i;
-      lv.rec_coef[rec0 + (t - t % LPN) + lt] = rec_c;
+    if (lt < t % K) {
+      lv.rec_idx[rec0 + (t - t % K) + lt] = rec_i;
+      lv.rec_coef[rec0 + (t - t % K) + lt] = rec_c;
     }
     if (lt == 0) {
       lv.e[node] = e;
@@ -802,15 +801,44 @@ __global__ __launch_bounds__(256) void k_gram4(const JobDev* __restrict__ jobs, 
   }
 }
 
-// N = 8: four nodes per wave, 16 lanes each.  Lane li of a node holds pixels
+template <int NFAM>
+__global__ __launch_bounds__(256) void k_gram4(const JobDev* __restrict__ jobs, LevelDev lv,
+                                               const int32_t* __restrict__ count_ptr, const double* __restrict__ tab,
+                                               const double* __restrict__ xg) {
+  constexpr int N = 4, K = N * N;
+  constexpr int NG = 256 / K;            // nodes per workgroup
+  constexpr int NX = NFAM == 2 ? N : 1;
+  __shared__ double sT[NFAM][K];         // T_f[p][y] at [f][p N + y]
+  __shared__ double sX[NX][NX + 1];      // X[p][p'] = <T_0[p], T_1[p']>
+  __shared__ double sY[NG][K];           // the node's pixels (group-private)
+  const int tid = threadIdx.x, grp = tid / K, pa = tid % N, qa = tid % K / N;
+  for (int i = tid; i < NFAM * K; i += 256) (&sT[0][0])[i] = tab[i];
+  if constexpr (NFAM == 2)
+    for (int i = tid; i < K; i += 256) sX[i / N][i % N] = xg[i];
+  __syncthreads();
+  gram_pixels<N, NFAM>(jobs, lv, blockIdx.x * NG + grp, gridDim.x * NG, *count_ptr, &sT[0][0], sY[grp],
+                       [&](int f, int p, int q) -> double {
+                         return f ? sX[pa][p] * sX[qa][q] : sX[p][pa] * sX[q][qa];
+                       });
+}
+
+// N = 8.  Up to kGram8Waves nodes: a wave each, a lane per pixel
+// (gram_pixels).  More: four nodes per wave, 16 lanes each.
+// Lane li of a node holds pixels
 // (li / 2, 4 (li % 2) ..) and, of each family, atoms q = li / 2, p = 4 (li %
 // 2) + r, r = 0..3, so that a reduction over a node is four row operations
-// for all four nodes at once.  The sums and the updates are those of
-// a lane per pixel.  A slot whose node has ended takes its next one
-// from the queues.
+// for all four nodes at once.  The sums and the updates are those of a lane per
+// pixel, bit for bit.  A slot whose node has ended takes its next one from the
+// queues.
 // What bounds it: the instructions of a step (about 200 for four nodes; 130
 // for one node with a lane per pixel).  11 152 nodes, 170 692 steps: 44 us,
 // 74 us with a wave per node and a lane per pixel.
+// The line between them, by the nodes that the level has: two waves per SIMD of
+// the chip.  Two families, all of 57 steps / pursuits that end early (3 on
+// average, at most 15), a wave per node against four to a wave: 1 024 nodes 53
+// / 38 against 63 / 46 us, 2 048 60 / 38 against 64 / 45, 2 304 70 / 40 against
+// 64 / 46, 4 096 92 / 45 against 65 / 47.
+constexpr int kGram8Waves = 2048;
 template <int NFAM>
 __global__ __launch_bounds__(256) void k_gram8(const JobDev* __restrict__ jobs, LevelDev lv,
                                                const int32_t* __restrict__ count_ptr, int32_t* __restrict__ queue,
@@ -836,6 +864,11 @@ __global__ __launch_bounds__(256) void k_gram8(const JobDev* __restrict__ jobs, 
     }
   __syncthreads();
   const int count = *count_ptr;
+  if (count <= kGram8Waves) {
+    gram_pixels<N, NFAM>(jobs, lv, (int)blockIdx.x * 4 + wv, (int)gridDim.x * 4, count, &sT[0][0][0], sY[wv],
+                         [&](int f, int p, int q) -> double { return sX[f][p][lane % N] * sX[f][q][lane / N]; });
+    return;
+  }
   const int slot = lane / LPS, li = lane % LPS, q = li >> 1, p0 = 4 * (li & 1);
   double* ys = sY[wv] + slot * YP;
   const int q0 = (int)gridDim.x * 4 * SN, qk = (int)blockIdx.x % kQueues;
@@ -1448,9 +1481,9 @@ hipError_t launch_gram_pursuit(int n, const JobDev* jobs, LevelDev lv, const int
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
-#define AQMP_GSMALL(KERN, WGS, ...)                                                       \
+#define AQMP_GSMALL(KERN, NODES, WGS, ...)   /* fewest nodes per workgroup, workgroups per CU */ \
   {                                                                                       \
-    int64_t wgs = (cap + 15) / 16;   /* sixteen nodes per workgroup */                    \
+    int64_t wgs = (cap + (NODES) - 1) / (NODES);                                          \
     if (wgs > (int64_t)n_cus * (WGS)) wgs = (int64_t)n_cus * (WGS);                       \
     if (wgs < 1) wgs = 1;                                                                 \
     if (nfam == 2)                                                                        \
@@ -1480,10 +1513,10 @@ hipError_t launch_gram_pursuit(int n, const JobDev* jobs, LevelDev lv, const int
   switch (n) {
     // four waves per SIMD of 16-lane slots, at most a slot per node
     case 4:
-      AQMP_GSMALL(k_gram4, 4, jobs, lv, count, tab, xg)
+      AQMP_GSMALL(k_gram4, 16, 4, jobs, lv, count, tab, xg)
       break;
     case 8:
-      AQMP_GSMALL(k_gram8, 4, jobs, lv, count, queue, tab, xg)
+      AQMP_GSMALL(k_gram8, 4, 4, jobs, lv, count, queue, tab, xg)
       break;
     AQMP_GPUR(16)
     AQMP_GPUR(32)

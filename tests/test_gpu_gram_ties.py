@@ -86,3 +86,34 @@ def test_steps_with_ties_cost_little_more(A, n):
     print("n", n, "us a step without and with ties", us, flush=True)
     sys.stdout.flush()
     assert us[1] <= 2.0 * us[0]
+
+
+@pytest.mark.parametrize("fam", [1, 2, 3])
+@pytest.mark.parametrize("blocks", [1, 5, 2047, 2048, 2049, 2112])
+def test_few_and_many_small_nodes_alike(A, fam, blocks):
+    """N = 8: up to 2048 nodes take a wave each, more share one by four, with
+    the same bits.  A plane of `blocks` blocks, alone and beside one that makes
+    them many; ordinary blocks, dots that tie, an empty one, and one with an
+    undefined pixel."""
+    from workloads import piecewise_image
+    rng = np.random.default_rng(70)
+    img = piecewise_image(8, 8 * blocks, seed=71)
+    img[:, :8 * (blocks // 3)] = (rng.random((8, 8 * (blocks // 3))) < 0.1)
+    if blocks > 4:
+        img[:, 16:24] = 0.0
+        img[3, 30] = np.nan
+    more = rng.random((8, 8 * 2100))
+    d = A.Dictionary(8, 8, families=fam)
+    got = []
+    for planes in ([img], [img, more]):
+        code = A.Code(d, [_dev(x) for x in planes], [dict(tol=0.01, max_atoms=20, n_min=8, n_max=8)],
+                      [(i, 0) for i in range(len(planes))], solver=A.SOLVER_GRAM, schedule=A.SCHED_BATCHED)
+        got.append(code.export_nodes())
+        code.free()
+    d.free()
+    n, na = len(got[0].leaves), len(got[0].atom_idx)
+    print("fam", fam, "blocks", blocks, "atoms", na, flush=True)
+    assert n == blocks
+    assert got[0].leaves.tobytes() == got[1].leaves[:n].tobytes()
+    assert got[0].atom_idx.tobytes() == got[1].atom_idx[:na].tobytes()
+    assert got[0].coef.tobytes() == got[1].coef[:na].tobytes()
