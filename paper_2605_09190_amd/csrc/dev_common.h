@@ -206,4 +206,29 @@ __device__ inline float wave_max_f32(float f) {
   return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)v));
 }
 
+// Largest of a row of 16 lanes, in each of them.
+__device__ inline unsigned long long row_max_u64(unsigned long long v) {
+#define AQMP_RMAX(C) { const unsigned long long o = dpp_u64<C, 0xF>(v); v = o > v ? o : v; }
+  AQMP_RMAX(0xB1) AQMP_RMAX(0x4E) AQMP_RMAX(0x141) AQMP_RMAX(0x140)
+#undef AQMP_RMAX
+  return v;
+}
+
+// Smallest of a row of 16 lanes, in each of them, and of the wave, uniform.
+__device__ inline int row_min_i32(int v) {
+#define AQMP_RMIN(C) { const int o = (int)row_perm_u32<C>((uint32_t)v); v = o < v ? o : v; }
+  AQMP_RMIN(0xB1) AQMP_RMIN(0x4E) AQMP_RMIN(0x141) AQMP_RMIN(0x140)
+#undef AQMP_RMIN
+  return v;
+}
+__device__ inline int wave_min_i32(int v) {
+  v = row_min_i32(v);
+  uint32_t p, q;
+  lane_pair_u32<16>((uint32_t)v, p, q);
+  v = (int)p < (int)q ? (int)p : (int)q;
+  lane_pair_u32<32>((uint32_t)v, p, q);
+  v = (int)p < (int)q ? (int)p : (int)q;
+  return __builtin_amdgcn_readfirstlane(v);
+}
+
 }  // namespace aqmp

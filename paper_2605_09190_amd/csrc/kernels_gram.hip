@@ -261,23 +261,6 @@ __device__ inline double wave_max_f64(double d) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-__device__ inline int row_min_i32(int v) {
-#define AQMP_GMIN(C) { const int o = (int)row_perm_u32<C>((uint32_t)v); v = o < v ? o : v; }
-  AQMP_GMIN(0xB1) AQMP_GMIN(0x4E) AQMP_GMIN(0x141) AQMP_GMIN(0x140)
-#undef AQMP_GMIN
-  return v;
-}
-// Smallest of the wave, uniform.
-__device__ inline int wave_min_i32(int v) {
-  v = row_min_i32(v);
-  uint32_t p, q;
-  lane_pair_u32<16>((uint32_t)v, p, q);
-  v = (int)p < (int)q ? (int)p : (int)q;
-  lane_pair_u32<32>((uint32_t)v, p, q);
-  v = (int)p < (int)q ? (int)p : (int)q;
-  return __builtin_amdgcn_readfirstlane(v);
-}
-
 // Best atom of a wave: largest |c|, lowest atom index among equal
 // magnitudes; the result is uniform across the wave.  |c| is non-negative,
 // so its bit pattern orders like its value.
@@ -684,12 +667,6 @@ __global__ __launch_bounds__(256, 2) void k_gram_pursuit(const JobDev* __restric
 // largest |c|, then the lowest atom index among the lanes holding it, then
 // that lane's c.
 // ---------------------------------------------------------------------------
-__device__ inline unsigned long long row_max_u64(unsigned long long v) {
-#define AQMP_GMAX(C) { const unsigned long long o = dpp_u64<C, 0xF>(v); v = o > v ? o : v; }
-  AQMP_GMAX(0xB1) AQMP_GMAX(0x4E) AQMP_GMAX(0x141) AQMP_GMAX(0x140)
-#undef AQMP_GMAX
-  return v;
-}
 __device__ inline double row_sum_f64(double d) {
   d += row_perm_f64<0xB1>(d);
   d += row_perm_f64<0x4E>(d);

@@ -41,7 +41,7 @@
 // (roundings of c, X, two products, the sum, and of the stored residual), 64
 // of them 2^-15.4 ||r'||: no other atom can be the arg-max of the FP64
 // re-score or tie it.  One atom is left in 98% of the steps of an ordinary
-// image.
+// image.  (More than a few dozen: see kSepMany.)
 // The FP64 re-score, the rank-1 update and the norm use the same lane
 // patches and the same order of operations as k_select, and the initial
 // norm those of k_gather, so the trees, atoms, coefficients and norms are
@@ -353,6 +353,16 @@ __device__ inline double sep_bcast_f64(double d) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// Candidates are re-scored one after the other, so their number is bounded:
+// where more than this many lanes hold one, the window shrinks to 2^-19 ||r'||
+// (twice the largest error measured is 1.2e-6 of it), and where that leaves as
+// many, they are ties that only roundings tell apart, and the lowest atom is
+// taken.  In the Haar basis alone a dithered or a checkered plane ties 200 to
+// 1 024 atoms at every step: 256 x 256 checkered, 16 steps, N = 64 / 32: 60 / 45
+// us, with all of them re-scored 7 772 / 1 384, eight per step in launches of
+// their own 709 / 321.
+constexpr int kSepMany = 32;
+
 template <int N, int FAMS>
 __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict__ jobs, LevelDev lv,
                                                         const int32_t* __restrict__ count_ptr,
@@ -375,7 +385,7 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
   char* sR = sRes[grp];
   double(*sPart)[PH][64] = (double(*)[PH][64])sR;        // two buffers, WPN > 1
   uint32_t* sMask = (uint32_t*)(sR + 2 * sizeof(*sPart));
-  static_assert(WPN == 1 || 2 * sizeof(*sPart) + 1024 <= G::RBYTES, "exchange buffers");
+  static_assert(WPN == 1 || 2 * sizeof(*sPart) + 2048 <= G::RBYTES, "exchange buffers");
   // [f][p][p']: row p of family f against the other family
   const float* gram = G::XLDS ? sTab.x : (const float*)(ops + G::OFF_X);
   sep_load_tab<G>(sTab, tab, ops);
@@ -645,31 +655,61 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
         } else if (mx < __builtin_inff()) {
           // several atoms within the window: every one of them, lowest index on
           // ties (a wave's mask is relative to its own largest: no fewer atoms)
-          uint32_t wsel = 1u;                            // waves with a candidate
+          const uint32_t* ms = sMask;                    // masks of the node's waves
+          uint32_t own = mask;
           if constexpr (WPN > 1) {
-            sMask[tid] = mask;
-            wsel = 0u;
-            for (int w = 0; w < 4; ++w) wsel |= __uint_as_float(((const uint32_t*)sTop)[w]) >= mx - win ? 1u << w : 0u;
-            wsel = (uint32_t)__builtin_amdgcn_readfirstlane((int)wsel);
+            // a wave whose largest is outside the node's window has no candidate
+            sMask[tid] = __uint_as_float(((const uint32_t*)sTop)[wq]) >= mx - win ? mask : 0u;
             sep_sync<WPN>();
           }
-          for (int w = 0; w < WPN; ++w) {
-            if (!((wsel >> w) & 1u)) continue;
-            const uint32_t mw = WPN > 1 ? sMask[64 * w + lane] : mask;
-            unsigned long long lanes = __ballot(mw != 0u);
-            while (lanes) {
-              const int l = __builtin_ctzll(lanes);
-              lanes &= lanes - 1ull;
-              uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)mw, l);
-              while (bits) {
-                const int bit = __builtin_ctz(bits);
-                bits &= bits - 1u;
-                const int at = atom_of(w, l, bit);
-                const double c0 = rescore(at), m0 = fabs(c0);
-                if (m0 > mag || (m0 == mag && at < atom)) {
-                  mag = m0;
-                  coef = c0;
-                  atom = at;
+          auto mask_of = [&](int w) -> uint32_t { return WPN > 1 ? ms[64 * w + lane] : own; };
+          auto lanes_with = [&]() -> int {
+            int n = 0;
+            for (int w = 0; w < WPN; ++w) n += __popcll(__ballot(mask_of(w) != 0u));
+            return n;
+          };
+          bool many = false;
+          if (lanes_with() > kSepMany) {
+            const float thr = mx - win * 0x1p-6f;
+            own = 0u;
+#pragma unroll
+            for (int j = 0; j < VPL; ++j)
+              own = __builtin_amdgcn_alignbit(own, __float_as_uint(thr - fabsf(C[j >> 4][j & 15])), 31);
+            if constexpr (WPN > 1) {
+              ms = sMask + 256;
+              sMask[256 + tid] = own;
+              sep_sync<WPN>();
+            }
+            many = lanes_with() > kSepMany;
+          }
+          if (many) {
+            int low = 0x7fffffff;
+            for (int w = 0; w < WPN; ++w) {
+              const uint32_t mw = mask_of(w);            // a lane's atoms ascend from the top bit
+              const int at = mw ? atom_of(w, lane, 31 - __builtin_clz(mw)) : low;
+              low = at < low ? at : low;
+            }
+            atom = wave_min_i32(low);
+            coef = rescore(atom);
+            mag = fabs(coef);
+          } else {
+            for (int w = 0; w < WPN; ++w) {
+              const uint32_t mw = mask_of(w);
+              unsigned long long lanes = __ballot(mw != 0u);
+              while (lanes) {
+                const int l = __builtin_ctzll(lanes);
+                lanes &= lanes - 1ull;
+                uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)mw, l);
+                while (bits) {
+                  const int bit = __builtin_ctz(bits);
+                  bits &= bits - 1u;
+                  const int at = atom_of(w, l, bit);
+                  const double c0 = rescore(at), m0 = fabs(c0);
+                  if (m0 > mag || (m0 == mag && at < atom)) {
+                    mag = m0;
+                    coef = c0;
+                    atom = at;
+                  }
                 }
               }
             }

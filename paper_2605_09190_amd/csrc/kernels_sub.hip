@@ -21,7 +21,7 @@
 // step 2.2e-6; N = 8 3.5e-7.  Selection as there, too: every atom whose |c| is
 // within 2^-13 ||r'|| of the largest is re-scored in FP64 (the bound holds with
 // room: 48 FP32 additions at most per product instead of 192, and 5 2^-22 for
-// the split of either).
+// the split of either); where they are many see kSubMany and kList.
 //
 // What bounds it: the instructions of a step (about 400 for the two nodes of
 // a wave), then the longest pursuits.  On three 2048 x 2048 planes N = 16
@@ -78,6 +78,8 @@ struct SubGeo {
   // N = 16: correlations carried from step to step (N = 8: one of the four
   // nodes of a wave would want them anew at most steps)
   static constexpr bool CARRY = N == 16;
+  // N = 8: several candidates of a node take a lane of its slot each
+  static constexpr bool WIDE = N == 8;
   // operand row in LDS (value half, remainder half, padding against bank
   // conflicts), and bytes per node
   static constexpr int ROWB = N == 16 ? 80 : 48;
@@ -277,6 +279,17 @@ __device__ inline double sub_slot_sum(double v) {
   }
 }
 
+// N = 16: more lanes than this with a candidate of one node shrink its window as
+// kSepMany does (256 x 256 checkered, Haar alone, 16 steps: 45 us, 348 with all
+// re-scored).
+constexpr int kSubMany = 8;
+// N = 8 re-scores them all.  The BF16 form takes up to this many in turn, its
+// lanes summing one together; more, and in the FP32 form any second one, at once,
+// a lane each with the same sums.  The same plane: 74 us BF16 and 75 FP32, 98
+// and 127 with all in turn; binary text, two families, 55 and 72 (56 and 69: two
+// candidates are the FP32 form's best case in turn).
+constexpr int kList = 5;
+
 template <class G>
 __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelDev& lv,
                                    const int32_t* __restrict__ count_ptr, int32_t* __restrict__ queue,
@@ -291,9 +304,12 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
   __shared__ __attribute__((aligned(16))) char sRows[4][SN * G::NODEB];
   // CARRY: FP32 <T_f[p], T_f'[p']> of the step's family f and each f'
   __shared__ __attribute__((aligned(16))) float sX[G::CARRY ? G::NFAM : 1][G::NFAM][G::CARRY ? N : 1][G::CARRY ? N : 1];
-  // EXACT: the FP64 residuals, every slot's on banks of its own
+  // WIDE: the residuals in FP64 (EXACT at every step, else for steps with
+  // several candidates), every slot's on banks of its own, and its candidates
+  constexpr bool WIDE = G::WIDE;
   constexpr int RP = K + 2;
-  __shared__ __attribute__((aligned(16))) double sPix[EXACT ? 4 : 1][EXACT ? SN * RP : 2];
+  __shared__ __attribute__((aligned(16))) double sPix[WIDE ? 4 : 1][WIDE ? SN * RP : 2];
+  __shared__ uint8_t sCand[WIDE ? 4 : 1][WIDE ? SN : 1][WIDE ? 2 * K : 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   char* sR = sRows[wv];
@@ -511,6 +527,23 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
           if ((far >> (n * LPS)) & 1ull) mask[n] = on && (lane >> 5) == fm && fm < G::NFAM ? (1u << VPL) - 1u : 0u;
         }
         lanes[n] = __ballot(mask[n] != 0u);
+        if constexpr (!WIDE) {
+          if (__popcll(lanes[n]) > kSubMany) {
+            // see kSepMany: a narrower window, then the lowest atom
+            const float th = mx - wn * 0x1p-6f;
+            mk = 0u;
+#pragma unroll
+            for (int v = 0; v < VPL; ++v) mk = __builtin_amdgcn_alignbit(mk, __float_as_uint(th - fabsf(V[n][v])), 31);
+            mask[n] = mk;
+            lanes[n] = __ballot(mk != 0u);
+            if (__popcll(lanes[n]) > kSubMany) {
+              const int top = 31 - __builtin_clz(mk | 1u);   // a lane's atoms ascend from the top bit
+              const int at = mk ? sub_atom<G>(lane, VPL - 1 - top) : 0x7fffffff;
+              mask[n] = at == wave_min_i32(at) && mk ? 1u << top : 0u;
+              lanes[n] = __ballot(mask[n] != 0u);
+            }
+          }
+        }
         // the first candidate; whether there are others
         const int l = lanes[n] ? __builtin_ctzll(lanes[n]) : 0;
         bits[n] = (uint32_t)__builtin_amdgcn_readlane((int)mask[n], l);
@@ -539,33 +572,61 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
 #pragma unroll
         for (int i = 0; i < PR; ++i) tp[i] = pr[i];
       };
-      auto rescore = [&](int a) -> double {   // a >= 0
-        rows(a);
-        if constexpr (EXACT) {
-          // the plain sum over the pixels, one after the other
-          const int f = a / K, q = (a % K) / N, p = a % N;
-          const bool dc = (a % K) == 0;
-          const double* tr = sTab[dc ? ONES : f * N + q];
-          const double* pr = sTab[dc ? ONES + 1 : f * N + p];
-          double tx[N], c = 0.0;
+      // WIDE: the correlation of the slot's residual with any lane's atom a, EXACT
+      // as the plain sum over the pixels, one after the other,
+      auto plain = [&](int a) -> double {
+        const int f = a / K, q = (a % K) / N, p = a % N;
+        const bool dc = (a % K) == 0;
+        const double* tr = sTab[dc ? ONES : f * N + q];
+        const double* pr = sTab[dc ? ONES + 1 : f * N + p];
+        double tx[N], c = 0.0;
+#pragma unroll
+        for (int x = 0; x < N; x += 2) {
+          const double2 v = *(const double2*)(tr + x);
+          tx[x] = v.x;
+          tx[x + 1] = v.y;
+        }
+#pragma unroll
+        for (int y = 0; y < N; ++y) {
+          const double ty = pr[y];
 #pragma unroll
           for (int x = 0; x < N; x += 2) {
-            const double2 v = *(const double2*)(tr + x);
-            tx[x] = v.x;
-            tx[x + 1] = v.y;
+            const double2 v = *(const double2*)&sPix[wv][slot * RP + N * y + x];
+            c = fma(v.x, ty * tx[x], c);
+            c = fma(v.y, ty * tx[x + 1], c);
           }
-#pragma unroll
-          for (int y = 0; y < N; ++y) {
-            const double ty = pr[y];
-#pragma unroll
-            for (int x = 0; x < N; x += 2) {
-              const double2 v = *(const double2*)&sPix[wv][slot * RP + N * y + x];
-              c = fma(v.x, ty * tx[x], c);
-              c = fma(v.y, ty * tx[x + 1], c);
-            }
-          }
-          return c;
         }
+        return c;
+      };
+      // else as the sums that the slot's lanes make together (see rescore and
+      // sub_slot_sum): lane l holds row l / 2, columns 4 (l % 2) ..; its part is
+      // added to those of l ^ 8, l ^ 7, l ^ 2 and l ^ 1 in turn.  (A few loads at
+      // a time: with all at once 60 registers too many.)
+      auto of_slot = [&](int a) __attribute__((always_inline)) -> double {
+        const int f = a / K, q = (a % K) / N, p = a % N;
+        const bool dc = (a % K) == 0;
+        const double* tr = sTab[dc ? ONES : f * N + q];
+        const double* pr = sTab[dc ? ONES + 1 : f * N + p];
+        const double* pix = &sPix[wv][slot * RP];
+        double h[8];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const double2 t0 = *(const double2*)(tr + 4 * s), t1 = *(const double2*)(tr + 4 * s + 2);
+          auto part = [&](int y) __attribute__((always_inline)) -> double {
+            const double2 u = *(const double2*)(pix + 8 * y + 4 * s), v = *(const double2*)(pix + 8 * y + 4 * s + 2);
+            return fma(pr[y], fma(u.x, t0.x, u.y * t0.y) + fma(v.x, t1.x, v.y * t1.y), 0.0);
+          };
+#pragma unroll
+          for (int y = 0; y < 4; ++y) {
+            h[2 * y + s] = part(y) + part(y + 4);
+            __asm__ volatile("" : "+v"(h[2 * y + s]));   // made here, not where the sum is used
+          }
+        }
+        return ((h[0] + h[7]) + (h[2] + h[5])) + ((h[1] + h[6]) + (h[3] + h[4]));
+      };
+      auto rescore = [&](int a) -> double {   // a >= 0
+        rows(a);
+        if constexpr (EXACT) return plain(a);
         double part = 0.0;
 #pragma unroll
         for (int i = 0; i < PR; ++i) {
@@ -584,7 +645,63 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
       int atom = cand;
       double coef = rescore(cand < 0 ? 0 : cand);
       double mag = cand < 0 ? 0.0 : fabs(coef);
-      if (more) {
+      bool lists = EXACT && more;      // (taken in turn beside it, the step itself was slower)
+      if (WIDE && !EXACT && more) {
+#pragma unroll
+        for (int n = 0; n < SN; ++n) {
+          if (!lanes[n]) continue;
+          int cnt = 0;
+#pragma unroll
+          for (int v = 0; v < VPL; ++v) cnt += __popcll(__ballot(((mask[n] >> v) & 1u) != 0u));
+          lists = lists || cnt > kList;
+        }
+      }
+      if (lists) {
+        // All atoms of a node, sixteen at a time, a lane of the slot each, lowest
+        // index on ties.
+        int total = 0;
+#pragma unroll
+        for (int n = 0; n < SN; ++n) {
+          if (!EXACT && !lanes[n]) continue;   // one candidate or none: done
+          int cnt = 0;
+#pragma unroll
+          for (int v = 0; v < VPL; ++v) {
+            const bool b = ((mask[n] >> (VPL - 1 - v)) & 1u) != 0u;
+            const unsigned long long m = __ballot(b);
+            if (b) sCand[wv][n][cnt + __popcll(m & ((1ull << lane) - 1ull))] = (uint8_t)sub_atom<G>(lane, v);
+            cnt += __popcll(m);
+          }
+          total = slot == n ? cnt : total;
+        }
+        if constexpr (!EXACT) {
+#pragma unroll
+          for (int j = 0; j < PC; j += 2)
+            *(double2*)&sPix[wv][slot * RP + N * py + px + j] = make_double2(rd[0][j], rd[0][j + 1]);
+        }
+        wave_sync();
+        double bm = 0.0, bc = 0.0;
+        int ba = 0x7fffffff;
+        for (int i = li; __ballot(i < total) != 0ull; i += LPS) {
+          if constexpr (!EXACT) __asm__ volatile("" ::: "memory");   // no pixels kept in registers from pass to pass
+          const int a = i < total ? (int)sCand[wv][slot][i] : 0;
+          const double c0 = EXACT ? plain(a) : of_slot(a), m0 = fabs(c0);
+          if (i < total && (m0 > bm || (m0 == bm && a < ba))) {
+            bm = m0;
+            bc = c0;
+            ba = a;
+          }
+        }
+        const unsigned long long mb = (unsigned long long)__double_as_longlong(bm), m = row_max_u64(mb);
+        const int at = row_min_i32(mb == m ? ba : 0x7fffffff);
+        const double c1 = sub_slot_sum<G>(mb == m && ba == at ? bc : 0.0);
+        if (EXACT || total > 0) {
+          mag = __longlong_as_double((long long)m);
+          coef = c1;
+          atom = at == 0x7fffffff ? -1 : at;
+        }
+        rows(atom < 0 ? 0 : atom);
+        wave_sync();   // the lists are read before a later step writes them
+      } else if (!EXACT && more) {
         // the other atoms of the windows, lowest index on ties
         while (more) {
           more = false;
