@@ -128,11 +128,14 @@ typedef struct {
                           the sum of two FP16 values (error below that of the
                           FP32 products).  The candidates (step by step the
                           AQMP_CANDIDATES best atoms, else every atom within
-                          the correlation's error bound of the best; where
-                          N >= 16 leaves more than a few dozen, those within
-                          2^-19 of the residual's norm, and of as many still
-                          the lowest) are re-scored in FP64, and the
-                          coefficient and the stop/split test are FP64. */
+                          the correlation's error bound of the best) are
+                          re-scored in FP64, and the coefficient and the
+                          stop/split test are FP64.  (Whole-level pursuits of
+                          N >= 16 with candidates in more than 8 lanes of a
+                          wave, N >= 32 12 of a node's: the correlations are
+                          made in FP64, and of the atoms within 2^-42 of the
+                          residual's norm of the largest the lowest is
+                          taken.) */
   int32_t schedule;    /* AQMP_SCHED_PLAIN: jobs one after another,
                           stream-ordered launches;
                           AQMP_SCHED_BATCHED: every job in one pass,

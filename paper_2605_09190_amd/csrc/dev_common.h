@@ -206,6 +206,36 @@ __device__ inline float wave_max_f32(float f) {
   return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)v));
 }
 
+// A lane's value, uniform.
+__device__ inline double lane_f64(double d, int lane) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(d);
+  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)u, lane);
+  const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// Largest of non-negative doubles over the wave, without NaNs, uniform.
+template <int X>
+__device__ inline double lane_pair_max_f64(double d) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(d);
+  uint32_t p0, q0, p1, q1;
+  lane_pair_u32<X>((uint32_t)u, p0, q0);
+  lane_pair_u32<X>((uint32_t)(u >> 32), p1, q1);
+  return fmax(__longlong_as_double((long long)(((unsigned long long)p1 << 32) | p0)),
+              __longlong_as_double((long long)(((unsigned long long)q1 << 32) | q0)));
+}
+__device__ inline double wave_max_f64(double d) {
+  d = fmax(d, row_perm_f64<0xB1>(d));
+  d = fmax(d, row_perm_f64<0x4E>(d));
+  d = fmax(d, row_perm_f64<0x141>(d));
+  d = fmax(d, row_perm_f64<0x140>(d));
+  d = lane_pair_max_f64<16>(d);
+  d = lane_pair_max_f64<32>(d);
+  const unsigned long long w = (unsigned long long)__double_as_longlong(d);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)w);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(w >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // Largest of a row of 16 lanes, in each of them.
 __device__ inline unsigned long long row_max_u64(unsigned long long v) {
 #define AQMP_RMAX(C) { const unsigned long long o = dpp_u64<C, 0xF>(v); v = o > v ? o : v; }
@@ -230,5 +260,29 @@ __device__ inline int wave_min_i32(int v) {
   v = (int)p < (int)q ? (int)p : (int)q;
   return __builtin_amdgcn_readfirstlane(v);
 }
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+// v_mfma_f64_16x16x4_f64: lane l supplies A[l % 16][l / 16] and
+// B[l / 16][l % 16]; it holds D[l / 16 + 4 r][l % 16], r = 0..3.
+__device__ inline d4 mfma64(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+// The largest |c| of a lane so far and its atom, the lower of two that differ by
+// no more than w (the rounding of the sums).
+struct LaneBest {
+  double mag = -1.0;
+  int atom = 0x7fffffff;
+  __device__ inline void take(double c, int a, double w) {
+    const double m = fabs(c);
+    const bool far = m > mag + w, near = m >= mag - w;
+    atom = far ? a : (near && a < atom ? a : atom);
+    mag = m > mag ? m : mag;
+  }
+  // over the wave: the lowest atom of the lanes within w of the largest
+  __device__ inline void over_wave(double w) {
+    const double m = wave_max_f64(mag);
+    atom = wave_min_i32(mag >= m - w ? atom : 0x7fffffff);
+    mag = m;
+  }
+};
 
 }  // namespace aqmp

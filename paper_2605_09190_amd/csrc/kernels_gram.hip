@@ -36,8 +36,6 @@ namespace aqmp {
 
 namespace {
 
-typedef double d4 __attribute__((ext_vector_type(4)));
-
 // LDS index of element (row, col) of an N x N FP64 tile.  The matrix-core
 // operands are read as four rows of 16 consecutive doubles; for N >= 32 the
 // odd rows swap their 16-column halves so that two such rows fall on
@@ -49,10 +47,6 @@ __device__ inline int sw(int row, int col) {
   else
     return row * N + col;
 }
-
-// v_mfma_f64_16x16x4_f64: lane l supplies A[l % 16][l / 16] and
-// B[l / 16][l % 16]; it holds D[l / 16 + 4 r][l % 16], r = 0..3.
-__device__ inline d4 mfma64(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
 template <int N, int NFAM>
 struct InitGeo {
@@ -238,29 +232,6 @@ __device__ inline double max_abs(double a, double b) {
   __asm__("v_max_f64 %0, |%1|, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
 }
-// Largest of non-negative doubles over the wave, without NaNs, uniform.
-__device__ inline double wave_max_f64(double d) {
-  d = fmax(d, row_perm_f64<0xB1>(d));
-  d = fmax(d, row_perm_f64<0x4E>(d));
-  d = fmax(d, row_perm_f64<0x141>(d));
-  d = fmax(d, row_perm_f64<0x140>(d));
-  auto pair = [](double v, auto x) -> double {
-    constexpr int X = decltype(x)::value;
-    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-    uint32_t p0, q0, p1, q1;
-    lane_pair_u32<X>((uint32_t)u, p0, q0);
-    lane_pair_u32<X>((uint32_t)(u >> 32), p1, q1);
-    return fmax(__longlong_as_double((long long)(((unsigned long long)p1 << 32) | p0)),
-                __longlong_as_double((long long)(((unsigned long long)q1 << 32) | q0)));
-  };
-  d = pair(d, std::integral_constant<int, 16>());
-  d = pair(d, std::integral_constant<int, 32>());
-  const unsigned long long w = (unsigned long long)__double_as_longlong(d);
-  const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)w);
-  const unsigned hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(w >> 32));
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
 // Best atom of a wave: largest |c|, lowest atom index among equal
 // magnitudes; the result is uniform across the wave.  |c| is non-negative,
 // so its bit pattern orders like its value.

@@ -41,7 +41,7 @@
 // (roundings of c, X, two products, the sum, and of the stored residual), 64
 // of them 2^-15.4 ||r'||: no other atom can be the arg-max of the FP64
 // re-score or tie it.  One atom is left in 98% of the steps of an ordinary
-// image.  (More than a few dozen: see kSepMany.)
+// image.  (Many: see kSepMany.)
 // The FP64 re-score, the rank-1 update and the norm use the same lane
 // patches and the same order of operations as k_select, and the initial
 // norm those of k_gather, so the trees, atoms, coefficients and norms are
@@ -353,18 +353,75 @@ __device__ inline double sep_bcast_f64(double d) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Candidates are re-scored one after the other, so their number is bounded:
-// where more than this many lanes hold one, the window shrinks to 2^-19 ||r'||
-// (twice the largest error measured is 1.2e-6 of it), and where that leaves as
-// many, they are ties that only roundings tell apart, and the lowest atom is
+// The arg-max over the tiles of the wave's columns q that hold a candidate (mask,
+// see k_pursuit_sep) of the correlations in FP64, made anew from the FP32
+// residual in sr (rows of N + 4): the products of sep_correlate on the FP64
+// matrix cores, whose layouts fit each other the same way.  (The Haar rows from
+// N / 2 on are of two pixels: 16 of them, of 32.)
+template <class G>
+__device__ inline LaneBest sep_exact(const float* sr, const SepTab<G>& S, int wq, uint32_t mask, double w) {
+  constexpr int N = G::N, K = G::K, TT = G::TT, TQ = G::TQ;
+  const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+  uint32_t tiles = 0u;
+#pragma unroll
+  for (int k = 0; k < G::VPL / 4; ++k) tiles |= __ballot((mask >> (G::VPL - 4 - 4 * k)) & 15u) != 0ull ? 1u << k : 0u;
+  LaneBest best;
+#pragma unroll 1
+  for (int f = 0; f < G::NFAM; ++f) {
+    const bool haar = sep_haar<G>(f);
+    auto table = [&](int row, int col) -> double {
+      if (haar) return (double)((const int8_t*)S.sgn)[row * N + col] * S.mag[sep_haar_scale(row)];
+      return S.dct[(G::FAMS & AQMP_DCT) ? row * N + col : 0];
+    };
+#pragma unroll 1
+    for (int i = 0; i < TQ; ++i) {
+      const uint32_t row = (tiles >> (4 * f + TT * i)) & ((1u << TT) - 1u);
+      if (row == 0u) continue;
+      const int tq = wq * TQ + i, q = 16 * tq + m;
+      d4 D[TT];
+#pragma unroll
+      for (int t = 0; t < TT; ++t) D[t] = d4{0.0, 0.0, 0.0, 0.0};
+      const int x0 = haar && 2 * tq >= TT ? 32 * tq - N : 0, x1 = haar && 2 * tq >= TT ? x0 + 32 : N;
+#pragma unroll 1
+      for (int x = x0; x < x1; x += 8) {
+#pragma unroll
+        for (int j = 0; j < 8; j += 4) {
+          const double b = table(q, x + j + g);
+#pragma unroll
+          for (int t = 0; t < TT; ++t) D[t] = mfma64((double)sr[(16 * t + m) * (N + 4) + x + j + g], b, D[t]);
+        }
+      }
+#pragma unroll 1
+      for (int tp = 0; tp < TT; ++tp) {
+        if (!((row >> tp) & 1u)) continue;
+        d4 c = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int y = 0; y < N; y += 4) c = mfma64(table(16 * tp + m, y + g), D[y / 16][y / 4 % 4], c);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int at = f * K + q * N + 16 * tp + g + 4 * r;
+          best.take(f == 1 && at == K ? 0.0 : c[r], at, w);   // (the second constant atom)
+        }
+      }
+    }
+  }
+  best.over_wave(w);
+  return best;
+}
+
+// Candidates are re-scored one after the other.  Where more lanes than this hold
+// one, all of their tiles are made in FP64 instead (sep_exact, up to 12 000 cycles
+// a family at N = 64 against 1 000 per candidate); atoms within 2^-42 ||r|| of the
+// largest tie, that is by all but the rounding of those sums, and the lowest is
 // taken.  In the Haar basis alone a dithered or a checkered plane ties 200 to
-// 1 024 atoms at every step: 256 x 256 checkered, 16 steps, N = 64 / 32: 60 / 45
+// 1 024 atoms at every step: 256 x 256 checkered, 16 steps, N = 64 / 32: 129 / 81
 // us, with all of them re-scored 7 772 / 1 384, eight per step in launches of
 // their own 709 / 321.
-constexpr int kSepMany = 32;
+constexpr int kSepMany = 12;
 
+// Workgroups per CU: as many as fit the registers without sep_exact (and LDS).
 template <int N, int FAMS>
-__global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict__ jobs, LevelDev lv,
+__global__ __launch_bounds__(256, N == 64 ? (FAMS == 2 ? 3 : 2) : (FAMS == 3 ? 3 : 4)) void k_pursuit_sep(const JobDev* __restrict__ jobs, LevelDev lv,
                                                         const int32_t* __restrict__ count_ptr,
                                                         int32_t* __restrict__ queue, int32_t lg,
                                                         const double* __restrict__ tab,
@@ -376,8 +433,8 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
   __shared__ __attribute__((aligned(16))) char sRes[NPG][G::RBYTES];
   __shared__ __attribute__((aligned(16))) SepTab<G> sTab;
   __shared__ __attribute__((aligned(16))) uint4 sTop[2];   // per wave: largest |c|; its atom, with the top bit if there are others
-  __shared__ double sRed[4];
-  __shared__ int sNode[4];
+  __shared__ double sRed[4], sBest[4];
+  __shared__ int sNode[4], sBestAt[4];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wq = WPN > 1 ? wv : 0;                       // wave within the node
@@ -385,7 +442,8 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
   char* sR = sRes[grp];
   double(*sPart)[PH][64] = (double(*)[PH][64])sR;        // two buffers, WPN > 1
   uint32_t* sMask = (uint32_t*)(sR + 2 * sizeof(*sPart));
-  static_assert(WPN == 1 || 2 * sizeof(*sPart) + 2048 <= G::RBYTES, "exchange buffers");
+  static_assert(WPN == 1 || 2 * sizeof(*sPart) + 1024 <= G::RBYTES, "exchange buffers");
+  static_assert(4 * N * (N + 4) <= G::RBYTES, "FP32 pixels for sep_exact");
   // [f][p][p']: row p of family f against the other family
   const float* gram = G::XLDS ? sTab.x : (const float*)(ops + G::OFF_X);
   sep_load_tab<G>(sTab, tab, ops);
@@ -566,6 +624,7 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
           ((uint32_t*)sTop)[4 + wv] = best;
         }
     };
+    int given = -1;                                      // the step's atom, where it was taken among many
     while (st == ST_RUN) {
       if (!(e > 0.0 && e < __builtin_inf())) {           // a zero residual, or undefined pixels: nothing to select
         st = ST_ZERO;
@@ -585,6 +644,7 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
       // 64 steps (and to the end of a window of records).
       const double elim = fmax(eps2, 0.25 * e), emax = 4.0 * e;
       const int tlim = min(kmax, (t & ~63) + 64);
+      bool many = false;
       for (;;) {
         uint32_t pick = best;
         if constexpr (WPN > 1) {
@@ -602,7 +662,8 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
           }
           pick = n == 1u ? pick : 0x80000000u;
         }
-        pick = (uint32_t)__builtin_amdgcn_readfirstlane((int)pick);
+        pick = (uint32_t)__builtin_amdgcn_readfirstlane(given >= 0 ? given : (int)pick);
+        given = -1;
         // rows of the 1D Gram matrix for the update of the correlations (read
         // ahead of the re-score that hides them)
         sp_f32x4 gp[G::NFAM == 2 ? G::TT : 1];
@@ -655,61 +716,42 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
         } else if (mx < __builtin_inff()) {
           // several atoms within the window: every one of them, lowest index on
           // ties (a wave's mask is relative to its own largest: no fewer atoms)
-          const uint32_t* ms = sMask;                    // masks of the node's waves
-          uint32_t own = mask;
           if constexpr (WPN > 1) {
             // a wave whose largest is outside the node's window has no candidate
-            sMask[tid] = __uint_as_float(((const uint32_t*)sTop)[wq]) >= mx - win ? mask : 0u;
+            mask = __uint_as_float(((const uint32_t*)sTop)[wq]) >= mx - win ? mask : 0u;
+          }
+          int held[WPN], n = 0;                          // lanes of each wave with a candidate
+          held[0] = __popcll(__ballot(mask != 0u));
+          if constexpr (WPN > 1) {
+            sMask[tid] = mask;
+            if (lane == 0) sBestAt[wv] = held[0];
             sep_sync<WPN>();
-          }
-          auto mask_of = [&](int w) -> uint32_t { return WPN > 1 ? ms[64 * w + lane] : own; };
-          auto lanes_with = [&]() -> int {
-            int n = 0;
-            for (int w = 0; w < WPN; ++w) n += __popcll(__ballot(mask_of(w) != 0u));
-            return n;
-          };
-          bool many = false;
-          if (lanes_with() > kSepMany) {
-            const float thr = mx - win * 0x1p-6f;
-            own = 0u;
 #pragma unroll
-            for (int j = 0; j < VPL; ++j)
-              own = __builtin_amdgcn_alignbit(own, __float_as_uint(thr - fabsf(C[j >> 4][j & 15])), 31);
-            if constexpr (WPN > 1) {
-              ms = sMask + 256;
-              sMask[256 + tid] = own;
-              sep_sync<WPN>();
-            }
-            many = lanes_with() > kSepMany;
+            for (int w = 0; w < WPN; ++w) held[w] = __builtin_amdgcn_readfirstlane(sBestAt[w]);
           }
-          if (many) {
-            int low = 0x7fffffff;
-            for (int w = 0; w < WPN; ++w) {
-              const uint32_t mw = mask_of(w);            // a lane's atoms ascend from the top bit
-              const int at = mw ? atom_of(w, lane, 31 - __builtin_clz(mw)) : low;
-              low = at < low ? at : low;
-            }
-            atom = wave_min_i32(low);
-            coef = rescore(atom);
-            mag = fabs(coef);
-          } else {
-            for (int w = 0; w < WPN; ++w) {
-              const uint32_t mw = mask_of(w);
-              unsigned long long lanes = __ballot(mw != 0u);
-              while (lanes) {
-                const int l = __builtin_ctzll(lanes);
-                lanes &= lanes - 1ull;
-                uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)mw, l);
-                while (bits) {
-                  const int bit = __builtin_ctz(bits);
-                  bits &= bits - 1u;
-                  const int at = atom_of(w, l, bit);
-                  const double c0 = rescore(at), m0 = fabs(c0);
-                  if (m0 > mag || (m0 == mag && at < atom)) {
-                    mag = m0;
-                    coef = c0;
-                    atom = at;
-                  }
+#pragma unroll
+          for (int w = 0; w < WPN; ++w) n += held[w];
+          if (n > kSepMany) {
+            many = true;
+            break;
+          }
+          for (int w = 0; w < WPN; ++w) {
+            if (held[w] == 0) continue;
+            const uint32_t mw = WPN > 1 ? sMask[64 * w + lane] : mask;
+            unsigned long long lanes = __ballot(mw != 0u);
+            while (lanes) {
+              const int l = __builtin_ctzll(lanes);
+              lanes &= lanes - 1ull;
+              uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)mw, l);
+              while (bits) {
+                const int bit = __builtin_ctz(bits);
+                bits &= bits - 1u;
+                const int at = atom_of(w, l, bit);
+                const double c0 = rescore(at), m0 = fabs(c0);
+                if (m0 > mag || (m0 == mag && at < atom)) {
+                  mag = m0;
+                  coef = c0;
+                  atom = at;
                 }
               }
             }
@@ -782,6 +824,29 @@ __global__ __launch_bounds__(256, 2) void k_pursuit_sep(const JobDev* __restrict
         }
         ++t;
         if (!(e >= elim && e < emax && t < tlim)) break;
+      }
+      if (many) {
+        sep_sync<WPN>();                                 // the masks are read
+        float* sr = (float*)sR;
+#pragma unroll
+        for (int i = 0; i < RPW; ++i)
+#pragma unroll
+          for (int j = 0; j < PW; ++j) sr[(py + i) * (N + 4) + px + j] = (float)r[i][j];
+        sep_sync<WPN>();
+        const double w = 0x1p-42 * __builtin_sqrt(e);
+        const LaneBest found = sep_exact<G>(sr, sTab, wq, mask, w);
+        given = found.atom;
+        if constexpr (WPN > 1) {
+          if (lane == 0) {
+            sBest[wv] = found.mag;
+            sBestAt[wv] = found.atom;
+          }
+          sep_sync<WPN>();
+          const double mag = fmax(fmax(sBest[0], sBest[1]), fmax(sBest[2], sBest[3]));
+          given = 0x7fffffff;
+          for (int v = 0; v < 4; ++v) given = sBest[v] >= mag - w ? min(given, sBestAt[v]) : given;
+        }
+        continue;
       }
       if (st != ST_RUN) break;
       if ((t & 63) == 0 && wq == 0) {

@@ -279,9 +279,37 @@ __device__ inline double sub_slot_sum(double v) {
   }
 }
 
-// N = 16: more lanes than this with a candidate of one node shrink its window as
-// kSepMany does (256 x 256 checkered, Haar alone, 16 steps: 45 us, 348 with all
-// re-scored).
+// The atom of the largest correlation of a node of N = 16, in FP64 from its FP32
+// pixels (rows of ROWB bytes), the lowest within w: see sep_exact.
+template <class G>
+__device__ inline int sub_exact(const char* px, const double* tab, double w) {
+  constexpr int N = G::N, K = G::K;
+  const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+  LaneBest best;
+#pragma unroll 1
+  for (int f = 0; f < G::NFAM; ++f) {
+    const double* row = tab + (f * N + m) * N + g;
+    d4 D = d4{0.0, 0.0, 0.0, 0.0}, c = D;
+#pragma unroll 1
+    for (int x = 0; x < N; x += 4) D = mfma64((double)((const float*)(px + m * G::ROWB))[x + g], row[x], D);
+#pragma unroll
+    for (int y = 0; y < N; y += 4) {
+      c = mfma64(row[y], D[y / 4], c);
+      __asm__ volatile("" : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]) : : "memory");
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int at = f * K + m * N + g + 4 * r;
+      best.take(f == 1 && at == K ? 0.0 : c[r], at, w);   // (the second constant atom)
+    }
+  }
+  best.over_wave(w);
+  return best.atom;
+}
+
+// N = 16: more lanes than this with a candidate of one node, and its
+// correlations are made in FP64 (256 x 256 checkered, Haar alone, 16 steps:
+// 66 us, 348 with all candidates re-scored in turn).
 constexpr int kSubMany = 8;
 // N = 8 re-scores them all.  The BF16 form takes up to this many in turn, its
 // lanes summing one together; more, and in the FP32 form any second one, at once,
@@ -506,6 +534,7 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
       unsigned long long lanes[SN];
       uint32_t mask[SN], bits[SN];
       bool more = false;
+      uint32_t many = 0u;              // nodes with candidates in more than kSubMany lanes
       int cand = 0;
 #pragma unroll
       for (int n = 0; n < SN; ++n) {
@@ -529,19 +558,8 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
         lanes[n] = __ballot(mask[n] != 0u);
         if constexpr (!WIDE) {
           if (__popcll(lanes[n]) > kSubMany) {
-            // see kSepMany: a narrower window, then the lowest atom
-            const float th = mx - wn * 0x1p-6f;
-            mk = 0u;
-#pragma unroll
-            for (int v = 0; v < VPL; ++v) mk = __builtin_amdgcn_alignbit(mk, __float_as_uint(th - fabsf(V[n][v])), 31);
-            mask[n] = mk;
-            lanes[n] = __ballot(mk != 0u);
-            if (__popcll(lanes[n]) > kSubMany) {
-              const int top = 31 - __builtin_clz(mk | 1u);   // a lane's atoms ascend from the top bit
-              const int at = mk ? sub_atom<G>(lane, VPL - 1 - top) : 0x7fffffff;
-              mask[n] = at == wave_min_i32(at) && mk ? 1u << top : 0u;
-              lanes[n] = __ballot(mask[n] != 0u);
-            }
+            many |= 1u << n;
+            lanes[n] = 0ull;
           }
         }
         // the first candidate; whether there are others
@@ -555,6 +573,28 @@ __device__ inline void pursuit_sub(const JobDev* __restrict__ jobs, const LevelD
           more = more || lanes[n] != 0ull;
         }
         cand = slot == n ? at : cand;
+      }
+      if (!WIDE && many) {
+        do {
+          const int n = __builtin_ctz(many);
+          many &= many - 1u;
+          if (slot == n) {
+#pragma unroll
+            for (int i = 0; i < PR; ++i)
+#pragma unroll
+              for (int j = 0; j < PC; ++j) ((float*)(sRow + (py + i) * G::ROWB))[px + j] = (float)rd[i][j];
+          }
+          wave_sync();
+          const int at = sub_exact<G>(sR + n * G::NODEB, &sTab[0][0], 0x1p-42 * __builtin_sqrt(lane_f64(e, n * LPS)));
+          wave_sync();
+          cand = slot == n ? at : cand;
+        } while (many);
+        // the correlations anew: kept over the products they were 23 registers
+        // too many (BF16, both families)
+        if (run) put_rows();
+        wave_sync();
+        sub_correlate<G>(sR, T, V);
+        wave_sync();
       }
       // ---- FP64 re-score of the slot's candidate ----
       double tq[PC], tp[PR];

@@ -65,9 +65,9 @@ def test_exact_ties_in_ascending_order(A, haar, n, prec):
 @pytest.mark.parametrize("n", [8, 16, 32, 64])
 def test_dithered_planes_take_an_arg_max(A, haar, n, prec):
     """Every atom is the FP64 arg-max of the encoder's own residual (stored in
-    FP32 but for N = 8 of the FP32 form) to within the window that is left
-    where many atoms compete, 2^-19 of a norm at most twice this one, and its
-    coefficient the FP64 correlation (N^2 products)."""
+    FP32 but for N = 8 of the FP32 form) to within the 2^-42 of its norm that
+    count as a tie where many atoms compete and the rounding of N^2 products
+    on either side, and its coefficient the FP64 correlation (N^2 products)."""
     img = _dither(n, 4 * n)
     _, code = _code(A, haar, img, n, 40, prec)
     e = code.export_nodes()
@@ -80,7 +80,7 @@ def test_dithered_planes_take_an_arg_max(A, haar, n, prec):
             a, coef = int(e.atom_idx[leaf["atom_off"] + t]), e.coef[leaf["atom_off"] + t]
             c = (T @ r @ T.T).T.ravel()                     # q N + p
             norm = np.linalg.norm(r)
-            assert abs(c[a]) >= np.abs(c).max() - 2.0 ** -18 * norm, (leaf["x0"], t, a)
+            assert abs(c[a]) >= np.abs(c).max() - (2.0 ** -42 + 2 * n * n * 2.0 ** -52) * norm, (leaf["x0"], t, a)
             assert abs(coef - c[a]) <= n * n * 2.0 ** -52 * norm, (leaf["x0"], t, a)
             q, p = a // n, a % n
             phi = np.outer(T[p], T[q]) if a else np.full((n, n), 1.0 / n)
@@ -92,7 +92,7 @@ def test_dithered_planes_take_an_arg_max(A, haar, n, prec):
 @pytest.mark.parametrize("n", [16, 32, 64])
 def test_many_ties_cost_little_more(A, haar, n):
     """A level of checkered blocks takes less than three times that of noise
-    (1.0 to 1.3 times); with every tied atom re-scored in turn it took 6 to 70
+    (N = 16: 2.1, 32: 2.8, 64: 2.7 times); with every tied atom re-scored in turn it took 6 to 70
     times as long."""
     noise = np.random.default_rng(3).standard_normal((4 * n, 4 * n))
     ms = []
