@@ -51,7 +51,7 @@
 // of residual and correlations 1 060, arg-max 720, norm and stop test 700;
 // correlations anew 4 700, 1.9 times a node), and the last long nodes of a
 // level.  On three 2048 x 2048 planes (36 432 node-steps at N = 64, 74 821 at
-// N = 32) the levels take 228 and 84 us; with the correlations made anew at
+// N = 32) the levels take 233 and 87 us; with the correlations made anew at
 // every step 444 and 191 us, and with a correlation and a select launch per
 // step 2 510 and 980 us.
 #include "internal.h"
